@@ -125,7 +125,7 @@ int usp_layout_a2a(const usp_problem* p, int heads, int dir, const void* src, vo
  * causal != 0: key j is visible to query i iff kpos(j) <= qpos(i) (global positions from the
  * descriptors); causal == 0: every key is visible and qpos/kpos may be NULL.
  * A row with no visible key gets o = 0 and lse = -inf.  scale = 0 means 1/sqrt(hs).
- * bf16 inputs run on MFMA with fp32 accumulation; fp32 inputs run a plain-ALU instance. */
+ * bf16 inputs run on bf16 MFMA, fp32 inputs on fp32 MFMA; fp32 accumulation. */
 int usp_block_attn_fwd(const void* q, const void* k, const void* v, void* o_part, float* lse_part, int bs,
                        int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                        const usp_posdesc* qpos, const usp_posdesc* kpos, int in_dtype, int o_dtype,
@@ -205,9 +205,10 @@ int usp_ring_attn_fwd_partials(const void* q, const void* const* k_blocks, const
 /* Algorithm 1 forward for virtual ranks [rank_begin, rank_end):
  * all-to-all of Q,K,V -> ring loop of block attention -> LSE merge -> all-to-all of O.
  * With bf16 data and R <= USP_MAX_RING_BLOCKS the ring loop and the merge are the single launch of
- * usp_ring_attn_fwd (all blocks are resident on the one GPU); otherwise one usp_block_attn_fwd per ring step
- * with fp32 partials, then usp_lse_merge.  Short sequences (fewer query tiles x heads than keep 256 CUs busy for
- * as long as the last tile takes) run the single launch of usp_ring_attn_fwd_partials over two to eight parts of
+ * usp_ring_attn_fwd (all blocks are resident on the one GPU); with more blocks one usp_block_attn_fwd per ring step
+ * with fp32 partials, then usp_lse_merge.  fp32 data, and the shortest bf16 sequences, run all ranks of the range in one
+ * launch that reads and writes the shards directly (the workspace is then checked, but not used).  Short sequences (fewer
+ * query tiles x heads than keep 256 CUs busy for as long as the last tile takes) run the single launch of usp_ring_attn_fwd_partials over two to eight parts of
  * the keys, then usp_lse_merge; a little longer (more than one work item per CU, the heaviest still longer than
  * a CU's share) only the last query tiles of a causal rank are cut so, in the same launch as the whole ones, and
  * the merge covers their rows; the workspace query knows.

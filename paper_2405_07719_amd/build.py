@@ -9,7 +9,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libusp.so")
-SOURCES = ["usp_api.cpp", "layout_a2a.hip", "lse_merge.hip", "block_attn_fwd.hip", "block_attn_bwd.hip"]
+SOURCES = ["usp_api.cpp", "layout_a2a.hip", "lse_merge.hip", "block_attn_fwd.hip", "wave_split_attn_fwd.hip",
+           "block_attn_bwd.hip"]
 # measurement aid for bench.py only (matrix-core calibration loops): a library of its own, not part of the product
 CALIB_LIB = os.path.join(PKG, "libusp_calib.so")
 CALIB_SOURCES = ["calib_mfma.hip"]

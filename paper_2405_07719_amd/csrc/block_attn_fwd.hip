@@ -659,75 +659,6 @@ void block_attn_fwd_mfma(const AttnArgs) {
   }   // next work item
 }
 
-// -------------------------------------------------------------------------------------------
-// fp32 instance: plain ALU, one thread per query row, key tiles staged in LDS.  Exists so that the
-// ring / merge / layout logic can be checked at fp32 accuracy on fp32 inputs; not tuned.
-// -------------------------------------------------------------------------------------------
-template <int HS, typename OutT>
-__global__ __launch_bounds__(64) void block_attn_fwd_fp32(const AttnArgs a) {
-  constexpr int KT = 32;
-  __shared__ float ks[KT][HS], vs[KT][HS];
-  const int n_groups = a.bs * a.hkv;
-  int w = blockIdx.x;
-  const int group = w % n_groups; w /= n_groups;
-  const int hg = w % a.g;
-  const int t = w / a.g;
-  const int qtile = a.causal ? a.n_qtiles - 1 - t : t;
-  const int b = group / a.hkv, kvh = group % a.hkv;
-  const int h = kvh * a.g + hg;
-  const int row0 = qtile * 64, row1 = min(a.Lq, row0 + 64);
-  const int row = row0 + threadIdx.x;
-  const bool live = row < a.Lq;
-  const int rr = min(row, a.Lq - 1);
-  const int qp = a.causal ? pos_of(a.qpos, rr) : 0;
-  const float* qsrc = (const float*)a.q + (((size_t)b * a.Lq + rr) * a.hq + h) * HS;
-  float q[HS], o[HS];
-#pragma unroll
-  for (int e = 0; e < HS; ++e) { q[e] = qsrc[e]; o[e] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  const PosDesc32 kpos = a.kpos[0];   // this instance takes one block per launch
-  const TileRanges tr = visible_key_tiles<KT>(a.causal, a.qpos, kpos, a.Lk, row0, row1);
-  const float* kg = (const float*)a.k[0] + ((size_t)b * a.Lk * a.hkv + kvh) * HS;
-  const float* vg = (const float*)a.v[0] + ((size_t)b * a.Lk * a.hkv + kvh) * HS;
-  const size_t stride = (size_t)a.hkv * HS;
-  for (int pass = 0; pass < 2; ++pass) {
-    const int j0 = pass ? tr.b0 : tr.a0, j1 = pass ? tr.b1 : tr.a1;
-    for (int jt = j0; jt < j1; ++jt) {
-      __syncthreads();
-      for (int c = threadIdx.x; c < KT * HS; c += 64) {
-        const int r = c / HS, e = c % HS;
-        const int key = min(jt * KT + r, a.Lk - 1);
-        ks[r][e] = kg[(size_t)key * stride + e];
-        vs[r][e] = vg[(size_t)key * stride + e];
-      }
-      __syncthreads();
-      for (int r = 0; r < KT; ++r) {
-        const int key = jt * KT + r;
-        if (key >= a.Lk) break;
-        if (a.causal && pos_of(kpos, key) > qp) continue;
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < HS; ++e) s = __builtin_fmaf(q[e], ks[r][e], s);
-        s *= a.scale;
-        const float mn = fmaxf(m, s);
-        const float alpha = expf(m - mn);     // m = -inf -> 0
-        const float p = expf(s - mn);
-        l = l * alpha + p;
-#pragma unroll
-        for (int e = 0; e < HS; ++e) o[e] = o[e] * alpha + p * vs[r][e];
-        m = mn;
-      }
-    }
-  }
-  if (live) {
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    OutT* dst = (OutT*)a.o + (((size_t)b * a.Lq + row) * a.hq + h) * HS;
-#pragma unroll
-    for (int e = 0; e < HS; ++e) dst[e] = (OutT)(o[e] * inv);
-    a.lse[((size_t)b * a.hq + h) * a.Lq + row] = l > 0.f ? m + logf(l) : -INFINITY;
-  }
-}
-
 template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
 int launch_mfma(AttnArgs a, hipStream_t stream) {
   constexpr int BM = NWAVES * NQB * 32;
@@ -755,15 +686,6 @@ int launch_mfma(AttnArgs a, hipStream_t stream) {
   return launch_status();
 }
 
-template <int HS, typename OutT>
-int launch_fp32(AttnArgs a, hipStream_t stream) {
-  a.n_qtiles = (a.Lq + 63) / 64;
-  const int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs;
-  if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((block_attn_fwd_fp32<HS, OutT>), dim3((unsigned)grid), dim3(64), 0, stream, a);
-  return launch_status();
-}
-
 }  // namespace
 
 int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void* const* v_blocks,
@@ -772,7 +694,7 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
                          int in_dtype, int o_dtype, hipStream_t stream, const SeqLayoutIO* seq, const RingState* state,
                          bool v_transposed) {
   if (n_blocks < 1 || n_blocks > kMaxBlocks) return USP_ERR_UNSUPPORTED;
-  if (in_dtype == USP_FP32 && (n_blocks != 1 || seq)) return USP_ERR_UNSUPPORTED;
+  if (in_dtype != USP_BF16) return USP_ERR_DTYPE;
   AttnArgs a;
   a.seq_n = seq ? seq->rows_per_shard : 0;
   a.seq_heads = seq ? seq->heads : 0;
@@ -791,7 +713,6 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
   a.state = state ? state->state : nullptr;
   a.state_first = state ? state->first : 0;
   a.state_last = state ? state->last : 0;
-  if (state && in_dtype != USP_BF16) return USP_ERR_DTYPE;
   for (int j = 0; j < kMaxBlocks; ++j) {
     a.lk_blk[j] = (int)Lk;
     a.o_part[j] = nullptr;
@@ -807,13 +728,9 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
   a.scale = scale;
   a.scale_log2 = scale * 1.4426950408889634f;
   a.qpos = PosDesc32{(int)qpos.start0, (int)qpos.len0, (int)qpos.start1, (int)qpos.len1};
-  if (in_dtype == USP_FP32) {
-    if (hs == 128) return o_dtype == USP_FP32 ? launch_fp32<128, float>(a, stream) : launch_fp32<128, __bf16>(a, stream);
-    return o_dtype == USP_FP32 ? launch_fp32<64, float>(a, stream) : launch_fp32<64, __bf16>(a, stream);
-  }
   if (state && v_transposed) return USP_ERR_UNSUPPORTED;
   if (v_transposed) {   // V blocks in key-tile-transposed layout (bf16 in and out)
-    if (in_dtype != USP_BF16 || o_dtype != USP_BF16) return USP_ERR_DTYPE;
+    if (o_dtype != USP_BF16) return USP_ERR_DTYPE;
     return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, __bf16, false, true>(a, stream)
                      : launch_mfma<64, 1, 8, 64, 2, __bf16, false, true>(a, stream);
   }
@@ -835,6 +752,16 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
 int launch_block_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
                           int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
                           const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream) {
+  // fp32 has the one kernel.  bf16: the launch of 256-row items takes 6 us and its longest item (1.75 us per 64 keys at
+  // head size 128), or its work at 1.1 (0.8) PFLOP/s; short blocks, whose items are few and long, are faster with their
+  // keys split over the waves of a workgroup.  Measured, the ring of 32/8 heads, one call per block and the merge, 256-row
+  // items against waves: 8 blocks of 256 keys 145 / 74 us, of 512 keys 178 / 126, 2 blocks of 1024 keys 78 / 83; head size
+  // 64: 8 blocks of 512 keys 132 / 73, 2 of 1024 56 / 56.
+  const double flop = 4.0 * hs * bs * hq * (double)Lq * (double)Lk * (causal ? 0.5 : 1.0);
+  if (in_dtype == USP_FP32 || wave_split_us(Lq, bs * hq, hs, flop) <
+                                  6.0 + std::max(1.75 * (double)Lk / 64 * (hs / 128.0), flop / (hs == 128 ? 1.1e9 : 0.8e9)))
+    return launch_wave_split_block_fwd(q, k, v, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal, qpos, kpos, in_dtype, o_dtype,
+                                       stream);
   return launch_ring_attn_fwd(q, &k, &v, &kpos, 1, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal, qpos, in_dtype,
                               o_dtype, stream);
 }

@@ -515,6 +515,20 @@ int heavy_max_pieces(const usp_problem& p) {
   return m;
 }
 
+// Short sequences: whether all ranks of a range go through the one launch of wave_split_attn_fwd.hip instead of two to
+// four launches per rank, one rank after the other.  Those take at least 30 us (25 at head size 64) per rank and run at
+// 1.15 (0.8) PFLOP/s beyond that, the one launch as wave_split_us() says.  Measured, per-rank launches against the one:
+// 32/8 heads, U 8, one rank: L = 1024 45 / 13 us, 2048 46 / 19, 4096 52 / 39, 6144 72 / 80; without a mask L = 3072
+// 50 / 47, 4096 59 / 63; U 1 (32 heads): L = 1024 41 / 37, 1536 55 / 62; head size 64, U 8: L = 4096 39 / 23, 6144 51 / 42;
+// all four ranks of 8/4 heads, U 2 x R 2: L = 1024 121 / 13, 4096 182 / 74.
+bool short_in_one_launch(const usp_problem& p, int n_ranks) {
+  const int64_t Lq = p.L / p.ring;
+  const int heads = p.bs * (p.hc / p.ulysses);
+  const double flop = 4.0 * p.hs * heads * (double)Lq * (double)p.L * (p.causal ? 0.5 : 1.0);   // of one rank
+  const double by_rank = p.hs == 128 ? 30.0 + flop / 1.15e9 : 25.0 + flop / 0.8e9;
+  return wave_split_us(Lq, heads * n_ranks, p.hs, flop * n_ranks) < by_rank * n_ranks;
+}
+
 // allow_heavy = false: as if no rank cut its heaviest tiles (the entry point without a workspace of its own falls back
 // to that when the partials would not fit its array).
 FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true) {
@@ -639,6 +653,9 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   const int hq = p->hc / U, hkv = p->hk / U;
   const float scale = p->scale == 0.0f ? 1.0f / sqrtf((float)p->hs) : p->scale;
 
+  // fp32 data, and short sequences: all ranks of the range in one launch that reads and writes the shards themselves
+  if (p->dtype == USP_FP32 || short_in_one_launch(*p, rank_end - rank_begin))
+    return launch_wave_split_usp_fwd(*p, q, k, v, o, lse, rank_begin, rank_end, scale, stream);
 
   // Steps 3-4 of Algorithm 1 for every K/V block the ranks in range will visit.  The workspace slot of
   // block (r, u) is r * n_cols + (u - c0): with all U columns that is the rank order (one launch per

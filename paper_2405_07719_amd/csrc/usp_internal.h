@@ -118,6 +118,23 @@ int launch_block_attn_fwd(const void* q, const void* k, const void* v, void* o, 
                           int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
                           const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream);
 
+// wave_split_attn_fwd.hip: the keys of 32 query rows split over the waves of one workgroup; bf16 or fp32 data.
+// The whole of Algorithm 1's forward for ranks [rank_begin, rank_end) in one launch, everything read and written in the
+// sequence-layout shards, no workspace; and one ring step on dense tensors.
+int launch_wave_split_usp_fwd(const usp_problem& p, const void* q, const void* k, const void* v, void* o, float* lse,
+                              int rank_begin, int rank_end, float scale, hipStream_t stream);
+int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
+                                int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
+                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream);
+// Time of such a launch, in us: rounds of one workgroup (32 rows of a head; two at head size 64) per CU, 4 us each for its
+// first loads and the merge of its waves, and 0.6 PFLOP/s, where reading every key for only 32 rows leaves it.  Measured
+// (this formula): one rank of four heads, causal, L = 4096 38 us (41), 8192 128 (134); 32 heads, L = 1024 37 (34),
+// 2048 92 (93); four heads of size 64, L = 4096 23 (22), 6144 42 (44).
+inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
+  const int64_t wgs = (rows + 31) / 32 * heads, round = hs == 64 ? 2 * kPlanCUs : kPlanCUs;
+  return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
+}
+
 // seq: o and d_o are the sequence-layout shards of the rank's Ulysses group (their first shard), not dense tensors.
 int launch_bwd_delta(const void* o, const void* d_o, float* delta, int bs, int64_t L, int h, int hs,
                      hipStream_t stream, const SeqLayoutIO* seq = nullptr);

@@ -1,0 +1,477 @@
+// Attention forward with the keys of 32 query rows split over the eight waves of ONE workgroup: the whole ring loop of
+// Algorithm 1 (all-to-alls, blocks, merge) for a range of virtual ranks in a single launch, for the problems where
+// launches and latency are the time rather than the matrix core, and for fp32 data of every size.
+//
+//   * A workgroup owns 32 query rows of one (rank, batch, head).  Its waves take the visible 32-key tiles of all K/V
+//     blocks in turn (tile j of the walk to wave j mod 8), each with an online-softmax state of its own, and combine the
+//     eight states through LDS at the end: the key split and its merge cost two barriers instead of fp32 partials in
+//     memory and a launch.  A rank of 512 rows is 16 workgroups per head here where the 256-row kernel has 2.
+//   * Q, K and V are read and O is written where the caller holds them, in the sequence-layout shards: the all-to-alls
+//     are address arithmetic.  (Consecutive shards of one batch entry are contiguous when bs = 1.)
+//   * Ranks, batch and heads are the grid: all ranks of a range run side by side.
+//   * Operands.  Waves share no keys: each passes its K tile through a tile of LDS of its own (whole rows in, fragments
+//     out: A operand of S^T = K Q^T, lane = key).  bf16: V rows follow through the same tile and come back by transpose
+//     reads.  fp32: v_mfma_f32_32x32x2_f32 takes ONE value per lane and product, so V needs no transposition at all:
+//     product i multiplies the two keys that the lane halves hold in score register i with 32 head dims, lane = dim.
+// What bounds it.  Small problems: the chain of latencies of one workgroup (arguments, Q, K and V, two products, merge,
+// store: 6 us), so the prologue has no divisions, the merge no dependent LDS reads, a tile's loads no branches (loops over
+// the waves with a run-time bound alone cost 15 %: eight LDS reads, each waited for).  Large ones: every workgroup reads
+// all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the 256-row kernel: 0.54 PFLOP/s at
+// L = 8192, where that one has 0.71 (K fragments loaded straight from their rows, 32 lines per instruction, had 0.39).
+// Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at fp32 rate, 104
+// TFLOP/s at L = 2048, head size 128 (154 is what a large fp32 matrix product reaches); one thread per row on the vector
+// ALU, as it was before, took 1230 us for the four ranks of L = 256 that take 9 us here, and the four bf16 ranks of
+// L = 1024 took 121 us in nine launches where this is one of 12 us.
+#include "attn_device.h"
+#include "usp_internal.h"
+
+namespace usp {
+namespace {
+
+using namespace dev;
+
+constexpr int kWaves = 8, kRows = 32, kTile = 32;
+
+// Exact quotients of n < 2^31 by a divisor known on the host: one multiplication and a shift of scalar registers.  (A
+// division by a kernel argument is thirty vector instructions; the ten of them in front of the first load were 1 us.)
+struct FastDiv {
+  uint32_t d, mul;
+  int shift;
+  __device__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+  // n / d, and n becomes the remainder
+  __device__ int split(int& n) const {
+    const int q = div(n);
+    n -= q * (int)d;
+    return q;
+  }
+};
+FastDiv fast_div(int64_t d) {   // 1 <= d < 2^31: mul = ceil(2^(31 + s) / d) with 2^s >= d fits 32 bits, and its error times n stays below 2^(31 + s) / d
+  int s = 0;
+  while (((int64_t)1 << s) < d) ++s;
+  return FastDiv{(uint32_t)d, (uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), 31 + s};
+}
+
+struct WsArgs {
+  const void* q;
+  const void* k;
+  const void* v;
+  void* o;
+  float* lse;
+  int bs, hq, hkv, g;         // heads of one rank
+  int q_heads, kv_heads;      // heads in a row of Q / O and of K / V
+  int U, R, rank_begin, n_ranks;
+  FastDiv n_q, n_k;           // rows of a Q and of a K/V shard
+  FastDiv by_hkv, by_bs, by_ranks, by_g, by_U;
+  int Lq, Lk;                 // rows of a ring block
+  int n_qtiles, causal, split;
+  PosDesc32 qpos, kpos;       // split < 0: the one block's positions as given, else by Algorithm 2 from the ring rank
+  float scale, scale_log2;
+};
+
+// Algorithm 2 for ring rank r: chunks r and 2R-1-r of 2R, or block r of R
+__device__ inline PosDesc32 block_positions(const WsArgs& a, const PosDesc32& given, int len, int r) {
+  if (a.split < 0) return given;
+  if (a.split == USP_SPLIT_ZIGZAG) {
+    const int c = len / 2;
+    return PosDesc32{r * c, c, (2 * a.R - 1 - r) * c, c};
+  }
+  return PosDesc32{r * len, len, 0, 0};
+}
+
+// The rows of a ring block (one batch entry, one head) inside the shards [U][bs][n][heads][hs]: row j lies at
+// base + j row_bytes + (j / n) jump, and jump is 0 when bs = 1.
+struct BlockRows {
+  const char* base;
+  FastDiv n;
+  uint32_t row_bytes;
+  int64_t jump;
+  __device__ const char* row(int j) const { return base + (int64_t)j * row_bytes + (int64_t)n.div(j) * jump; }
+};
+
+__device__ inline BlockRows block_rows(const void* t, int esize, int hs, int bs, FastDiv n, int heads, int first_shard, int b, int head) {
+  const uint32_t row_bytes = (uint32_t)heads * hs * esize;
+  const int64_t run_bytes = (int64_t)n.d * row_bytes, shard_bytes = bs * run_bytes;
+  return BlockRows{(const char*)t + first_shard * shard_bytes + b * run_bytes + (int64_t)head * hs * esize, n, row_bytes,
+                   shard_bytes - run_bytes};
+}
+
+// One 32-key tile of such rows.  Inside one shard (and always when bs = 1) it is read through a buffer descriptor: the
+// lane's byte offset is the same for every tile, the row within the tile goes into the scalar offset, rows past the last
+// key read as zeros.  (With a 64-bit row address per load the address arithmetic took as long as the products.)  A tile
+// that crosses from one shard into the next, which lie bs entries apart, finds each row on its own.
+struct Tile {
+  BlockRows rows;
+  int key0, last;       // first key; last valid row of the tile
+  bool whole;           // inside one shard
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ Tile(const BlockRows& r, int key0_, int len, int row_len) : rows(r), key0(key0_) {
+    last = min(kTile, len - key0) - 1;
+    whole = r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)r.row(key0), 0, last * (int)r.row_bytes + row_len, kRawBufferFlags);
+  }
+  // t[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
+  template <bool kWhole, typename V, int N, typename Step>
+  __device__ void load(V (&t)[N], int lane_row, Step step, int col) const {
+    static_assert(sizeof(V) == 16 || sizeof(V) == 8, "");
+    const int at = lane_row * (int)rows.row_bytes + col;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if constexpr (!kWhole) t[i] = *(const V*)(rows.row(key0 + min(lane_row + step(i), last)) + col);
+      else if constexpr (sizeof(V) == 16) t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, step(i) * (int)rows.row_bytes, 0));
+      else t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, step(i) * (int)rows.row_bytes, 0));
+    }
+  }
+};
+
+// ---- operands of one data type: the fragments of Q and of a 32-key tile, and the two products -------------------
+template <typename T, int HS> struct Operands;
+
+template <int HS> struct Operands<__bf16, HS> {
+  static constexpr int KSTEPS = HS / 16, DB = HS / 32, CPR = HS / 8;
+  static constexpr int kWavesPerSimd = HS == 64 ? 4 : 2;   // head size 64: two workgroups to a CU
+  // Rows of the wave's LDS tile.  K: an odd number of 16-byte chunks, no bank conflicts on the fragment reads; V: an odd
+  // multiple of 64 bytes, none on the transpose reads.  K and V take turns in one tile (a wave's LDS accesses are in order).
+  static constexpr int KSTR = HS * 2 + 48, VSTR = HS * 2 + 64;
+  static constexpr int kLdsPerWave = kTile * VSTR;
+  static constexpr int TL = kTile * CPR / 64;            // 16-byte loads per lane of a tile
+  bf16x8 q[KSTEPS];
+  u32x4 k[TL], v[TL];
+
+  __device__ void load_q(const char* row, int hl) {
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = *(const bf16x8*)(row + 32 * ks + 16 * hl);
+  }
+  template <bool kWhole> __device__ static void load_rows(u32x4 (&t)[TL], const Tile& tile, int lane) {
+    tile.load<kWhole>(t, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  }
+  template <int STR> __device__ static void stash_rows(char* lds, const u32x4 (&t)[TL], int lane) {
+#pragma unroll
+    for (int c = 0; c < TL; ++c) {
+      const int ch = lane + 64 * c;
+      *(u32x4*)(lds + (ch / CPR) * STR + (ch % CPR) * 16) = t[c];
+    }
+    __builtin_amdgcn_wave_barrier();   // this wave's own LDS accesses stay in this order
+  }
+  template <bool kWhole> __device__ void load_tile(const Tile& kt, const Tile& vt, int lane) {
+    load_rows<kWhole>(k, kt, lane);
+    load_rows<kWhole>(v, vt, lane);
+  }
+  __device__ void stash_k(char* lds, int lane) { stash_rows<KSTR>(lds, k, lane); }
+  // S^T = K Q^T; leaves V in the LDS tile
+  __device__ f32x16 scores(char* lds, int lane) {
+    f32x16 s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    const char* row = lds + (lane & 31) * KSTR + 16 * (lane >> 5);
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(row + 32 * ks), q[ks], s, 0, 0, 0);
+    __builtin_amdgcn_wave_barrier();
+    stash_rows<VSTR>(lds, v, lane);
+    return s;
+  }
+  // O^T += V^T P^T; p = the tile's 16 weights of this lane
+  __device__ void accumulate(const f32x16& p, f32x16 (&o)[DB], const char* lds, int lane) {
+    const int hl = lane >> 5, grp = lane >> 4, j16 = lane & 15;
+    const char* vlane = lds + (4 * hl + (j16 >> 2)) * VSTR + (16 * (grp & 1) + 4 * (j16 & 3)) * 2;
+    __builtin_amdgcn_wave_barrier();   // the tile was written by this wave's own, in-order LDS stores
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      u32x4 pk;
+#pragma unroll
+      for (int pr = 0; pr < 4; ++pr) pk[pr] = pack_bf16(p[8 * s + 2 * pr], p[8 * s + 2 * pr + 1]);
+      const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const char* p0 = vlane + (16 * s) * VSTR + db * 64;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * VSTR));
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[db], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // head dim of element e of register group j (registers 4j .. 4j + 3) of block db: four consecutive dims from here
+  static __device__ int dim4(int db, int j, int hl) { return 32 * db + 8 * j + 4 * hl; }
+  static __device__ f32x4 out4(const f32x16 (&o)[DB], int db, int j) {
+    return f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
+  }
+  static constexpr int kGroups = DB * 4;   // groups of four dims per lane
+  static __device__ int group_dim(int gi, int hl) { return dim4(gi / 4, gi % 4, hl); }
+  static __device__ f32x4 group(const f32x16 (&o)[DB], int gi) { return out4(o, gi / 4, gi % 4); }
+};
+
+template <int HS> struct Operands<float, HS> {
+  static constexpr int DB = HS / 32, KC = HS / 8, CPR = HS / 4;
+  static constexpr int kWavesPerSimd = 2;
+  static constexpr int KSTR = HS * 4 + 16;               // an odd number of 16-byte chunks
+  static constexpr int kLdsPerWave = kTile * KSTR;
+  static constexpr int TL = kTile * CPR / 64;
+  typedef float vrow __attribute__((ext_vector_type(DB)));
+  f32x4 q[KC];           // dims 8 c + 4 (lane half) .. + 3: the product's two k indices are the lane halves
+  f32x4 k[TL];           // a tile's K rows on their way to LDS
+  vrow v[16];            // V of the key that score register i of this lane half holds, dims DB l32 .. + DB - 1
+
+  __device__ void load_q(const char* row, int hl) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(row + 32 * c + 16 * hl);
+  }
+  template <bool kWhole> __device__ void load_tile(const Tile& kt, const Tile& vt, int lane) {
+    kt.load<kWhole>(k, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+    if constexpr (HS == 64) load_v<kWhole>(vt, lane);
+  }
+  template <bool kWhole> __device__ void load_v(const Tile& vt, int lane) {
+    vt.load<kWhole>(v, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
+  }
+  __device__ void stash_k(char* lds, int lane) {
+#pragma unroll
+    for (int c = 0; c < TL; ++c) {
+      const int ch = lane + 64 * c;
+      *(f32x4*)(lds + (ch / CPR) * KSTR + (ch % CPR) * 16) = k[c];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ f32x16 scores(char* lds, int lane) {
+    f32x16 s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    const char* row = lds + (lane & 31) * KSTR + 16 * (lane >> 5);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const f32x4 kc = *(const f32x4*)(row + 32 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ka = kc[e], qa = q[c][e];
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka, qa, s, 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    return s;
+  }
+  __device__ void accumulate(const f32x16& p, f32x16 (&o)[DB], const char*, int) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float pi = p[i];
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const float va = v[i][db];
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, pi, o[db], 0, 0, 0);
+      }
+    }
+  }
+  // register i of block db is head dim DB (row i of the product) + db
+  static constexpr int kGroups = DB * 4;
+  static __device__ int group_dim(int gi, int hl) {
+    const int r = DB == 4 ? gi : 2 * gi;                 // the product rows of this group: one (DB = 4) or two (DB = 2)
+    return DB * (8 * (r >> 2) + 4 * hl + (r & 3));
+  }
+  static __device__ f32x4 group(const f32x16 (&o)[DB], int gi) {
+    if constexpr (DB == 4) return f32x4{o[0][gi], o[1][gi], o[2][gi], o[3][gi]};
+    else return f32x4{o[0][2 * gi], o[1][2 * gi], o[0][2 * gi + 1], o[1][2 * gi + 1]};
+  }
+};
+
+template <typename T, int HS>
+constexpr size_t lds_bytes() {
+  const size_t states = (size_t)kWaves * kRows * (HS + 4) * sizeof(float), tiles = (size_t)kWaves * Operands<T, HS>::kLdsPerWave;
+  return (states > tiles ? states : tiles);
+}
+
+template <typename T, int HS, typename OutT>
+__global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS>::kWavesPerSimd, Operands<T, HS>::kWavesPerSimd)))
+void wave_split_attn_fwd(const WsArgs a) {
+  using Op = Operands<T, HS>;
+  constexpr int DB = HS / 32, OSTR = HS + 4;   // floats between the rows of a state in LDS: an odd number of 16 B chunks
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows], inv_s[kRows];
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hl = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+
+  // KV group fastest (neighbouring workgroups go to different XCDs: one XCD's L2 then holds few KV heads), then head,
+  // then query tile, heaviest first under a causal mask
+  int kvh = blockIdx.x;
+  int b = a.by_hkv.split(kvh);
+  int rank = a.by_bs.split(b);
+  int hg = a.by_ranks.split(rank);
+  const int t = a.by_g.split(hg);
+  rank += a.rank_begin;
+  int u = rank;
+  const int r = a.by_U.split(u);
+  const int h = kvh * a.g + hg;
+  const int row0 = (a.causal ? a.n_qtiles - 1 - t : t) * kRows, row1 = min(a.Lq, row0 + kRows);
+  const PosDesc32 qpos = block_positions(a, a.qpos, a.Lq, r);
+  const int qmin = a.causal ? pos_min(qpos, row0, row1) : 0;
+  const int my_row = min(row0 + l32, a.Lq - 1);
+  const int qp = a.causal ? pos_of(qpos, my_row) : 0;
+
+  Op op;
+  const BlockRows qr = block_rows(a.q, sizeof(T), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
+  op.load_q(qr.row(my_row), hl);
+
+  f32x16 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  float m = -INFINITY, l = 0.f;
+
+  char* const lds = smem + wave * Op::kLdsPerWave;
+  int turn = wave;        // tiles of the walk until this wave's next one
+  for (int i = 0; i < a.R; ++i) {
+    const int blk = r - i < 0 ? r - i + a.R : r - i;   // Algorithm 1 step 5: step i visits block (r - i) mod R
+    const PosDesc32 kpos = block_positions(a, a.kpos, a.Lk, blk);
+    const TileRanges tr = visible_key_tiles<kTile>(a.causal, qpos, kpos, a.Lk, row0, row1);
+    const int na = tr.a1 - tr.a0, nt = na + (tr.b1 - tr.b0);
+    const BlockRows kr = block_rows(a.k, sizeof(T), HS, a.bs, a.n_k, a.kv_heads, blk * a.U, b, u * a.hkv + kvh);
+    const BlockRows vr = block_rows(a.v, sizeof(T), HS, a.bs, a.n_k, a.kv_heads, blk * a.U, b, u * a.hkv + kvh);
+    for (; turn < nt; turn += kWaves) {
+      const int key0 = (turn < na ? tr.a0 + turn : tr.b0 + (turn - na)) * kTile;
+      const Tile kt(kr, key0, a.Lk, HS * (int)sizeof(T)), vt(vr, key0, a.Lk, HS * (int)sizeof(T));
+      if (kt.whole) op.template load_tile<true>(kt, vt, lane);   // (K and V are cut into shards alike)
+      else op.template load_tile<false>(kt, vt, lane);
+      op.stash_k(lds, lane);
+      if constexpr (sizeof(T) == 4 && HS == 128) {
+        if (kt.whole) op.template load_v<true>(vt, lane);
+        else op.template load_v<false>(vt, lane);
+      }   // K, V, Q and O together are more than the registers
+      f32x16 s = op.scores(lds, lane);
+      const bool need_mask = key0 + kTile > a.Lk || (a.causal && pos_max(kpos, key0, min(a.Lk, key0 + kTile)) > qmin);
+      if (need_mask) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int key = key0 + 8 * (e >> 2) + 4 * hl + (e & 3);
+          const bool vis = key < a.Lk && (!a.causal || pos_of(kpos, key) <= qp);
+          s[e] = vis ? s[e] : -INFINITY;
+        }
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
+      const float m_new = fmaxf(m, both_halves_max(mx));
+      const float mc = m_new == -INFINITY ? 0.f : m_new * a.scale_log2;
+      if (__any(m_new > m)) {
+        const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);   // m = -inf -> 0
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+        m = m_new;
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.scale_log2, -mc));
+        l += s[e];
+      }
+      op.accumulate(s, o, lds, lane);
+    }
+    turn -= nt;
+  }
+
+  // ---- the waves' states are combined: common maximum, scaled outputs side by side in LDS, summed row by row
+  l = both_halves_sum(l);
+  if (hl == 0) {
+    m_s[wave][l32] = m;
+    l_s[wave][l32] = l;
+  }
+  __syncthreads();
+  // (every loop over the waves is unrolled, all its LDS reads in flight at once: a wave that had no tile adds zeros)
+  float mw[kWaves], m_all = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][l32];
+#pragma unroll
+  for (int j = 0; j < kWaves; ++j) m_all = fmaxf(m_all, mw[j]);
+  const float mc = m_all == -INFINITY ? 0.f : m_all * a.scale_log2;
+  {
+    const float f = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);
+    float* dst = (float*)smem + (wave * kRows + l32) * OSTR;
+#pragma unroll
+    for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, hl)) = Op::group(o, gi) * f;
+  }
+  if (wave == 0 && hl == 0) {
+    float tot = 0.f;
+#pragma unroll
+    for (int j = 0; j < kWaves; ++j) tot += l_s[j][l32] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
+    inv_s[l32] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
+    if (row0 + l32 < a.Lq)
+      a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + l32] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
+  }
+  __syncthreads();
+  const BlockRows orow = block_rows(a.o, sizeof(OutT), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
+  constexpr int PER_ROW = HS / 4, ROWS_PER_PASS = kWaves * 64 / PER_ROW;
+#pragma unroll
+  for (int pass = 0; pass < kRows / ROWS_PER_PASS; ++pass) {
+    const int rr = pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, c = (int)threadIdx.x % PER_ROW;
+    const float* src = (const float*)smem + rr * OSTR + 4 * c;
+    f32x4 sum = *(const f32x4*)src;
+#pragma unroll
+    for (int j = 1; j < kWaves; ++j) sum += *(const f32x4*)(src + j * (kRows * OSTR));
+    sum *= inv_s[rr];
+    if (row0 + rr < a.Lq) {
+      OutT* dst = (OutT*)orow.row(row0 + rr) + 4 * c;
+      if constexpr (sizeof(OutT) == 4) *(f32x4*)dst = sum;
+      else *(u32x2*)dst = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+    }
+  }
+}
+
+template <typename T, int HS, typename OutT>
+int launch_typed(const WsArgs& a, int64_t grid, hipStream_t stream) {
+  constexpr size_t lds = lds_bytes<T, HS>();
+  auto kern = wave_split_attn_fwd<T, HS, OutT>;
+  static LdsLimitRaised lds_limit;   // per kernel instance
+  if (!raise_dynamic_lds_limit((const void*)kern, lds, lds_limit)) return USP_ERR_LAUNCH;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kWaves * 64), lds, stream, a);
+  return launch_status();
+}
+
+int launch(WsArgs a, int hs, int in_dtype, int o_dtype, hipStream_t stream) {
+  a.g = a.hq / a.hkv;
+  a.by_hkv = fast_div(a.hkv); a.by_bs = fast_div(a.bs); a.by_ranks = fast_div(a.n_ranks);
+  a.by_g = fast_div(a.g); a.by_U = fast_div(a.U);
+  a.n_qtiles = (a.Lq + kRows - 1) / kRows;
+  a.scale_log2 = a.scale * 1.4426950408889634f;
+  const int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * a.n_ranks;
+  if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
+  if (in_dtype == USP_FP32) {
+    if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<float, 128, float>(a, grid, stream) : launch_typed<float, 128, __bf16>(a, grid, stream);
+    return o_dtype == USP_FP32 ? launch_typed<float, 64, float>(a, grid, stream) : launch_typed<float, 64, __bf16>(a, grid, stream);
+  }
+  if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<__bf16, 128, float>(a, grid, stream) : launch_typed<__bf16, 128, __bf16>(a, grid, stream);
+  return o_dtype == USP_FP32 ? launch_typed<__bf16, 64, float>(a, grid, stream) : launch_typed<__bf16, 64, __bf16>(a, grid, stream);
+}
+
+}  // namespace
+
+int launch_wave_split_usp_fwd(const usp_problem& p, const void* q, const void* k, const void* v, void* o, float* lse,
+                              int rank_begin, int rank_end, float scale, hipStream_t stream) {
+  WsArgs a = {};
+  a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
+  a.bs = p.bs; a.hq = p.hc / p.ulysses; a.hkv = p.hk / p.ulysses;
+  a.q_heads = p.hc; a.kv_heads = p.hk;
+  a.U = p.ulysses; a.R = p.ring; a.rank_begin = rank_begin; a.n_ranks = rank_end - rank_begin;
+  a.n_q = a.n_k = fast_div(p.L / ((int64_t)p.ulysses * p.ring));
+  a.Lq = a.Lk = (int)(p.L / p.ring);
+  a.causal = p.causal ? 1 : 0; a.split = p.split;
+  a.scale = scale;
+  return launch(a, p.hs, p.dtype, p.dtype, stream);
+}
+
+int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
+                                int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
+                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream) {
+  WsArgs a = {};
+  a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
+  a.bs = bs; a.hq = a.q_heads = hq; a.hkv = a.kv_heads = hkv;
+  a.U = a.R = a.n_ranks = 1;
+  a.Lq = (int)Lq; a.n_q = fast_div(Lq);
+  a.Lk = (int)Lk; a.n_k = fast_div(Lk);
+  a.causal = causal; a.split = -1;
+  a.qpos = PosDesc32{(int)qpos.start0, (int)qpos.len0, (int)qpos.start1, (int)qpos.len1};
+  a.kpos = PosDesc32{(int)kpos.start0, (int)kpos.len0, (int)kpos.start1, (int)kpos.len1};
+  a.scale = scale;
+  return launch(a, hs, in_dtype, o_dtype, stream);
+}
+
+}  // namespace usp

@@ -1,0 +1,63 @@
+"""GPU parity of the forward that splits the keys of 32 rows over the waves of a workgroup: every rank of a problem in one
+launch on the sequence-layout shards (short bf16 sequences, fp32 of every size), and one ring step on dense tensors.  The
+sizes are the edges of its tiles: rows and keys around 32, tiles that cross from one shard into the next (bs > 1), shards
+shorter than a tile, fewer visible tiles than waves, more ring blocks than a launch of the other kernel takes."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import usp_oracle as orc
+from tests import usp_testlib as tl
+from tests.test_gpu_attn_fwd import BLOCK_CASES, _check_against_reference, _desc, _run_block, _run_usp_fwd  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def usp():
+    import paper_2405_07719_amd as pkg
+    pkg.load()
+    return pkg
+
+
+@pytest.mark.parametrize("dtype", [tl.BF16, tl.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("bs,L,hc,hk,hs,U,R,causal,zigzag", [
+    (1, 2, 2, 1, 64, 1, 1, True, True),             # two rows in all
+    (1, 31, 2, 2, 128, 1, 1, False, False),         # less than a tile
+    (2, 66, 2, 1, 64, 1, 1, True, False),           # two tiles and two rows
+    (3, 40, 4, 2, 128, 2, 2, True, True),           # shards of 10 rows, blocks of 20: tiles span three shards
+    (2, 264, 4, 4, 64, 2, 2, True, True),           # shards of 66 rows: tiles straddle one boundary
+    (2, 296, 8, 2, 128, 2, 1, False, False),        # shards of 148 rows, group of four heads
+    (1, 1056, 4, 2, 128, 1, 4, True, True),         # runs of 132 positions: a tile holds keys of both runs
+    (1, 640, 4, 1, 64, 1, 20, True, True),          # 20 ring blocks of 32 keys
+    (1, 1536, 8, 8, 128, 4, 2, True, False),        # contiguous blocks: rank 0 sees nothing of block 1
+])
+def test_all_ranks_match_the_oracle(usp, dtype, bs, L, hc, hk, hs, U, R, causal, zigzag):
+    prob = tl.Problem(900 + L, bs, L, hc, hk, hs, U, R, causal, zigzag, dtype)
+    o, lse = _run_usp_fwd(usp, prob)
+    ref_o, tol = _check_against_reference(prob, o, lse)
+    for rank in range(prob.N):
+        assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
+
+
+def test_a_rank_range_writes_only_its_slices(usp):
+    """bs = 2, ranks 1 and 2 of four: their head slices, everything else as it was; the other ranks' LSE too."""
+    prob = tl.Problem(951, 2, 160, 4, 2, 64, 2, 2, True, True, tl.FP32)
+    o, lse = _run_usp_fwd(usp, prob, 1, 3)
+    ref_o, tol = _check_against_reference(prob, o, lse, ranks=[1, 2])
+    assert np.isnan(lse[0]).all() and np.isnan(lse[3]).all()
+    for shard in range(4):      # rank 1 = (r 0, u 1): heads 2, 3 of shards 0, 1; rank 2 = (r 1, u 0): heads 0, 1 of shards 2, 3
+        mine = slice(2, 4) if shard < 2 else slice(0, 2)
+        other = slice(0, 2) if shard < 2 else slice(2, 4)
+        assert tl.max_abs(o[shard][:, :, mine], ref_o[shard][:, :, mine]) <= tol
+        assert np.isnan(o[shard][:, :, other]).all()
+
+
+@pytest.mark.parametrize("o_dtype", [tl.FP32, tl.BF16])
+@pytest.mark.parametrize("case", BLOCK_CASES, ids=[c[0] for c in BLOCK_CASES])
+def test_block_step_fp32_every_mask(usp, case, o_dtype):
+    _, bs, Lq, Lk, hq, hkv, hs, causal, qd, kd = case
+    qd, kd = (_desc(usp, *d) if d else None for d in (qd, kd))
+    o, lse, ref_o, ref_l = _run_block(usp, 77, bs, Lq, Lk, hq, hkv, hs, causal, qd, kd, tl.FP32, o_dtype)
+    tl.assert_lse_close(lse, ref_l, 2e-5)
+    assert tl.max_abs(o, ref_o) <= (2e-5 if o_dtype == tl.FP32 else 2e-2)
