@@ -58,6 +58,10 @@ struct AttnArgs {
   // [U][bs][seq_n][seq_heads][hs] with this rank's heads at seq_head0: the all-to-all of Q (Algorithm 1 step 2)
   // and of O (step 6) folded into the one read of Q and the one write of O that the kernel does anyway.
   int seq_n, seq_heads, seq_head0;
+  // Heads in a row of K and of row-major V: hkv (dense), or all KV heads of the model where the kernel reads a batch
+  // of one straight from the sequence-layout shards of the rank's Ulysses group (k and v then point at the rank's first
+  // head).  The staged copy this replaces was a launch ahead of every forward, 5.6 us at L = 8192.
+  int kv_pitch;
   int ticket_slot;   // counter the workgroups draw their work items from (MFMA kernel)
   int n_items;       // work items of the launch: query tiles x heads x batch
   int n_queues;      // gcd(8, batch x KV heads): item w waits in queue w mod n_queues
@@ -97,6 +101,7 @@ struct ItemArgs {
   float scale, scale_log2;
   PosDesc32 qpos;
   int seq_n, seq_heads, seq_head0;
+  int kv_pitch;
 };
 
 // element offset of (batch b, local row, local head h) in the Q / O tensor
@@ -181,7 +186,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
     a.n_qtiles = ap->n_qtiles; a.n_blocks = ap->n_blocks; a.causal = ap->causal;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
     a.qpos = PosDesc32{ap->qpos.start0, ap->qpos.len0, ap->qpos.start1, ap->qpos.len1};
-    a.seq_n = ap->seq_n; a.seq_heads = ap->seq_heads; a.seq_head0 = ap->seq_head0;
+    a.seq_n = ap->seq_n; a.seq_heads = ap->seq_heads; a.seq_head0 = ap->seq_head0; a.kv_pitch = ap->kv_pitch;
     const int n_groups = a.bs * a.hkv;
     // The lane constants are derived anew for every item from a thread index the compiler cannot see through:
     // hoisted out of the item loop they would stay in registers across it, and the tile loop has none to spare.
@@ -241,7 +246,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
     }
 
     const __bf16* qg = (const __bf16*)a.q;
-    const size_t kv_head_off = ((size_t)b * a.Lk * a.hkv + kvh) * HS * 2;   // bytes; + key * hkv * HS * 2
+    const size_t kv_head_off = ((size_t)b * a.Lk * a.kv_pitch + kvh) * HS * 2;   // bytes; + key * kv_pitch * HS * 2
     // transposed V: the tiles of (batch, KV head) are contiguous; a.Lk (the batch stride in rows) gives their number
     const size_t vt_head_off = ((size_t)b * a.hkv + kvh) * (size_t)((a.Lk + KT - 1) / KT) * VT_TILE_BYTES;
     int Lk_b = a.Lk;   // keys of the current block (a.Lk stays the batch stride of every block's tensors)
@@ -314,7 +319,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
     // (this KV head), extent = up to the end of its last valid row.  Each thread adds a 32-bit byte offset that is
     // the same for every tile; rows past the last key (ragged final tile only) lie beyond the extent and read as
     // zeros (the mask hides those keys).  No 64-bit address arithmetic on the vector ALU, no clamping.
-    const uint32_t row_bytes = (uint32_t)a.hkv * HS * 2;
+    const uint32_t row_bytes = (uint32_t)a.kv_pitch * HS * 2;
     uint32_t st_off[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) st_off[c] = (uint32_t)(st_row + c * ROWS_PER_PASS) * row_bytes + st_col * 16;
@@ -699,6 +704,7 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
   a.seq_n = seq ? seq->rows_per_shard : 0;
   a.seq_heads = seq ? seq->heads : 0;
   a.seq_head0 = seq ? seq->head0 : 0;
+  a.kv_pitch = seq && seq->kv_heads ? seq->kv_heads : hkv;
   a.q = q; a.o = o; a.lse = lse;
   for (int j = 0; j < kMaxBlocks; ++j) {
     const int jj = j < n_blocks ? j : 0;
@@ -784,6 +790,7 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
   a.seq_n = seq ? seq->rows_per_shard : 0;
   a.seq_heads = seq ? seq->heads : 0;
   a.seq_head0 = seq ? seq->head0 : 0;
+  a.kv_pitch = seq && seq->kv_heads ? seq->kv_heads : hkv;
   a.q = q; a.o = nullptr; a.lse = nullptr;
   for (int j = 0; j < kMaxBlocks; ++j) {
     const int jj = j < n_blocks ? j : 0;

@@ -305,7 +305,8 @@ struct FwdPlan {
   size_t kv_block_bytes, v_block_bytes, part_o_bytes, part_lse_bytes;
   int n_cols;
   bool v_transposed;   // V blocks are staged in key-tile-transposed layout (the one-launch ring loop reads them so)
-  // Ulysses degree 1: a K/V block in head layout IS its sequence-layout shard.  K is then never staged; V only when it
+  // Ulysses degree 1: a K/V block in head layout IS its sequence-layout shard.  A batch of one: the shards of a ring row
+  // are contiguous, and a block is they with the rank's heads inside longer rows.  K is then never staged; V only when it
   // is wanted in transposed tiles and re-tiling it costs less than the tiles save.
   bool k_in_place, v_in_place;
 };
@@ -530,8 +531,9 @@ bool short_in_one_launch(const usp_problem& p, int n_ranks) {
 }
 
 // allow_heavy = false: as if no rank cut its heaviest tiles (the entry point without a workspace of its own falls back
-// to that when the partials would not fit its array).
-FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true) {
+// to that when the partials would not fit its array).  aligned = false: K or V does not lie on 16 bytes, as the kernels'
+// reads of whole chunks want them; the staged copies do.  (The sizes are the same.)
+FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true, bool aligned = true) {
   FwdPlan f;
   const size_t es = dtype_size(p.dtype);
   const size_t Lq = p.L / p.ring, hq = p.hc / p.ulysses, hkv = p.hk / p.ulysses;
@@ -557,16 +559,23 @@ FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true) {
   // re-tiled); one KV head 0.954 -> 0.960 ms with both in place, hence V re-tiled there.
   f.k_in_place = p.ulysses == 1;
   f.v_transposed = ring_in_one_launch(p) && splits == 0;
-  if (f.k_in_place && f.v_transposed) {
+  auto retiling_pays = [&]() {
     const double pairs = (double)p.bs * hq * (double)Lq * (double)p.L * (p.causal ? 0.5 : 1.0);
     const double attention_us = pairs * 4.0 * p.hs / 1.1e9;
     const double retile_us = 2.0 * (double)p.bs * p.L * hkv * p.hs * es / 5e6 + 6.0;
-    if (retile_us > 0.013 * attention_us) f.v_transposed = false;
-  }
-  f.v_in_place = f.k_in_place && !f.v_transposed;
+    return retile_us <= 0.013 * attention_us;
+  };
+  if (f.k_in_place && f.v_transposed) f.v_transposed = retiling_pays();
   f.v_block_bytes = f.v_transposed ? vt_block_bytes(p.bs, (int64_t)Lq, (int)hkv, p.hs) : f.kv_block_bytes;
   f.k_head = off; off += f.k_in_place ? 0 : up256(f.kv_block_bytes * p.ring * n_cols);
-  f.v_head = off; off += f.v_in_place ? 0 : up256(f.v_block_bytes * p.ring * n_cols);
+  f.v_head = off; off += f.k_in_place && !f.v_transposed ? 0 : up256(f.v_block_bytes * p.ring * n_cols);
+  // A batch of one is read in place at every Ulysses degree (the room for its staged copies stays in the plan: callers
+  // have been told the size).  Measured, L = 8192, one of eight Ulysses ranks: 99.0 us staged, 95.0 in place; L = 32768 984.1, 982.4.
+  if (p.bs == 1 && aligned && !f.k_in_place && ring_in_one_launch(p)) {
+    f.k_in_place = true;
+    f.v_transposed = f.v_transposed && retiling_pays();
+  }
+  f.v_in_place = f.k_in_place && !f.v_transposed;
   size_t parts = splits > 0 ? (size_t)splits * p.ring : (p.ring > 1 && !ring_in_one_launch(p)) ? p.ring : 0;
   parts = std::max<size_t>(parts, (size_t)heavy);
   f.o_parts = off; off += f.part_o_bytes * parts;
@@ -579,6 +588,17 @@ FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true) {
 
 namespace {
 
+// V of every (ring row, Ulysses column in [c0, c1)) in key-tile-transposed layout, packed by slot r * n_cols + (u - c0).
+int stage_vt_blocks(const usp_problem& p, const void* v, char* v_head, size_t block_bytes, int c0, int c1, hipStream_t stream) {
+  const int U = p.ulysses, R = p.ring, n_cols = c1 - c0;
+  if (n_cols == U) return launch_layout_a2a_vt(p, p.hk, v, v_head, 0, U * R, -1, stream);
+  if (n_cols == 1) return launch_layout_a2a_vt(p, p.hk, v, v_head, c0, U * R, -1, stream, U);
+  int st = USP_OK;
+  for (int r = 0; r < R && st == USP_OK; ++r)
+    st = launch_layout_a2a_vt(p, p.hk, v, v_head + (size_t)r * n_cols * block_bytes, r * U + c0, r * U + c1, -1, stream);
+  return st;
+}
+
 // K and V of every (ring row, Ulysses column in [c0, c1)) to head layout, packed by slot r * n_cols + (u - c0).
 int stage_kv_blocks(const usp_problem& p, const void* k, const void* v, char* k_head, char* v_head, size_t block_bytes,
                     int c0, int c1, hipStream_t stream, size_t vt_block_bytes_ = 0) {
@@ -587,23 +607,18 @@ int stage_kv_blocks(const usp_problem& p, const void* k, const void* v, char* k_
     // K as rows, V in key-tile-transposed layout: one launch each, same ranks and slots
     int st = USP_OK;
     const void* ksrc[1] = {k};
+    void* kdst[1] = {k_head};
     if (n_cols == U) {
-      void* kdst[1] = {k_head};
       st = launch_layout_a2a_multi(p, p.hk, USP_SEQ_TO_HEAD, 1, ksrc, kdst, 0, U * R, -1, stream);
-      if (st == USP_OK) st = launch_layout_a2a_vt(p, p.hk, v, v_head, 0, U * R, -1, stream);
     } else if (n_cols == 1) {
-      void* kdst[1] = {k_head};
       st = launch_layout_a2a_multi(p, p.hk, USP_SEQ_TO_HEAD, 1, ksrc, kdst, c0, U * R, -1, stream, U);
-      if (st == USP_OK) st = launch_layout_a2a_vt(p, p.hk, v, v_head, c0, U * R, -1, stream, U);
     } else {
       for (int r = 0; r < R && st == USP_OK; ++r) {
-        void* kdst[1] = {k_head + (size_t)r * n_cols * block_bytes};
+        kdst[0] = k_head + (size_t)r * n_cols * block_bytes;
         st = launch_layout_a2a_multi(p, p.hk, USP_SEQ_TO_HEAD, 1, ksrc, kdst, r * U + c0, r * U + c1, -1, stream);
-        if (st == USP_OK)
-          st = launch_layout_a2a_vt(p, p.hk, v, v_head + (size_t)r * n_cols * vt_block_bytes_, r * U + c0, r * U + c1, -1, stream);
       }
     }
-    return st;
+    return st == USP_OK ? stage_vt_blocks(p, v, v_head, vt_block_bytes_, c0, c1, stream) : st;
   }
   // K and V have one geometry: both go through the same launches
   const void* src[2] = {k, v};
@@ -643,7 +658,8 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   if (rank_begin < 0 || rank_end > N || rank_begin >= rank_end) return USP_ERR_UNSUPPORTED;
   int c0, c1;
   column_range(*p, rank_begin, rank_end, &c0, &c1);
-  const FwdPlan f = plan_fwd(*p, c1 - c0, allow_heavy);
+  const bool aligned = (((uintptr_t)k | (uintptr_t)v) & 15) == 0;
+  const FwdPlan f = plan_fwd(*p, c1 - c0, allow_heavy, aligned);
   // (a plan that needs no workspace at all, as a ring-only problem in one launch, takes any pointer, null included)
   if (f.total > 0 && (!workspace || workspace_bytes < f.total || ((uintptr_t)workspace & 255))) return USP_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)stream_;
@@ -654,23 +670,31 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   const float scale = p->scale == 0.0f ? 1.0f / sqrtf((float)p->hs) : p->scale;
 
   // fp32 data, and short sequences: all ranks of the range in one launch that reads and writes the shards themselves
-  if (p->dtype == USP_FP32 || short_in_one_launch(*p, rank_end - rank_begin))
+  if (p->dtype == USP_FP32 && R > USP_MAX_MERGE_PARTS) return USP_ERR_UNSUPPORTED;
+  if (p->dtype == USP_FP32 || (aligned && R <= USP_MAX_MERGE_PARTS && short_in_one_launch(*p, rank_end - rank_begin)))
     return launch_wave_split_usp_fwd(*p, q, k, v, o, lse, rank_begin, rank_end, scale, stream);
 
   // Steps 3-4 of Algorithm 1 for every K/V block the ranks in range will visit.  The workspace slot of
   // block (r, u) is r * n_cols + (u - c0): with all U columns that is the rank order (one launch per
   // tensor); with one column the ranks r * U + u are a stride-U sequence (again one launch per tensor).
-  const char* const k_blocks = f.k_in_place ? (const char*)k : ws + f.k_head;   // block slot 0 of K, of V
-  const char* const v_blocks = f.v_in_place ? (const char*)v : ws + f.v_head;
   if (!f.k_in_place) {
     st = stage_kv_blocks(*p, k, v, ws + f.k_head, ws + f.v_head, f.kv_block_bytes, c0, c1, stream,
                          f.v_transposed ? f.v_block_bytes : 0);
     if (st != USP_OK) return st;
   } else if (!f.v_in_place) {
-    // Ulysses degree 1, V wanted in transposed tiles: all R blocks in one launch, slot = ring row
-    st = launch_layout_a2a_vt(*p, p->hk, v, ws + f.v_head, 0, R, -1, stream);
+    st = stage_vt_blocks(*p, v, ws + f.v_head, f.v_block_bytes, c0, c1, stream);
     if (st != USP_OK) return st;
   }
+
+  // K and V of ring row s for Ulysses rank u: in place, the row's shards from the rank's first KV head on (rows of hk
+  // heads), else the workspace slot (rows of hkv heads)
+  const int kv_pitch = f.k_in_place ? p->hk : hkv;
+  auto kv_block = [&](bool in_place, const void* t, size_t region, size_t block_bytes, int s, int u) -> const char* {
+    return in_place ? (const char*)t + ((size_t)s * p->bs * Lq * p->hk + (size_t)u * hkv) * p->hs * es
+                    : ws + region + ((size_t)s * (c1 - c0) + (u - c0)) * block_bytes;
+  };
+  auto k_block = [&](int s, int u) { return kv_block(f.k_in_place, k, f.k_head, f.kv_block_bytes, s, u); };
+  auto v_block = [&](int s, int u) { return kv_block(f.v_in_place, v, f.v_head, f.v_block_bytes, s, u); };
 
   for (int rank = rank_begin; rank < rank_end; ++rank) {
     const int r = rank / U, u = rank % U;
@@ -690,13 +714,12 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
       for (int i = 0; i < R; ++i) {
         const int s = ((r - i) % R + R) % R;
         usp_local_positions(p, s, u, nullptr, &kds[i]);
-        const size_t slot = (size_t)s * (c1 - c0) + (u - c0);
-        kb[i] = k_blocks + slot * f.kv_block_bytes;
-        vb[i] = v_blocks + slot * f.v_block_bytes;
+        kb[i] = k_block(s, u);
+        vb[i] = v_block(s, u);
       }
       // Steps 2 and 6 for Q and O ride on the kernel's own accesses: it reads each Q row once and writes each O
       // row once, so it does that straight from / to the sequence-layout shards of the Ulysses group.
-      const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq};
+      const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq, kv_pitch};
       const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * es;
       const HeavyChoice heavy = allow_heavy ? heavy_choice(*p, r) : HeavyChoice{0, 0};
       if (heavy.tiles > 0) {
@@ -711,7 +734,7 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
         float* o_ptrs[kMaxHeavyPieces];
         float* l_ptrs[kMaxHeavyPieces];
         for (int n = 0; n < hp.n; ++n) {
-          const size_t row_off = (size_t)hp.first[n] * hkv * p->hs * es;
+          const size_t row_off = (size_t)hp.first[n] * kv_pitch * p->hs * es;
           kp[n] = (const char*)kb[hp.block[n]] + row_off;
           // (transposed tiles: a piece begins hp.first / 64 tiles into every head's run of tiles)
           vp[n] = (const char*)vb[hp.block[n]] + (f.v_transposed ? (size_t)(hp.first[n] / 64) * p->hs * 64 * es : row_off);
@@ -745,7 +768,7 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
         for (int i = 0; i < R; ++i)
           for (int64_t a0 = 0; a0 < Lq; a0 += piece, ++n) {
             const int64_t a1 = std::min(Lq, a0 + piece);
-            const size_t row_off = (size_t)a0 * hkv * p->hs * es;
+            const size_t row_off = (size_t)a0 * kv_pitch * p->hs * es;
             kp[n] = (const char*)kb[i] + row_off;
             vp[n] = (const char*)vb[i] + row_off;
             pd[n] = piece_of(kds[i], a0, a1);
@@ -775,10 +798,9 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
       const int s = ((r - i) % R + R) % R;
       usp_posdesc kd;
       usp_local_positions(p, s, u, nullptr, &kd);
-      const size_t slot = ((size_t)s * (c1 - c0) + (u - c0)) * f.kv_block_bytes;
       void* o_dst = R > 1 ? (void*)(ws + f.o_parts + (size_t)i * f.part_o_bytes) : (void*)(ws + f.o_head);
       float* l_dst = R > 1 ? (float*)(ws + f.lse_parts + (size_t)i * f.part_lse_bytes) : lse_rank;
-      st = launch_block_attn_fwd(ws + f.q_head, k_blocks + slot, v_blocks + slot, o_dst, l_dst, p->bs, Lq,
+      st = launch_block_attn_fwd(ws + f.q_head, k_block(s, u), v_block(s, u), o_dst, l_dst, p->bs, Lq,
                                  Lq, hq, hkv, p->hs, scale, p->causal ? 1 : 0, qd, kd, p->dtype,
                                  R > 1 ? USP_FP32 : p->dtype, stream);
       if (st != USP_OK) return st;

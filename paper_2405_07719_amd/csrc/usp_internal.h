@@ -76,7 +76,9 @@ int launch_layout_a2a_multi(const usp_problem& p, int heads, int dir, int n_tens
 // ([U][bs][rows_per_shard][heads][hs], q and o pointing at the group's first shard) instead of dense head-layout
 // tensors; head0 is the rank's first head.  Attention kernels: bf16 instance only.  Merge: fp32 partials only (the
 // merged O goes to the shards, the merged LSE stays [bs,hq,Lq]).
-struct SeqLayoutIO { int rows_per_shard, heads, head0; };
+// kv_heads > 0 (attention forward, batch of one): row-major K and V, too, lie in the shards, rows of kv_heads heads, the
+// pointers at the rank's first KV head; 0: dense.
+struct SeqLayoutIO { int rows_per_shard, heads, head0, kv_heads = 0; };
 // row0 > 0: only the rows [row0, Lq) of every batch are merged (and written); the tensors keep their full shapes.
 int launch_lse_merge(const void* const* o_parts, const float* const* lse_parts, int n_parts, void* o_out,
                      float* lse_out, int bs, int64_t Lq, int hq, int hs, int part_dtype, int out_dtype,
