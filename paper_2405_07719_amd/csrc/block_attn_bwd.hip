@@ -42,6 +42,10 @@ struct BwdArgs {
   const void* d_o;
   const float* lse;     // [bs,hq,Lq]  final LSE (natural log)
   const float* delta;   // [bs,hq,Lq]  D_i
+  // Given (dQ kernel running first): O, laid out like d_o.  The dQ kernel, which holds a row's dO anyway, then forms
+  // D_i itself and leaves it in delta_out (= delta) for the dK/dV kernel: a pass over O and dO and a launch less.
+  const void* o;
+  float* delta_out;
   float* dq;            // [bs,Lq,hq,hs]  fp32
   float* dk[kMaxBlocks];   // [bs,Lk,hkv,hs] fp32 per block
   float* dv[kMaxBlocks];
@@ -54,7 +58,16 @@ struct BwdArgs {
   int heads_per_wg;     // dkdv: query heads of a KV group walked by one workgroup (g: plain stores; else atomics)
   int acc_dkdv[kMaxBlocks];   // dkdv with heads_per_wg == g: 0 overwrite the block's dK/dV, 1 add to them
   float scale, scale_log2;
-  PosDesc32 qpos;
+  // Heads in a row of Q, dO and O, and of K and V: hq and hkv (dense), or all heads of the model where a batch of one is
+  // read straight from the sequence-layout shards (the pointers then are at the rank's first head).
+  int q_pitch, kv_pitch;
+  // Results that have one writer per element and need no fp32 sum leave as bf16, rows of q_pitch (kv_pitch) heads, at dq
+  // (dk and dv): no accumulator in memory and no conversion pass.
+  int dq_bf16, dkdv_bf16;
+  // Query blocks of the launch: the ranks of a whole ring (their rows [n_qblk][bs][Lq][hq][hs], statistics
+  // [n_qblk][bs][hq][Lq]), each with its own positions, or one.
+  int n_qblk;
+  PosDesc32 qpos[kMaxBlocks];
   PosDesc32 kpos[kMaxBlocks];
   // the workgroups of both kernels are persistent and draw their work items (attn_device.h); set per launch
   int ticket_slot, n_items, n_queues;
@@ -85,6 +98,7 @@ struct DqItemArgs {
   int bs, hq, hkv, g;
   int Lq, Lk;
   int n_tiles, n_blocks, causal, accumulate;
+  int q_pitch, kv_pitch;
   float scale, scale_log2;
   PosDesc32 qpos;
 };
@@ -98,6 +112,7 @@ struct DkdvItemArgs {
   int bs, hq, hkv, g;
   int Lq, Lk;
   int n_tiles, causal, heads_per_wg;
+  int q_pitch, kv_pitch;
   float scale, scale_log2;
   PosDesc32 qpos;
 };
@@ -142,6 +157,17 @@ __device__ inline void pack_b_operand(const float (&x)[16], bf16x8& lo, bf16x8& 
   }
   lo = __builtin_bit_cast(bf16x8, a);
   hi = __builtin_bit_cast(bf16x8, b);
+}
+
+// a lane's part of a finished row (dims 32 db + 8 j + 4 hl .. + 3, dst at 4 hl), times f, as bf16
+template <int DB>
+__device__ inline void store_bf16_row(__bf16* dst, const f32x16 (&x)[DB], float f) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(u32x2*)(dst + db * 32 + j * 8) = u32x2{pack_bf16(x[db][4 * j] * f, x[db][4 * j + 1] * f),
+                                               pack_bf16(x[db][4 * j + 2] * f, x[db][4 * j + 3] * f)};
 }
 
 // -------------------------------------------------------------------------------------------------
@@ -221,8 +247,8 @@ void bwd_dq_kernel(const BwdArgs) {
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
     a.n_tiles = ap->n_tiles; a.n_blocks = ap->n_blocks; a.causal = ap->causal; a.accumulate = ap->accumulate;
+    a.q_pitch = ap->q_pitch; a.kv_pitch = ap->kv_pitch;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
-    a.qpos = PosDesc32{ap->qpos.start0, ap->qpos.len0, ap->qpos.start1, ap->qpos.len1};
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
@@ -233,7 +259,11 @@ void bwd_dq_kernel(const BwdArgs) {
     const int hg = w % a.g; w /= a.g;
     const int k_splits = ap->k_splits;
     const int kslice = w % k_splits;             // this item's slice of the visible key tiles of every block
-    const int t = w / k_splits;
+    int t = w / k_splits;
+    const int n_qblk = ap->n_qblk;
+    const int qblk = n_qblk - 1 - t % n_qblk;    // the rank whose rows these are
+    t /= n_qblk;
+    a.qpos = PosDesc32{ap->qpos[qblk].start0, ap->qpos[qblk].len0, ap->qpos[qblk].start1, ap->qpos[qblk].len1};
     const int qtile = a.causal ? a.n_tiles - 1 - t : t;
     const int b = group / a.hkv, kvh = group % a.hkv;
     const int h = kvh * a.g + hg;
@@ -243,23 +273,37 @@ void bwd_dq_kernel(const BwdArgs) {
     const int rr = min(qrow, a.Lq - 1);
     const int qp = a.causal ? pos_of(a.qpos, rr) : 0;
 
-    const size_t kv_head_off = ((size_t)b * a.Lk * a.hkv + kvh) * HS * 2;   // bytes
+    const size_t kv_head_off = ((size_t)b * a.Lk * a.kv_pitch + kvh) * HS * 2;   // bytes
     const char* kg = nullptr;   // per block, set at the top of the block loop
     const char* vg = nullptr;
-    const uint32_t row_bytes = (uint32_t)a.hkv * HS * 2;
+    const uint32_t row_bytes = (uint32_t)a.kv_pitch * HS * 2;
 
     bf16x8 qf[KSTEPS], dof[KSTEPS];
     {
-      const size_t off = (((size_t)b * a.Lq + rr) * a.hq + h) * HS + 8 * hl;
+      const size_t off = (((size_t)(qblk * a.bs + b) * a.Lq + rr) * a.q_pitch + h) * HS + 8 * hl;
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) {
         qf[ks] = *(const bf16x8*)((const __bf16*)a.q + off + 16 * ks);
         dof[ks] = *(const bf16x8*)((const __bf16*)a.d_o + off + 16 * ks);
       }
     }
-    const size_t stat = ((size_t)b * a.hq + h) * a.Lq + rr;
+    const size_t stat = ((size_t)(qblk * a.bs + b) * a.hq + h) * a.Lq + rr;
     const float lse = a.lse[stat];
-    float dlt = a.delta[stat];
+    float dlt;
+    if (ap->o) {   // D_i, the lane halves holding half of the row's dims each
+      const __bf16* o_row = (const __bf16*)ap->o + (((size_t)(qblk * a.bs + b) * a.Lq + rr) * a.q_pitch + h) * HS + 8 * hl;
+      float part[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        const bf16x8 ov = *(const bf16x8*)(o_row + 16 * ks);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[e] += (float)ov[e] * (float)dof[ks][e];
+      }
+      dlt = both_halves_sum(((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7])));
+      if (kslice == 0 && hl == 0 && qrow < a.Lq) ap->delta_out[stat] = dlt;
+    } else {
+      dlt = a.delta[stat];
+    }
     float l2 = (lse == -INFINITY) ? INFINITY : lse * kLog2e;   // a row that saw nothing: P = 0
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -387,7 +431,9 @@ void bwd_dq_kernel(const BwdArgs) {
 
     unsigned own_ticket = kNoDraw;
     if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (qrow < a.Lq) {
+    if (qrow < a.Lq && ap->dq_bf16) {
+      store_bf16_row((__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + qrow) * a.q_pitch + h) * HS + 4 * hl, dq, a.scale);
+    } else if (qrow < a.Lq) {
       float* dst = a.dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -455,7 +501,7 @@ void bwd_dq_ds_kernel(const BwdArgs) {
     }
     const int bs = ap->bs, hq = ap->hq, hkv = ap->hkv, g = ap->g, Lq = ap->Lq, Lk = ap->Lk;
     const int causal = ap->causal, n_blocks = ap->n_blocks;
-    const PosDesc32 qpos = {ap->qpos.start0, ap->qpos.len0, ap->qpos.start1, ap->qpos.len1};
+    const PosDesc32 qpos = {ap->qpos[0].start0, ap->qpos[0].len0, ap->qpos[0].start1, ap->qpos[0].len1};   // (one query block)
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
@@ -476,8 +522,9 @@ void bwd_dq_ds_kernel(const BwdArgs) {
     const bool wave_live = wave_row0 < Lq;
     const int wave_qmax = (causal && wave_live) ? pos_max(qpos, wave_row0, min(Lq, wave_row0 + 32)) : 0;
 
-    const size_t kv_head_off = ((size_t)b * Lk * hkv + kvh) * HS * 2;   // bytes
-    const uint32_t row_bytes = (uint32_t)hkv * HS * 2;
+    const int kv_pitch = ap->kv_pitch;
+    const size_t kv_head_off = ((size_t)b * Lk * kv_pitch + kvh) * HS * 2;   // bytes
+    const uint32_t row_bytes = (uint32_t)kv_pitch * HS * 2;
     const char* kg = nullptr;      // per block
     const char* dsg = nullptr;     // per block: this wave's column of dS blocks (query tile qtile * 8 + wave)
     constexpr size_t ds_kt_stride = 8 * 2048;   // bytes from one key tile of 32 to the next: the workgroup's 8 blocks
@@ -570,7 +617,9 @@ void bwd_dq_ds_kernel(const BwdArgs) {
 
     unsigned own_ticket = kNoDraw;
     if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (qrow < Lq) {
+    if (qrow < Lq && ap->dq_bf16) {
+      store_bf16_row((__bf16*)ap->dq + (((size_t)b * Lq + qrow) * ap->q_pitch + h) * HS + 4 * hl, dq, ap->scale);
+    } else if (qrow < Lq) {
       const float scale = ap->scale;
       const int accumulate = ap->accumulate;
       float* dst = ap->dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * Lq + qrow) * hq + h) * HS + 4 * hl;
@@ -648,8 +697,8 @@ void bwd_dkdv_kernel(const BwdArgs) {
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
     a.n_tiles = ap->n_tiles; a.causal = ap->causal; a.heads_per_wg = ap->heads_per_wg;
+    a.q_pitch = ap->q_pitch; a.kv_pitch = ap->kv_pitch;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
-    a.qpos = PosDesc32{ap->qpos.start0, ap->qpos.len0, ap->qpos.start1, ap->qpos.len1};
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
@@ -678,11 +727,11 @@ void bwd_dkdv_kernel(const BwdArgs) {
     // do not fit 256 VGPRs: the spills' reloads share the counter of the prefetch loads and stall on them).
     bf16x8 kf[KSTEPS];
     {
-      const size_t off = (((size_t)b * a.Lk + kk) * a.hkv + kvh) * HS + 8 * hl;
+      const size_t off = (((size_t)b * a.Lk + kk) * a.kv_pitch + kvh) * HS + 8 * hl;
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = *(const bf16x8*)((const __bf16*)ap->k[blk] + off + 16 * ks);
-      const char* vg = (const char*)((const __bf16*)ap->v[blk] + ((size_t)b * a.Lk * a.hkv + kvh) * HS);
-      const uint32_t v_row_bytes = (uint32_t)a.hkv * HS * 2;
+      const char* vg = (const char*)((const __bf16*)ap->v[blk] + ((size_t)b * a.Lk * a.kv_pitch + kvh) * HS);
+      const uint32_t v_row_bytes = (uint32_t)a.kv_pitch * HS * 2;
 #pragma unroll
       for (int c = 0; c < BN * CPR / NT; ++c) {
         const int r = (tid + c * NT) / CPR, col = (tid + c * NT) % CPR;
@@ -700,6 +749,9 @@ void bwd_dkdv_kernel(const BwdArgs) {
       zero16(dv[db]);
     }
 
+    const int n_qblk = WRITE_DS ? 1 : ap->n_qblk;
+    for (int qblk = 0; qblk < n_qblk; ++qblk) {   // the query blocks (ranks) of the launch, one after the other
+    a.qpos = PosDesc32{ap->qpos[qblk].start0, ap->qpos[qblk].len0, ap->qpos[qblk].start1, ap->qpos[qblk].len1};
     const TileRanges tr = visible_query_tiles<QT>(a.causal, a.qpos, kpos, a.Lq, tile_key0, tile_key1);
     const int na = tr.a1 - tr.a0, nt = na + (tr.b1 - tr.b0);
     // Query tiles are walked from the LAST one down: every workgroup of a head then starts on the same tile and
@@ -736,7 +788,7 @@ void bwd_dkdv_kernel(const BwdArgs) {
     float streg = 0.f;
     // tile base addresses are wave-uniform; the per-thread byte offset is the same for every tile, clamped by a
     // min on the offset for rows past the last query (offsets grow with the row)
-    const uint32_t row_bytes = (uint32_t)a.hq * HS * 2;
+    const uint32_t row_bytes = (uint32_t)a.q_pitch * HS * 2;
     const uint32_t st_off = (uint32_t)st_row * row_bytes + st_col * 16;
     const char* qg = nullptr;      // per query head, set at the top of the head loop
     const char* og = nullptr;
@@ -779,9 +831,10 @@ void bwd_dkdv_kernel(const BwdArgs) {
     // without splitting them: then nobody else adds to these keys' dK/dV and the epilogue is a plain store).
     for (int hh = 0; hh < a.heads_per_wg; ++hh) {
     const int h = kvh * a.g + hg0 + hh;
-    qg = (const char*)((const __bf16*)a.q + ((size_t)b * a.Lq * a.hq + h) * HS);
-    og = (const char*)((const __bf16*)a.d_o + ((size_t)b * a.Lq * a.hq + h) * HS);
-    stat_g = (tid < QT ? a.lse : a.delta) + ((size_t)b * a.hq + h) * a.Lq;
+    const size_t qb = (size_t)(qblk * a.bs + b);
+    qg = (const char*)((const __bf16*)a.q + (qb * a.Lq * a.q_pitch + h) * HS);
+    og = (const char*)((const __bf16*)a.d_o + (qb * a.Lq * a.q_pitch + h) * HS);
+    stat_g = (tid < QT ? a.lse : a.delta) + (qb * a.hq + h) * a.Lq;
     const int it0 = (int)((int64_t)nt * qs / q_splits), it1 = (int)((int64_t)nt * (qs + 1) / q_splits);
     // where the dS blocks of this head and K/V block begin
     char* ds_head = nullptr;
@@ -923,10 +976,15 @@ void bwd_dkdv_kernel(const BwdArgs) {
       __syncthreads();
     }
     }   // query heads
+    }   // query blocks
 
     unsigned own_ticket = kNoDraw;
     if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (key_ok) {
+    if (key_ok && ap->dkdv_bf16) {
+      const size_t off = (((size_t)b * a.Lk + key) * a.kv_pitch + kvh) * HS + 4 * hl;
+      store_bf16_row((__bf16*)ap->dk[blk] + off, dk, a.scale);
+      store_bf16_row((__bf16*)ap->dv[blk] + off, dv, 1.f);
+    } else if (key_ok) {
       const size_t part_stride = ap->dkdv_part_stride;   // > 0: every (head split, query slice) has its own copy
       const size_t off = (size_t)(hsplit * q_splits + qs) * part_stride + (((size_t)b * a.Lk + key) * a.hkv + kvh) * HS + 4 * hl;
       float* dkp = ap->dk[blk] + off;
@@ -978,34 +1036,57 @@ __global__ __launch_bounds__(256) void bwd_zero_kernel(f32x4* dst, size_t n4) {
 // Where the converted tensor goes when that is not the dense [bs, rows, heads, hs] it comes from but the sequence-layout
 // shards of the rank's Ulysses group ([U][bs][rows_per_shard][seq_heads][hs], dst = the group's first shard, the
 // rank's heads from head0 on): Algorithm 1's reverse all-to-all rides on the conversion's stores.  rows_per_shard = 0: dense.
-struct ConvertSeq { int rows_per_shard = 0, seq_heads = 0, head0 = 0, heads = 0, hs4 = 0, bs = 0; int64_t rows = 0; };
+struct ConvertSeq { uint32_t rows_per_shard = 0, seq_heads = 0, head0 = 0, heads = 0, hs4 = 0, bs = 0, rows = 0; };
 
-// fp32 accumulator -> bf16 / fp32 output, 4 elements per lane; blockIdx.y picks one of two tensors of the same size
-// (dK and dV go through one launch)
+// One tensor of a conversion launch: n_blocks blocks of n4 groups of four elements, src and dst strides between blocks in
+// such groups; every element is the sum of n_copies copies copy_stride4 apart.
+struct ConvertJob {
+  const float* src;
+  void* dst;
+  size_t n4, src_blk4, dst_blk4, copy_stride4;
+  uint32_t wgs_per_blk, first_wg;
+  int n_copies, add_to_dst;
+  ConvertSeq cs;
+};
+constexpr int kMaxConvertJobs = 3;   // dQ, dK, dV
+struct ConvertArgs { ConvertJob job[kMaxConvertJobs]; int n_jobs; };
+
+// fp32 accumulators -> bf16 / fp32 outputs, 4 elements per lane; all tensors of a call go through one launch
 template <typename OutT>
-__global__ __launch_bounds__(256) void bwd_convert_kernel(const float* src0, OutT* dst0, const float* src1, OutT* dst1,
-                                                          size_t n4, int n_copies, size_t copy_stride4, int add_to_dst,
-                                                          ConvertSeq cs) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const float* src = blockIdx.y ? src1 : src0;
-  OutT* dst = blockIdx.y ? dst1 : dst0;
-  f32x4 v = __builtin_nontemporal_load((const f32x4*)src + i);
-  for (int c = 1; c < n_copies; ++c) v += __builtin_nontemporal_load((const f32x4*)src + c * copy_stride4 + i);
-  size_t o = i;   // in groups of four elements
+__global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
+  int j = 0;
+  while (j + 1 < a.n_jobs && blockIdx.x >= a.job[j + 1].first_wg) ++j;
+  const ConvertJob& job = a.job[j];
+  const uint32_t wg = blockIdx.x - job.first_wg, blk = wg / job.wgs_per_blk;
+  const size_t i = (size_t)(wg - blk * job.wgs_per_blk) * 256 + threadIdx.x;
+  if (i >= job.n4) return;
+  const f32x4* src = (const f32x4*)job.src + blk * job.src_blk4 + i;
+  f32x4 v = __builtin_nontemporal_load(src);
+  int c = 1;
+  for (; c + 3 <= job.n_copies; c += 3) {   // three loads in flight, added in the order of the copies
+    const f32x4 x = __builtin_nontemporal_load(src + c * job.copy_stride4);
+    const f32x4 y = __builtin_nontemporal_load(src + (c + 1) * job.copy_stride4);
+    const f32x4 z = __builtin_nontemporal_load(src + (c + 2) * job.copy_stride4);
+    v += x;
+    v += y;
+    v += z;
+  }
+  for (; c < job.n_copies; ++c) v += __builtin_nontemporal_load(src + c * job.copy_stride4);
+  size_t o = blk * job.dst_blk4 + i;   // in groups of four elements
+  const ConvertSeq& cs = job.cs;
   if (cs.rows_per_shard) {
-    const size_t e4 = i % cs.hs4, rh = i / cs.hs4;
-    const size_t h = rh % cs.heads, br = rh / cs.heads;
-    const size_t row = br % cs.rows, b = br / cs.rows;
-    const size_t shard = row / cs.rows_per_shard, sr = row - shard * cs.rows_per_shard;
-    o = (((shard * cs.bs + b) * cs.rows_per_shard + sr) * cs.seq_heads + cs.head0 + h) * cs.hs4 + e4;
+    const uint32_t rh = (uint32_t)(i / cs.hs4), e4 = (uint32_t)(i - (size_t)rh * cs.hs4);
+    const uint32_t br = rh / cs.heads, h = rh - br * cs.heads;
+    const uint32_t b = br / cs.rows, row = br - b * cs.rows;
+    const uint32_t shard = row / cs.rows_per_shard, sr = row - shard * cs.rows_per_shard;
+    o = blk * job.dst_blk4 + ((((size_t)shard * cs.bs + b) * cs.rows_per_shard + sr) * cs.seq_heads + cs.head0 + h) * cs.hs4 + e4;
   }
   if constexpr (sizeof(OutT) == 4) {
-    if (add_to_dst) v += *((const f32x4*)dst + o);
-    __builtin_nontemporal_store(v, (f32x4*)dst + o);
+    if (job.add_to_dst) v += *((const f32x4*)job.dst + o);
+    __builtin_nontemporal_store(v, (f32x4*)job.dst + o);
   } else {
     u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-    __builtin_nontemporal_store(pk, (u32x2*)dst + o);
+    __builtin_nontemporal_store(pk, (u32x2*)job.dst + o);
   }
 }
 
@@ -1105,7 +1186,7 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
                          const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks, int bs,
                          int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                          const usp_posdesc& qpos, int accumulate_dq, const int* accumulate_dkdv,
-                         hipStream_t stream, const BwdCopies* copies) {
+                         hipStream_t stream, const BwdCopies* copies, const BwdInPlace* io) {
   if (n_blocks < 1 || n_blocks > kMaxBlocks) return USP_ERR_UNSUPPORTED;
   // without room for copies: items are not cut, and heads that are split over workgroups meet through atomic adds
   const BwdCut cut = copies ? copies->cut : plan_bwd_cut(bs, Lq, Lk, hq, hkv, n_blocks, false, false);
@@ -1116,6 +1197,14 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.dkdv_part_stride = copies ? copies->dkdv_stride : 0;
   a.q = q; a.d_o = d_o; a.lse = lse; a.delta = delta;
   a.dq = dq;
+  a.o = io ? io->o : nullptr;
+  a.delta_out = io && io->o ? (float*)delta : nullptr;
+  a.q_pitch = io ? io->q_pitch : hq;
+  a.kv_pitch = io ? io->kv_pitch : hkv;
+  a.dq_bf16 = io && io->dq_bf16;
+  a.dkdv_bf16 = io && io->dkdv_bf16;
+  a.n_qblk = io ? io->n_qblk : 1;
+  if (a.n_qblk < 1 || a.n_qblk > kMaxBlocks) return USP_ERR_UNSUPPORTED;
   for (int j = 0; j < kMaxBlocks; ++j) {
     const int jj = j < n_blocks ? j : 0;
     a.k[j] = k_blocks[jj];
@@ -1132,13 +1221,16 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.accumulate = accumulate_dq;
   a.scale = scale;
   a.scale_log2 = scale * kLog2e;
-  a.qpos = PosDesc32{(int)qpos.start0, (int)qpos.len0, (int)qpos.start1, (int)qpos.len1};
+  for (int j = 0; j < kMaxBlocks; ++j) {
+    const usp_posdesc& qp = a.n_qblk > 1 && j < a.n_qblk ? io->qpos_blocks[j] : qpos;
+    a.qpos[j] = PosDesc32{(int)qp.start0, (int)qp.len0, (int)qp.start1, (int)qp.len1};
+  }
   a.ds = copies ? copies->ds : nullptr;
   a.ds_kt = (int)((Lk + 255) / 256) * 8;
   a.ds_qt8 = (int)((Lq + 255) / 256);
   auto launch_dq = [&]() -> int {
     a.n_tiles = (a.Lq + 255) / 256;
-    const int64_t grid = (int64_t)a.n_tiles * hq * bs * a.k_splits;
+    const int64_t grid = (int64_t)a.n_tiles * hq * bs * a.k_splits * a.n_qblk;
     if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
     // one workgroup per CU (256 VGPRs x 8 waves fill it), fewer when there are fewer items
     a.ticket_slot = ticket_slot_for(stream);
@@ -1200,37 +1292,37 @@ int launch_block_attn_bwd(const void* q, const void* k, const void* v, const voi
                               causal, qpos, accumulate_dq, &accumulate_dkdv, stream);
 }
 
-int launch_bwd_convert(const float* src, void* dst, size_t n, int out_dtype, hipStream_t stream, int n_copies,
-                       size_t copy_stride, int add_to_dst) {
-  return launch_bwd_convert2(src, dst, nullptr, nullptr, n, out_dtype, stream, n_copies, copy_stride, add_to_dst);
-}
-
-int launch_bwd_convert2(const float* src0, void* dst0, const float* src1, void* dst1, size_t n, int out_dtype,
-                        hipStream_t stream, int n_copies, size_t copy_stride, int add_to_dst) {
-  return launch_bwd_convert_seq(src0, dst0, src1, dst1, n, out_dtype, stream, n_copies, copy_stride, add_to_dst, nullptr,
-                                0, 0, 0, 0);
-}
-
-int launch_bwd_convert_seq(const float* src0, void* dst0, const float* src1, void* dst1, size_t n, int out_dtype,
-                           hipStream_t stream, int n_copies, size_t copy_stride, int add_to_dst, const SeqLayoutIO* seq,
-                           int bs, int64_t rows, int heads, int hs) {
-  ConvertSeq cs;
-  if (seq) {
-    if ((size_t)bs * rows * heads * hs != n || hs % 4) return USP_ERR_UNSUPPORTED;
-    cs.rows_per_shard = seq->rows_per_shard; cs.seq_heads = seq->heads; cs.head0 = seq->head0;
-    cs.heads = heads; cs.hs4 = hs / 4; cs.bs = bs; cs.rows = rows;
+int launch_bwd_convert(const ConvertTensor* tensors, int n_tensors, int out_dtype, hipStream_t stream) {
+  if (n_tensors < 1 || n_tensors > kMaxConvertJobs) return USP_ERR_UNSUPPORTED;
+  ConvertArgs a = {};
+  a.n_jobs = n_tensors;
+  uint64_t wgs = 0;
+  for (int j = 0; j < n_tensors; ++j) {
+    const ConvertTensor& t = tensors[j];
+    ConvertJob& job = a.job[j];
+    if (t.n_copies < 1 || t.n_blocks < 1 || ((t.copy_stride | t.n | t.src_blk | t.dst_blk) & 3)) return USP_ERR_UNSUPPORTED;
+    job.src = t.src; job.dst = t.dst;
+    job.n4 = t.n / 4; job.src_blk4 = t.src_blk / 4; job.dst_blk4 = t.dst_blk / 4; job.copy_stride4 = t.copy_stride / 4;
+    if (t.add_to_dst && out_dtype != USP_FP32) return USP_ERR_UNSUPPORTED;
+    job.n_copies = t.n_copies;
+    job.add_to_dst = t.add_to_dst;
+    if (t.seq) {
+      const uint64_t rows = (uint64_t)t.bs * t.rows * t.heads;
+      if (rows * t.hs != t.n || t.hs % 4 || rows > 0xffffffffull) return USP_ERR_UNSUPPORTED;
+      job.cs.rows_per_shard = t.seq->rows_per_shard; job.cs.seq_heads = t.seq->heads; job.cs.head0 = t.seq->head0;
+      job.cs.heads = t.heads; job.cs.hs4 = t.hs / 4; job.cs.bs = t.bs; job.cs.rows = (uint32_t)t.rows;
+    }
+    const uint64_t per_blk = (job.n4 + 255) / 256;
+    if (per_blk > 0x7fffffffull) return USP_ERR_UNSUPPORTED;
+    job.wgs_per_blk = (uint32_t)per_blk;
+    job.first_wg = (uint32_t)wgs;
+    wgs += per_blk * t.n_blocks;
+    if (wgs > 0x7fffffffull) return USP_ERR_UNSUPPORTED;
   }
-  if (add_to_dst && out_dtype != USP_FP32) return USP_ERR_UNSUPPORTED;
-  const size_t n4 = n / 4;
-  const size_t grid = (n4 + 255) / 256;
-  if (grid > 0x7fffffffull || n_copies < 1 || (copy_stride & 3)) return USP_ERR_UNSUPPORTED;
-  const dim3 g((unsigned)grid, src1 ? 2u : 1u);
   if (out_dtype == USP_FP32)
-    hipLaunchKernelGGL((bwd_convert_kernel<float>), g, dim3(256), 0, stream, src0, (float*)dst0, src1, (float*)dst1, n4,
-                       n_copies, copy_stride / 4, add_to_dst, cs);
+    hipLaunchKernelGGL((bwd_convert_kernel<float>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL((bwd_convert_kernel<__bf16>), g, dim3(256), 0, stream, src0, (__bf16*)dst0, src1, (__bf16*)dst1,
-                       n4, n_copies, copy_stride / 4, 0, cs);
+    hipLaunchKernelGGL((bwd_convert_kernel<__bf16>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
   return launch_status();
 }
 

@@ -992,12 +992,77 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
   const int hq = p->hc / U, hkv = p->hk / U;
   const float scale = p->scale == 0.0f ? 1.0f / sqrtf((float)p->hs) : p->scale;
   const size_t q_elems = (size_t)p->bs * Lq * hq * p->hs, kv_elems = (size_t)p->bs * Lq * hkv * p->hs;
+  const size_t es = dtype_size(p->dtype);
   auto slot = [&](int r, int u) { return (size_t)r * n_cols + (u - c0); };
+  if ((size_t)R * n_cols > USP_MAX_MERGE_PARTS) return USP_ERR_UNSUPPORTED;
 
-  // Ulysses degree 1: the all-to-alls are the identity, a rank's Q / dO and every K/V block are shards as they stand
-  const bool in_place = U == 1;
-  const char* const k_blocks = in_place ? (const char*)k : ws + f.k_head;   // block slot 0 of K, of V
-  const char* const v_blocks = in_place ? (const char*)v : ws + f.v_head;
+  // Results may only be written while inputs are still read if they share no memory.
+  const size_t q_all = q_elems * N * es, kv_all = kv_elems * N * es;
+  bool apart = true;
+  {
+    const void* const in[] = {q, k, v, o, d_o, lse};
+    const size_t in_bytes[] = {q_all, kv_all, kv_all, q_all, q_all, (size_t)p->bs * Lq * hq * N * sizeof(float)};
+    const void* const out[] = {dq, dk, dv};
+    const size_t out_bytes[] = {q_all, kv_all, kv_all};
+    for (int i = 0; i < 6; ++i)
+      for (int j = 0; j < 3; ++j)
+        if ((const char*)in[i] < (const char*)out[j] + out_bytes[j] && (const char*)out[j] < (const char*)in[i] + in_bytes[i])
+          apart = false;
+  }
+  // In place: with Ulysses degree 1 the all-to-alls are the identity; with a batch of one the shards of a ring row are
+  // contiguous, [Lq][heads][hs], and a rank's tensors are its heads of those rows.  The kernels then read Q, dO, O, K and V
+  // where the caller holds them (whole 16-byte chunks: tensors that do not lie on 16 bytes are staged instead).
+  const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)d_o) & 15) == 0;
+  const bool in_place = U == 1 || (p->bs == 1 && aligned && apart);
+  const bool direct = in_place && apart && R <= USP_MAX_RING_BLOCKS;   // results may leave the kernels as bf16, to their place
+  auto q_at = [&](const void* t, int r, int u) { return (char*)t + ((size_t)r * p->bs * Lq * p->hc + (size_t)u * hq) * p->hs * es; };
+  auto kv_at = [&](const void* t, int r, int u) { return (char*)t + ((size_t)r * p->bs * Lq * p->hk + (size_t)u * hkv) * p->hs * es; };
+  usp_posdesc ring_pos[USP_MAX_MERGE_PARTS];   // positions of every ring row
+  for (int r = 0; r < R; ++r) usp_local_positions(p, r, 0, nullptr, &ring_pos[r]);
+
+  // Every rank at once: in place, the tensors of all ranks are one dense problem of R query blocks, R key blocks and all
+  // heads, which goes through ONE launch pair instead of a pair (and conversions) per rank.  Not where dS is kept and a
+  // rank is long enough to gain by that (some 10 % of its time; a rank's launches and their tails cost some 40 us).
+  if (direct && N > 1 && rank_begin == 0 && rank_end == N) {
+    const double rank_us = 10.0 * p->hs * p->bs * hq * (double)Lq * (double)p->L * (p->causal ? 0.5 : 1.0) / 0.8e9;
+    BwdCopies c;
+    c.cut = plan_bwd_cut(p->bs, Lq, Lq, p->hc, p->hk, R, true, !p->causal);
+    c.cut.k_splits = 1;   // dQ leaves as bf16
+    auto n_copies = [&]() { return p->hc / p->hk / c.cut.heads_per_wg * c.cut.q_splits; };
+    if (n_copies() > f.dkdv_copies) c.cut.q_splits = 1;
+    const size_t delta_bytes = up256(q_elems / p->hs * N * sizeof(float));   // in the room from q_head up to the accumulators
+    if ((!f.copies.ds || rank_us < 400.0) && n_copies() <= f.dkdv_copies && delta_bytes <= f.dk_acc - f.q_head) {
+      const size_t kv_block = kv_elems * U;   // elements of a ring row, all heads
+      const int copies = n_copies();
+      c.dq_stride = 0;
+      c.dkdv_stride = kv_block;
+      const bool dkdv_bf16 = copies == 1;
+      const void *kb[USP_MAX_RING_BLOCKS], *vb[USP_MAX_RING_BLOCKS];
+      float *dkb[USP_MAX_RING_BLOCKS], *dvb[USP_MAX_RING_BLOCKS];
+      const int acc[USP_MAX_RING_BLOCKS] = {0};
+      for (int s = 0; s < R; ++s) {
+        kb[s] = kv_at(k, s, 0);
+        vb[s] = kv_at(v, s, 0);
+        dkb[s] = dkdv_bf16 ? (float*)kv_at(dk, s, 0) : (float*)(ws + f.dk_acc) + (size_t)s * copies * kv_block;
+        dvb[s] = dkdv_bf16 ? (float*)kv_at(dv, s, 0) : (float*)(ws + f.dv_acc) + (size_t)s * copies * kv_block;
+      }
+      const BwdInPlace io = {p->hc, p->hk, o, true, dkdv_bf16, R, ring_pos};
+      st = launch_ring_attn_bwd(q, kb, vb, ring_pos, R, d_o, lse, (float*)(ws + f.q_head), (float*)dq, dkb, dvb, p->bs, Lq, Lq,
+                                p->hc, p->hk, p->hs, scale, p->causal ? 1 : 0, ring_pos[0], 0, acc, stream, &c, &io);
+      if (st != USP_OK || dkdv_bf16) return st;
+      ConvertTensor t[2];
+      for (int i = 0; i < 2; ++i) {
+        t[i].src = i ? dvb[0] : dkb[0];
+        t[i].dst = i ? dv : dk;
+        t[i].n = t[i].copy_stride = t[i].dst_blk = kv_block;
+        t[i].n_copies = copies;
+        t[i].n_blocks = R;
+        t[i].src_blk = kv_block * copies;
+      }
+      return launch_bwd_convert(t, 2, p->dtype, stream);
+    }
+  }
+
   if (!in_place) {
     st = stage_kv_blocks(*p, k, v, ws + f.k_head, ws + f.v_head, f.kv_block_bytes, c0, c1, stream);
     if (st != USP_OK) return st;
@@ -1005,31 +1070,36 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
 
   // first contribution to a K/V block overwrites its accumulator, later ones add
   bool touched[USP_MAX_MERGE_PARTS] = {false};
-  if ((size_t)R * n_cols > USP_MAX_MERGE_PARTS) return USP_ERR_UNSUPPORTED;
 
+  const bool one_rank = rank_end - rank_begin == 1;
+  const bool dq_bf16 = direct && f.copies.cut.k_splits == 1;
+  const bool dkdv_bf16 = direct && one_rank && f.dkdv_copies == 1;
+  SeqLayoutIO seq_q = {(int)(p->L / N), p->hc, 0};
+  ConvertTensor convert[3];
+  int n_convert = 0;
   for (int rank = rank_begin; rank < rank_end; ++rank) {
     const int r = rank / U, u = rank % U;
-    const char* q_rank = (const char*)q + (size_t)rank * q_elems * dtype_size(p->dtype);      // used when in place
-    const char* do_rank = (const char*)d_o + (size_t)rank * q_elems * dtype_size(p->dtype);
+    const char* q_rank = in_place ? q_at(q, r, u) : ws + f.q_head;
+    const char* do_rank = in_place ? q_at(d_o, r, u) : ws + f.do_head;
     if (!in_place) {   // Q and dO of this rank to head layout: one geometry, one launch
       const void* srcs[2] = {q, d_o};
       void* dsts[2] = {ws + f.q_head, ws + f.do_head};
       st = launch_layout_a2a_multi(*p, p->hc, USP_SEQ_TO_HEAD, 2, srcs, dsts, rank, rank + 1, rank, stream);
       if (st != USP_OK) return st;
-      q_rank = ws + f.q_head;
-      do_rank = ws + f.do_head;
     }
-    // delta reads O (and dO) once: straight from the sequence-layout shards of the rank's Ulysses group, no copy of O
+    seq_q.head0 = u * hq;
+    const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * es;   // the Ulysses group's first shard
+    // D_i: formed by the dQ kernel where that runs first and finds O where it finds dO, else by a launch that reads O (and
+    // dO) once, straight from the sequence-layout shards
     float* delta = (float*)(ws + f.delta);
-    {
-      const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq};
-      const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * dtype_size(p->dtype);
-      st = launch_bwd_delta((const char*)o + group_off, (const char*)d_o + group_off, delta, p->bs, Lq, hq, p->hs, stream, &seq);
+    const bool delta_inside = in_place && !f.copies.ds && R <= USP_MAX_RING_BLOCKS;
+    if (!delta_inside) {
+      st = launch_bwd_delta((const char*)o + group_off, (const char*)d_o + group_off, delta, p->bs, Lq, hq, p->hs, stream, &seq_q);
       if (st != USP_OK) return st;
     }
-    usp_posdesc qd;
-    usp_local_positions(p, r, u, nullptr, &qd);
     const float* lse_rank = lse + (size_t)rank * p->bs * hq * Lq;
+    const BwdInPlace io = {in_place ? p->hc : hq, in_place ? p->hk : hkv, delta_inside ? (const void*)q_at(o, r, u) : nullptr,
+                           dq_bf16, dkdv_bf16, 1, nullptr};
     // The ring loop of this rank, step i on block s = (r - i) mod R: up to USP_MAX_RING_BLOCKS steps per launch
     // pair (the dQ kernel keeps its accumulator in registers across them, the dK/dV kernel spreads them over
     // its grid).  dQ adds after the first launch of this rank; a block's dK/dV add after the first rank that
@@ -1044,48 +1114,64 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
       int acc[USP_MAX_RING_BLOCKS];
       for (int j = 0; j < nb; ++j) {
         const int s = ((r - (i0 + j)) % R + R) % R;
-        usp_local_positions(p, s, u, nullptr, &kds[j]);
+        kds[j] = ring_pos[s];
         const size_t sl = slot(s, u);
-        kb[j] = k_blocks + sl * f.kv_block_bytes;
-        vb[j] = v_blocks + sl * f.kv_block_bytes;
-        dkb[j] = (float*)(ws + f.dk_acc + sl * f.kv_acc_bytes);
-        dvb[j] = (float*)(ws + f.dv_acc + sl * f.kv_acc_bytes);
+        kb[j] = in_place ? kv_at(k, s, u) : ws + f.k_head + sl * f.kv_block_bytes;
+        vb[j] = in_place ? kv_at(v, s, u) : ws + f.v_head + sl * f.kv_block_bytes;
+        dkb[j] = (float*)(dkdv_bf16 ? kv_at(dk, s, u) : ws + f.dk_acc + sl * f.kv_acc_bytes);
+        dvb[j] = (float*)(dkdv_bf16 ? kv_at(dv, s, u) : ws + f.dv_acc + sl * f.kv_acc_bytes);
         acc[j] = touched[sl] ? 1 : 0;
         touched[sl] = true;
       }
       st = launch_ring_attn_bwd(q_rank, kb, vb, kds, nb, do_rank, lse_rank, delta,
-                                (float*)(ws + f.dq_acc), dkb, dvb, p->bs, Lq, Lq, hq, hkv, p->hs, scale,
-                                p->causal ? 1 : 0, qd, i0 > 0 ? 1 : 0, acc, stream, &f.copies);
+                                (float*)(dq_bf16 ? q_at(dq, r, u) : ws + f.dq_acc), dkb, dvb, p->bs, Lq, Lq, hq, hkv, p->hs,
+                                scale, p->causal ? 1 : 0, ring_pos[r], i0 > 0 ? 1 : 0, acc, stream, &f.copies, &io);
       if (st != USP_OK) return st;
     }
     // dQ of this rank: the copies summed, converted and written straight to the sequence-layout shards of its Ulysses
     // group (the reverse all-to-all rides on the conversion's stores)
-    {
-      const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq};
-      const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * dtype_size(p->dtype);
-      st = launch_bwd_convert_seq((const float*)(ws + f.dq_acc), (char*)dq + group_off, nullptr, nullptr, q_elems, p->dtype,
-                                  stream, f.copies.cut.k_splits, f.copies.dq_stride, 0, &seq, p->bs, Lq, hq, p->hs);
-      if (st != USP_OK) return st;
+    if (!dq_bf16) {
+      ConvertTensor& t = convert[n_convert++];
+      t.src = (const float*)(ws + f.dq_acc);
+      t.dst = (char*)dq + group_off;
+      t.n = t.copy_stride = q_elems;
+      t.n_copies = f.copies.cut.k_splits;
+      t.seq = &seq_q;
+      t.bs = p->bs; t.rows = Lq; t.heads = hq; t.hs = p->hs;
+      if (!one_rank) {   // the next rank uses the accumulator
+        st = launch_bwd_convert(convert, n_convert, p->dtype, stream);
+        if (st != USP_OK) return st;
+        n_convert = 0;
+      }
     }
   }
 
   // dK, dV of every block the range touched: all ring rows of the columns whose ranks were run.  A range that
   // straddles ring rows without covering every column (say [U-1, U+1)) leaves columns between c0 and c1 unvisited:
   // their accumulators were never written, and their head slices of dk / dv stay as the caller left them.
-  for (int r = 0; r < R; ++r)
+  // The copies are summed, converted and written straight to the blocks' sequence-layout shards; a single rank's in one
+  // launch with its dQ.
+  if (!dkdv_bf16)
     for (int u = c0; u < c1; ++u) {
-      const int rank = r * U + u;
-      const size_t sl = slot(r, u);
-      if (!touched[sl]) continue;
-      // the copies summed, converted and written straight to the block's sequence-layout shards
-      const SeqLayoutIO seq = {(int)(p->L / N), p->hk, u * hkv};
-      const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hk * p->hs * dtype_size(p->dtype);
-      st = launch_bwd_convert_seq((const float*)(ws + f.dk_acc + sl * f.kv_acc_bytes), (char*)dk + group_off,
-                                  (const float*)(ws + f.dv_acc + sl * f.kv_acc_bytes), (char*)dv + group_off, kv_elems,
-                                  p->dtype, stream, f.dkdv_copies, f.copies.dkdv_stride, 0, &seq, p->bs, Lq, hkv, p->hs);
+      if (!touched[slot(0, u)]) continue;   // (a rank visits every ring row of its column)
+      const SeqLayoutIO seq_u = {(int)(p->L / N), p->hk, u * hkv};
+      for (int i = 0; i < 2; ++i) {
+        ConvertTensor& t = convert[n_convert++];
+        t.src = (const float*)(ws + (i ? f.dv_acc : f.dk_acc) + slot(0, u) * f.kv_acc_bytes);
+        t.dst = i ? dv : dk;
+        t.n = t.copy_stride = kv_elems;
+        t.n_copies = f.dkdv_copies;
+        t.n_blocks = R;
+        t.src_blk = n_cols * f.kv_acc_bytes / sizeof(float);
+        t.dst_blk = kv_elems * U;
+        t.seq = &seq_u;
+        t.bs = p->bs; t.rows = Lq; t.heads = hkv; t.hs = p->hs;
+      }
+      st = launch_bwd_convert(convert, n_convert, p->dtype, stream);
       if (st != USP_OK) return st;
+      n_convert = 0;
     }
-  return USP_OK;
+  return n_convert ? launch_bwd_convert(convert, n_convert, p->dtype, stream) : USP_OK;
 }
 
 extern "C" int usp_ring_attn_bwd(const void* q, const void* const* k_blocks, const void* const* v_blocks,
@@ -1216,18 +1302,24 @@ extern "C" int usp_ring_attn_bwd_ws(const void* q, const void* const* k_blocks, 
                                 hq, hkv, hs, scale, causal ? 1 : 0, qd, w.dq_bytes ? 0 : (accumulate_dq ? 1 : 0), acc,
                                 stream, &w.copies);
   if (st != USP_OK) return st;
+  auto sum_copies = [&](const float* src, float* dst, size_t n, int n_copies, int add) {
+    ConvertTensor t;
+    t.src = src; t.dst = dst;
+    t.n = t.copy_stride = n;
+    t.n_copies = n_copies;
+    t.add_to_dst = add ? 1 : 0;
+    return t;
+  };
   if (w.dq_bytes) {
-    st = launch_bwd_convert(dq_dst, dq, w.copies.dq_stride, USP_FP32, stream, w.copies.cut.k_splits, w.copies.dq_stride,
-                            accumulate_dq ? 1 : 0);
+    const ConvertTensor t = sum_copies(dq_dst, dq, w.copies.dq_stride, w.copies.cut.k_splits, accumulate_dq);
+    st = launch_bwd_convert(&t, 1, USP_FP32, stream);
     if (st != USP_OK) return st;
   }
   if (w.kv_bytes_per_block)
     for (int j = 0; j < n_blocks; ++j) {
-      st = launch_bwd_convert(dk_dst[j], dk_blocks[j], w.copies.dkdv_stride, USP_FP32, stream, w.dkdv_copies,
-                              w.copies.dkdv_stride, accumulate_dkdv[j] ? 1 : 0);
-      if (st != USP_OK) return st;
-      st = launch_bwd_convert(dv_dst[j], dv_blocks[j], w.copies.dkdv_stride, USP_FP32, stream, w.dkdv_copies,
-                              w.copies.dkdv_stride, accumulate_dkdv[j] ? 1 : 0);
+      const ConvertTensor t[2] = {sum_copies(dk_dst[j], dk_blocks[j], w.copies.dkdv_stride, w.dkdv_copies, accumulate_dkdv[j]),
+                                  sum_copies(dv_dst[j], dv_blocks[j], w.copies.dkdv_stride, w.dkdv_copies, accumulate_dkdv[j])};
+      st = launch_bwd_convert(t, 2, USP_FP32, stream);
       if (st != USP_OK) return st;
     }
   return USP_OK;

@@ -152,6 +152,18 @@ BwdCut plan_bwd_cut(int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int n_block
 // first and writes the dS blocks it forms, and the dQ kernel reads them back instead of forming S and dP again
 // (5 matrix products per tile pair instead of 7, for 2 bytes written and read per visible pair).
 struct BwdCopies { BwdCut cut; size_t dq_stride, dkdv_stride; void* ds = nullptr; };
+// Where a launch pair finds and leaves its tensors when that is not dense head layout.  Pitches: heads in a row of Q, dO, O
+// and of K, V (the pointers at the first head of the launch).  o: form D_i in the dQ kernel and leave it in delta (only
+// without kept dS, whose dK/dV kernel runs first).  dq_bf16 / dkdv_bf16: the results leave as bf16 in rows of the
+// same pitches, for outputs with one writer per element that nothing is added to.  n_qblk > 1: Q, dO, O, LSE, delta and dQ
+// hold the rows of that many ring ranks back to back, each with its own positions (no kept dS, dq_bf16).
+struct BwdInPlace {
+  int q_pitch, kv_pitch;
+  const void* o;
+  bool dq_bf16, dkdv_bf16;
+  int n_qblk;
+  const usp_posdesc* qpos_blocks;
+};
 inline bool bwd_keeps_ds(int hs) { return hs >= 128; }   // see plan_bwd
 inline size_t bwd_ds_bytes(int bs, int64_t Lq, int64_t Lk, int hq, int n_blocks) {
   return (size_t)bs * hq * n_blocks * (size_t)((Lk + 255) / 256 * 8) * (size_t)((Lq + 255) / 256 * 8) * 2048;
@@ -161,22 +173,29 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
                          const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks, int bs,
                          int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                          const usp_posdesc& qpos, int accumulate_dq, const int* accumulate_dkdv, hipStream_t stream,
-                         const struct BwdCopies* copies = nullptr);
+                         const struct BwdCopies* copies = nullptr, const struct BwdInPlace* io = nullptr);
 int launch_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                           const float* delta, float* dq, float* dk, float* dv, int bs, int64_t Lq, int64_t Lk, int hq,
                           int hkv, int hs, float scale, int causal, const usp_posdesc& qpos, const usp_posdesc& kpos,
                           int accumulate_dq, int accumulate_dkdv, hipStream_t stream);
-// dst[i] = sum over n_copies of src[c * copy_stride + i], converted (fp32 output: optionally added to dst[i])
-int launch_bwd_convert(const float* src, void* dst, size_t n, int out_dtype, hipStream_t stream, int n_copies = 1,
-                       size_t copy_stride = 0, int add_to_dst = 0);
-// The same for two tensors of the same size and copy layout in one launch (src1 == nullptr: one tensor).
-int launch_bwd_convert2(const float* src0, void* dst0, const float* src1, void* dst1, size_t n, int out_dtype,
-                        hipStream_t stream, int n_copies = 1, size_t copy_stride = 0, int add_to_dst = 0);
-// The same with the result written to the sequence-layout shards of the rank's Ulysses group (seq; dst0 / dst1 = the
-// group's first shard) instead of the dense [bs, rows, heads, hs] tensor the sources are: the reverse all-to-all of
-// Algorithm 1 rides on the conversion's stores.  seq = null: dense, as above.
-int launch_bwd_convert_seq(const float* src0, void* dst0, const float* src1, void* dst1, size_t n, int out_dtype,
-                           hipStream_t stream, int n_copies, size_t copy_stride, int add_to_dst, const SeqLayoutIO* seq,
-                           int bs, int64_t rows, int heads, int hs);
+// One tensor of a conversion: dst[i] = sum over n_copies of src[c * copy_stride + i], i < n, for n_blocks blocks src_blk and
+// dst_blk elements apart, converted (fp32 output: optionally added to dst).  seq: the result goes to the sequence-layout
+// shards of the rank's Ulysses group (dst = the group's first shard) instead of the dense [bs, rows, heads, hs] tensor the
+// source is: the reverse all-to-all of Algorithm 1 rides on the conversion's stores.
+struct ConvertTensor {
+  const float* src;
+  void* dst;
+  size_t n, copy_stride;
+  int n_copies;
+  int add_to_dst = 0;
+  int n_blocks = 1;
+  size_t src_blk = 0, dst_blk = 0;
+  const SeqLayoutIO* seq = nullptr;
+  int bs = 0;
+  int64_t rows = 0;
+  int heads = 0, hs = 0;
+};
+// Up to three of them in one launch.
+int launch_bwd_convert(const ConvertTensor* tensors, int n_tensors, int out_dtype, hipStream_t stream);
 
 }  // namespace usp
