@@ -43,6 +43,25 @@ __device__ inline int pos_max(const PosDesc32& d, int a, int b) {
   return m;
 }
 
+// Exact quotients of n < 2^31 by a divisor known on the host: one multiplication and a shift of scalar registers.  (A
+// division by a kernel argument is thirty vector instructions; the ten of them in front of the first load were 1 us.)
+struct FastDiv {
+  uint32_t d, mul;
+  int shift;
+  __device__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+  // n / d, and n becomes the remainder
+  __device__ int split(int& n) const {
+    const int q = div(n);
+    n -= q * (int)d;
+    return q;
+  }
+};
+inline FastDiv fast_div(int64_t d) {   // 1 <= d < 2^31: mul = ceil(2^(31 + s) / d) with 2^s >= d fits 32 bits, and its error times n stays below 2^(31 + s) / d
+  int s = 0;
+  while (((int64_t)1 << s) < d) ++s;
+  return FastDiv{(uint32_t)d, (uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), 31 + s};
+}
+
 // Tiles of a local index range that can hold a visible (query, key) pair: [a0,a1) then [b0,b1) (b may be empty).
 struct TileRanges { int a0, a1, b0, b1; };
 

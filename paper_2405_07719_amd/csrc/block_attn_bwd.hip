@@ -6,15 +6,17 @@
 //   dQ_i = scale sum_j dS_ij k_j,     dK_j = scale sum_i dS_ij q_i.
 // P and dS are exact per element, so the contributions of different K/V blocks simply add.
 //
-// Two kernels, both on v_mfma_f32_32x32x16_bf16 with fp32 accumulation:
-//   dq_kernel    a workgroup owns 256 query rows, walks the visible key tiles:  S^T = K Q^T, dP^T = V dO^T
-//                (lane = query, so L_i and D_i are per-lane scalars), dQ^T += K^T dS^T.  Deterministic.
-//   dkdv_kernel  a workgroup owns 256 keys of one KV head and walks the visible query tiles of one query
-//                head, or of all query heads of the group when the grid is large enough without splitting them:
-//                S = Q K^T, dP = dO V^T (lane = key; L_i and D_i enter through one extra MFMA k-step),
-//                dV^T += dO^T P, dK^T += Q^T dS; split heads meet through fp32 atomic adds.
-// Both take up to USP_MAX_RING_BLOCKS K/V blocks per launch (the ring loop of one rank).
-// In both, the accumulator layout of the first product is the B-operand layout of the second, and the
+// Two kinds of work items, both on v_mfma_f32_32x32x16_bf16 with fp32 accumulation:
+//   dQ       a workgroup owns 256 query rows, walks the visible key tiles:  S^T = K Q^T, dP^T = V dO^T
+//            (lane = query, so L_i and D_i are per-lane scalars), dQ^T += K^T dS^T.  Deterministic.
+//   dK/dV    a workgroup owns 256 keys of one KV head and walks the visible query tiles of one query
+//            head, or of several heads of the group when the grid is large enough without splitting them:
+//            S = Q K^T, dP = dO V^T (lane = key; L_i and D_i enter through one extra MFMA k-step),
+//            dV^T += dO^T P, dK^T += Q^T dS; split heads meet in copies of the outputs that are added up afterwards, or,
+//            without room for those, through fp32 atomic adds.
+// Both kinds run in ONE launch (bwd_kernel), unless dS is kept between them.
+// A launch covers up to USP_MAX_RING_BLOCKS K/V blocks (the ring loop of one rank) and as many query blocks (ranks).
+// In both kinds, the accumulator layout of the first product is the B-operand layout of the second, and the
 // transposed A operands come from LDS transpose reads of the same tile copy: a row stride of 2*hs + 48 bytes is
 // free of bank conflicts for the 16 B row reads and for the transpose reads alike.
 // Outputs are fp32 accumulators (overwrite or add), so ring steps and ranks can be summed before the
@@ -42,10 +44,6 @@ struct BwdArgs {
   const void* d_o;
   const float* lse;     // [bs,hq,Lq]  final LSE (natural log)
   const float* delta;   // [bs,hq,Lq]  D_i
-  // Given (dQ kernel running first): O, laid out like d_o.  The dQ kernel, which holds a row's dO anyway, then forms
-  // D_i itself and leaves it in delta_out (= delta) for the dK/dV kernel: a pass over O and dO and a launch less.
-  const void* o;
-  float* delta_out;
   float* dq;            // [bs,Lq,hq,hs]  fp32
   float* dk[kMaxBlocks];   // [bs,Lk,hkv,hs] fp32 per block
   float* dv[kMaxBlocks];
@@ -58,12 +56,13 @@ struct BwdArgs {
   int heads_per_wg;     // dkdv: query heads of a KV group walked by one workgroup (g: plain stores; else atomics)
   int acc_dkdv[kMaxBlocks];   // dkdv with heads_per_wg == g: 0 overwrite the block's dK/dV, 1 add to them
   float scale, scale_log2;
-  // Heads in a row of Q, dO and O, and of K and V: hq and hkv (dense), or all heads of the model where a batch of one is
-  // read straight from the sequence-layout shards (the pointers then are at the rank's first head).
-  int q_pitch, kv_pitch;
-  // Results that have one writer per element and need no fp32 sum leave as bf16, rows of q_pitch (kv_pitch) heads, at dq
-  // (dk and dv): no accumulator in memory and no conversion pass.
-  int dq_bf16, dkdv_bf16;
+  // Where row i of head h of (query or key block, batch entry) rb lies in Q and dO, and in K and V: rb, i and h times these
+  // many rows of hs elements.
+  int64_t q_rb, kv_rb;
+  int q_row, q_head, kv_row, kv_head;
+  // > 0: results that have one writer per element and need no fp32 sum leave as bf16, at dq (dk, dv), in rows of this many
+  // heads: no accumulator in memory and no conversion pass.
+  int dq_heads, dkdv_heads;
   // Query blocks of the launch: the ranks of a whole ring (their rows [n_qblk][bs][Lq][hq][hs], statistics
   // [n_qblk][bs][hq][Lq]), each with its own positions, or one.
   int n_qblk;
@@ -71,6 +70,7 @@ struct BwdArgs {
   PosDesc32 kpos[kMaxBlocks];
   // the workgroups of both kernels are persistent and draw their work items (attn_device.h); set per launch
   int ticket_slot, n_items, n_queues;
+  int n_dkdv_items;     // of a launch that holds both kinds: the first ones
   // Short sequences (few, long work items): the dQ kernel's items are cut into k_splits slices of their visible key
   // tiles, the dK/dV kernel's into q_splits slices of their visible query tiles.  Slice s of the dQ kernel writes the
   // s-th copy of dq, dq_part_stride elements further on; part (head split x q_splits + query slice) of the dK/dV
@@ -98,7 +98,8 @@ struct DqItemArgs {
   int bs, hq, hkv, g;
   int Lq, Lk;
   int n_tiles, n_blocks, causal, accumulate;
-  int q_pitch, kv_pitch;
+  int q_row, q_head, kv_row, kv_head;
+  int64_t q_rb, kv_rb;
   float scale, scale_log2;
   PosDesc32 qpos;
 };
@@ -112,7 +113,8 @@ struct DkdvItemArgs {
   int bs, hq, hkv, g;
   int Lq, Lk;
   int n_tiles, causal, heads_per_wg;
-  int q_pitch, kv_pitch;
+  int q_row, q_head, kv_row, kv_head;
+  int64_t q_rb, kv_rb;
   float scale, scale_log2;
   PosDesc32 qpos;
 };
@@ -171,83 +173,97 @@ __device__ inline void store_bf16_row(__bf16* dst, const f32x16 (&x)[DB], float 
 }
 
 // -------------------------------------------------------------------------------------------------
-// D_i = sum_e dO_ie * O_ie   (rows of [bs,L,h,hs] tensors -> [bs,h,L] fp32)
+// What the MFMA kernels need that the caller does not hold, in ONE launch: D_i = sum_e dO_ie O_ie of every query row
+// ([block][bs][heads][L] fp32), and, for tensors that they do not read in place, copies of Q, dO, K and V in head layout
+// (the forward all-to-all).  The launches it replaces (two layout launches and one for D) took 5 to 7 us each at L = 8192,
+// most of it starting up, and read dO twice.  One thread moves 16 bytes; bound by HBM.
+// The copies hold a head's rows back to back ([block][bs][head][row][hs]): the streams of the MFMA kernels then touch
+// every L2 channel evenly, where rows of four heads, 1 KiB apart, touch a quarter of them.
 // -------------------------------------------------------------------------------------------------
-// seq_n > 0: o and d_o are not dense [bs, L, h, hs] tensors but the sequence-layout shards of the rank's Ulysses group
-// ([U][bs][seq_n][seq_heads][hs], the rank's h heads from seq_head0 on): row i of the rank lies in shard i / seq_n.
+struct PrepareJob {
+  const __bf16* src;    // sequence layout [N][bs][n][heads][hs]
+  const __bf16* o;      // given: D of the rows (src is dO), O laid out like it
+  __bf16* dst;          // given: the copy
+  float* delta;
+  uint32_t rows;        // rows of hs elements in all: blocks x bs x L x heads of a rank
+  uint32_t first_wg;
+  FastDiv by_heads, by_L, by_bs, by_cols, by_n;   // heads of a rank, rows of a ring block, batch, columns, rows of a shard
+  int U, r0, c0, heads;  // ring row and Ulysses column of the first block; heads in a row of src
+};
+constexpr int kMaxPrepareJobs = 4;
+struct PrepareArgs { PrepareJob job[kMaxPrepareJobs]; int n_jobs; };
+
 template <int HS>
-__global__ __launch_bounds__(256) void bwd_delta_kernel(const __bf16* o, const __bf16* d_o, float* delta, int bs,
-                                                        int L, int h, int seq_n, int seq_heads, int seq_head0) {
-  constexpr int TPR = HS / 8;   // lanes per row, 8 elements each
-  const int64_t rows = (int64_t)bs * L * h;
-  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / TPR;
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(const PrepareArgs a) {
+  constexpr int TPR = HS / 8;   // threads per row, 8 elements each
+  int jn = 0;
+  while (jn + 1 < a.n_jobs && blockIdx.x >= a.job[jn + 1].first_wg) ++jn;
+  const PrepareJob& job = a.job[jn];
+  const uint32_t row = (blockIdx.x - job.first_wg) * (256 / TPR) + threadIdx.x / TPR;
   const int part = threadIdx.x % TPR;
-  float acc = 0.f;
-  if (row < rows) {
-    int64_t at = row;   // the row's place in o and d_o, in rows of HS elements
-    if (seq_n) {
-      const int64_t hh = row % h, i = (row / h) % L, b = row / ((int64_t)h * L);
-      const int64_t shard = i / seq_n, sr = i - shard * seq_n;
-      at = ((shard * bs + b) * seq_n + sr) * seq_heads + seq_head0 + hh;
-    }
-    const bf16x8 a = *(const bf16x8*)(o + at * HS + part * 8);
-    const bf16x8 b = *(const bf16x8*)(d_o + at * HS + part * 8);
+  if (row >= job.rows) return;   // whole rows of threads: the sums below stay inside one
+  int h = (int)row;
+  int i = job.by_heads.split(h);
+  int b = job.by_L.split(i);
+  int col = job.by_bs.split(b);
+  const int blk = col;                    // ring row major, then column
+  const int r = job.by_cols.split(col);
+  int s = i;
+  const int shard = job.by_n.split(s);
+  const int hl = (int)job.by_heads.d, bs = (int)job.by_bs.d, L = (int)job.by_L.d, n = (int)job.by_n.d;
+  const int64_t at = ((((int64_t)(job.r0 + r) * job.U + shard) * bs + b) * n + s) * job.heads + (job.c0 + col) * hl + h;
+  const int64_t out = ((int64_t)blk * bs + b) * hl + h;   // of [block][bs][head]
+  const bf16x8 x = __builtin_nontemporal_load((const bf16x8*)(job.src + at * HS) + part);
+  if (job.dst) *((bf16x8*)(job.dst + (out * L + i) * HS) + part) = x;
+  if (job.o) {
+    const bf16x8 y = __builtin_nontemporal_load((const bf16x8*)(job.o + at * HS) + part);
+    float acc = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc += (float)a[e] * (float)b[e];
-  }
+    for (int e = 0; e < 8; ++e) acc += (float)y[e] * (float)x[e];
 #pragma unroll
-  for (int m = TPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
-  if (row < rows && part == 0) {
-    const int64_t hh = row % h, i = (row / h) % L, b = row / ((int64_t)h * L);
-    delta[(b * h + hh) * L + i] = acc;
+    for (int m = TPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+    if (part == 0) job.delta[out * L + i] = acc;
   }
 }
 
 // -------------------------------------------------------------------------------------------------
 // dQ
 // -------------------------------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) BwdArgs* KernArgs;   // the kernel's argument segment
+
+// What an item's code needs to draw the workgroup's next item (one thread's business): asked for at the start of the
+// item's epilogue, read after its stores.
+struct NextItem {
+  ItemQueues queues;
+  int* slot;
+  unsigned* empty_queues;
+  __device__ unsigned begin() const { return threadIdx.x == 0 ? queues.begin(*empty_queues) : kNoDraw; }
+  __device__ void finish(unsigned own_ticket) const {
+    if (threadIdx.x != 0) return;
+    unsigned empty = *empty_queues;
+    *slot = queues.finish(own_ticket, empty);
+    *empty_queues = empty;
+  }
+};
+
+// One work item (number w among the dQ items) of a persistent workgroup.  Item order as the forward kernel's: KV group
+// fastest, then head within group, then query tile, heavy first.
 template <int HS>
-__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void bwd_dq_kernel(const BwdArgs) {
+__device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next, char* lds) {
   constexpr int NT = 512, BM = 256, KT = 32;
   constexpr int KSTEPS = HS / 16, DB = HS / 32;
   constexpr int USTR = HS * 2 + 48;                 // conflict-free for 16 B row reads and for transpose reads
   constexpr int CPR = HS / 8;                       // 16 B chunks per row
   constexpr int STAGE = 2 * KT * USTR;              // K, V
   static_assert(KT * CPR <= NT, "one chunk per thread and tensor");
-  __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
-
-  // Persistent workgroups, one per CU, that draw their work items as the forward kernel's do (same item order:
-  // KV group fastest, then head within group, then query tile, heavy first; the next item is asked for at the start
-  // of the epilogue and the answer read after the stores).
-  __shared__ int next_item[2];
-  __shared__ unsigned empty_queues;
-  int turn = 0;
-  if (threadIdx.x == 0) {
-    auto ap0 = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    // the first item is given, not drawn
-    next_item[0] = ItemQueues{ap0->ticket_slot, ap0->n_items, (int)gridDim.x, ap0->n_queues}.first_item(blockIdx.x);
-    empty_queues = 0;
-  }
-  for (;;) {
-    // arguments and lane constants are read / derived anew for every item, so that nothing derived from them is
-    // carried in registers across the item loop
-    auto ap = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ap));
-    const ItemQueues queues = {ap->ticket_slot, ap->n_items, (int)gridDim.x, ap->n_queues};
-    __syncthreads();   // the previous item is done with LDS, and next_item[turn] has been written
-    int w = __builtin_amdgcn_readfirstlane(next_item[turn]);
-    turn ^= 1;
-    if (w >= queues.n_items) {
-      if (threadIdx.x == 0) queues.leave();
-      break;
-    }
+  static_assert(2 * STAGE <= 256 * USTR, "the two stages lie in the dK/dV items' V rows");
     DqItemArgs a;
     a.q = ap->q; a.d_o = ap->d_o; a.lse = ap->lse; a.delta = ap->delta; a.dq = ap->dq;
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
-    a.n_tiles = ap->n_tiles; a.n_blocks = ap->n_blocks; a.causal = ap->causal; a.accumulate = ap->accumulate;
-    a.q_pitch = ap->q_pitch; a.kv_pitch = ap->kv_pitch;
+    a.n_tiles = (a.Lq + BM - 1) / BM; a.n_blocks = ap->n_blocks; a.causal = ap->causal; a.accumulate = ap->accumulate;
+    a.q_rb = ap->q_rb; a.q_row = ap->q_row; a.q_head = ap->q_head;
+    a.kv_rb = ap->kv_rb; a.kv_row = ap->kv_row; a.kv_head = ap->kv_head;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -273,14 +289,14 @@ void bwd_dq_kernel(const BwdArgs) {
     const int rr = min(qrow, a.Lq - 1);
     const int qp = a.causal ? pos_of(a.qpos, rr) : 0;
 
-    const size_t kv_head_off = ((size_t)b * a.Lk * a.kv_pitch + kvh) * HS * 2;   // bytes
+    const size_t kv_head_off = (size_t)(b * a.kv_rb + (int64_t)kvh * a.kv_head) * HS * 2;   // bytes
     const char* kg = nullptr;   // per block, set at the top of the block loop
     const char* vg = nullptr;
-    const uint32_t row_bytes = (uint32_t)a.kv_pitch * HS * 2;
+    const uint32_t row_bytes = (uint32_t)a.kv_row * HS * 2;
 
     bf16x8 qf[KSTEPS], dof[KSTEPS];
     {
-      const size_t off = (((size_t)(qblk * a.bs + b) * a.Lq + rr) * a.q_pitch + h) * HS + 8 * hl;
+      const size_t off = (size_t)((qblk * a.bs + b) * a.q_rb + (int64_t)rr * a.q_row + (int64_t)h * a.q_head) * HS + 8 * hl;
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) {
         qf[ks] = *(const bf16x8*)((const __bf16*)a.q + off + 16 * ks);
@@ -289,21 +305,7 @@ void bwd_dq_kernel(const BwdArgs) {
     }
     const size_t stat = ((size_t)(qblk * a.bs + b) * a.hq + h) * a.Lq + rr;
     const float lse = a.lse[stat];
-    float dlt;
-    if (ap->o) {   // D_i, the lane halves holding half of the row's dims each
-      const __bf16* o_row = (const __bf16*)ap->o + (((size_t)(qblk * a.bs + b) * a.Lq + rr) * a.q_pitch + h) * HS + 8 * hl;
-      float part[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        const bf16x8 ov = *(const bf16x8*)(o_row + 16 * ks);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) part[e] += (float)ov[e] * (float)dof[ks][e];
-      }
-      dlt = both_halves_sum(((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7])));
-      if (kslice == 0 && hl == 0 && qrow < a.Lq) ap->delta_out[stat] = dlt;
-    } else {
-      dlt = a.delta[stat];
-    }
+    float dlt = a.delta[stat];
     float l2 = (lse == -INFINITY) ? INFINITY : lse * kLog2e;   // a row that saw nothing: P = 0
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -429,10 +431,9 @@ void bwd_dq_kernel(const BwdArgs) {
     }
     }   // blocks
 
-    unsigned own_ticket = kNoDraw;
-    if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (qrow < a.Lq && ap->dq_bf16) {
-      store_bf16_row((__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + qrow) * a.q_pitch + h) * HS + 4 * hl, dq, a.scale);
+    const unsigned own_ticket = next.begin();
+    if (qrow < a.Lq && ap->dq_heads) {
+      store_bf16_row((__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + qrow) * ap->dq_heads + h) * HS + 4 * hl, dq, a.scale);
     } else if (qrow < a.Lq) {
       float* dst = a.dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
 #pragma unroll
@@ -446,12 +447,7 @@ void bwd_dq_kernel(const BwdArgs) {
           *d = v4;
         }
     }
-    if (threadIdx.x == 0) {
-      unsigned empty = empty_queues;
-      next_item[turn] = queues.finish(own_ticket, empty);
-      empty_queues = empty;
-    }
-  }   // next work item
+    next.finish(own_ticket);
 }
 
 // -------------------------------------------------------------------------------------------------
@@ -522,9 +518,8 @@ void bwd_dq_ds_kernel(const BwdArgs) {
     const bool wave_live = wave_row0 < Lq;
     const int wave_qmax = (causal && wave_live) ? pos_max(qpos, wave_row0, min(Lq, wave_row0 + 32)) : 0;
 
-    const int kv_pitch = ap->kv_pitch;
-    const size_t kv_head_off = ((size_t)b * Lk * kv_pitch + kvh) * HS * 2;   // bytes
-    const uint32_t row_bytes = (uint32_t)kv_pitch * HS * 2;
+    const size_t kv_head_off = (size_t)(b * ap->kv_rb + (int64_t)kvh * ap->kv_head) * HS * 2;   // bytes
+    const uint32_t row_bytes = (uint32_t)ap->kv_row * HS * 2;
     const char* kg = nullptr;      // per block
     const char* dsg = nullptr;     // per block: this wave's column of dS blocks (query tile qtile * 8 + wave)
     constexpr size_t ds_kt_stride = 8 * 2048;   // bytes from one key tile of 32 to the next: the workgroup's 8 blocks
@@ -617,8 +612,8 @@ void bwd_dq_ds_kernel(const BwdArgs) {
 
     unsigned own_ticket = kNoDraw;
     if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (qrow < Lq && ap->dq_bf16) {
-      store_bf16_row((__bf16*)ap->dq + (((size_t)b * Lq + qrow) * ap->q_pitch + h) * HS + 4 * hl, dq, ap->scale);
+    if (qrow < Lq && ap->dq_heads) {
+      store_bf16_row((__bf16*)ap->dq + (((size_t)b * Lq + qrow) * ap->dq_heads + h) * HS + 4 * hl, dq, ap->scale);
     } else if (qrow < Lq) {
       const float scale = ap->scale;
       const int accumulate = ap->accumulate;
@@ -643,14 +638,13 @@ void bwd_dq_ds_kernel(const BwdArgs) {
 }
 
 // -------------------------------------------------------------------------------------------------
-// dK, dV.  A workgroup owns 256 keys of one KV head (eight waves of 32 keys) and ONE query head of its
-// group, and walks the visible query tiles of 32 rows, double buffered in LDS.  The query heads of a
-// group (and nothing else) meet in the fp32 outputs through atomic adds: at most hq/hkv addends per
-// element, the only non-deterministic rounding of the backward.
+// dK, dV.  A workgroup owns 256 keys of one KV head (eight waves of 32 keys) and some query heads of its
+// group, and walks the visible query tiles of 32 rows, double buffered in LDS.
 // -------------------------------------------------------------------------------------------------
+// One work item (number w among the dK/dV items).  Item order: KV group fastest, then the head split, the slice of the
+// query tiles, the key tile (ascending: keys seen by the most queries first), the K/V block of the ring loop.
 template <int HS, bool WRITE_DS>
-__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void bwd_dkdv_kernel(const BwdArgs) {
+__device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& next, char* smem) {
   constexpr int NT = 512, BN = 256, QT = 32;
   constexpr int KSTEPS = HS / 16, DB = HS / 32;
   constexpr int USTR = HS * 2 + 48;        // one row stride that is conflict-free for 16 B row reads AND transpose reads
@@ -659,45 +653,15 @@ void bwd_dkdv_kernel(const BwdArgs) {
   constexpr int XOFF = HS * 2;             // byte offset, inside a row, of the extra k-step that holds the statistic
   static_assert(QT * CPR <= NT, "one chunk per thread and tensor");
   static_assert(XOFF + 32 <= USTR, "the extra k-step lives in the row padding");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  char* const v_s = smem;                  // [BN][USTR]: the workgroup's V rows, resident for the whole kernel
+  char* const v_s = smem;                  // [BN][USTR]: the workgroup's V rows, resident for the whole item
   char* const lds = smem + BN * USTR;      // [2][STAGE]
-
-  // the upper 16 bytes of the A rows' extra k-step (see stash below) are zeroed once: nothing else writes them
-  if (threadIdx.x < 4 * QT)
-    *(u32x4*)(lds + (threadIdx.x / QT) * (QT * USTR) + (threadIdx.x % QT) * USTR + XOFF + 16) = u32x4{0, 0, 0, 0};
-
-  // Persistent workgroups, one per CU, that draw their work items as the forward kernel's do.  Item order: KV
-  // group fastest, then the head split, then the key tile (ascending: keys seen by the most queries first), then
-  // the K/V block of the ring loop.
-  __shared__ int next_item[2];
-  __shared__ unsigned empty_queues;
-  int turn = 0;
-  if (threadIdx.x == 0) {
-    auto ap0 = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    // the first item is given, not drawn
-    next_item[0] = ItemQueues{ap0->ticket_slot, ap0->n_items, (int)gridDim.x, ap0->n_queues}.first_item(blockIdx.x);
-    empty_queues = 0;
-  }
-  for (;;) {
-    // arguments and lane constants are read / derived anew for every item, so that nothing derived from them is
-    // carried in registers across the item loop
-    auto ap = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ap));
-    const ItemQueues queues = {ap->ticket_slot, ap->n_items, (int)gridDim.x, ap->n_queues};
-    __syncthreads();   // the previous item is done with LDS, and next_item[turn] has been written
-    int w = __builtin_amdgcn_readfirstlane(next_item[turn]);
-    turn ^= 1;
-    if (w >= queues.n_items) {
-      if (threadIdx.x == 0) queues.leave();
-      break;
-    }
     DkdvItemArgs a;
     a.q = ap->q; a.d_o = ap->d_o; a.lse = ap->lse; a.delta = ap->delta;
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
-    a.n_tiles = ap->n_tiles; a.causal = ap->causal; a.heads_per_wg = ap->heads_per_wg;
-    a.q_pitch = ap->q_pitch; a.kv_pitch = ap->kv_pitch;
+    a.n_tiles = (a.Lk + BN - 1) / BN; a.causal = ap->causal; a.heads_per_wg = ap->heads_per_wg;
+    a.q_rb = ap->q_rb; a.q_row = ap->q_row; a.q_head = ap->q_head;
+    a.kv_rb = ap->kv_rb; a.kv_row = ap->kv_row; a.kv_head = ap->kv_head;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -727,11 +691,11 @@ void bwd_dkdv_kernel(const BwdArgs) {
     // do not fit 256 VGPRs: the spills' reloads share the counter of the prefetch loads and stall on them).
     bf16x8 kf[KSTEPS];
     {
-      const size_t off = (((size_t)b * a.Lk + kk) * a.kv_pitch + kvh) * HS + 8 * hl;
+      const size_t off = (size_t)(b * a.kv_rb + (int64_t)kk * a.kv_row + (int64_t)kvh * a.kv_head) * HS + 8 * hl;
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = *(const bf16x8*)((const __bf16*)ap->k[blk] + off + 16 * ks);
-      const char* vg = (const char*)((const __bf16*)ap->v[blk] + ((size_t)b * a.Lk * a.kv_pitch + kvh) * HS);
-      const uint32_t v_row_bytes = (uint32_t)a.kv_pitch * HS * 2;
+      const char* vg = (const char*)((const __bf16*)ap->v[blk] + (size_t)(b * a.kv_rb + (int64_t)kvh * a.kv_head) * HS);
+      const uint32_t v_row_bytes = (uint32_t)a.kv_row * HS * 2;
 #pragma unroll
       for (int c = 0; c < BN * CPR / NT; ++c) {
         const int r = (tid + c * NT) / CPR, col = (tid + c * NT) % CPR;
@@ -788,7 +752,7 @@ void bwd_dkdv_kernel(const BwdArgs) {
     float streg = 0.f;
     // tile base addresses are wave-uniform; the per-thread byte offset is the same for every tile, clamped by a
     // min on the offset for rows past the last query (offsets grow with the row)
-    const uint32_t row_bytes = (uint32_t)a.q_pitch * HS * 2;
+    const uint32_t row_bytes = (uint32_t)a.q_row * HS * 2;
     const uint32_t st_off = (uint32_t)st_row * row_bytes + st_col * 16;
     const char* qg = nullptr;      // per query head, set at the top of the head loop
     const char* og = nullptr;
@@ -832,8 +796,9 @@ void bwd_dkdv_kernel(const BwdArgs) {
     for (int hh = 0; hh < a.heads_per_wg; ++hh) {
     const int h = kvh * a.g + hg0 + hh;
     const size_t qb = (size_t)(qblk * a.bs + b);
-    qg = (const char*)((const __bf16*)a.q + (qb * a.Lq * a.q_pitch + h) * HS);
-    og = (const char*)((const __bf16*)a.d_o + (qb * a.Lq * a.q_pitch + h) * HS);
+    const size_t q_off = (qb * (size_t)a.q_rb + (size_t)h * a.q_head) * HS;
+    qg = (const char*)((const __bf16*)a.q + q_off);
+    og = (const char*)((const __bf16*)a.d_o + q_off);
     stat_g = (tid < QT ? a.lse : a.delta) + (qb * a.hq + h) * a.Lq;
     const int it0 = (int)((int64_t)nt * qs / q_splits), it1 = (int)((int64_t)nt * (qs + 1) / q_splits);
     // where the dS blocks of this head and K/V block begin
@@ -978,10 +943,9 @@ void bwd_dkdv_kernel(const BwdArgs) {
     }   // query heads
     }   // query blocks
 
-    unsigned own_ticket = kNoDraw;
-    if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (key_ok && ap->dkdv_bf16) {
-      const size_t off = (((size_t)b * a.Lk + key) * a.kv_pitch + kvh) * HS + 4 * hl;
+    const unsigned own_ticket = next.begin();
+    if (key_ok && ap->dkdv_heads) {
+      const size_t off = (((size_t)b * a.Lk + key) * ap->dkdv_heads + kvh) * HS + 4 * hl;
       store_bf16_row((__bf16*)ap->dk[blk] + off, dk, a.scale);
       store_bf16_row((__bf16*)ap->dv[blk] + off, dv, 1.f);
     } else if (key_ok) {
@@ -1020,10 +984,51 @@ void bwd_dkdv_kernel(const BwdArgs) {
       }
     }
 
-    if (threadIdx.x == 0) {
-      unsigned empty = empty_queues;
-      next_item[turn] = queues.finish(own_ticket, empty);
-      empty_queues = empty;
+    next.finish(own_ticket);
+}
+
+// Persistent workgroups, one per CU (255 registers x 8 waves fill it), that draw their work items as the forward kernel's
+// do.  PAIR: the dK/dV items and, after them, the dQ items of a launch pair whose kernels do not depend on each other: the
+// dQ items fill the CUs that the last, long dK/dV items leave idle, so that a pair has one tail instead of two and its items
+// need less cutting (fewer fp32 copies of the outputs).  Measured, one of eight Ulysses ranks, the whole backward: two
+// launches 302 us at L = 8192 and 172 at L = 4640 (two heads), one 273 and 95; L = 32768 3275 and 3243.  !PAIR: dK/dV items that leave their dS behind for bwd_dq_ds_kernel.
+template <int HS, bool PAIR>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void bwd_kernel(const BwdArgs) {
+  constexpr int QT = 32, BN = 256, USTR = HS * 2 + 48, XOFF = HS * 2;   // as in dkdv_item
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // the upper 16 bytes of the A rows' extra k-step (see dkdv_item) are zeroed once: nothing else writes them
+  if (threadIdx.x < 4 * QT)
+    *(u32x4*)(smem + BN * USTR + (threadIdx.x / QT) * (QT * USTR) + (threadIdx.x % QT) * USTR + XOFF + 16) = u32x4{0, 0, 0, 0};
+
+  __shared__ int next_item[2];
+  __shared__ unsigned empty_queues;
+  int turn = 0;
+  if (threadIdx.x == 0) {
+    auto ap0 = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    // the first item is given, not drawn
+    next_item[0] = ItemQueues{ap0->ticket_slot, ap0->n_items, (int)gridDim.x, ap0->n_queues}.first_item(blockIdx.x);
+    empty_queues = 0;
+  }
+  for (;;) {
+    // arguments and lane constants are read / derived anew for every item, so that nothing derived from them is
+    // carried in registers across the item loop
+    auto ap = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    const ItemQueues queues = {ap->ticket_slot, ap->n_items, (int)gridDim.x, ap->n_queues};
+    __syncthreads();   // the previous item is done with LDS, and next_item[turn] has been written
+    const int w = __builtin_amdgcn_readfirstlane(next_item[turn]);
+    turn ^= 1;
+    if (w >= queues.n_items) {
+      if (threadIdx.x == 0) queues.leave();
+      break;
+    }
+    const NextItem next = {queues, &next_item[turn], &empty_queues};
+    if constexpr (PAIR) {
+      if (w < ap->n_dkdv_items) dkdv_item<HS, false>(ap, w, next, smem);
+      else dq_item<HS>(ap, w - ap->n_dkdv_items, next, smem);   // its stages lie where a dK/dV item has its V rows
+    } else {
+      dkdv_item<HS, true>(ap, w, next, smem);
     }
   }   // next work item
 }
@@ -1044,6 +1049,7 @@ struct ConvertJob {
   const float* src;
   void* dst;
   size_t n4, src_blk4, dst_blk4, copy_stride4;
+  uint64_t absent;   // bit b: block b has no source, its elements are zero
   uint32_t wgs_per_blk, first_wg;
   int n_copies, add_to_dst;
   ConvertSeq cs;
@@ -1061,9 +1067,10 @@ __global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
   const size_t i = (size_t)(wg - blk * job.wgs_per_blk) * 256 + threadIdx.x;
   if (i >= job.n4) return;
   const f32x4* src = (const f32x4*)job.src + blk * job.src_blk4 + i;
-  f32x4 v = __builtin_nontemporal_load(src);
+  const int n_copies = blk < 64 && (job.absent >> blk & 1) ? 0 : job.n_copies;
+  f32x4 v = n_copies ? __builtin_nontemporal_load(src) : f32x4{0.f, 0.f, 0.f, 0.f};
   int c = 1;
-  for (; c + 3 <= job.n_copies; c += 3) {   // three loads in flight, added in the order of the copies
+  for (; c + 3 <= n_copies; c += 3) {   // three loads in flight, added in the order of the copies
     const f32x4 x = __builtin_nontemporal_load(src + c * job.copy_stride4);
     const f32x4 y = __builtin_nontemporal_load(src + (c + 1) * job.copy_stride4);
     const f32x4 z = __builtin_nontemporal_load(src + (c + 2) * job.copy_stride4);
@@ -1071,7 +1078,7 @@ __global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
     v += y;
     v += z;
   }
-  for (; c < job.n_copies; ++c) v += __builtin_nontemporal_load(src + c * job.copy_stride4);
+  for (; c < n_copies; ++c) v += __builtin_nontemporal_load(src + c * job.copy_stride4);
   size_t o = blk * job.dst_blk4 + i;   // in groups of four elements
   const ConvertSeq& cs = job.cs;
   if (cs.rows_per_shard) {
@@ -1090,13 +1097,13 @@ __global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
   }
 }
 
-template <int HS, bool WRITE_DS>
-int launch_dkdv(const BwdArgs& a, int64_t grid, hipStream_t stream) {
+template <int HS, bool PAIR>
+int launch_bwd(const BwdArgs& a, int64_t grid, hipStream_t stream) {
   constexpr int USTR = HS * 2 + 48;
   constexpr size_t lds = 256 * USTR + 2 * (2 * 32 * USTR);
   static LdsLimitRaised lds_limit;   // per kernel instance
-  if (!raise_dynamic_lds_limit((const void*)bwd_dkdv_kernel<HS, WRITE_DS>, lds, lds_limit)) return USP_ERR_LAUNCH;
-  hipLaunchKernelGGL((bwd_dkdv_kernel<HS, WRITE_DS>), dim3((unsigned)grid), dim3(512), lds, stream, a);
+  if (!raise_dynamic_lds_limit((const void*)bwd_kernel<HS, PAIR>, lds, lds_limit)) return USP_ERR_LAUNCH;
+  hipLaunchKernelGGL((bwd_kernel<HS, PAIR>), dim3((unsigned)grid), dim3(512), lds, stream, a);
   return launch_status();
 }
 
@@ -1113,19 +1120,29 @@ int launch_dq_ds(const BwdArgs& a, int64_t grid, hipStream_t stream) {
 
 }  // namespace
 
-int launch_bwd_delta(const void* o, const void* d_o, float* delta, int bs, int64_t L, int h, int hs,
-                     hipStream_t stream, const SeqLayoutIO* seq) {
-  const int seq_n = seq ? seq->rows_per_shard : 0, seq_heads = seq ? seq->heads : 0, seq_head0 = seq ? seq->head0 : 0;
-  const int64_t rows = (int64_t)bs * L * h;
-  const int tpr = hs / 8;
-  const int64_t grid = (rows * tpr + 255) / 256;
-  if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
+int launch_bwd_prepare(const PrepareTensor* tensors, int n_tensors, int bs, int64_t L, int hs, hipStream_t stream) {
+  if (n_tensors < 1 || n_tensors > kMaxPrepareJobs) return USP_ERR_UNSUPPORTED;
+  PrepareArgs a = {};
+  a.n_jobs = n_tensors;
+  uint64_t wgs = 0;
+  const int rows_per_wg = 256 / (hs / 8);
+  for (int j = 0; j < n_tensors; ++j) {
+    const PrepareTensor& t = tensors[j];
+    PrepareJob& job = a.job[j];
+    const uint64_t rows = (uint64_t)t.n_rings * t.n_cols * bs * L * t.heads_per_rank;
+    if (rows >= 1ull << 31) return USP_ERR_UNSUPPORTED;
+    job.src = (const __bf16*)t.src; job.o = (const __bf16*)t.o; job.dst = (__bf16*)t.dst; job.delta = t.delta;
+    job.rows = (uint32_t)rows;
+    job.first_wg = (uint32_t)wgs;
+    job.by_heads = fast_div(t.heads_per_rank); job.by_L = fast_div(L); job.by_bs = fast_div(bs);
+    job.by_cols = fast_div(t.n_cols); job.by_n = fast_div(L / t.U);
+    job.U = t.U; job.r0 = t.r0; job.c0 = t.c0; job.heads = t.heads;
+    wgs += (rows + rows_per_wg - 1) / rows_per_wg;
+  }
   if (hs == 128)
-    hipLaunchKernelGGL((bwd_delta_kernel<128>), dim3((unsigned)grid), dim3(256), 0, stream, (const __bf16*)o,
-                       (const __bf16*)d_o, delta, bs, (int)L, h, seq_n, seq_heads, seq_head0);
+    hipLaunchKernelGGL((bwd_prepare_kernel<128>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL((bwd_delta_kernel<64>), dim3((unsigned)grid), dim3(256), 0, stream, (const __bf16*)o,
-                       (const __bf16*)d_o, delta, bs, (int)L, h, seq_n, seq_heads, seq_head0);
+    hipLaunchKernelGGL((bwd_prepare_kernel<64>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
   return launch_status();
 }
 
@@ -1186,7 +1203,7 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
                          const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks, int bs,
                          int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                          const usp_posdesc& qpos, int accumulate_dq, const int* accumulate_dkdv,
-                         hipStream_t stream, const BwdCopies* copies, const BwdInPlace* io) {
+                         hipStream_t stream, const BwdCopies* copies, const BwdPlace* io) {
   if (n_blocks < 1 || n_blocks > kMaxBlocks) return USP_ERR_UNSUPPORTED;
   // without room for copies: items are not cut, and heads that are split over workgroups meet through atomic adds
   const BwdCut cut = copies ? copies->cut : plan_bwd_cut(bs, Lq, Lk, hq, hkv, n_blocks, false, false);
@@ -1197,12 +1214,11 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.dkdv_part_stride = copies ? copies->dkdv_stride : 0;
   a.q = q; a.d_o = d_o; a.lse = lse; a.delta = delta;
   a.dq = dq;
-  a.o = io ? io->o : nullptr;
-  a.delta_out = io && io->o ? (float*)delta : nullptr;
-  a.q_pitch = io ? io->q_pitch : hq;
-  a.kv_pitch = io ? io->kv_pitch : hkv;
-  a.dq_bf16 = io && io->dq_bf16;
-  a.dkdv_bf16 = io && io->dkdv_bf16;
+  const RowPlace rq = io ? io->q : RowPlace{Lq * hq, hq, 1}, rk = io ? io->kv : RowPlace{Lk * hkv, hkv, 1};   // (dense)
+  a.q_rb = rq.block; a.q_row = rq.row; a.q_head = rq.head;
+  a.kv_rb = rk.block; a.kv_row = rk.row; a.kv_head = rk.head;
+  a.dq_heads = io ? io->dq_heads : 0;
+  a.dkdv_heads = io ? io->dkdv_heads : 0;
   a.n_qblk = io ? io->n_qblk : 1;
   if (a.n_qblk < 1 || a.n_qblk > kMaxBlocks) return USP_ERR_UNSUPPORTED;
   for (int j = 0; j < kMaxBlocks; ++j) {
@@ -1228,60 +1244,45 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.ds = copies ? copies->ds : nullptr;
   a.ds_kt = (int)((Lk + 255) / 256) * 8;
   a.ds_qt8 = (int)((Lq + 255) / 256);
-  auto launch_dq = [&]() -> int {
-    a.n_tiles = (a.Lq + 255) / 256;
-    const int64_t grid = (int64_t)a.n_tiles * hq * bs * a.k_splits * a.n_qblk;
-    if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
-    // one workgroup per CU (256 VGPRs x 8 waves fill it), fewer when there are fewer items
-    a.ticket_slot = ticket_slot_for(stream);
-    a.n_items = (int)grid;
-    a.n_queues = std::gcd(dev::kMaxItemQueues, bs * hkv);
-    const unsigned n_wgs = (unsigned)std::min<int64_t>(grid, compute_units());
-    int st;
-    if (a.ds) {
-      st = hs == 128 ? launch_dq_ds<128>(a, n_wgs, stream) : launch_dq_ds<64>(a, n_wgs, stream);
-    } else {
-      if (hs == 128)
-        hipLaunchKernelGGL((bwd_dq_kernel<128>), dim3(n_wgs), dim3(512), 0, stream, a);
-      else
-        hipLaunchKernelGGL((bwd_dq_kernel<64>), dim3(n_wgs), dim3(512), 0, stream, a);
-      st = launch_status();
+  // work items of both kinds; one workgroup per CU draws them (fewer when there are fewer items)
+  const int64_t q_tiles = (Lq + 255) / 256, k_tiles = (Lk + 255) / 256;
+  const int64_t dq_items = q_tiles * hq * bs * a.k_splits * a.n_qblk;
+  a.heads_per_wg = cut.heads_per_wg;
+  const int head_splits = a.g / a.heads_per_wg;
+  const int64_t dkdv_items = k_tiles * hkv * bs * n_blocks * head_splits * a.q_splits;
+  if (dq_items + dkdv_items > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
+  for (int j = 0; j < kMaxBlocks; ++j) a.acc_dkdv[j] = accumulate_dkdv[j < n_blocks ? j : 0];
+  if (head_splits > 1 && !copies) {   // atomic adds need accumulators that start from zero
+    const size_t n4 = (size_t)bs * Lk * hkv * hs / 4;
+    const size_t zg = (n4 + 255) / 256;
+    if (zg > 0x7fffffffull) return USP_ERR_UNSUPPORTED;
+    for (int j = 0; j < n_blocks; ++j) {
+      if (accumulate_dkdv[j]) continue;
+      hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)zg), dim3(256), 0, stream, (f32x4*)dk_blocks[j], n4);
+      hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)zg), dim3(256), 0, stream, (f32x4*)dv_blocks[j], n4);
     }
-    return st;
-  };
-  auto launch_dkdv_pair = [&]() -> int {
-    a.n_tiles = (a.Lk + 255) / 256;
-    const int64_t unsplit = (int64_t)a.n_tiles * hkv * bs * n_blocks;
-    a.heads_per_wg = cut.heads_per_wg;
-    for (int j = 0; j < kMaxBlocks; ++j) a.acc_dkdv[j] = accumulate_dkdv[j < n_blocks ? j : 0];
-    if (a.heads_per_wg != a.g && !copies) {   // atomic adds need accumulators that start from zero
-      const size_t n4 = (size_t)bs * Lk * hkv * hs / 4;
-      const size_t zg = (n4 + 255) / 256;
-      if (zg > 0x7fffffffull) return USP_ERR_UNSUPPORTED;
-      for (int j = 0; j < n_blocks; ++j) {
-        if (accumulate_dkdv[j]) continue;
-        hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)zg), dim3(256), 0, stream, (f32x4*)dk_blocks[j], n4);
-        hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)zg), dim3(256), 0, stream, (f32x4*)dv_blocks[j], n4);
-      }
-    }
-    const int64_t grid = unsplit * (a.g / a.heads_per_wg) * a.q_splits;
-    if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
-    // one workgroup per CU (256 VGPRs x 8 waves fill it), fewer when there are fewer items
+  }
+  a.n_tiles = (int)q_tiles;   // (of bwd_dq_ds_kernel)
+  a.n_dkdv_items = (int)dkdv_items;
+  // workgroups that walk the same query head share its Q / dO rows through the XCD's L2: one queue per
+  // (KV group, head split) value, the two fastest indices of a dK/dV item's number (and a divisor of their count)
+  a.n_queues = std::gcd(dev::kMaxItemQueues, bs * hkv * head_splits);
+  auto prepare = [&](int64_t items) {
     a.ticket_slot = ticket_slot_for(stream);
-    a.n_items = (int)grid;
-    // workgroups that walk the same query head share its Q / dO rows through the XCD's L2: one queue per
-    // (KV group, head split) value, the two fastest indices of the item number
-    a.n_queues = std::gcd(dev::kMaxItemQueues, bs * hkv * (a.g / a.heads_per_wg));
-    const int64_t n_wgs = std::min<int64_t>(grid, compute_units());
-    return a.ds ? (hs == 128 ? launch_dkdv<128, true>(a, n_wgs, stream) : launch_dkdv<64, true>(a, n_wgs, stream))
-                : (hs == 128 ? launch_dkdv<128, false>(a, n_wgs, stream) : launch_dkdv<64, false>(a, n_wgs, stream));
+    a.n_items = (int)items;
+    return std::min<int64_t>(items, compute_units());
   };
-  // with dS kept, the dK/dV kernel (which writes it) runs first; otherwise the two are independent
-  int st = a.ds ? launch_dkdv_pair() : launch_dq();
+  if (!a.ds) {
+    const int64_t n_wgs = prepare(dkdv_items + dq_items);
+    return hs == 128 ? launch_bwd<128, true>(a, n_wgs, stream) : launch_bwd<64, true>(a, n_wgs, stream);
+  }
+  // dS kept: the dK/dV kernel, which writes it, and then the dQ kernel, which reads it
+  int64_t n_wgs = prepare(dkdv_items);
+  const int st = hs == 128 ? launch_bwd<128, false>(a, n_wgs, stream) : launch_bwd<64, false>(a, n_wgs, stream);
   if (st != USP_OK) return st;
-  st = a.ds ? launch_dq() : launch_dkdv_pair();
-  if (st != USP_OK) return st;
-  return launch_status();
+  a.n_queues = std::gcd(dev::kMaxItemQueues, bs * hkv);
+  n_wgs = prepare(dq_items);
+  return hs == 128 ? launch_dq_ds<128>(a, n_wgs, stream) : launch_dq_ds<64>(a, n_wgs, stream);
 }
 
 int launch_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
@@ -1301,7 +1302,7 @@ int launch_bwd_convert(const ConvertTensor* tensors, int n_tensors, int out_dtyp
     const ConvertTensor& t = tensors[j];
     ConvertJob& job = a.job[j];
     if (t.n_copies < 1 || t.n_blocks < 1 || ((t.copy_stride | t.n | t.src_blk | t.dst_blk) & 3)) return USP_ERR_UNSUPPORTED;
-    job.src = t.src; job.dst = t.dst;
+    job.src = t.src; job.dst = t.dst; job.absent = t.absent;
     job.n4 = t.n / 4; job.src_blk4 = t.src_blk / 4; job.dst_blk4 = t.dst_blk / 4; job.copy_stride4 = t.copy_stride / 4;
     if (t.add_to_dst && out_dtype != USP_FP32) return USP_ERR_UNSUPPORTED;
     job.n_copies = t.n_copies;

@@ -485,19 +485,21 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   return best;
 }
 
+// (the scale plays no part in how a problem is cut)
+bool same_problem(const usp_problem& a, const usp_problem& b) {
+  return a.bs == b.bs && a.L == b.L && a.hc == b.hc && a.hk == b.hk && a.hs == b.hs && a.ulysses == b.ulysses &&
+         a.ring == b.ring && a.causal == b.causal && a.split == b.split && a.dtype == b.dtype;
+}
+
 // Playing a launch through takes the host 0.1-0.3 ms per ring rank, as long as a short launch itself: the answers
 // for the last problems seen are kept (every ring rank's, worked out at the first question about the problem).
 HeavyChoice heavy_choice(const usp_problem& p, int r) {
   struct Entry { usp_problem p; std::vector<HeavyChoice> per_rank; };
   static std::mutex mu;
   static std::vector<Entry> seen;
-  auto same = [](const usp_problem& a, const usp_problem& b) {
-    return a.bs == b.bs && a.L == b.L && a.hc == b.hc && a.hk == b.hk && a.hs == b.hs && a.ulysses == b.ulysses &&
-           a.ring == b.ring && a.causal == b.causal && a.split == b.split && a.dtype == b.dtype;   // (the scale plays no part)
-  };
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : seen)
-    if (same(e.p, p)) return e.per_rank[r];
+    if (same_problem(e.p, p)) return e.per_rank[r];
   if (seen.size() >= 64) seen.erase(seen.begin());
   Entry e{p, {}};
   for (int rr = 0; rr < p.ring; ++rr) e.per_rank.push_back(work_out_heavy_choice(p, rr));
@@ -877,7 +879,8 @@ extern "C" int usp_attn_delta(const void* o, const void* d_o, float* delta, int 
   if (bs < 1 || L < 1 || h < 1) return USP_ERR_SHAPE;
   if (hs != 64 && hs != 128) return USP_ERR_UNSUPPORTED;
   if (L >= (int64_t)1 << 31) return USP_ERR_UNSUPPORTED;
-  return launch_bwd_delta(o, d_o, delta, bs, L, h, hs, (hipStream_t)stream);
+  const PrepareTensor t = {d_o, o, nullptr, delta, 1, 0, 1, 0, 1, h, h};
+  return launch_bwd_prepare(&t, 1, bs, L, hs, (hipStream_t)stream);
 }
 
 extern "C" int usp_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
@@ -956,6 +959,93 @@ BwdPlan plan_bwd(const usp_problem& p, int n_cols) {
   return f;
 }
 
+// How the launch pair of ring rank r (r < 0: of all ranks at once) is cut: within what the workspace was sized for (`most`),
+// the number of slices and of heads per item under which the pair ends first.  dQ items fill the gaps behind the dK/dV items,
+// so that long sequences need no slices where the two kernels on their own took two to four of each, and every slice
+// saved is a copy of the outputs less.  Worked out by playing the launch through, as work_out_heavy_choice() does for the
+// forward: 10 us per dQ item and 1.2 per 32 of its keys, 6 and 1.68 per 32 queries of a dK/dV item (0.62 of these at head
+// size 64), the copies at 4.5 TB/s and 6 us for their launch.  Against 130 measured cuts of eleven problems, L = 2048 to
+// 16384, this is off by 6 % on average and picks a cut within 0.3 % of the best one (one of eight Ulysses ranks of L = 8192:
+// 4 + 4 slices 298 us, 2 + 2 279; 32 heads of L = 2048: 2 + 2 slices 217 us, none 168).
+BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
+  const int64_t Lq = p.L / p.ring, T = (Lq + 255) / 256;
+  const int hq = r < 0 ? p.hc : p.hc / p.ulysses, hkv = r < 0 ? p.hk : p.hk / p.ulysses, g = hq / hkv;
+  const int q_first = r < 0 ? 0 : r, q_last = r < 0 ? p.ring - 1 : r;
+  BwdCut best = most;
+  if (r < 0) best.k_splits = 1;   // dQ leaves as bf16
+  const int m = p.bs * hkv;       // KV groups: alike, so one of them is played, on its share of the CUs
+  if (T * (q_last - q_first + 1) * m * g > 8 * kPlanCUs) return best;   // items to spare
+  const int cus = std::max(1, (kPlanCUs + m / 2) / m);
+  // 32-key steps of every (ring row, query tile), 32-query steps of every (K/V block, key tile): under kpos <= qpos the
+  // keys that a run of queries sees are a prefix of each run of keys, the queries that see a key a suffix of theirs
+  std::vector<usp_posdesc> pos(p.ring);
+  for (int s = 0; s < p.ring; ++s) ring_block_desc(p, s, &pos[s]);
+  std::vector<double> dq, dkdv;
+  auto steps = [](int64_t n) { return (double)((n + 31) / 32); };
+  for (int64_t t = T - 1; t >= 0; --t)
+    for (int i = q_first; i <= q_last; ++i) {
+      const int64_t last = pos_max(pos[i], t * 256, std::min(Lq, t * 256 + 256));
+      double w = 0.0;
+      for (const usp_posdesc& k : pos)
+        w += p.causal ? steps(std::clamp<int64_t>(last - k.start0 + 1, 0, k.len0)) + steps(std::clamp<int64_t>(last - k.start1 + 1, 0, k.len1)) : steps(Lq);
+      dq.push_back(w);
+    }
+  for (const usp_posdesc& k : pos)
+    for (int64_t t = 0; t < T; ++t) {
+      const int64_t first = pos_min(k, t * 256, std::min(Lq, t * 256 + 256));
+      double w = 0.0;
+      for (int i = q_first; i <= q_last; ++i)
+        w += p.causal ? steps(pos[i].len0 - std::clamp<int64_t>(first - pos[i].start0, 0, pos[i].len0)) +
+                            steps(pos[i].len1 - std::clamp<int64_t>(first - pos[i].start1, 0, pos[i].len1))
+                      : steps(Lq);
+      dkdv.push_back(w);
+    }
+  const double f = p.hs == 128 ? 1.0 : 0.62;
+  const int max_copies = g / most.heads_per_wg * most.q_splits;
+  const int max_q = (int)std::clamp<int64_t>(Lq / 512, 1, 4), max_k = best.k_splits;
+  double best_us = 0.0;
+  std::vector<double> free_at;
+  for (int h = g; h >= 1; --h) {
+    if (g % h) continue;
+    for (int q = 1; q <= max_q && g / h * q <= max_copies; ++q)
+      for (int k = 1; k <= max_k; ++k) {
+        free_at.assign(cus, 0.0);   // a min-heap of the workgroups' finish times
+        double end = 0.0;
+        auto play = [&](double us, int times) {
+          for (int i = 0; i < times; ++i) {
+            std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+            end = std::max(end, free_at.back() += us);
+            std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+          }
+        };
+        for (double w : dkdv) play(6.0 + 1.68 * f * h * w / q, g / h * q);
+        for (double w : dq) play(10.0 + 1.2 * f * w / k, g * k);
+        const double copied = (k > 1 ? (double)k * hq * (q_last - q_first + 1) : 0.0) + (g / h * q > 1 ? 2.0 * (g / h * q) * hkv * p.ring : 0.0);
+        double us = end + (copied > 0.0 ? 6.0 + copied * p.bs * Lq * p.hs * 4.0 / 4.5e6 : 0.0);
+        // (what the workspace was sized for is left for a gain of 3 % or more: at L = 32768 cuts that look alike here differ by 1 %)
+        if (h == most.heads_per_wg && q == most.q_splits && (k == most.k_splits || r < 0)) us *= 0.97;
+        if (best_us == 0.0 || us < best_us) {
+          best_us = us;
+          best = BwdCut{h, k, q};
+        }
+      }
+  }
+  return best;
+}
+
+// Playing the cuts of a problem through takes the host 0.1-0.5 ms: the last answers are kept, as heavy_choice() keeps its.
+BwdCut bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
+  struct Entry { usp_problem p; int r; BwdCut cut; };   // (`most` follows from the problem)
+  static std::mutex mu;
+  static std::vector<Entry> seen;
+  std::lock_guard<std::mutex> lock(mu);
+  for (const Entry& e : seen)
+    if (e.r == r && same_problem(e.p, p)) return e.cut;
+  if (seen.size() >= 256) seen.erase(seen.begin());
+  seen.push_back(Entry{p, r, work_out_bwd_cut(p, r, most)});
+  return seen.back().cut;
+}
+
 }  // namespace
 
 extern "C" size_t usp_attn_bwd_workspace_bytes(const usp_problem* p, int n_ranks) {
@@ -1009,12 +1099,11 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
         if ((const char*)in[i] < (const char*)out[j] + out_bytes[j] && (const char*)out[j] < (const char*)in[i] + in_bytes[i])
           apart = false;
   }
-  // In place: with Ulysses degree 1 the all-to-alls are the identity; with a batch of one the shards of a ring row are
-  // contiguous, [Lq][heads][hs], and a rank's tensors are its heads of those rows.  The kernels then read Q, dO, O, K and V
-  // where the caller holds them (whole 16-byte chunks: tensors that do not lie on 16 bytes are staged instead).
-  const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)d_o) & 15) == 0;
-  const bool in_place = U == 1 || (p->bs == 1 && aligned && apart);
-  const bool direct = in_place && apart && R <= USP_MAX_RING_BLOCKS;   // results may leave the kernels as bf16, to their place
+  // With Ulysses degree 1 the all-to-alls are the identity; with a batch of one the shards of a ring row are contiguous,
+  // [Lq][heads][hs].  Either way a rank's tensors are its heads of the ring row's rows.
+  const bool seq_rows = U == 1 || p->bs == 1;
+  const bool direct = seq_rows && apart && R <= USP_MAX_RING_BLOCKS;   // results may leave the kernels as bf16, to their place
+  const double rank_us = 10.0 * p->hs * p->bs * hq * (double)Lq * (double)p->L * (p->causal ? 0.5 : 1.0) / 0.8e9;
   auto q_at = [&](const void* t, int r, int u) { return (char*)t + ((size_t)r * p->bs * Lq * p->hc + (size_t)u * hq) * p->hs * es; };
   auto kv_at = [&](const void* t, int r, int u) { return (char*)t + ((size_t)r * p->bs * Lq * p->hk + (size_t)u * hkv) * p->hs * es; };
   usp_posdesc ring_pos[USP_MAX_MERGE_PARTS];   // positions of every ring row
@@ -1023,20 +1112,21 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
   // Every rank at once: in place, the tensors of all ranks are one dense problem of R query blocks, R key blocks and all
   // heads, which goes through ONE launch pair instead of a pair (and conversions) per rank.  Not where dS is kept and a
   // rank is long enough to gain by that (some 10 % of its time; a rank's launches and their tails cost some 40 us).
-  if (direct && N > 1 && rank_begin == 0 && rank_end == N) {
-    const double rank_us = 10.0 * p->hs * p->bs * hq * (double)Lq * (double)p->L * (p->causal ? 0.5 : 1.0) / 0.8e9;
+  const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)d_o) & 15) == 0;
+  if (direct && aligned && N > 1 && rank_begin == 0 && rank_end == N) {
     BwdCopies c;
-    c.cut = plan_bwd_cut(p->bs, Lq, Lq, p->hc, p->hk, R, true, !p->causal);
-    c.cut.k_splits = 1;   // dQ leaves as bf16
-    auto n_copies = [&]() { return p->hc / p->hk / c.cut.heads_per_wg * c.cut.q_splits; };
-    if (n_copies() > f.dkdv_copies) c.cut.q_splits = 1;
+    c.cut = bwd_cut(*p, -1, f.copies.cut);
+    const int copies = p->hc / p->hk / c.cut.heads_per_wg * c.cut.q_splits;
     const size_t delta_bytes = up256(q_elems / p->hs * N * sizeof(float));   // in the room from q_head up to the accumulators
-    if ((!f.copies.ds || rank_us < 400.0) && n_copies() <= f.dkdv_copies && delta_bytes <= f.dk_acc - f.q_head) {
+    if ((!f.copies.ds || rank_us < 400.0) && delta_bytes <= f.dk_acc - f.q_head) {
       const size_t kv_block = kv_elems * U;   // elements of a ring row, all heads
-      const int copies = n_copies();
       c.dq_stride = 0;
       c.dkdv_stride = kv_block;
       const bool dkdv_bf16 = copies == 1;
+      float* delta = (float*)(ws + f.q_head);
+      const PrepareTensor d = {d_o, o, nullptr, delta, 1, 0, R, 0, 1, p->hc, p->hc};
+      st = launch_bwd_prepare(&d, 1, p->bs, Lq, p->hs, stream);
+      if (st != USP_OK) return st;
       const void *kb[USP_MAX_RING_BLOCKS], *vb[USP_MAX_RING_BLOCKS];
       float *dkb[USP_MAX_RING_BLOCKS], *dvb[USP_MAX_RING_BLOCKS];
       const int acc[USP_MAX_RING_BLOCKS] = {0};
@@ -1046,8 +1136,8 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
         dkb[s] = dkdv_bf16 ? (float*)kv_at(dk, s, 0) : (float*)(ws + f.dk_acc) + (size_t)s * copies * kv_block;
         dvb[s] = dkdv_bf16 ? (float*)kv_at(dv, s, 0) : (float*)(ws + f.dv_acc) + (size_t)s * copies * kv_block;
       }
-      const BwdInPlace io = {p->hc, p->hk, o, true, dkdv_bf16, R, ring_pos};
-      st = launch_ring_attn_bwd(q, kb, vb, ring_pos, R, d_o, lse, (float*)(ws + f.q_head), (float*)dq, dkb, dvb, p->bs, Lq, Lq,
+      const BwdPlace io = {{Lq * p->hc, p->hc, 1}, {Lq * p->hk, p->hk, 1}, p->hc, dkdv_bf16 ? p->hk : 0, R, ring_pos};
+      st = launch_ring_attn_bwd(q, kb, vb, ring_pos, R, d_o, lse, delta, (float*)dq, dkb, dvb, p->bs, Lq, Lq,
                                 p->hc, p->hk, p->hs, scale, p->causal ? 1 : 0, ring_pos[0], 0, acc, stream, &c, &io);
       if (st != USP_OK || dkdv_bf16) return st;
       ConvertTensor t[2];
@@ -1063,17 +1153,23 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
     }
   }
 
-  if (!in_place) {
-    st = stage_kv_blocks(*p, k, v, ws + f.k_head, ws + f.v_head, f.kv_block_bytes, c0, c1, stream);
-    if (st != USP_OK) return st;
-  }
+  // Otherwise rank after rank.  Ulysses degree 1: everything is read in place.  Else Q, dO, K and V are staged in head
+  // layout, in the launch that forms D_i, also where a batch of one could be read in place: rows as far apart as the whole
+  // model's heads are long (8 KiB) cost the dK/dV kernel 2.4 %, more than the copies (L = 32768: 1837 -> 1882 us).
+  const bool in_place = U == 1;
+  const RowPlace place_q = in_place ? RowPlace{Lq * hq, hq, 1} : RowPlace{Lq * hq, 1, (int)Lq};
+  const RowPlace place_kv = in_place ? RowPlace{Lq * hkv, hkv, 1} : RowPlace{Lq * hkv, 1, (int)Lq};
 
   // first contribution to a K/V block overwrites its accumulator, later ones add
   bool touched[USP_MAX_MERGE_PARTS] = {false};
 
   const bool one_rank = rank_end - rank_begin == 1;
-  const bool dq_bf16 = direct && f.copies.cut.k_splits == 1;
-  const bool dkdv_bf16 = direct && one_rank && f.dkdv_copies == 1;
+  BwdCopies run = f.copies;
+  if (!run.ds) run.cut = bwd_cut(*p, rank_begin / U, run.cut);   // (with dS kept the two kernels run one after the other)
+  const int dkdv_copies = hq / hkv / run.cut.heads_per_wg * run.cut.q_splits;
+  const bool dq_bf16 = direct && run.cut.k_splits == 1;
+  const bool dkdv_bf16 = direct && one_rank && dkdv_copies == 1;
+  const BwdPlace place = {place_q, place_kv, dq_bf16 ? p->hc : 0, dkdv_bf16 ? p->hk : 0, 1, nullptr};
   SeqLayoutIO seq_q = {(int)(p->L / N), p->hc, 0};
   ConvertTensor convert[3];
   int n_convert = 0;
@@ -1081,31 +1177,31 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
     const int r = rank / U, u = rank % U;
     const char* q_rank = in_place ? q_at(q, r, u) : ws + f.q_head;
     const char* do_rank = in_place ? q_at(d_o, r, u) : ws + f.do_head;
-    if (!in_place) {   // Q and dO of this rank to head layout: one geometry, one launch
-      const void* srcs[2] = {q, d_o};
-      void* dsts[2] = {ws + f.q_head, ws + f.do_head};
-      st = launch_layout_a2a_multi(*p, p->hc, USP_SEQ_TO_HEAD, 2, srcs, dsts, rank, rank + 1, rank, stream);
-      if (st != USP_OK) return st;
-    }
     seq_q.head0 = u * hq;
     const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * es;   // the Ulysses group's first shard
-    // D_i: formed by the dQ kernel where that runs first and finds O where it finds dO, else by a launch that reads O (and
-    // dO) once, straight from the sequence-layout shards
     float* delta = (float*)(ws + f.delta);
-    const bool delta_inside = in_place && !f.copies.ds && R <= USP_MAX_RING_BLOCKS;
-    if (!delta_inside) {
-      st = launch_bwd_delta((const char*)o + group_off, (const char*)d_o + group_off, delta, p->bs, Lq, hq, p->hs, stream, &seq_q);
+    {
+      // D_i of this rank's rows, and what has to be staged: its Q and dO, and once, the K/V blocks of every ring row
+      PrepareTensor t[4] = {{d_o, o, in_place ? nullptr : ws + f.do_head, delta, U, r, 1, u, 1, p->hc, hq},
+                            {q, nullptr, ws + f.q_head, nullptr, U, r, 1, u, 1, p->hc, hq},
+                            {k, nullptr, ws + f.k_head, nullptr, U, 0, R, c0, n_cols, p->hk, hkv},
+                            {v, nullptr, ws + f.v_head, nullptr, U, 0, R, c0, n_cols, p->hk, hkv}};
+      st = launch_bwd_prepare(t, in_place ? 1 : rank == rank_begin ? 4 : 2, p->bs, Lq, p->hs, stream);
       if (st != USP_OK) return st;
     }
     const float* lse_rank = lse + (size_t)rank * p->bs * hq * Lq;
-    const BwdInPlace io = {in_place ? p->hc : hq, in_place ? p->hk : hkv, delta_inside ? (const void*)q_at(o, r, u) : nullptr,
-                           dq_bf16, dkdv_bf16, 1, nullptr};
     // The ring loop of this rank, step i on block s = (r - i) mod R: up to USP_MAX_RING_BLOCKS steps per launch
-    // pair (the dQ kernel keeps its accumulator in registers across them, the dK/dV kernel spreads them over
-    // its grid).  dQ adds after the first launch of this rank; a block's dK/dV add after the first rank that
-    // touched it.
-    for (int i0 = 0; i0 < R; i0 += USP_MAX_RING_BLOCKS) {
-      const int nb = R - i0 < USP_MAX_RING_BLOCKS ? R - i0 : USP_MAX_RING_BLOCKS;
+    // pair (a dQ item keeps its accumulator in registers across them, the dK/dV items are spread over them).  dQ adds
+    // after the first launch of this rank; a block's dK/dV add after the first rank that touched it.  Blocks that lie
+    // wholly behind the rank's rows (contiguous split, causal) are left out where an absent block costs nothing: not where
+    // the kernels write dK/dV themselves, zeros then included.
+    int steps[USP_MAX_MERGE_PARTS], n_steps = 0;
+    for (int i = 0; i < R; ++i) {
+      const int s = ((r - i) % R + R) % R;
+      if (dkdv_bf16 || !p->causal || pos_min(ring_pos[s], 0, Lq) <= pos_max(ring_pos[r], 0, Lq)) steps[n_steps++] = s;
+    }
+    for (int i0 = 0; i0 < n_steps; i0 += USP_MAX_RING_BLOCKS) {
+      const int nb = n_steps - i0 < USP_MAX_RING_BLOCKS ? n_steps - i0 : USP_MAX_RING_BLOCKS;
       const void* kb[USP_MAX_RING_BLOCKS];
       const void* vb[USP_MAX_RING_BLOCKS];
       float* dkb[USP_MAX_RING_BLOCKS];
@@ -1113,7 +1209,7 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
       usp_posdesc kds[USP_MAX_RING_BLOCKS];
       int acc[USP_MAX_RING_BLOCKS];
       for (int j = 0; j < nb; ++j) {
-        const int s = ((r - (i0 + j)) % R + R) % R;
+        const int s = steps[i0 + j];
         kds[j] = ring_pos[s];
         const size_t sl = slot(s, u);
         kb[j] = in_place ? kv_at(k, s, u) : ws + f.k_head + sl * f.kv_block_bytes;
@@ -1125,7 +1221,7 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
       }
       st = launch_ring_attn_bwd(q_rank, kb, vb, kds, nb, do_rank, lse_rank, delta,
                                 (float*)(dq_bf16 ? q_at(dq, r, u) : ws + f.dq_acc), dkb, dvb, p->bs, Lq, Lq, hq, hkv, p->hs,
-                                scale, p->causal ? 1 : 0, ring_pos[r], i0 > 0 ? 1 : 0, acc, stream, &f.copies, &io);
+                                scale, p->causal ? 1 : 0, ring_pos[r], i0 > 0 ? 1 : 0, acc, stream, &run, &place);
       if (st != USP_OK) return st;
     }
     // dQ of this rank: the copies summed, converted and written straight to the sequence-layout shards of its Ulysses
@@ -1135,7 +1231,7 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
       t.src = (const float*)(ws + f.dq_acc);
       t.dst = (char*)dq + group_off;
       t.n = t.copy_stride = q_elems;
-      t.n_copies = f.copies.cut.k_splits;
+      t.n_copies = run.cut.k_splits;
       t.seq = &seq_q;
       t.bs = p->bs; t.rows = Lq; t.heads = hq; t.hs = p->hs;
       if (!one_rank) {   // the next rank uses the accumulator
@@ -1153,15 +1249,19 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
   // launch with its dQ.
   if (!dkdv_bf16)
     for (int u = c0; u < c1; ++u) {
-      if (!touched[slot(0, u)]) continue;   // (a rank visits every ring row of its column)
+      uint64_t absent = 0;   // ring rows that no rank of the range sees: zeros
+      for (int s = 0; s < R; ++s)
+        if (!touched[slot(s, u)]) absent |= 1ull << s;
+      if (absent == ~0ull >> (64 - R)) continue;   // (every rank sees its own block)
       const SeqLayoutIO seq_u = {(int)(p->L / N), p->hk, u * hkv};
       for (int i = 0; i < 2; ++i) {
         ConvertTensor& t = convert[n_convert++];
         t.src = (const float*)(ws + (i ? f.dv_acc : f.dk_acc) + slot(0, u) * f.kv_acc_bytes);
         t.dst = i ? dv : dk;
         t.n = t.copy_stride = kv_elems;
-        t.n_copies = f.dkdv_copies;
+        t.n_copies = dkdv_copies;
         t.n_blocks = R;
+        t.absent = absent;
         t.src_blk = n_cols * f.kv_acc_bytes / sizeof(float);
         t.dst_blk = kv_elems * U;
         t.seq = &seq_u;

@@ -137,9 +137,17 @@ inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
   return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
 }
 
-// seq: o and d_o are the sequence-layout shards of the rank's Ulysses group (their first shard), not dense tensors.
-int launch_bwd_delta(const void* o, const void* d_o, float* delta, int bs, int64_t L, int h, int hs,
-                     hipStream_t stream, const SeqLayoutIO* seq = nullptr);
+// One tensor of the launch that prepares a backward: rows [r0, r0 + n_rings) x columns [c0, c0 + n_cols) of ring blocks of the
+// sequence layout [N][bs][L/U][heads][hs].  dst: their copy in [block][bs][head][row][hs]; o (src is dO): D_i of their rows,
+// [block][bs][head][row] fp32 at delta.
+struct PrepareTensor {
+  const void* src;
+  const void* o;
+  void* dst;
+  float* delta;
+  int U, r0, n_rings, c0, n_cols, heads, heads_per_rank;
+};
+int launch_bwd_prepare(const PrepareTensor* tensors, int n_tensors, int bs, int64_t L, int hs, hipStream_t stream);
 // How a backward launch pair divides its work (plan_bwd_cut): query heads of a KV group walked by one dK/dV
 // workgroup, slices of a dQ item's key tiles, slices of a dK/dV item's query tiles.
 struct BwdCut { int heads_per_wg, k_splits, q_splits; };
@@ -152,15 +160,15 @@ BwdCut plan_bwd_cut(int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int n_block
 // first and writes the dS blocks it forms, and the dQ kernel reads them back instead of forming S and dP again
 // (5 matrix products per tile pair instead of 7, for 2 bytes written and read per visible pair).
 struct BwdCopies { BwdCut cut; size_t dq_stride, dkdv_stride; void* ds = nullptr; };
-// Where a launch pair finds and leaves its tensors when that is not dense head layout.  Pitches: heads in a row of Q, dO, O
-// and of K, V (the pointers at the first head of the launch).  o: form D_i in the dQ kernel and leave it in delta (only
-// without kept dS, whose dK/dV kernel runs first).  dq_bf16 / dkdv_bf16: the results leave as bf16 in rows of the
-// same pitches, for outputs with one writer per element that nothing is added to.  n_qblk > 1: Q, dO, O, LSE, delta and dQ
-// hold the rows of that many ring ranks back to back, each with its own positions (no kept dS, dq_bf16).
-struct BwdInPlace {
-  int q_pitch, kv_pitch;
-  const void* o;
-  bool dq_bf16, dkdv_bf16;
+// Where a launch pair finds its tensors when that is not dense row-major head layout [bs][L][heads][hs]: row i of head h of
+// (block, batch entry) rb lies rb * block + i * row + h * head rows of hs elements into the tensor.
+struct RowPlace { int64_t block; int row, head; };
+// dq_heads / dkdv_heads > 0: the results leave as bf16, in rows of that many heads, for outputs with one writer per element
+// that nothing is added to.  n_qblk > 1: Q, dO, LSE, delta and dQ hold the rows of that many ring ranks back to back, each
+// with its own positions (no kept dS; dq_heads > 0).
+struct BwdPlace {
+  RowPlace q, kv;
+  int dq_heads, dkdv_heads;
   int n_qblk;
   const usp_posdesc* qpos_blocks;
 };
@@ -173,7 +181,7 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
                          const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks, int bs,
                          int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                          const usp_posdesc& qpos, int accumulate_dq, const int* accumulate_dkdv, hipStream_t stream,
-                         const struct BwdCopies* copies = nullptr, const struct BwdInPlace* io = nullptr);
+                         const struct BwdCopies* copies = nullptr, const struct BwdPlace* io = nullptr);
 int launch_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                           const float* delta, float* dq, float* dk, float* dv, int bs, int64_t Lq, int64_t Lk, int hq,
                           int hkv, int hs, float scale, int causal, const usp_posdesc& qpos, const usp_posdesc& kpos,
@@ -190,6 +198,7 @@ struct ConvertTensor {
   int add_to_dst = 0;
   int n_blocks = 1;
   size_t src_blk = 0, dst_blk = 0;
+  uint64_t absent = 0;   // bit b: block b (of at most 64) has no source, zeros are written
   const SeqLayoutIO* seq = nullptr;
   int bs = 0;
   int64_t rows = 0;

@@ -32,25 +32,6 @@ using namespace dev;
 
 constexpr int kWaves = 8, kRows = 32, kTile = 32;
 
-// Exact quotients of n < 2^31 by a divisor known on the host: one multiplication and a shift of scalar registers.  (A
-// division by a kernel argument is thirty vector instructions; the ten of them in front of the first load were 1 us.)
-struct FastDiv {
-  uint32_t d, mul;
-  int shift;
-  __device__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
-  // n / d, and n becomes the remainder
-  __device__ int split(int& n) const {
-    const int q = div(n);
-    n -= q * (int)d;
-    return q;
-  }
-};
-FastDiv fast_div(int64_t d) {   // 1 <= d < 2^31: mul = ceil(2^(31 + s) / d) with 2^s >= d fits 32 bits, and its error times n stays below 2^(31 + s) / d
-  int s = 0;
-  while (((int64_t)1 << s) < d) ++s;
-  return FastDiv{(uint32_t)d, (uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), 31 + s};
-}
-
 struct WsArgs {
   const void* q;
   const void* k;
