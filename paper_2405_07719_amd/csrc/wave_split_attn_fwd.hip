@@ -265,7 +265,7 @@ void wave_split_attn_fwd(const WsArgs a) {
   using Op = Operands<T, HS>;
   constexpr int DB = HS / 32, OSTR = HS + 4;   // floats between the rows of a state in LDS: an odd number of 16 B chunks
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows], inv_s[kRows];
+  __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows], inv_s[kRows], first_s[2][kRows];
   const int lane = threadIdx.x & 63, l32 = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
@@ -299,6 +299,14 @@ void wave_split_attn_fwd(const WsArgs a) {
 
   char* const lds = smem + wave * Op::kLdsPerWave;
   int turn = wave;        // tiles of the walk until this wave's next one
+  // bf16: every wave starts from the row maxima over the walk's first 64 keys, which waves 0 and 1 hold after their first
+  // products, and moves on from them only where a row grows by more than 2^8 (P is then bounded by that instead of 1).
+  // The weights are rounded to bf16 as in the 256-row kernel that way, to the same bits where its items begin with the same
+  // keys, and the O that the two leave a backward differ by the order of fp32 sums instead of by a rounding in every
+  // weight.  Costs one barrier (12.2 -> 12.4 us at four ranks of L = 1024).
+  constexpr bool kShareFirst = sizeof(T) == 2;
+  constexpr float kRescaleThreshold = kShareFirst ? 8.f : 0.f;   // log2 units
+  bool shared_first = !kShareFirst;   // wave-uniform: every wave passes the one barrier exactly once
   for (int i = 0; i < a.R; ++i) {
     const int blk = r - i < 0 ? r - i + a.R : r - i;   // Algorithm 1 step 5: step i visits block (r - i) mod R
     const PosDesc32 kpos = block_positions(a, a.kpos, a.Lk, blk);
@@ -329,10 +337,18 @@ void wave_split_attn_fwd(const WsArgs a) {
       float mx = -INFINITY;
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
-      const float m_new = fmaxf(m, both_halves_max(mx));
-      const float mc = m_new == -INFINITY ? 0.f : m_new * a.scale_log2;
-      if (__any(m_new > m)) {
-        const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);   // m = -inf -> 0
+      mx = both_halves_max(mx);
+      if (!shared_first) {
+        int t = lane;   // places in LDS derived here, from a lane index the compiler cannot see through: kept, they are spilled
+        asm volatile("" : "+v"(t));
+        if (wave < 2 && t < 32) first_s[wave][t] = (wave == 0 || i == 0) ? mx : -INFINITY;
+        __syncthreads();
+        m = fmaxf(first_s[0][t & 31], first_s[1][t & 31]);
+        shared_first = true;
+      }
+      if (__any((mx - m) * a.scale_log2 > kRescaleThreshold)) {   // (m = -inf and a key: inf; no key at all: NaN, no)
+        const float m_new = fmaxf(m, mx);
+        const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - (m_new == -INFINITY ? 0.f : m_new * a.scale_log2));   // m = -inf -> 0
         l *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -340,6 +356,7 @@ void wave_split_attn_fwd(const WsArgs a) {
           for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
         m = m_new;
       }
+      const float mc = m == -INFINITY ? 0.f : m * a.scale_log2;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.scale_log2, -mc));
@@ -349,34 +366,40 @@ void wave_split_attn_fwd(const WsArgs a) {
     }
     turn -= nt;
   }
+  if (!shared_first) {   // no tile for this wave
+    if (wave < 2 && lane < 32) first_s[wave][lane] = -INFINITY;
+    __syncthreads();
+  }
 
   // ---- the waves' states are combined: common maximum, scaled outputs side by side in LDS, summed row by row
+  int end_lane = lane;   // (a lane index of its own for the epilogue: what derives from it is not kept across the loop)
+  asm volatile("" : "+v"(end_lane));
   l = both_halves_sum(l);
-  if (hl == 0) {
-    m_s[wave][l32] = m;
-    l_s[wave][l32] = l;
+  if (end_lane < 32) {
+    m_s[wave][(end_lane & 31)] = m;
+    l_s[wave][(end_lane & 31)] = l;
   }
   __syncthreads();
   // (every loop over the waves is unrolled, all its LDS reads in flight at once: a wave that had no tile adds zeros)
   float mw[kWaves], m_all = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][l32];
+  for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][(end_lane & 31)];
 #pragma unroll
   for (int j = 0; j < kWaves; ++j) m_all = fmaxf(m_all, mw[j]);
   const float mc = m_all == -INFINITY ? 0.f : m_all * a.scale_log2;
   {
     const float f = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);
-    float* dst = (float*)smem + (wave * kRows + l32) * OSTR;
+    float* dst = (float*)smem + (wave * kRows + (end_lane & 31)) * OSTR;
 #pragma unroll
-    for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, hl)) = Op::group(o, gi) * f;
+    for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, end_lane >> 5)) = Op::group(o, gi) * f;
   }
-  if (wave == 0 && hl == 0) {
+  if (wave == 0 && end_lane < 32) {
     float tot = 0.f;
 #pragma unroll
-    for (int j = 0; j < kWaves; ++j) tot += l_s[j][l32] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
-    inv_s[l32] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
-    if (row0 + l32 < a.Lq)
-      a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + l32] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
+    for (int j = 0; j < kWaves; ++j) tot += l_s[j][(end_lane & 31)] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
+    inv_s[(end_lane & 31)] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
+    if (row0 + (end_lane & 31) < a.Lq)
+      a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + (end_lane & 31)] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
   }
   __syncthreads();
   const BlockRows orow = block_rows(a.o, sizeof(OutT), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
