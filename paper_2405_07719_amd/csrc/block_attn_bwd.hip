@@ -49,7 +49,10 @@ struct BwdArgs {
   float* dv[kMaxBlocks];
   int bs, hq, hkv, g;
   int Lq, Lk;
-  int n_tiles;          // query tiles (dq) or key tiles per block (dkdv)
+  int n_tiles;          // query tiles (of the kernel that reads kept dS)
+  // 256-row query tiles and 256-key tiles, and how many of them are the first run's where no tile may hold positions of both
+  // runs (RowTiles; 0: cut in a row, as always where dS is kept).  Every query block, and every key block, is cut alike.
+  int q_tiles, q_tiles_run0, k_tiles, k_tiles_run0;
   int n_blocks;
   int causal;
   int accumulate;       // dq: 0 overwrite, 1 add
@@ -261,7 +264,7 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
     a.q = ap->q; a.d_o = ap->d_o; a.lse = ap->lse; a.delta = ap->delta; a.dq = ap->dq;
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
-    a.n_tiles = (a.Lq + BM - 1) / BM; a.n_blocks = ap->n_blocks; a.causal = ap->causal; a.accumulate = ap->accumulate;
+    a.n_tiles = ap->q_tiles; a.n_blocks = ap->n_blocks; a.causal = ap->causal; a.accumulate = ap->accumulate;
     a.q_rb = ap->q_rb; a.q_row = ap->q_row; a.q_head = ap->q_head;
     a.kv_rb = ap->kv_rb; a.kv_row = ap->kv_row; a.kv_head = ap->kv_head;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
@@ -283,10 +286,16 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
     const int qtile = a.causal ? a.n_tiles - 1 - t : t;
     const int b = group / a.hkv, kvh = group % a.hkv;
     const int h = kvh * a.g + hg;
-    const int tile_row0 = qtile * BM, tile_row1 = min(a.Lq, tile_row0 + BM);
+    int tile_row0 = qtile * BM, row_end = a.Lq;   // rows from row_end on are none of this tile's
+    const int run0 = ap->q_tiles_run0;
+    if (run0 > 0) {
+      if (qtile < run0) row_end = a.qpos.len0;
+      else tile_row0 = a.qpos.len0 + (qtile - run0) * BM;
+    }
+    const int tile_row1 = min(row_end, tile_row0 + BM);
     const int wave_row0 = tile_row0 + wave * 32;
     const int qrow = wave_row0 + l32;
-    const int rr = min(qrow, a.Lq - 1);
+    const int rr = min(qrow, row_end - 1);
     const int qp = a.causal ? pos_of(a.qpos, rr) : 0;
 
     const size_t kv_head_off = (size_t)(b * a.kv_rb + (int64_t)kvh * a.kv_head) * HS * 2;   // bytes
@@ -323,8 +332,8 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
     TileRanges tr = {0, 0, 0, 0};
     int na = 0, nt = 0;
     auto tile_of = [&](int it) { return it < na ? tr.a0 + it : tr.b0 + (it - na); };
-    const bool wave_live = wave_row0 < a.Lq;
-    const int wave_qmin = (a.causal && wave_live) ? pos_min(a.qpos, wave_row0, min(a.Lq, wave_row0 + 32)) : 0;
+    const bool wave_live = wave_row0 < row_end;
+    const int wave_qmin = (a.causal && wave_live) ? pos_min(a.qpos, wave_row0, min(row_end, wave_row0 + 32)) : 0;
 
     // staging: one 16 B chunk of K and of V per thread and tile; the tile base is wave-uniform, the per-thread
     // byte offset constant, rows past the last key clamped by a min on the offset
@@ -432,9 +441,9 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
     }   // blocks
 
     const unsigned own_ticket = next.begin();
-    if (qrow < a.Lq && ap->dq_heads) {
+    if (qrow < row_end && ap->dq_heads) {
       store_bf16_row((__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + qrow) * ap->dq_heads + h) * HS + 4 * hl, dq, a.scale);
-    } else if (qrow < a.Lq) {
+    } else if (qrow < row_end) {
       float* dst = a.dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -659,7 +668,7 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
     a.q = ap->q; a.d_o = ap->d_o; a.lse = ap->lse; a.delta = ap->delta;
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
     a.Lq = ap->Lq; a.Lk = ap->Lk;
-    a.n_tiles = (a.Lk + BN - 1) / BN; a.causal = ap->causal; a.heads_per_wg = ap->heads_per_wg;
+    a.n_tiles = ap->k_tiles; a.causal = ap->causal; a.heads_per_wg = ap->heads_per_wg;
     a.q_rb = ap->q_rb; a.q_row = ap->q_row; a.q_head = ap->q_head;
     a.kv_rb = ap->kv_rb; a.kv_row = ap->kv_row; a.kv_head = ap->kv_head;
     a.scale = ap->scale; a.scale_log2 = ap->scale_log2;
@@ -679,12 +688,20 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
     const int blk = w / a.n_tiles;           // K/V block of the ring loop
     const PosDesc32 kpos = {ap->kpos[blk].start0, ap->kpos[blk].len0, ap->kpos[blk].start1, ap->kpos[blk].len1};
     const int b = group / a.hkv, kvh = group % a.hkv;
-    const int tile_key0 = ktile * BN, tile_key1 = min(a.Lk, tile_key0 + BN);
+    int tile_key0 = ktile * BN, key_end = a.Lk;   // keys from key_end on are none of this tile's
+    if constexpr (!WRITE_DS) {   // (the blocks of dS are numbered by tiles in a row)
+      const int run0 = ap->k_tiles_run0;
+      if (run0 > 0) {
+        if (ktile < run0) key_end = kpos.len0;
+        else tile_key0 = kpos.len0 + (ktile - run0) * BN;
+      }
+    }
+    const int tile_key1 = min(key_end, tile_key0 + BN);
     const int wave_key0 = tile_key0 + wave * 32;
     const int key = wave_key0 + l32;
-    const int kk = min(key, a.Lk - 1);
+    const int kk = min(key, key_end - 1);
     const int kp = a.causal ? pos_of(kpos, kk) : 0;
-    const bool key_ok = key < a.Lk;
+    const bool key_ok = key < key_end;
 
     // B operands of S = Q K^T and dP = dO V^T: lane = key l32, dims 16 ks + 8 hl ..  The K fragments stay in
     // registers; the V fragments are read from LDS every step (both in registers next to the two accumulators
@@ -699,7 +716,7 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
 #pragma unroll
       for (int c = 0; c < BN * CPR / NT; ++c) {
         const int r = (tid + c * NT) / CPR, col = (tid + c * NT) % CPR;
-        const int krow = min(tile_key0 + r, a.Lk - 1);
+        const int krow = min(tile_key0 + r, key_end - 1);
         *(u32x4*)(v_s + r * USTR + col * 16) = *(const u32x4*)(vg + (size_t)krow * v_row_bytes + col * 16);
       }
     }
@@ -722,14 +739,14 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
     // the ones running side by side on an XCD read the same Q / dO rows at about the same time (one L2 fill
     // serves them all); walking up from each workgroup's own diagonal would spread them over the sequence.
     auto tile_of = [&](int it) { const int j = nt - 1 - it; return j < na ? tr.a0 + j : tr.b0 + (j - na); };
-    const bool wave_live = wave_key0 < a.Lk;
-    const int wave_kmax = (a.causal && wave_live) ? pos_max(kpos, wave_key0, min(a.Lk, wave_key0 + 32)) : 0;
+    const bool wave_live = wave_key0 < key_end;
+    const int wave_kmax = (a.causal && wave_live) ? pos_max(kpos, wave_key0, min(key_end, wave_key0 + 32)) : 0;
     // Query tiles this wave need not mask: full tiles that lie wholly in one ascending run of the query positions
     // and whose first row none of the wave's keys follows (and only if the wave's 32 keys all exist).  As places
     // j in the visible ranges (tile_of(it) is place nt - 1 - it) they are [free_a0, free_a1) and [free_b0, free_b1),
     // worked out here once per work item; the decision per tile is then a few comparisons.
     int free_a0 = 0, free_a1 = 0, free_b0 = 0, free_b1 = 0;
-    if (wave_live && wave_key0 + 32 <= a.Lk) {
+    if (wave_live && wave_key0 + 32 <= key_end) {
       const int full = a.Lq / QT;
       int ta0 = 0, ta1 = full, tb0 = 0, tb1 = 0;   // as tile numbers
       if (a.causal) {
@@ -1245,7 +1262,22 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.ds_kt = (int)((Lk + 255) / 256) * 8;
   a.ds_qt8 = (int)((Lq + 255) / 256);
   // work items of both kinds; one workgroup per CU draws them (fewer when there are fewer items)
-  const int64_t q_tiles = (Lq + 255) / 256, k_tiles = (Lk + 255) / 256;
+  const int own_runs = causal && !a.ds;
+  const RowTiles q_rows(a.n_qblk > 1 ? io->qpos_blocks[0] : qpos, Lq, own_runs), k_rows(kpos_blocks[0], Lk, own_runs);
+  // (blocks of one call that are not all cut where the first one is: in a row)
+  auto alike = [&](const RowTiles& rows, const usp_posdesc* d, int n, int64_t len) {
+    for (int j = 1; j < n; ++j) {
+      const RowTiles x(d[j], len, own_runs);
+      if (x.in_run0 != rows.in_run0 || (rows.in_run0 && x.len0 != rows.len0)) return false;
+    }
+    return true;
+  };
+  const RowTiles plain_q(qpos, Lq, 0), plain_k(kpos_blocks[0], Lk, 0);
+  const RowTiles& qt = a.n_qblk == 1 || alike(q_rows, io->qpos_blocks, a.n_qblk, Lq) ? q_rows : plain_q;
+  const RowTiles& kt = alike(k_rows, kpos_blocks, n_blocks, Lk) ? k_rows : plain_k;
+  a.q_tiles = qt.n; a.q_tiles_run0 = qt.in_run0;
+  a.k_tiles = kt.n; a.k_tiles_run0 = kt.in_run0;
+  const int64_t q_tiles = qt.n, k_tiles = kt.n;
   const int64_t dq_items = q_tiles * hq * bs * a.k_splits * a.n_qblk;
   a.heads_per_wg = cut.heads_per_wg;
   const int head_splits = a.g / a.heads_per_wg;

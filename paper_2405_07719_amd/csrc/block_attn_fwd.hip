@@ -47,6 +47,7 @@ struct AttnArgs {
   int bs, hq, hkv, g;
   int Lq, Lk;
   int n_qtiles;
+  int tiles_run0;     // > 0: the query tiles of the first run of positions, the others begin at row qpos.len0 (RowTiles)
   int n_blocks;
   int causal;
   float scale;        // natural-units scale (for the LSE)
@@ -216,8 +217,15 @@ void block_attn_fwd_mfma(const AttnArgs) {
     const int b = group / a.hkv, kvh = group % a.hkv;
     const int h = kvh * a.g + hg;
 
-    const int tile_row0 = qtile * BM;
-    const int tile_row1 = min(a.Lq, tile_row0 + BM);
+    int tile_row0 = qtile * BM, row_end = a.Lq;   // rows from row_end on are none of this tile's
+    if constexpr (!STATE) {   // (the state's records are 256 rows in a row)
+      const int run0 = ap->tiles_run0;
+      if (run0 > 0) {
+        if (qtile < run0) row_end = a.qpos.len0;
+        else tile_row0 = a.qpos.len0 + (qtile - run0) * BM;
+      }
+    }
+    const int tile_row1 = min(row_end, tile_row0 + BM);
     const int wave_row0 = tile_row0 + wave * (NQB * 32);
 
     if constexpr (STATE) {
@@ -255,7 +263,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
     bf16x8 qf[NQB][KSTEPS];
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
-      const int rr = min(wave_row0 + qb * 32 + l32, a.Lq - 1);
+      const int rr = min(wave_row0 + qb * 32 + l32, row_end - 1);
       const __bf16* src = qg + qo_offset(a, b, rr, h, HS) + 8 * hl;
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) qf[qb][ks] = *(const bf16x8*)(src + 16 * ks);
@@ -307,8 +315,8 @@ void block_attn_fwd_mfma(const AttnArgs) {
     }
 
     // wave-level bounds for the mask decision
-    const int wave_row1 = min(a.Lq, wave_row0 + NQB * 32);
-    const bool wave_live = wave_row0 < a.Lq;
+    const int wave_row1 = min(row_end, wave_row0 + NQB * 32);
+    const bool wave_live = wave_row0 < row_end;
     const int wave_qmin = (a.causal && wave_live) ? pos_min(a.qpos, wave_row0, wave_row1) : 0;
 
     // ---- staging: each thread moves CPT 16 B chunks of a K tile and of a V tile
@@ -402,7 +410,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
       if (need_mask) {
         int qp[NQB];   // the lane's query position: derived here, where it is rarely needed, rather than kept in a register
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) qp[qb] = a.causal ? pos_of(a.qpos, min(wave_row0 + qb * 32 + l32, a.Lq - 1)) : 0;
+        for (int qb = 0; qb < NQB; ++qb) qp[qb] = a.causal ? pos_of(a.qpos, min(wave_row0 + qb * 32 + l32, row_end - 1)) : 0;
 #pragma unroll
         for (int kbk = 0; kbk < KB; ++kbk)
 #pragma unroll
@@ -613,7 +621,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
         const float l_tot = both_halves_sum(l_run[qb]);
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
         const int qrow = wave_row0 + qb * 32 + l32;
-        if (qrow < a.Lq) {
+        if (qrow < row_end) {
           float* dst = (float*)ap->o_part[blk0] + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
 #pragma unroll
           for (int db = 0; db < DB; ++db)
@@ -633,7 +641,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
       const float l_tot = both_halves_sum(l_run[qb]);
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
       const int qrow = wave_row0 + qb * 32 + l32;
-      if (qrow < a.Lq) {
+      if (qrow < row_end) {
         OutT* dst = (per_block && !MIXED) ? (OutT*)ap->o_part[blk0] + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl
                               : (OutT*)a.o + qo_offset(a, b, qrow, h, HS) + 4 * hl;
 #pragma unroll
@@ -669,7 +677,10 @@ int launch_mfma(AttnArgs a, hipStream_t stream) {
   constexpr int BM = NWAVES * NQB * 32;
   constexpr int KSTR = HS * 2 + 48, VSTR = VT ? KT * 2 + 16 : HS * 2 + 64;
   constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR));
-  a.n_qtiles = (a.Lq + BM - 1) / BM;
+  static_assert(BM == 256, "RowTiles");
+  const RowTiles tiles(usp_posdesc{a.qpos.start0, a.qpos.len0, a.qpos.start1, a.qpos.len1}, a.Lq, a.causal && !STATE);
+  a.n_qtiles = tiles.n;
+  a.tiles_run0 = tiles.in_run0;
   int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * (a.per_block ? a.n_blocks : 1);
   if constexpr (MIXED) {
     if (a.n_split_tiles < 0 || a.n_split_tiles > a.n_qtiles) return USP_ERR_UNSUPPORTED;
@@ -726,7 +737,7 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
   }
   a.bs = bs; a.hq = hq; a.hkv = hkv; a.g = hq / hkv;
   a.Lq = (int)Lq; a.Lk = (int)Lk;
-  a.n_qtiles = 0;
+  a.n_qtiles = a.tiles_run0 = 0;
   a.ticket_slot = 0;
   a.n_items = 0;
   a.n_queues = 1;
@@ -810,7 +821,7 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
   a.state_first = a.state_last = 0;
   a.bs = bs; a.hq = hq; a.hkv = hkv; a.g = hq / hkv;
   a.Lq = (int)Lq; a.Lk = (int)Lk;
-  a.n_qtiles = 0;
+  a.n_qtiles = a.tiles_run0 = 0;
   a.ticket_slot = 0;
   a.n_items = 0;
   a.n_queues = 1;

@@ -395,15 +395,16 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   const HeavyChoice none = {0, 0};
   if (!ring_in_one_launch(p)) return none;
   const int64_t Lq = p.L / p.ring;
-  const int T = (int)((Lq + 255) / 256), n = (p.hc / p.ulysses) * p.bs;
+  usp_posdesc qd;
+  ring_block_desc(p, r, &qd);
+  const RowTiles rows(qd, Lq, p.causal);
+  const int T = rows.n, n = (p.hc / p.ulysses) * p.bs;
   const int64_t items = (int64_t)T * n;
   if (items > 4 * kPlanCUs || Lq < 4096 || T < 8) return none;
   if (p.ring > 1 && items <= kPlanCUs) return none;   // short ring ranks: every tile per block, as key_splits() has it
   // Without a mask all items weigh the same and what is lost is the last, partly filled round (320 items on 256 CUs
   // take two rounds): the cut tiles' pieces then fill the first round and the whole items follow.
   if (!p.causal && items <= kPlanCUs) return none;
-  usp_posdesc qd;
-  ring_block_desc(p, r, &qd);
   const double kItem = 8.0, kTile = 1.85, kCross = 3.0;
   auto pos_of = [&](int64_t i) { return i < qd.len0 ? qd.start0 + i : qd.start1 + (i - qd.len0); };
   auto play = [&](const std::vector<double>& w) {
@@ -430,7 +431,7 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
       ring_block_desc(p, ((r - hp.block[j]) % p.ring + p.ring) % p.ring, &kd);
       const usp_posdesc pd = piece_of(kd, hp.first[j], hp.last[j]);
       for (int i = 0; i < T; ++i) {
-        const int64_t a = (int64_t)i * 256, b = std::min<int64_t>(Lq, a + 256);
+        const int64_t a = rows.begin(i), b = rows.end(i);
         int64_t qmax = std::max(pos_of(a), pos_of(b - 1));
         if (a < qd.len0 && b > qd.len0) qmax = std::max({qmax, pos_of(qd.len0 - 1), pos_of(qd.len0)});
         const int64_t c0 = p.causal ? std::clamp<int64_t>(qmax - pd.start0 + 1, 0, pd.len0) : pd.len0;
@@ -456,8 +457,8 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
     }
     double us = play(w);
     if (k > 0) {
-      const double rows = (double)std::min<int64_t>(Lq, (int64_t)k * 256) * n;
-      us += 10.0 + rows * p.hs * (hp.n * 2.0 * 4.0 + 2.0) / 5.0e6;   // the fp32 partials written and read, bf16 out
+      const double cut_rows = (double)(Lq - rows.begin(T - k)) * n;
+      us += 10.0 + cut_rows * p.hs * (hp.n * 2.0 * 4.0 + 2.0) / 5.0e6;   // the fp32 partials written and read, bf16 out
     }
     return us;
   };
@@ -749,7 +750,8 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
         st = launch_attn_fwd_partials((const char*)q + group_off, kp, vp, pd, lk, hp.n, o_ptrs, l_ptrs, p->bs, Lq, Lq, hq,
                                       hkv, p->hs, scale, p->causal ? 1 : 0, qd, stream, &seq, &mixed);
         if (st != USP_OK) return st;
-        const int64_t row0 = ((Lq + 255) / 256 - heavy.tiles) * 256;
+        const RowTiles rows(qd, Lq, p->causal);
+        const int64_t row0 = rows.begin(rows.n - heavy.tiles);
         st = launch_lse_merge((const void* const*)o_ptrs, (const float* const*)l_ptrs, hp.n, (char*)o + group_off, lse_rank,
                               p->bs, Lq, hq, p->hs, USP_FP32, p->dtype, stream, &seq, row0);
         if (st != USP_OK) return st;
@@ -968,31 +970,36 @@ BwdPlan plan_bwd(const usp_problem& p, int n_cols) {
 // 16384, this is off by 6 % on average and picks a cut within 0.3 % of the best one (one of eight Ulysses ranks of L = 8192:
 // 4 + 4 slices 298 us, 2 + 2 279; 32 heads of L = 2048: 2 + 2 slices 217 us, none 168).
 BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
-  const int64_t Lq = p.L / p.ring, T = (Lq + 255) / 256;
+  const int64_t Lq = p.L / p.ring;
   const int hq = r < 0 ? p.hc : p.hc / p.ulysses, hkv = r < 0 ? p.hk : p.hk / p.ulysses, g = hq / hkv;
   const int q_first = r < 0 ? 0 : r, q_last = r < 0 ? p.ring - 1 : r;
   BwdCut best = most;
   if (r < 0) best.k_splits = 1;   // dQ leaves as bf16
   const int m = p.bs * hkv;       // KV groups: alike, so one of them is played, on its share of the CUs
-  if (T * (q_last - q_first + 1) * m * g > 8 * kPlanCUs) return best;   // items to spare
+  if ((Lq + 255) / 256 * (q_last - q_first + 1) * m * g > 8 * kPlanCUs) return best;   // items to spare
   const int cus = std::max(1, (kPlanCUs + m / 2) / m);
   // 32-key steps of every (ring row, query tile), 32-query steps of every (K/V block, key tile): under kpos <= qpos the
   // keys that a run of queries sees are a prefix of each run of keys, the queries that see a key a suffix of theirs
   std::vector<usp_posdesc> pos(p.ring);
-  for (int s = 0; s < p.ring; ++s) ring_block_desc(p, s, &pos[s]);
+  std::vector<RowTiles> tiles;
+  for (int s = 0; s < p.ring; ++s) {
+    ring_block_desc(p, s, &pos[s]);
+    tiles.emplace_back(pos[s], Lq, p.causal);
+  }
+  const int T = tiles[0].n;   // (of every ring row)
   std::vector<double> dq, dkdv;
   auto steps = [](int64_t n) { return (double)((n + 31) / 32); };
-  for (int64_t t = T - 1; t >= 0; --t)
+  for (int t = T - 1; t >= 0; --t)
     for (int i = q_first; i <= q_last; ++i) {
-      const int64_t last = pos_max(pos[i], t * 256, std::min(Lq, t * 256 + 256));
+      const int64_t last = pos_max(pos[i], tiles[i].begin(t), tiles[i].end(t));
       double w = 0.0;
       for (const usp_posdesc& k : pos)
         w += p.causal ? steps(std::clamp<int64_t>(last - k.start0 + 1, 0, k.len0)) + steps(std::clamp<int64_t>(last - k.start1 + 1, 0, k.len1)) : steps(Lq);
       dq.push_back(w);
     }
-  for (const usp_posdesc& k : pos)
-    for (int64_t t = 0; t < T; ++t) {
-      const int64_t first = pos_min(k, t * 256, std::min(Lq, t * 256 + 256));
+  for (int s = 0; s < p.ring; ++s)
+    for (int t = 0; t < T; ++t) {
+      const int64_t first = pos_min(pos[s], tiles[s].begin(t), tiles[s].end(t));
       double w = 0.0;
       for (int i = q_first; i <= q_last; ++i)
         w += p.causal ? steps(pos[i].len0 - std::clamp<int64_t>(first - pos[i].start0, 0, pos[i].len0)) +
