@@ -162,8 +162,8 @@ extern "C" int usp_block_attn_fwd_state(const void* q, const void* k, const void
   }
   if (scale == 0.0f) scale = 1.0f / sqrtf((float)hs);
   const RingState rs = {(float*)state, first ? 1 : 0, last ? 1 : 0};
-  return launch_ring_attn_fwd(q, &k, &v, &kd, 1, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal ? 1 : 0, qd, USP_BF16,
-                              o_dtype, (hipStream_t)stream, nullptr, &rs);
+  return launch_block_attn_fwd(q, k, v, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal ? 1 : 0, qd, kd, USP_BF16, o_dtype,
+                               (hipStream_t)stream, &rs);
 }
 
 namespace {

@@ -137,7 +137,7 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
                              const SeqLayoutIO* seq = nullptr, const MixedLaunch* mixed = nullptr);
 int launch_block_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
                           int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
-                          const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream);
+                          const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream, const RingState* state = nullptr);
 
 // wave_split_attn_fwd.hip: the keys of 32 query rows split over the waves of one workgroup; bf16 or fp32 data.
 // The whole of Algorithm 1's forward for ranks [rank_begin, rank_end) in one launch, everything read and written in the
@@ -146,7 +146,8 @@ int launch_wave_split_usp_fwd(const usp_problem& p, const void* q, const void* k
                               int rank_begin, int rank_end, float scale, hipStream_t stream);
 int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
                                 int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
-                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream);
+                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream,
+                                const RingState* state = nullptr);
 // Time of such a launch, in us: rounds of one workgroup (32 rows of a head; two at head size 64) per CU, 4 us each for its
 // first loads and the merge of its waves, and 0.6 PFLOP/s, where reading every key for only 32 rows leaves it.  Measured
 // (this formula): one rank of four heads, causal, L = 4096 38 us (41), 8192 128 (134); 32 heads, L = 1024 37 (34),

@@ -47,6 +47,10 @@ struct WsArgs {
   int n_qtiles, causal, split;
   PosDesc32 qpos, kpos;       // split < 0: the one block's positions as given, else by Algorithm 2 from the ring rank
   float scale, scale_log2;
+  // Running state of a ring that delivers its blocks one per call (STATE instances), in the 256-row kernel's records
+  // (block_attn_fwd.hip): per 32 rows of a (batch, head) the O^T accumulator as [hs / 8][64 lanes][4], m, and l, per lane.
+  float* state;
+  int state_first, state_last, state_records;   // records of a (batch, head)
 };
 
 // Algorithm 2 for ring rank r: chunks r and 2R-1-r of 2R, or block r of R
@@ -259,7 +263,7 @@ constexpr size_t lds_bytes() {
   return (states > tiles ? states : tiles);
 }
 
-template <typename T, int HS, typename OutT>
+template <typename T, int HS, typename OutT, bool STATE = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS>::kWavesPerSimd, Operands<T, HS>::kWavesPerSimd)))
 void wave_split_attn_fwd(const WsArgs a) {
   using Op = Operands<T, HS>;
@@ -296,6 +300,18 @@ void wave_split_attn_fwd(const WsArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
   float m = -INFINITY, l = 0.f;
+
+  // The state enters with the merge, as a ninth wave's would, and leaves from there: nothing of it is held meanwhile.
+  float* rec = nullptr;
+  __shared__ float m_state_s[kRows], f_state_s[kRows];
+  if constexpr (STATE) {
+    rec = a.state + ((size_t)(b * a.hq + h) * a.state_records + row0 / kRows) * (HS * kRows + 128);
+    if (!a.state_first && !a.state_last) {   // rows that see nothing of this block: their state stays as it is
+      const TileRanges tr = visible_key_tiles<kTile>(a.causal, qpos, a.kpos, a.Lk, row0, row1);
+      if (tr.a1 - tr.a0 + tr.b1 - tr.b0 == 0) return;   // workgroup-uniform
+    }
+    if (threadIdx.x < kRows) m_state_s[threadIdx.x] = a.state_first ? -INFINITY : rec[HS * kRows + threadIdx.x];
+  }
 
   char* const lds = smem + wave * Op::kLdsPerWave;
   int turn = wave;        // tiles of the walk until this wave's next one
@@ -344,6 +360,10 @@ void wave_split_attn_fwd(const WsArgs a) {
         if (wave < 2 && t < 32) first_s[wave][t] = (wave == 0 || i == 0) ? mx : -INFINITY;
         __syncthreads();
         m = fmaxf(first_s[0][t & 31], first_s[1][t & 31]);
+        if constexpr (STATE) {   // (a row that has a state goes on from its maximum)
+          const float ms = m_state_s[t & 31];
+          m = ms > -INFINITY ? ms : m;
+        }
         shared_first = true;
       }
       if (__any((mx - m) * a.scale_log2 > kRescaleThreshold)) {   // (m = -inf and a key: inf; no key at all: NaN, no)
@@ -374,6 +394,17 @@ void wave_split_attn_fwd(const WsArgs a) {
   // ---- the waves' states are combined: common maximum, scaled outputs side by side in LDS, summed row by row
   int end_lane = lane;   // (a lane index of its own for the epilogue: what derives from it is not kept across the loop)
   asm volatile("" : "+v"(end_lane));
+  constexpr int PER_ROW = HS / 4, ROWS_PER_PASS = kWaves * 64 / PER_ROW, PASSES = kRows / ROWS_PER_PASS;
+  // where the record holds dims 4 c .. 4 c + 3 of row rr: this thread's part of the last step
+  auto rec_at = [&](int rr, int c) { return rec + ((c >> 1) * 64 + (c & 1) * 32 + rr) * 4; };
+  f32x4 o_state[STATE ? PASSES : 1];
+  if constexpr (STATE) {   // asked for here, needed behind two barriers
+    if (!a.state_first) {
+#pragma unroll
+      for (int pass = 0; pass < PASSES; ++pass)
+        o_state[pass] = *(const f32x4*)rec_at(pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, (int)threadIdx.x % PER_ROW);
+    }
+  }
   l = both_halves_sum(l);
   if (end_lane < 32) {
     m_s[wave][(end_lane & 31)] = m;
@@ -386,6 +417,7 @@ void wave_split_attn_fwd(const WsArgs a) {
   for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][(end_lane & 31)];
 #pragma unroll
   for (int j = 0; j < kWaves; ++j) m_all = fmaxf(m_all, mw[j]);
+  if constexpr (STATE) m_all = fmaxf(m_all, m_state_s[end_lane & 31]);
   const float mc = m_all == -INFINITY ? 0.f : m_all * a.scale_log2;
   {
     const float f = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);
@@ -393,24 +425,45 @@ void wave_split_attn_fwd(const WsArgs a) {
 #pragma unroll
     for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, end_lane >> 5)) = Op::group(o, gi) * f;
   }
-  if (wave == 0 && end_lane < 32) {
+  if (wave == 0 && (STATE || end_lane < 32)) {
     float tot = 0.f;
 #pragma unroll
     for (int j = 0; j < kWaves; ++j) tot += l_s[j][(end_lane & 31)] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
+    if constexpr (STATE) {
+      float f = 0.f;
+      float* const lane_rec = rec + HS * kRows;   // m of 64 lanes, l of 64 lanes: a row's l is the sum of its two
+      if (!a.state_first) {
+        f = __builtin_amdgcn_exp2f(m_state_s[end_lane & 31] * a.scale_log2 - mc);
+        tot += (lane_rec[64 + (end_lane & 31)] + lane_rec[96 + (end_lane & 31)]) * f;
+      }
+      f_state_s[end_lane & 31] = f;
+      if (!a.state_last) {
+        lane_rec[end_lane] = m_all;
+        lane_rec[64 + end_lane] = end_lane < 32 ? tot : 0.f;
+      }
+    }
+    if (!STATE || a.state_last) {
     inv_s[(end_lane & 31)] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
     if (row0 + (end_lane & 31) < a.Lq)
       a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + (end_lane & 31)] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
+    }
   }
   __syncthreads();
   const BlockRows orow = block_rows(a.o, sizeof(OutT), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
-  constexpr int PER_ROW = HS / 4, ROWS_PER_PASS = kWaves * 64 / PER_ROW;
 #pragma unroll
-  for (int pass = 0; pass < kRows / ROWS_PER_PASS; ++pass) {
+  for (int pass = 0; pass < PASSES; ++pass) {
     const int rr = pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, c = (int)threadIdx.x % PER_ROW;
     const float* src = (const float*)smem + rr * OSTR + 4 * c;
     f32x4 sum = *(const f32x4*)src;
 #pragma unroll
     for (int j = 1; j < kWaves; ++j) sum += *(const f32x4*)(src + j * (kRows * OSTR));
+    if constexpr (STATE) {
+      if (!a.state_first) sum += o_state[pass] * f_state_s[rr];
+      if (!a.state_last) {
+        *(f32x4*)rec_at(rr, c) = sum;
+        continue;
+      }
+    }
     sum *= inv_s[rr];
     if (row0 + rr < a.Lq) {
       OutT* dst = (OutT*)orow.row(row0 + rr) + 4 * c;
@@ -420,10 +473,10 @@ void wave_split_attn_fwd(const WsArgs a) {
   }
 }
 
-template <typename T, int HS, typename OutT>
+template <typename T, int HS, typename OutT, bool STATE = false>
 int launch_typed(const WsArgs& a, int64_t grid, hipStream_t stream) {
   constexpr size_t lds = lds_bytes<T, HS>();
-  auto kern = wave_split_attn_fwd<T, HS, OutT>;
+  auto kern = wave_split_attn_fwd<T, HS, OutT, STATE>;
   static LdsLimitRaised lds_limit;   // per kernel instance
   if (!raise_dynamic_lds_limit((const void*)kern, lds, lds_limit)) return USP_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kWaves * 64), lds, stream, a);
@@ -438,6 +491,10 @@ int launch(WsArgs a, int hs, int in_dtype, int o_dtype, hipStream_t stream) {
   a.scale_log2 = a.scale * 1.4426950408889634f;
   const int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * a.n_ranks;
   if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
+  if (a.state) {   // bf16 data
+    if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<__bf16, 128, float, true>(a, grid, stream) : launch_typed<__bf16, 128, __bf16, true>(a, grid, stream);
+    return o_dtype == USP_FP32 ? launch_typed<__bf16, 64, float, true>(a, grid, stream) : launch_typed<__bf16, 64, __bf16, true>(a, grid, stream);
+  }
   if (in_dtype == USP_FP32) {
     if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<float, 128, float>(a, grid, stream) : launch_typed<float, 128, __bf16>(a, grid, stream);
     return o_dtype == USP_FP32 ? launch_typed<float, 64, float>(a, grid, stream) : launch_typed<float, 64, __bf16>(a, grid, stream);
@@ -464,7 +521,7 @@ int launch_wave_split_usp_fwd(const usp_problem& p, const void* q, const void* k
 
 int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
                                 int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
-                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream) {
+                                const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream, const RingState* state) {
   WsArgs a = {};
   a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
   a.bs = bs; a.hq = a.q_heads = hq; a.hkv = a.kv_heads = hkv;
@@ -472,6 +529,10 @@ int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, voi
   a.Lq = (int)Lq; a.n_q = fast_div(Lq);
   a.Lk = (int)Lk; a.n_k = fast_div(Lk);
   a.causal = causal; a.split = -1;
+  if (state) {
+    a.state = state->state; a.state_first = state->first; a.state_last = state->last;
+    a.state_records = (int)((Lq + 255) / 256) * 8;
+  }
   a.qpos = PosDesc32{(int)qpos.start0, (int)qpos.len0, (int)qpos.start1, (int)qpos.len1};
   a.kpos = PosDesc32{(int)kpos.start0, (int)kpos.len0, (int)kpos.start1, (int)kpos.len1};
   a.scale = scale;

@@ -61,3 +61,26 @@ def test_block_step_fp32_every_mask(usp, case, o_dtype):
     o, lse, ref_o, ref_l = _run_block(usp, 77, bs, Lq, Lk, hq, hkv, hs, causal, qd, kd, tl.FP32, o_dtype)
     tl.assert_lse_close(lse, ref_l, 2e-5)
     assert tl.max_abs(o, ref_o) <= (2e-5 if o_dtype == tl.FP32 else 2e-2)
+
+
+@pytest.mark.parametrize("hs", [64, 128])
+@pytest.mark.parametrize("blocks", [[64, 1500, 100, 1500], [1500, 64], [1500], [33, 1], [1400, 1400, 7]])
+def test_state_passes_between_the_kernels(usp, blocks, hs):
+    """A ring whose calls are short and long in turn: the 256-row kernel and this one take up each other's running state
+    (same records).  Against double precision: weights and O rounded to bf16, below 2^-7."""
+    Lq, hq, hkv = 1000, 16, 8
+    gen = torch.Generator(device="cuda").manual_seed(len(blocks))
+    q = torch.randn((1, Lq, hq, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
+    kv = [[torch.randn((1, n, hkv, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for n in blocks] for _ in range(2)]
+    state = torch.full((usp.usp_block_attn_fwd_state_bytes(1, Lq, hq, hs),), 0xFF, dtype=torch.uint8, device="cuda")
+    o = torch.zeros_like(q)
+    lse = torch.zeros((1, hq, Lq), device="cuda")
+    for i, n in enumerate(blocks):
+        usp.usp_block_attn_fwd_state(q, kv[0][i], kv[1][i], state, o, lse, 1, Lq, n, hq, hkv, hs, 0.0, False, None, None,
+                                     i == 0, i == len(blocks) - 1, usp.USP_BF16)
+    k, v = (torch.cat([x[0] for x in t]).double().repeat_interleave(hq // hkv, 1) for t in kv)
+    for h in range(hq):
+        s = q[0, :, h].double() @ k[:, h].T * hs ** -0.5
+        ref = s.softmax(-1) @ v[:, h]
+        assert ((o[0, :, h].double() - ref).norm() / ref.norm()).item() < 2 ** -7
+        assert (lse[0, h].double() - s.logsumexp(-1)).abs().max().item() < 1e-4
