@@ -34,9 +34,9 @@ using namespace dev;
 
 constexpr int kMaxBlocks = USP_MAX_RING_BLOCKS;
 
-// One launch covers the n_blocks K/V blocks of a rank's ring loop (n_blocks = 1: a single ring step): the dQ
-// kernel walks them one after the other with its accumulator in registers, the dK/dV kernel spreads them over
-// the grid (each block has its own output accumulators).
+// One launch covers the n_blocks K/V blocks of a rank's ring loop (n_blocks = 1: a single ring step): a dQ
+// item walks them one after the other with its accumulator in registers, the dK/dV items are spread over
+// them (each block has its own output accumulators).
 struct BwdArgs {
   const void* q;
   const void* k[kMaxBlocks];
@@ -462,7 +462,7 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
 // -------------------------------------------------------------------------------------------------
 // dQ from a stored dS: what is left of the dQ kernel when the dK/dV kernel has written its dS blocks
 // (BwdArgs::ds).  One product, dQ^T += K^T dS^T, and the kernel is bound by reading dS: 2 bytes per visible
-// (query, key) pair.  Same work items, slices and epilogue as bwd_dq_kernel.  A step covers KT keys (64 or
+// (query, key) pair.  Same work items, slices and epilogue as dq_item.  A step covers KT keys (64 or
 // 128): the K rows staged by the workgroup (double buffered), and per wave KT / 32 blocks of dS (2 KiB: its 32
 // queries x 32 keys each) that the wave copies as they are into its own part of LDS and reads back through
 // transpose reads, which yields the B operand (lane = query, k = keys in the order of the K^T fragments).  A

@@ -1007,40 +1007,54 @@ BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
                       : steps(Lq);
       dkdv.push_back(w);
     }
-  const double f = p.hs == 128 ? 1.0 : 0.62;
-  const int max_copies = g / most.heads_per_wg * most.q_splits;
-  const int max_q = (int)std::clamp<int64_t>(Lq / 512, 1, 4), max_k = best.k_splits;
-  double best_us = 0.0;
-  std::vector<double> free_at;
-  for (int h = g; h >= 1; --h) {
-    if (g % h) continue;
-    for (int q = 1; q <= max_q && g / h * q <= max_copies; ++q)
-      for (int k = 1; k <= max_k; ++k) {
-        free_at.assign(cus, 0.0);   // a min-heap of the workgroups' finish times
-        double end = 0.0;
-        auto play = [&](double us, int times) {
-          for (int i = 0; i < times; ++i) {
-            std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
-            end = std::max(end, free_at.back() += us);
-            std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
-          }
-        };
-        for (double w : dkdv) play(6.0 + 1.68 * f * h * w / q, g / h * q);
-        for (double w : dq) play(10.0 + 1.2 * f * w / k, g * k);
-        const double copied = (k > 1 ? (double)k * hq * (q_last - q_first + 1) : 0.0) + (g / h * q > 1 ? 2.0 * (g / h * q) * hkv * p.ring : 0.0);
-        double us = end + (copied > 0.0 ? 6.0 + copied * p.bs * Lq * p.hs * 4.0 / 4.5e6 : 0.0);
-        // (what the workspace was sized for is left for a gain of 3 % or more: at L = 32768 cuts that look alike here differ by 1 %)
-        if (h == most.heads_per_wg && q == most.q_splits && (k == most.k_splits || r < 0)) us *= 0.97;
-        if (best_us == 0.0 || us < best_us) {
-          best_us = us;
-          best = BwdCut{h, k, q};
+  const double f = p.hs == 128 ? 1.0 : 0.62, tq = 1.2 * f, tk = 1.68 * f;
+  double sum_q = 0.0, sum_k = 0.0, max_q = 0.0, max_k = 0.0;
+  for (double w : dq) { sum_q += w; max_q = std::max(max_q, w); }
+  for (double w : dkdv) { sum_k += w; max_k = std::max(max_k, w); }
+  std::vector<double> free_at;   // the workgroups' finish times, a min-heap
+  double best_us = 1e30;
+  auto consider = [&](const BwdCut& c, double factor) {
+    const int parts = g / c.heads_per_wg * c.q_splits;   // dK/dV items per key tile, copies of dK and dV
+    const double copied = (c.k_splits > 1 ? (double)c.k_splits * hq * (q_last - q_first + 1) : 0.0) + (parts > 1 ? 2.0 * parts * hkv * p.ring : 0.0);
+    const double copies_us = copied > 0.0 ? 6.0 + copied * p.bs * Lq * p.hs * 4.0 / 4.5e6 : 0.0;
+    const double limit = best_us / factor - copies_us;   // it has to end before this
+    const double item_k = tk * c.heads_per_wg / c.q_splits, item_q = tq / c.k_splits;
+    const double share = (parts * (6.0 * dkdv.size() + item_k * sum_k) + g * c.k_splits * (10.0 * dq.size() + item_q * sum_q)) / cus;
+    if (std::max({share, 6.0 + item_k * max_k, 10.0 + item_q * max_q}) >= limit) return;   // most cuts end here, unplayed
+    free_at.assign(cus, 0.0);
+    double end = 0.0;
+    auto play = [&](double us, int times) {
+      for (int i = 0; i < times; ++i) {
+        const double t = free_at[0] + us;
+        end = std::max(end, t);
+        int at = 0;   // the first to be free takes the item; its new time sinks to its place
+        for (int kid; (kid = 2 * at + 1) < cus; at = kid) {
+          if (kid + 1 < cus && free_at[kid + 1] < free_at[kid]) ++kid;
+          if (free_at[kid] >= t) break;
+          free_at[at] = free_at[kid];
         }
+        free_at[at] = t;
       }
-  }
+      return end < limit;
+    };
+    for (double w : dkdv)
+      if (!play(6.0 + item_k * w, parts)) return;
+    for (double w : dq)
+      if (!play(10.0 + item_q * w, g * c.k_splits)) return;
+    best_us = factor * (end + copies_us);
+    best = c;
+  };
+  // (what the workspace was sized for is left for a gain of 3 % or more: at L = 32768 cuts that look alike here differ by 1 %)
+  consider(best, 0.97);
+  const int max_copies = g / most.heads_per_wg * most.q_splits;
+  const int max_slices = (int)std::clamp<int64_t>(Lq / 512, 1, 4), max_k_splits = best.k_splits;
+  for (int h = g; h >= 1; --h)
+    for (int q = 1; g % h == 0 && q <= max_slices && g / h * q <= max_copies; q *= 2)
+      for (int k = 1; k <= max_k_splits; k = k < 2 ? 2 : k + 2) consider(BwdCut{h, k, q}, 1.0);
   return best;
 }
 
-// Playing the cuts of a problem through takes the host 0.1-0.5 ms: the last answers are kept, as heavy_choice() keeps its.
+// Playing the cuts of a problem through takes the host 0.1 ms, 0.7 at most: the last answers are kept, as heavy_choice() keeps its.
 BwdCut bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   struct Entry { usp_problem p; int r; BwdCut cut; };   // (`most` follows from the problem)
   static std::mutex mu;
