@@ -49,14 +49,20 @@ __host__ __device__ inline int64_t pos_max(const usp_posdesc& d, int64_t a, int6
 // The 256-row tiles that local rows (or keys) [0, len) with positions d are cut into.  Rows of two separate runs under a
 // causal mask (the zigzag split of two and more ring ranks): no tile holds rows of both, because it would walk everything
 // that the later run sees for the rows of the earlier one as well, one more long item per head.  Measured, ring rank 1 of
-// 8, two of L = 16000, 32 heads: eight tiles of 256 in a row, five of them long, 1054 us; four per run 546 us.
+// 8, two of L = 16000, 32 heads: eight tiles of 256 in a row, five of them long, 1054 us; four per run 546 us.  Where that takes one tile
+// more, as many tiles are long as before, and of few tiles the one more costs (rank 3 of 8, L = 6000: 101 us in a row, 104 apart).
 struct RowTiles {
   int n, in_run0;     // tiles in all; in_run0 > 0: the first run's, the rest are cut from row len0 on; 0: [0, len) in a row
   int64_t len0, len;
   RowTiles(const usp_posdesc& d, int64_t len_, int causal) : len0(d.len0), len(len_) {
     const bool apart = causal && d.len0 > 0 && d.len1 > 0 && d.start1 != d.start0 + d.len0 && d.len0 % 256 != 0;
-    in_run0 = apart ? (int)((len0 + 255) / 256) : 0;
-    n = apart ? in_run0 + (int)((len - len0 + 255) / 256) : (int)((len + 255) / 256);
+    n = (int)((len + 255) / 256);
+    in_run0 = 0;
+    const int first = (int)((len0 + 255) / 256), both = first + (int)((len - len0 + 255) / 256);
+    if (apart && (both == n || n >= 8)) {
+      in_run0 = first;
+      n = both;
+    }
   }
   int64_t begin(int64_t i) const { return in_run0 && i >= in_run0 ? len0 + (i - in_run0) * 256 : i * 256; }
   int64_t end(int64_t i) const {
