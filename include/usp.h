@@ -207,16 +207,20 @@ int usp_ring_attn_fwd_partials(const void* q, const void* const* k_blocks, const
  * With bf16 data and R <= USP_MAX_RING_BLOCKS the ring loop and the merge are the single launch of
  * usp_ring_attn_fwd (all blocks are resident on the one GPU); with more blocks one usp_block_attn_fwd per ring step
  * with fp32 partials, then usp_lse_merge.  fp32 data, and the shortest bf16 sequences, run all ranks of the range in one
- * launch that reads and writes the shards directly (the workspace is then checked, but not used).  Short sequences (fewer
- * query tiles x heads than keep 256 CUs busy for as long as the last tile takes) run the single launch of usp_ring_attn_fwd_partials over two to eight parts of
- * the keys, then usp_lse_merge; a little longer (more than one work item per CU, the heaviest still longer than
- * a CU's share) only the last query tiles of a causal rank are cut so, in the same launch as the whole ones, and
- * the merge covers their rows; the workspace query knows.
+ * launch that reads and writes the shards directly (the workspace is then checked, but used only where o or lse lies over
+ * an input).  Short sequences (fewer query tiles x heads than keep 256 CUs busy for as long as the last tile takes) run the
+ * single launch of usp_ring_attn_fwd_partials over two to eight parts of the keys, then usp_lse_merge; a little longer
+ * (more than one work item per CU, the heaviest still longer than a CU's share) only the last query tiles of a causal rank
+ * are cut so, in the same launch as the whole ones, and the merge covers their rows; the workspace query knows.
  *   q, o: seq layout with hc heads; k, v: seq layout with hk heads (ALL N shards must be
  *   present: the ring reads the other ring ranks' K/V where hardware would receive them);
  *   lse: [N][bs][hc/U][L/R] float, written for the ranks in range.
  * With Ulysses degree 1 the all-to-alls are the identity (a block in head layout is its shard as it stands): K, and
- * V unless re-tiling it pays, are read where the caller holds them, not copied.
+ * V unless re-tiling it pays, are read where the caller holds them, not copied; so they are with a batch of one, bf16 data
+ * and any degree.
+ * o and lse may lie over inputs as follows: o may be q's own buffer; with a Ulysses degree above 1, o and lse may lie over
+ * k and v (these are then copied to the workspace before anything is written).  With Ulysses degree 1 o and lse must lie
+ * apart from k and v (but for o of a single rank of fp32 data).
  * The workspace query returns 0 for an invalid problem or n_ranks < 1, and also for a plan that needs none (a
  * ring-only bf16 problem whose ring loop is one launch): usp_attn_fwd then accepts any workspace pointer, NULL
  * included; usp_validate tells the two apart. */

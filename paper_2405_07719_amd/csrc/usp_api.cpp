@@ -104,6 +104,11 @@ extern "C" int usp_layout_a2a(const usp_problem* p, int heads, int dir, const vo
   return launch_layout_a2a(*p, heads, dir, src, dst, rank_begin, rank_end, 0, (hipStream_t)stream);
 }
 
+// Whether na bytes at a and nb bytes at b share memory.
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (const char*)a < (const char*)b + nb && (const char*)b < (const char*)a + na;
+}
+
 static bool desc_ok(const usp_posdesc* d, int64_t len) {
   // positions must fit 32 bits: the kernels narrow them
   const int64_t lim = (int64_t)1 << 31;
@@ -275,9 +280,6 @@ extern "C" int usp_lse_merge(const void* const* o_parts, const float* const* lse
     const size_t rows = (size_t)bs * (size_t)Lq * hq;
     const size_t ob = rows * hs * dtype_size(out_dtype), pb = rows * hs * dtype_size(part_dtype), lb = rows * sizeof(float);
     const bool in_place_ok = part_dtype == out_dtype && (hs == 64 || hs == 128);
-    auto overlap = [](const void* a, size_t na, const void* b, size_t nb) {
-      return (const char*)a < (const char*)b + nb && (const char*)b < (const char*)a + na;
-    };
     for (int i = 0; i < n_parts; ++i) {
       if (overlap(o_out, ob, o_parts[i], pb) && !(in_place_ok && o_out == o_parts[i])) return USP_ERR_UNSUPPORTED;
       if (overlap(lse_out, lb, lse_parts[i], lb) && !(in_place_ok && lse_out == lse_parts[i])) return USP_ERR_UNSUPPORTED;
@@ -534,9 +536,10 @@ bool short_in_one_launch(const usp_problem& p, int n_ranks) {
 }
 
 // allow_heavy = false: as if no rank cut its heaviest tiles (the entry point without a workspace of its own falls back
-// to that when the partials would not fit its array).  aligned = false: K or V does not lie on 16 bytes, as the kernels'
-// reads of whole chunks want them; the staged copies do.  (The sizes are the same.)
-FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true, bool aligned = true) {
+// to that when the partials would not fit its array).  may_read_in_place = false: K or V does not lie on 16 bytes, as the
+// kernels' reads of whole chunks want them, or the results go over them; the staged copies are neither.  (The sizes are
+// the same.)
+FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true, bool may_read_in_place = true) {
   FwdPlan f;
   const size_t es = dtype_size(p.dtype);
   const size_t Lq = p.L / p.ring, hq = p.hc / p.ulysses, hkv = p.hk / p.ulysses;
@@ -574,7 +577,7 @@ FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true, bool
   f.v_head = off; off += f.k_in_place && !f.v_transposed ? 0 : up256(f.v_block_bytes * p.ring * n_cols);
   // A batch of one is read in place at every Ulysses degree (the room for its staged copies stays in the plan: callers
   // have been told the size).  Measured, L = 8192, one of eight Ulysses ranks: 99.0 us staged, 95.0 in place; L = 32768 984.1, 982.4.
-  if (p.bs == 1 && aligned && !f.k_in_place && ring_in_one_launch(p)) {
+  if (p.bs == 1 && may_read_in_place && !f.k_in_place && ring_in_one_launch(p)) {
     f.k_in_place = true;
     f.v_transposed = f.v_transposed && retiling_pays();
   }
@@ -662,19 +665,35 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   int c0, c1;
   column_range(*p, rank_begin, rank_end, &c0, &c1);
   const bool aligned = (((uintptr_t)k | (uintptr_t)v) & 15) == 0;
-  const FwdPlan f = plan_fwd(*p, c1 - c0, allow_heavy, aligned);
+  const size_t es = dtype_size(p->dtype);
+  const int64_t Lq = p->L / R;
+  const int hq = p->hc / U, hkv = p->hk / U;
+  // Results may only be written while inputs are still read if they share no memory (O over Q itself apart: whoever writes
+  // rows of O has read these rows of Q, and nobody else reads them).
+  bool kv_apart = true, q_apart = true;
+  {
+    const size_t ring_row = (size_t)p->bs * Lq * p->hc * p->hs * es, kv_all = (size_t)p->bs * p->L * p->hk * p->hs * es;
+    const size_t lse_rank_bytes = (size_t)p->bs * hq * Lq * sizeof(float);
+    const size_t first = rank_begin / U * ring_row, qo_bytes = ((rank_end - 1) / U + 1) * ring_row - first;
+    const char *o_out = (const char*)o + first, *q_in = (const char*)q + first;
+    const char* lse_out = (const char*)lse + rank_begin * lse_rank_bytes;
+    const size_t lse_bytes = (rank_end - rank_begin) * lse_rank_bytes;
+    for (const void* in : {k, v})
+      if (overlap(in, kv_all, o_out, qo_bytes) || overlap(in, kv_all, lse_out, lse_bytes)) kv_apart = false;
+    if ((o != q && overlap(q_in, qo_bytes, o_out, qo_bytes)) || overlap(q_in, qo_bytes, lse_out, lse_bytes)) q_apart = false;
+  }
+  const FwdPlan f = plan_fwd(*p, c1 - c0, allow_heavy, aligned && kv_apart);
   // (a plan that needs no workspace at all, as a ring-only problem in one launch, takes any pointer, null included)
   if (f.total > 0 && (!workspace || workspace_bytes < f.total || ((uintptr_t)workspace & 255))) return USP_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)stream_;
   char* ws = (char*)workspace;
-  const size_t es = dtype_size(p->dtype);
-  const int64_t Lq = p->L / R;
-  const int hq = p->hc / U, hkv = p->hk / U;
   const float scale = p->scale == 0.0f ? 1.0f / sqrtf((float)p->hs) : p->scale;
 
   // fp32 data, and short sequences: all ranks of the range in one launch that reads and writes the shards themselves
+  // (results over inputs: step by step, from staged copies)
   if (p->dtype == USP_FP32 && R > USP_MAX_MERGE_PARTS) return USP_ERR_UNSUPPORTED;
-  if (p->dtype == USP_FP32 || (aligned && R <= USP_MAX_MERGE_PARTS && short_in_one_launch(*p, rank_end - rank_begin)))
+  if (kv_apart && q_apart &&
+      (p->dtype == USP_FP32 || (aligned && R <= USP_MAX_MERGE_PARTS && short_in_one_launch(*p, rank_end - rank_begin))))
     return launch_wave_split_usp_fwd(*p, q, k, v, o, lse, rank_begin, rank_end, scale, stream);
 
   // Steps 3-4 of Algorithm 1 for every K/V block the ranks in range will visit.  The workspace slot of
@@ -1117,8 +1136,7 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
     const size_t out_bytes[] = {q_all, kv_all, kv_all};
     for (int i = 0; i < 6; ++i)
       for (int j = 0; j < 3; ++j)
-        if ((const char*)in[i] < (const char*)out[j] + out_bytes[j] && (const char*)out[j] < (const char*)in[i] + in_bytes[i])
-          apart = false;
+        if (overlap(in[i], in_bytes[i], out[j], out_bytes[j])) apart = false;
   }
   // With Ulysses degree 1 the all-to-alls are the identity; with a batch of one the shards of a ring row are contiguous,
   // [Lq][heads][hs].  Either way a rank's tensors are its heads of the ring row's rows.
