@@ -80,18 +80,19 @@ __device__ inline BlockRows block_rows(const void* t, int esize, int hs, int bs,
                    shard_bytes - run_bytes};
 }
 
-// One 32-key tile of such rows.  Inside one shard (and always when bs = 1) it is read through a buffer descriptor: the
-// lane's byte offset is the same for every tile, the row within the tile goes into the scalar offset, rows past the last
-// key read as zeros.  (With a 64-bit row address per load the address arithmetic took as long as the products.)  A tile
-// that crosses from one shard into the next, which lie bs entries apart, finds each row on its own.
+// One 32-key tile of such rows.  All 32 of them inside one shard (always, when bs = 1) are read through a buffer
+// descriptor: the lane's byte offset is the same for every tile, the row within the tile goes into the scalar offset.
+// (With a 64-bit row address per load the address arithmetic took as long as the products.)  A tile that crosses from one
+// shard into the next, which lie bs entries apart, finds each row on its own, and so does the last, ragged one, where a row
+// past the last key is that key's again (the mask hides it): a buffer's range check does not cover the scalar offset.
 struct Tile {
   BlockRows rows;
   int key0, last;       // first key; last valid row of the tile
-  bool whole;           // inside one shard
+  bool whole;           // 32 rows inside one shard
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ Tile(const BlockRows& r, int key0_, int len, int row_len) : rows(r), key0(key0_) {
     last = min(kTile, len - key0) - 1;
-    whole = r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last);
+    whole = last == kTile - 1 && (r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last));
     rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)r.row(key0), 0, last * (int)r.row_bytes + row_len, kRawBufferFlags);
   }
   // t[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
