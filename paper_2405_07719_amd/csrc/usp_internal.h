@@ -71,6 +71,9 @@ struct RowTiles {
   }
 };
 
+// Workgroups of so many threads that one dimension of a grid holds: HIP refuses 2^32 threads and more.
+constexpr int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
+
 inline int launch_status() { return hipGetLastError() == hipSuccess ? USP_OK : USP_ERR_LAUNCH; }
 
 // Raises a kernel's limit of dynamic LDS, once per kernel instance and device (the attribute belongs to the device's
