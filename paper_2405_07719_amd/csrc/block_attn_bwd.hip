@@ -1072,15 +1072,16 @@ struct ConvertJob {
   ConvertSeq cs;
 };
 constexpr int kMaxConvertJobs = 3;   // dQ, dK, dV
-struct ConvertArgs { ConvertJob job[kMaxConvertJobs]; int n_jobs; };
+struct ConvertArgs { ConvertJob job[kMaxConvertJobs]; int n_jobs; uint32_t first_wg; };   // first_wg: of this launch
 
 // fp32 accumulators -> bf16 / fp32 outputs, 4 elements per lane; all tensors of a call go through one launch
 template <typename OutT>
 __global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
+  const uint32_t at = a.first_wg + blockIdx.x;
   int j = 0;
-  while (j + 1 < a.n_jobs && blockIdx.x >= a.job[j + 1].first_wg) ++j;
+  while (j + 1 < a.n_jobs && at >= a.job[j + 1].first_wg) ++j;
   const ConvertJob& job = a.job[j];
-  const uint32_t wg = blockIdx.x - job.first_wg, blk = wg / job.wgs_per_blk;
+  const uint32_t wg = at - job.first_wg, blk = wg / job.wgs_per_blk;
   const size_t i = (size_t)(wg - blk * job.wgs_per_blk) * 256 + threadIdx.x;
   if (i >= job.n4) return;
   const f32x4* src = (const f32x4*)job.src + blk * job.src_blk4 + i;
@@ -1352,11 +1353,18 @@ int launch_bwd_convert(const ConvertTensor* tensors, int n_tensors, int out_dtyp
     wgs += per_blk * t.n_blocks;
     if (wgs > 0x7fffffffull) return USP_ERR_UNSUPPORTED;
   }
-  if (out_dtype == USP_FP32)
-    hipLaunchKernelGGL((bwd_convert_kernel<float>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
-  else
-    hipLaunchKernelGGL((bwd_convert_kernel<__bf16>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
-  return launch_status();
+  const uint64_t at_once = max_workgroups(256);
+  for (uint64_t first = 0; first < wgs; first += at_once) {
+    a.first_wg = (uint32_t)first;
+    const dim3 grid((unsigned)std::min(wgs - first, at_once));
+    if (out_dtype == USP_FP32)
+      hipLaunchKernelGGL((bwd_convert_kernel<float>), grid, dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL((bwd_convert_kernel<__bf16>), grid, dim3(256), 0, stream, a);
+    const int st = launch_status();
+    if (st != USP_OK) return st;
+  }
+  return USP_OK;
 }
 
 }  // namespace usp

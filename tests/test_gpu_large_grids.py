@@ -54,3 +54,39 @@ def test_fp32_forward_of_a_long_batch():
     zero = torch.log(torch.arange(1, L + 1, device="cuda", dtype=torch.float64)).float()
     for b in others.nonzero()[::97, 0].tolist():         # scores of zero: LSE is the log of the number of visible keys
         assert (lse[:, b] - zero).abs().max() < 2e-5 and q[:, b].abs().max() == 0
+
+
+def test_backward_of_some_ranks_of_a_long_batch():
+    """2^33 + 2^18 elements of dK and as many of dV, from fp32 accumulators (two of three ranks add to them) in one
+    conversion of four elements to a thread: just above 2^32 threads.  Q is its own O and dO, K its own V."""
+    room(165)
+    bs, L, heads, hs, R = 10923, 192, 32, 128, 3
+    assert 2 * bs * L * heads * hs // 4 > 2 ** 32
+    p = usp.problem(bs, L, heads, heads, hs, 1, R, False, usp.USP_SPLIT_CONTIG, usp.USP_BF16)
+    shape = (R, bs, L // R, heads, hs)
+    q, k = (torch.zeros(shape, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    entries = [0, 1, bs // 2, bs - 2, bs - 1]
+    for t in (q, k):
+        for b in entries:
+            t[:, b] = torch.randn(t[:, b].shape, generator=gen, device="cuda", dtype=torch.float32)
+    lse = torch.full((R, bs, heads, L // R), 6.0, device="cuda")     # any value will do: P = exp(s - LSE)
+    dq = torch.empty_like(q)
+    dk, dv = (torch.full_like(k, float("nan")) for _ in range(2))
+    ws = torch.empty(usp.usp_attn_bwd_workspace_bytes(p, 2), dtype=torch.uint8, device="cuda")
+    usp.usp_attn_bwd(p, q, k, k, q, lse, q, dq, dk, dv, 0, 2, ws)
+    scale = hs ** -0.5
+    for b in entries:
+        kd = k[:, b].reshape(L, heads, hs).double().cpu()
+        qd = q[:2, b].reshape(2 * L // R, heads, hs).double().cpu()   # the rows of ranks 0 and 1
+        w = torch.exp(torch.einsum("qhe,khe->hqk", qd, kd) * scale - 6.0)
+        ds = w * (torch.einsum("qhe,khe->hqk", qd, kd) - (qd * qd).sum(-1).T[:, :, None])
+        for got, want in ((dk, torch.einsum("hqk,qhe->khe", ds, qd) * scale), (dv, torch.einsum("hqk,qhe->khe", w, qd))):
+            x = got[:, b].reshape(L, heads, hs).double().cpu()
+            assert (x - want).norm() / want.norm() < 2 ** -7          # P, dS and the result rounded to bf16
+        x, want = dq[:2, b].reshape(2 * L // R, heads, hs).double().cpu(), torch.einsum("hqk,khe->qhe", ds, kd) * scale
+        assert (x - want).norm() / want.norm() < 2 ** -7
+    others = torch.ones(bs, dtype=torch.bool)
+    others[entries] = False
+    for b in others.nonzero()[::97, 0].tolist():
+        assert dk[:, b].abs().max() == 0 and dv[:, b].abs().max() == 0
