@@ -51,7 +51,7 @@ struct BwdArgs {
   int Lq, Lk;
   int n_tiles;          // query tiles (of the kernel that reads kept dS)
   // 256-row query tiles and 256-key tiles, and how many of them are the first run's where no tile may hold positions of both
-  // runs (RowTiles; 0: cut in a row, as always where dS is kept).  Every query block, and every key block, is cut alike.
+  // runs (common_row_tiles; 0: cut in a row, as always where dS is kept, and as the blocks of a whole zigzag ring are).
   int q_tiles, q_tiles_run0, k_tiles, k_tiles_run0;
   int n_blocks;
   int causal;
@@ -1264,18 +1264,8 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
   a.ds_qt8 = (int)((Lq + 255) / 256);
   // work items of both kinds; one workgroup per CU draws them (fewer when there are fewer items)
   const int own_runs = causal && !a.ds;
-  const RowTiles q_rows(a.n_qblk > 1 ? io->qpos_blocks[0] : qpos, Lq, own_runs), k_rows(kpos_blocks[0], Lk, own_runs);
-  // (blocks of one call that are not all cut where the first one is: in a row)
-  auto alike = [&](const RowTiles& rows, const usp_posdesc* d, int n, int64_t len) {
-    for (int j = 1; j < n; ++j) {
-      const RowTiles x(d[j], len, own_runs);
-      if (x.in_run0 != rows.in_run0 || (rows.in_run0 && x.len0 != rows.len0)) return false;
-    }
-    return true;
-  };
-  const RowTiles plain_q(qpos, Lq, 0), plain_k(kpos_blocks[0], Lk, 0);
-  const RowTiles& qt = a.n_qblk == 1 || alike(q_rows, io->qpos_blocks, a.n_qblk, Lq) ? q_rows : plain_q;
-  const RowTiles& kt = alike(k_rows, kpos_blocks, n_blocks, Lk) ? k_rows : plain_k;
+  const RowTiles qt = common_row_tiles(a.n_qblk > 1 ? io->qpos_blocks : &qpos, a.n_qblk, Lq, own_runs);
+  const RowTiles kt = common_row_tiles(kpos_blocks, n_blocks, Lk, own_runs);
   a.q_tiles = qt.n; a.q_tiles_run0 = qt.in_run0;
   a.k_tiles = kt.n; a.k_tiles_run0 = kt.in_run0;
   const int64_t q_tiles = qt.n, k_tiles = kt.n;

@@ -987,7 +987,11 @@ BwdPlan plan_bwd(const usp_problem& p, int n_cols) {
 // forward: 10 us per dQ item and 1.2 per 32 of its keys, 6 and 1.68 per 32 queries of a dK/dV item (0.62 of these at head
 // size 64), the copies at 4.5 TB/s and 6 us for their launch.  Against 130 measured cuts of eleven problems, L = 2048 to
 // 16384, this is off by 6 % on average and picks a cut within 0.3 % of the best one (one of eight Ulysses ranks of L = 8192:
-// 4 + 4 slices 298 us, 2 + 2 279; 32 heads of L = 2048: 2 + 2 slices 217 us, none 168).
+// 4 + 4 slices 298 us, 2 + 2 279; 32 heads of L = 2048: 2 + 2 slices 217 us, none 168).  What is played is not in every
+// zigzag ring what is launched: every block's tiles are taken as RowTiles has them and as many as the first ring row's,
+// where the launch cuts all blocks alike (common_row_tiles: a whole ring in a row) and takes the blocks in ring order.  One
+// zigzag problem in ten is then cut otherwise; playing the very launch was no better on these (35 measured: 2.3 % slower on
+// average, 0.76 to 1.07 x), the model is not that fine.
 BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   const int64_t Lq = p.L / p.ring;
   const int hq = r < 0 ? p.hc : p.hc / p.ulysses, hkv = r < 0 ? p.hk : p.hk / p.ulysses, g = hq / hkv;
@@ -1005,7 +1009,7 @@ BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
     ring_block_desc(p, s, &pos[s]);
     tiles.emplace_back(pos[s], Lq, p.causal);
   }
-  const int T = tiles[0].n;   // (of every ring row)
+  const int T = tiles[0].n;   // (the ring row whose runs adjoin may have one less: it is charged the one more)
   std::vector<double> dq, dkdv;
   auto steps = [](int64_t n) { return (double)((n + 31) / 32); };
   for (int t = T - 1; t >= 0; --t)
@@ -1204,7 +1208,9 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
 
   const bool one_rank = rank_end - rank_begin == 1;
   BwdCopies run = f.copies;
-  if (!run.ds) run.cut = bwd_cut(*p, rank_begin / U, run.cut);   // (with dS kept the two kernels run one after the other)
+  // one cut for all ranks of the call, which add to the same copies: that of the first one's ring row (with dS kept the two
+  // kernels run one after the other)
+  if (!run.ds) run.cut = bwd_cut(*p, rank_begin / U, run.cut);
   const int dkdv_copies = hq / hkv / run.cut.heads_per_wg * run.cut.q_splits;
   const bool dq_bf16 = direct && run.cut.k_splits == 1;
   const bool dkdv_bf16 = direct && one_rank && dkdv_copies == 1;

@@ -49,8 +49,9 @@ __host__ __device__ inline int64_t pos_max(const usp_posdesc& d, int64_t a, int6
 // The 256-row tiles that local rows (or keys) [0, len) with positions d are cut into.  Rows of two separate runs under a
 // causal mask (the zigzag split of two and more ring ranks): no tile holds rows of both, because it would walk everything
 // that the later run sees for the rows of the earlier one as well, one more long item per head.  Measured, ring rank 1 of
-// 8, two of L = 16000, 32 heads: eight tiles of 256 in a row, five of them long, 1054 us; four per run 546 us.  Where that takes one tile
-// more, as many tiles are long as before, and of few tiles the one more costs (rank 3 of 8, L = 6000: 101 us in a row, 104 apart).
+// 8, two of L = 16000, 32 heads: eight tiles of 256 in a row, five of them long, 1054 us; four per run 546 us.  Where that
+// takes one tile more, as many tiles are long as before, and of few tiles the one more costs (rank 3 of 8, L = 6000: 101 us
+// in a row, 104 apart).
 struct RowTiles {
   int n, in_run0;     // tiles in all; in_run0 > 0: the first run's, the rest are cut from row len0 on; 0: [0, len) in a row
   int64_t len0, len;
@@ -70,6 +71,18 @@ struct RowTiles {
     return e < stop ? e : stop;
   }
 };
+
+// The tiles of n blocks of len rows (keys) each in one backward launch, which cuts all of them in the same places: those of
+// RowTiles where it cuts every block alike, else in a row.  (In a whole zigzag ring the last ring rank's two runs adjoin,
+// and RowTiles has them in a row: blocks are cut apart for one block at a time, the rows of one rank among them.)
+inline RowTiles common_row_tiles(const usp_posdesc* d, int n, int64_t len, int causal) {
+  const RowTiles first(d[0], len, causal);
+  for (int j = 1; j < n; ++j) {
+    const RowTiles x(d[j], len, causal);
+    if (x.in_run0 != first.in_run0 || (first.in_run0 && x.len0 != first.len0)) return RowTiles(d[0], len, 0);
+  }
+  return first;
+}
 
 // Workgroups of so many threads that one dimension of a grid holds: HIP refuses 2^32 threads and more.
 constexpr int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) / threads; }

@@ -137,3 +137,10 @@ class OneRankCase:
         must = {0, self.Lq - 1, c - 1, c % self.Lq, tile - 1, tile, self.Lq - tile, self.Lq - tile - 1}
         rows = set(int(x) for x in rng.choice(self.Lq, size=min(count, self.Lq), replace=False)) | {m for m in must if 0 <= m < self.Lq}
         return np.array(sorted(rows), dtype=np.int64)
+
+
+def cut_apart(c, R, r):
+    """Whether the 256-row tiles of ring rank r of R (zigzag split, two runs of c rows) end with its first run: a run that ends
+    inside a tile, runs that do not adjoin, and no tile more by it, or eight and more in a row (RowTiles in csrc/usp_internal.h)."""
+    both, in_a_row = 2 * -(-c // 256), -(-2 * c // 256)
+    return r < R - 1 and c % 256 != 0 and (both == in_a_row or in_a_row >= 8)
