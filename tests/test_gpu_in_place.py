@@ -1,5 +1,6 @@
 """K and V (and Q, dO of the backward) of a batch of one, read where the caller holds them at any Ulysses degree: bitwise
-what the staged copies give, which tensors that do not lie on 16 bytes still take."""
+what the staged copies give, which tensors that do not lie on 16 bytes still take, and where items are whole, bitwise what the
+all-to-alls and the ring loop give as calls of their own."""
 import pytest
 import torch
 
@@ -7,9 +8,14 @@ import paper_2405_07719_amd as usp
 
 pytestmark = pytest.mark.gpu
 
-# whole launch with V rows / with V tiles, all tiles cut, heaviest tiles cut, ring of two with a ragged last key tile
-SHAPES = [(8192, 8, 4, 2, 1, 128, True, True), (16384, 16, 4, 2, 1, 128, True, True), (10240, 32, 8, 8, 1, 128, True, False),
-          (12288, 32, 8, 8, 1, 64, False, True), (4 * 1100, 16, 8, 2, 2, 128, True, True)]
+# ..., how the launch divides the rank: whole items, V as rows / V in transposed tiles; heaviest tiles cut; every tile cut.
+# A ring of two with a ragged last key tile, and tiles that end with a run, among them.
+SHAPES = [(16384, 16, 4, 2, 1, 128, True, True, "whole"), (12288, 32, 8, 8, 1, 64, False, True, "whole"),
+          (4 * 1100, 128, 16, 2, 2, 128, True, True, "whole"), (16384, 32, 2, 2, 1, 128, True, True, "whole, V in tiles"),
+          (24576, 32, 8, 8, 1, 128, True, True, "heaviest cut"), (8192, 8, 4, 2, 1, 128, True, True, "heaviest cut"),
+          (10240, 32, 8, 8, 1, 128, True, False, "heaviest cut"), (4 * 1100, 16, 8, 2, 2, 128, True, True, "all cut")]
+# V staged as rows, which tensors that do not lie on 16 bytes can be (tiles are not made from such: refused)
+ROWS_STAGED = {SHAPES[5], SHAPES[6], SHAPES[7]}
 
 
 def shifted(t):
@@ -19,26 +25,54 @@ def shifted(t):
     return out.copy_(t)
 
 
-@pytest.mark.parametrize("L,hc,hk,U,R,hs,causal,zigzag", SHAPES)
-def test_forward_in_place_is_bitwise_the_staged_one(L, hc, hk, U, R, hs, causal, zigzag):
+def dense_forward(p, q, k, v, rank):
+    """The rank's O and LSE through the separate entry points: all-to-alls to tensors in head layout, its ring loop in one launch."""
+    bs, L, U, R, hs = p.bs, p.L, p.ulysses, p.ring, p.hs
+    hq, hkv, Lq, r, u = p.hc // U, p.hk // U, L // R, rank // U, rank % U
+    qh = torch.zeros((U * R, bs, Lq, hq, hs), device="cuda", dtype=torch.bfloat16)
+    kh, vh = (torch.zeros((U * R, bs, Lq, hkv, hs), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    for heads, src, dst in ((p.hc, q, qh), (p.hk, k, kh), (p.hk, v, vh)):
+        usp.usp_layout_a2a(p, heads, usp.USP_SEQ_TO_HEAD, src, dst, 0, U * R)
+    pos = [usp.usp_local_positions(p, s, u)[1] for s in range(R)]
+    steps = [(r - i) % R for i in range(R)]
+    o, lse = torch.zeros_like(qh[0]), torch.zeros((bs, hq, Lq), device="cuda")
+    usp.usp_ring_attn_fwd(qh[rank], [kh[s * U + u] for s in steps], [vh[s * U + u] for s in steps], [pos[s] for s in steps], o, lse, bs,
+                          Lq, Lq, hq, hkv, hs, 0.0, p.causal, pos[r], usp.USP_BF16, usp.USP_BF16)
+    return o, lse
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[str(s) for s in SHAPES])
+def test_forward_in_place_is_bitwise_the_staged_one(shape):
+    L, hc, hk, U, R, hs, causal, zigzag, cut = shape
     N = U * R
     p = usp.problem(1, L, hc, hk, hs, U, R, causal, usp.USP_SPLIT_ZIGZAG if zigzag else usp.USP_SPLIT_CONTIG, usp.USP_BF16)
     gen = torch.Generator(device="cuda").manual_seed(11)
     q = torch.randn((N, 1, L // N, hc, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
     k, v = (torch.randn((N, 1, L // N, hk, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
     ws = torch.empty(max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)), dtype=torch.uint8, device="cuda")
-    rank, outs = N - 1, []
-    for kk, vv in ((k, v), (shifted(k), shifted(v))):
-        o = torch.zeros_like(q)
-        lse = torch.zeros((N, 1, hc // U, L // R), device="cuda")
-        try:
-            usp.usp_attn_fwd(p, q, kk, vv, o, lse, rank, rank + 1, ws)
-        except usp.UspError:      # V tiles are not made from such tensors: refused, as it always was
-            assert kk is not k
-            return
-        outs.append((o, lse))
-    assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16))
-    assert torch.equal(outs[0][1], outs[1][1])
+
+    def forward(rank, k, v):
+        o, lse = torch.zeros_like(q), torch.zeros((N, 1, hc // U, L // R), device="cuda")
+        usp.usp_attn_fwd(p, q, k, v, o, lse, rank, rank + 1, ws)
+        head = torch.zeros((N, 1, L // R, hc // U, hs), device="cuda", dtype=torch.bfloat16)
+        usp.usp_layout_a2a(p, hc, usp.USP_SEQ_TO_HEAD, o, head, rank, rank + 1)
+        return head[rank], lse[rank]
+
+    for rank in sorted({0, N - U, N - 1}):
+        o, lse = forward(rank, k, v)
+        if shape in ROWS_STAGED:
+            staged_o, staged_lse = forward(rank, shifted(k), shifted(v))
+            assert torch.equal(o.view(torch.int16), staged_o.view(torch.int16)) and torch.equal(lse, staged_lse)
+        else:
+            with pytest.raises(usp.UspError) as refused:
+                forward(rank, shifted(k), shifted(v))
+            assert refused.value.status == 6      # USP_ERR_UNSUPPORTED, as it always was
+        dense_o, dense_lse = dense_forward(p, q, k, v, rank)
+        if cut.startswith("whole"):
+            assert torch.equal(o.view(torch.int16), dense_o.view(torch.int16)) and torch.equal(lse, dense_lse)
+        else:   # the pieces' weights are rounded to bf16 against other maxima, and O once more: a few roundings of 2^-9
+            assert ((o.double() - dense_o.double()).norm() / dense_o.double().norm()).item() < 2 ** -7
+            assert (lse - dense_lse).abs().max().item() < 1e-4
 
 
 # one writer per element (bf16 from the kernels) / copies; several head splits; ragged tiles; head size 64; batch of two at
