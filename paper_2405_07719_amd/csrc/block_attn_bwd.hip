@@ -196,6 +196,10 @@ struct PrepareJob {
 constexpr int kMaxPrepareJobs = 4;
 struct PrepareArgs { PrepareJob job[kMaxPrepareJobs]; int n_jobs; };
 
+// The caller's tensors lie anywhere (a view may begin at any element): loads that claim no more than an element's alignment.
+// On this chip they are the same 16-byte instructions, which take any address.
+typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
+
 template <int HS>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(const PrepareArgs a) {
   constexpr int TPR = HS / 8;   // threads per row, 8 elements each
@@ -216,10 +220,10 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const PrepareArgs a) {
   const int hl = (int)job.by_heads.d, bs = (int)job.by_bs.d, L = (int)job.by_L.d, n = (int)job.by_n.d;
   const int64_t at = ((((int64_t)(job.r0 + r) * job.U + shard) * bs + b) * n + s) * job.heads + (job.c0 + col) * hl + h;
   const int64_t out = ((int64_t)blk * bs + b) * hl + h;   // of [block][bs][head]
-  const bf16x8 x = __builtin_nontemporal_load((const bf16x8*)(job.src + at * HS) + part);
+  const bf16x8 x = __builtin_nontemporal_load((const bf16x8_any*)(job.src + at * HS) + part);
   if (job.dst) *((bf16x8*)(job.dst + (out * L + i) * HS) + part) = x;
   if (job.o) {
-    const bf16x8 y = __builtin_nontemporal_load((const bf16x8*)(job.o + at * HS) + part);
+    const bf16x8 y = __builtin_nontemporal_load((const bf16x8_any*)(job.o + at * HS) + part);
     float acc = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc += (float)y[e] * (float)x[e];

@@ -119,6 +119,6 @@ def test_backward_of_all_ranks_is_that_of_each_rank(bs, L, hc, hk, U, R, hs, cau
         assert apart(whole[0], dq) < 2 ** -8
         assert apart(whole[1], dk) < 2 ** -8 and apart(whole[2], dv) < 2 ** -8
         if U > 1:
-            staged = backward(N - 1, N, (shifted(q), shifted(k), shifted(v), o, shifted(do)), need)
+            staged = backward(N - 1, N, (shifted(q), shifted(k), shifted(v), shifted(o), shifted(do)), need)
             for a, b in zip(backward(N - 1, N, (q, k, v, o, do), need), staged):
                 assert apart(a, b) < 2 ** -8
