@@ -21,9 +21,11 @@ import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_KIB = 524288.0                       # the calibration copy: 512 MiB read, 512 MiB written
-KERNELS = {"attention_fwd": "block_attn_fwd_mfma", "bwd": "bwd_kernel",
-           "bwd_dq_ds": "bwd_dq_ds_kernel", "bwd_prepare": "bwd_prepare_kernel", "wave_split": "wave_split_attn_fwd", "layout_a2a": "layout_a2a_kernel", "lse_merge": "lse_merge_kernel",
-           "attention_fwd_fp32_out": "block_attn_fwd_mfma<.., float>", "attention_fwd_state": "block_attn_fwd_mfma<.., STATE>", "calib_pure_mfma": "calib_pure_mfma", "calib_attention_mix": "calib_attention_mix", "copy": "copyBuffer"}
+KERNELS = {"attention_fwd": "block_attn_fwd_mfma", "bwd": "bwd_kernel", "bwd_writes_ds": "bwd_kernel<.., false>",
+           "bwd_dq_ds": "bwd_dq_ds_kernel", "bwd_prepare": "bwd_prepare_kernel", "bwd_convert": "bwd_convert_kernel",
+           "wave_split": "wave_split_attn_fwd", "layout_a2a": "layout_a2a_kernel", "lse_merge": "lse_merge_kernel",
+           "attention_fwd_fp32_out": "block_attn_fwd_mfma<.., float>", "attention_fwd_state": "block_attn_fwd_mfma<.., STATE>",
+           "calib_pure_mfma": "calib_pure_mfma", "calib_attention_mix": "calib_attention_mix", "copy": "copyBuffer"}
 
 
 def _short(name):
@@ -38,6 +40,8 @@ def _short(name):
                 if "float" in name or "EfLb" in name:
                     return "attention_fwd_fp32_out"
                 return "attention_fwd_state"
+            if key == "bwd":   # both kinds of items in one launch, or the dK/dV items that leave their dS behind
+                return "bwd" if "true" in name or "Lb1E" in name else "bwd_writes_ds"
             return key
     return None
 
@@ -82,7 +86,7 @@ def clocks(counter_csv, trace_csv):
 
 def counter_table(paths):
     """Every counter of the given collection files as a table: one row per counter, one column per kernel (mean per
-    dispatch, summed over the chip by the profiler).  the backward kernel is split by its template flag (both kinds of items / dK/dV items that write dS)."""
+    dispatch, summed over the chip by the profiler)."""
     table = collections.defaultdict(lambda: collections.defaultdict(list))
     for path in paths:
         with open(path) as f:
@@ -90,8 +94,6 @@ def counter_table(paths):
                 k = _short(r["Kernel_Name"])
                 if not k or k == "copy":
                     continue
-                if k == "bwd":
-                    k = "bwd (dK/dV and dQ)" if "true" in r["Kernel_Name"] else "bwd (dK/dV, writes dS)"
                 table[r["Counter_Name"]][k].append(float(r["Counter_Value"]))
     cols = sorted({k for c in table.values() for k in c})
     print("| counter | " + " | ".join(cols) + " |")
