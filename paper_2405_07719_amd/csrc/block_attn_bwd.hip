@@ -1012,7 +1012,8 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
 // do.  PAIR: the dK/dV items and, after them, the dQ items of a launch pair whose kernels do not depend on each other: the
 // dQ items fill the CUs that the last, long dK/dV items leave idle, so that a pair has one tail instead of two and its items
 // need less cutting (fewer fp32 copies of the outputs).  Measured, one of eight Ulysses ranks, the whole backward: two
-// launches 302 us at L = 8192 and 172 at L = 4640 (two heads), one 273 and 95; L = 32768 3275 and 3243.  !PAIR: dK/dV items that leave their dS behind for bwd_dq_ds_kernel.
+// launches 302 us at L = 8192 and 172 at L = 4640 (two heads), one 273 and 95; L = 32768 no difference (3212 and 3229).
+// !PAIR: dK/dV items that leave their dS behind for bwd_dq_ds_kernel.
 template <int HS, bool PAIR>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void bwd_kernel(const BwdArgs) {
@@ -1304,12 +1305,14 @@ int launch_ring_attn_bwd(const void* q, const void* const* k_blocks, const void*
     return hs == 128 ? launch_bwd<128, true>(a, n_wgs, stream) : launch_bwd<64, true>(a, n_wgs, stream);
   }
   // dS kept: the dK/dV kernel, which writes it, and then the dQ kernel, which reads it
+  static_assert(!bwd_keeps_ds(64) && bwd_keeps_ds(128), "one instance");
+  if (hs != 128) return USP_ERR_UNSUPPORTED;
   int64_t n_wgs = prepare(dkdv_items);
-  const int st = hs == 128 ? launch_bwd<128, false>(a, n_wgs, stream) : launch_bwd<64, false>(a, n_wgs, stream);
+  const int st = launch_bwd<128, false>(a, n_wgs, stream);
   if (st != USP_OK) return st;
   a.n_queues = std::gcd(dev::kMaxItemQueues, bs * hkv);
   n_wgs = prepare(dq_items);
-  return hs == 128 ? launch_dq_ds<128>(a, n_wgs, stream) : launch_dq_ds<64>(a, n_wgs, stream);
+  return launch_dq_ds<128>(a, n_wgs, stream);
 }
 
 int launch_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,

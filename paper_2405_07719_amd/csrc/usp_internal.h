@@ -50,8 +50,10 @@ __host__ __device__ inline int64_t pos_max(const usp_posdesc& d, int64_t a, int6
 // causal mask (the zigzag split of two and more ring ranks): no tile holds rows of both, because it would walk everything
 // that the later run sees for the rows of the earlier one as well, one more long item per head.  Measured, ring rank 1 of
 // 8, two of L = 16000, 32 heads: eight tiles of 256 in a row, five of them long, 1054 us; four per run 546 us.  Where that
-// takes one tile more, as many tiles are long as before, and of few tiles the one more costs (rank 3 of 8, L = 6000: 101 us
-// in a row, 104 apart).
+// takes one tile more, as many tiles are long as before: measured in a row / apart, rank 0 of 2 (16 heads) with runs of 808,
+// 1064, 1832 rows forward 80.5 / 72.7, 100 / 89.5, 172 / 159 us, backward 153 / 151, 230 / 231, 487 / 472; rank 3 of 8 (32
+// heads), 552, 1064, 1832 rows, forward 174 / 176, 434 / 447, 966 / 979, backward 390 / 401, 1130 / 1129, 3154 / 3000.  So
+// from eight tiles on, where it gains more than it costs.
 struct RowTiles {
   int n, in_run0;     // tiles in all; in_run0 > 0: the first run's, the rest are cut from row len0 on; 0: [0, len) in a row
   int64_t len0, len;
@@ -214,7 +216,7 @@ struct BwdPlace {
   int n_qblk;
   const usp_posdesc* qpos_blocks;
 };
-inline bool bwd_keeps_ds(int hs) { return hs >= 128; }   // see plan_bwd
+constexpr bool bwd_keeps_ds(int hs) { return hs >= 128; }   // see plan_bwd
 inline size_t bwd_ds_bytes(int bs, int64_t Lq, int64_t Lk, int hq, int n_blocks) {
   return (size_t)bs * hq * n_blocks * (size_t)((Lk + 255) / 256 * 8) * (size_t)((Lq + 255) / 256 * 8) * 2048;
 }
