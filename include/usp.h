@@ -262,8 +262,8 @@ int usp_block_attn_bwd(const void* q, const void* k, const void* v, const void* 
                        int hkv, int hs, float scale, int causal, const usp_posdesc* qpos, const usp_posdesc* kpos,
                        int accumulate, void* stream);
 
-/* Backward of a rank's whole ring loop over its n_blocks resident K/V blocks in one launch pair (the backward
- * counterpart of usp_ring_attn_fwd; same result as one usp_block_attn_bwd per block, up to rounding).
+/* Backward of a rank's whole ring loop over its n_blocks resident K/V blocks in one launch (the backward counterpart of
+ * usp_ring_attn_fwd; same result as one usp_block_attn_bwd per block, up to rounding).
  *   k_blocks, v_blocks, dk_blocks, dv_blocks: HOST arrays of n_blocks DEVICE pointers ([bs,Lk,hkv,hs]; bf16 inputs,
  *   fp32 gradients); kpos_blocks: HOST array of n_blocks descriptors (may be NULL when causal == 0);
  *   accumulate_dq: 0 overwrites dq, 1 adds; accumulate_dkdv: HOST array of n_blocks flags, per block.
@@ -296,10 +296,13 @@ int usp_ring_attn_bwd_ws(const void* q, const void* const* k_blocks, const void*
  * [rank_begin, rank_end); bf16 problems only.
  *   q, k, v, o, d_o: seq layout (o as usp_attn_fwd wrote it); lse: [N][bs][hc/U][L/R] from usp_attn_fwd;
  *   dq, dk, dv: seq layout outputs in the problem dtype.
- * Per rank: all-to-all of Q and dO -> delta (O and dO read at their places in the shards) -> R block backwards (dQ
- * accumulated over the ring steps in fp32; the dK/dV contribution of step i is added to block (r-i) mod R's fp32
- * accumulator, the buffer that would travel the ring with the block) -> dQ converted and scattered back to the
- * shards.  After the last rank the dK/dV accumulators are converted and scattered back likewise.
+ * Per rank: one launch for the all-to-all of Q and dO (the first rank's: of K and V too) and delta (O and dO read at their
+ * places in the shards) -> R block backwards in one launch (dQ accumulated over the ring steps in fp32; the dK/dV
+ * contribution of step i is added to block (r-i) mod R's fp32 accumulator, the buffer that would travel the ring with the
+ * block) -> dQ converted and scattered back to the shards.  After the last rank the dK/dV accumulators are converted and
+ * scattered back likewise.  Where the tensors of all ranks lie as one dense problem (Ulysses degree 1 or a batch of one,
+ * R <= USP_MAX_RING_BLOCKS, everything on 16 bytes) and outputs apart from inputs, all ranks of the whole group go through
+ * one launch; results with one writer per element then leave it in the problem dtype.
  * dq is complete for the ranks in range (each fills its head slice of its Ulysses group's shards).
  * dk/dv: for every Ulysses column u that has a rank (r,u) in range, the column's head slice of ALL N shards is
  * OVERWRITTEN with the sum of the contributions of the column's ranks in range; the head slices of columns

@@ -576,7 +576,8 @@ FwdPlan plan_fwd(const usp_problem& p, int n_cols, bool allow_heavy = true, bool
   f.k_head = off; off += f.k_in_place ? 0 : up256(f.kv_block_bytes * p.ring * n_cols);
   f.v_head = off; off += f.k_in_place && !f.v_transposed ? 0 : up256(f.v_block_bytes * p.ring * n_cols);
   // A batch of one is read in place at every Ulysses degree (the room for its staged copies stays in the plan: callers
-  // have been told the size).  Measured, L = 8192, one of eight Ulysses ranks: 99.0 us staged, 95.0 in place; L = 32768 984.1, 982.4.
+  // have been told the size).  Measured, L = 8192, one of eight Ulysses ranks: 96.3 us staged, 92.8 in place; L = 32768 no
+  // difference (924, 921).
   if (p.bs == 1 && may_read_in_place && !f.k_in_place && ring_in_one_launch(p)) {
     f.k_in_place = true;
     f.v_transposed = f.v_transposed && retiling_pays();
@@ -928,13 +929,15 @@ extern "C" int usp_block_attn_bwd(const void* q, const void* k, const void* v, c
 
 // ---------------------------------------------------------------------------------------------
 // Algorithm 1 backward.  Workspace plan:
-//   q_head, do_head         : one rank's Q and dO in head layout (reused rank after rank); O is read once, for D_i,
+//   q_head, do_head         : one rank's Q and dO, [bs][head][row][hs] (reused rank after rank); O is read once, for D_i,
 //                             straight from the sequence-layout shards;
-//   (with Ulysses degree 1 a rank's Q, dO and every K/V block in head layout ARE the sequence-layout shards: these
+//   (with Ulysses degree 1 a rank's Q, dO and every K/V block lie in the sequence-layout shards as they are wanted: these
 //   four regions are empty and the kernels read the caller's tensors where they are)
 //   delta                   : one rank's D_i;
-//   k_head, v_head          : as in the forward; later hold the converted dK / dV blocks;
-//   dq_acc                  : one rank's fp32 dQ;  dk_acc, dv_acc : fp32, one per K/V block.
+//   k_head, v_head          : every K/V block of the columns in range, [bs][head][row][hs];
+//   dq_acc                  : one rank's fp32 dQ;  dk_acc, dv_acc : fp32, one per K/V block; each in as many copies as the
+//                             cut has slices.  Unused where results leave the kernels as bf16.
+// All ranks at once (see there): D_i of all of them from q_head on, in the room up to the accumulators.
 // ---------------------------------------------------------------------------------------------
 namespace {
 
@@ -1153,8 +1156,10 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
   for (int r = 0; r < R; ++r) usp_local_positions(p, r, 0, nullptr, &ring_pos[r]);
 
   // Every rank at once: in place, the tensors of all ranks are one dense problem of R query blocks, R key blocks and all
-  // heads, which goes through ONE launch pair instead of a pair (and conversions) per rank.  Not where dS is kept and a
-  // rank is long enough to gain by that (some 10 % of its time; a rank's launches and their tails cost some 40 us).
+  // heads, which go through ONE launch instead of one (and conversions) per rank.  Not where dS is kept and a rank is long
+  // enough to gain by that.  Measured, with dS kept rank by rank / all at once, 32/8 heads, U 2 x R 2: 107 us per rank (by
+  // the estimate above) 876 / 505 us, 328 1813 / 1402, 429 2070 / 1834, 966 4042 / 3889, 1717 6484 / 6887; MHA, U 2 x R 4:
+  // 483 4937 / 3998, 858 7674 / 6906.  (The two meet near 1 ms; the line lies lower.)
   const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)d_o) & 15) == 0;
   if (direct && aligned && N > 1 && rank_begin == 0 && rank_end == N) {
     BwdCopies c;

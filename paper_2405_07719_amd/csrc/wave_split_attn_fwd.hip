@@ -43,7 +43,8 @@ struct WsArgs {
   int bs, hq, hkv, g;         // heads of one rank
   int q_heads, kv_heads;      // heads in a row of Q / O and of K / V
   int U, R, rank_begin, n_ranks;
-  int first_wg;               // work items before this launch's first (0 but for 2^32 threads and more; a second grid dimension: 12.37 us for 12.17)
+  int first_wg;               // work items before this launch's first (0 but for 2^32 threads and more; a second grid
+                              // dimension instead: 12.37 us for 12.17)
   FastDiv n_q, n_k;           // rows of a Q and of a K/V shard
   FastDiv by_hkv, by_bs, by_ranks, by_g, by_U;
   int Lq, Lk;                 // rows of a ring block
@@ -447,9 +448,9 @@ void wave_split_attn_fwd(const WsArgs a) {
       }
     }
     if (!STATE || a.state_last) {
-    inv_s[(end_lane & 31)] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
-    if (row0 + (end_lane & 31) < a.Lq)
-      a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + (end_lane & 31)] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
+      inv_s[(end_lane & 31)] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
+      if (row0 + (end_lane & 31) < a.Lq)
+        a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + (end_lane & 31)] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
     }
   }
   __syncthreads();
