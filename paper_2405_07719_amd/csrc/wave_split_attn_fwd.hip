@@ -34,6 +34,11 @@ using namespace dev;
 
 constexpr int kWaves = 8, kRows = 32, kTile = 32;
 
+// The caller's tensors lie on an element's alignment, no more is claimed (this chip's wide accesses take any address).
+typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+
 struct WsArgs {
   const void* q;
   const void* k;
@@ -103,10 +108,11 @@ struct Tile {
   template <bool kWhole, typename V, int N, typename Step>
   __device__ void load(V (&t)[N], int lane_row, Step step, int col) const {
     static_assert(sizeof(V) == 16 || sizeof(V) == 8, "");
+    typedef V VAny __attribute__((aligned(2)));
     const int at = lane_row * (int)rows.row_bytes + col;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      if constexpr (!kWhole) t[i] = *(const V*)(rows.row(key0 + min(lane_row + step(i), last)) + col);
+      if constexpr (!kWhole) t[i] = *(const VAny*)(rows.row(key0 + min(lane_row + step(i), last)) + col);
       else if constexpr (sizeof(V) == 16) t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, step(i) * (int)rows.row_bytes, 0));
       else t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, step(i) * (int)rows.row_bytes, 0));
     }
@@ -129,7 +135,7 @@ template <int HS> struct Operands<__bf16, HS> {
 
   __device__ void load_q(const char* row, int hl) {
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = *(const bf16x8*)(row + 32 * ks + 16 * hl);
+    for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = *(const bf16x8_any*)(row + 32 * ks + 16 * hl);
   }
   template <bool kWhole> __device__ static void load_rows(u32x4 (&t)[TL], const Tile& tile, int lane) {
     tile.load<kWhole>(t, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
@@ -205,7 +211,7 @@ template <int HS> struct Operands<float, HS> {
 
   __device__ void load_q(const char* row, int hl) {
 #pragma unroll
-    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(row + 32 * c + 16 * hl);
+    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4_any*)(row + 32 * c + 16 * hl);
   }
   template <bool kWhole> __device__ void load_tile(const Tile& kt, const Tile& vt, int lane) {
     kt.load<kWhole>(k, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
@@ -472,8 +478,8 @@ void wave_split_attn_fwd(const WsArgs a) {
     sum *= inv_s[rr];
     if (row0 + rr < a.Lq) {
       OutT* dst = (OutT*)orow.row(row0 + rr) + 4 * c;
-      if constexpr (sizeof(OutT) == 4) *(f32x4*)dst = sum;
-      else *(u32x2*)dst = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+      if constexpr (sizeof(OutT) == 4) *(f32x4_any*)dst = sum;
+      else *(u32x2_any*)dst = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
     }
   }
 }

@@ -84,3 +84,40 @@ def test_state_passes_between_the_kernels(usp, blocks, hs):
         ref = s.softmax(-1) @ v[:, h]
         assert ((o[0, :, h].double() - ref).norm() / ref.norm()).item() < 2 ** -7
         assert (lse[0, h].double() - s.logsumexp(-1)).abs().max().item() < 1e-4
+
+
+def _shifted(t):
+    """The same values one element past a multiple of 16 bytes."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+    return buf[1:1 + t.numel()].view(t.shape).copy_(t)
+
+
+@pytest.mark.parametrize("hs", [64, 128])
+@pytest.mark.parametrize("dtype", [tl.BF16, tl.FP32], ids=["bf16", "fp32"])
+def test_tensors_may_begin_at_any_element(usp, dtype, hs):
+    """Bitwise the same results: one block on dense tensors, and (fp32; bf16 tensors like these are staged for other kernels)
+    all ranks of a batch of two whose tiles cross from shard to shard."""
+    torch_dtype = torch.float32 if dtype == tl.FP32 else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(hs)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch_dtype)
+
+    q, k, v = normal(2, 100, 4, hs), normal(2, 150, 2, hs), normal(2, 150, 2, hs)
+    results = []
+    for place in (torch.clone, _shifted):
+        o, lse = place(torch.zeros_like(q)), torch.zeros((2, 4, 100), device="cuda")
+        usp.usp_block_attn_fwd(place(q), place(k), place(v), o, lse, 2, 100, 150, 4, 2, hs, 0.0, False, None, None, dtype, dtype)
+        results.append((o, lse))
+    assert all(torch.equal(x, y) for x, y in zip(*results))
+    if dtype == tl.BF16:
+        return
+    p = usp.problem(2, 264, 4, 2, hs, 2, 2, True, usp.USP_SPLIT_ZIGZAG, usp.USP_FP32)
+    q, k, v = normal(4, 2, 66, 4, hs), normal(4, 2, 66, 2, hs), normal(4, 2, 66, 2, hs)
+    ws = torch.empty(usp.usp_attn_fwd_workspace_bytes(p, 4), dtype=torch.uint8, device="cuda")
+    results = []
+    for place in (torch.clone, _shifted):
+        o, lse = place(torch.zeros_like(q)), torch.zeros((4, 2, 2, 132), device="cuda")
+        usp.usp_attn_fwd(p, place(q), place(k), place(v), o, lse, 0, 4, ws)
+        results.append((o, lse))
+    assert all(torch.equal(x, y) for x, y in zip(*results))
