@@ -55,7 +55,7 @@ typedef enum {
   USP_ERR_DTYPE = 4,       /* unknown or unsupported dtype combination */
   USP_ERR_WORKSPACE = 5,   /* workspace NULL or smaller than the query says */
   USP_ERR_UNSUPPORTED = 6, /* e.g. hs not in {64,128}, too many merge parts, rank range out of bounds */
-  USP_ERR_LAUNCH = 7       /* the HIP runtime reported an error when enqueuing */
+  USP_ERR_LAUNCH = 7       /* the HIP runtime reported an error when enqueuing, or host memory ran out */
 } usp_status;
 
 typedef enum { USP_BF16 = 0, USP_FP32 = 1 } usp_dtype;

@@ -13,6 +13,9 @@
 
 using namespace usp;
 
+// (Entry points below that keep host-side records, of plans and of counter sets, are function-try-blocks: no exception, as of
+// host memory that runs out, passes the C boundary.)
+
 extern "C" const char* usp_status_str(int s) {
   switch (s) {
     case USP_OK: return "ok";
@@ -22,7 +25,7 @@ extern "C" const char* usp_status_str(int s) {
     case USP_ERR_DTYPE: return "bad dtype";
     case USP_ERR_WORKSPACE: return "workspace missing or too small";
     case USP_ERR_UNSUPPORTED: return "unsupported configuration";
-    case USP_ERR_LAUNCH: return "HIP launch error";
+    case USP_ERR_LAUNCH: return "HIP launch error (or host memory ran out)";
     default: return "unknown status";
   }
 }
@@ -119,7 +122,7 @@ static bool desc_ok(const usp_posdesc* d, int64_t len) {
 extern "C" int usp_block_attn_fwd(const void* q, const void* k, const void* v, void* o_part, float* lse_part, int bs,
                                   int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                                   const usp_posdesc* qpos, const usp_posdesc* kpos, int in_dtype, int o_dtype,
-                                  void* stream) {
+                                  void* stream) try {
   if (!q || !k || !v || !o_part || !lse_part) return USP_ERR_NULL;
   if (bs < 1 || Lq < 1 || Lk < 1 || hq < 1 || hkv < 1) return USP_ERR_SHAPE;
   if (hq % hkv) return USP_ERR_DEGREE;
@@ -138,6 +141,8 @@ extern "C" int usp_block_attn_fwd(const void* q, const void* k, const void* v, v
   if (scale == 0.0f) scale = 1.0f / sqrtf((float)hs);
   return launch_block_attn_fwd(q, k, v, o_part, lse_part, bs, Lq, Lk, hq, hkv, hs, scale, causal ? 1 : 0, qd, kd,
                                in_dtype, o_dtype, (hipStream_t)stream);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 extern "C" size_t usp_block_attn_fwd_state_bytes(int bs, int64_t Lq, int hq, int hs) {
@@ -148,7 +153,7 @@ extern "C" size_t usp_block_attn_fwd_state_bytes(int bs, int64_t Lq, int hq, int
 extern "C" int usp_block_attn_fwd_state(const void* q, const void* k, const void* v, void* state, size_t state_bytes,
                                         void* o, float* lse, int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int hs,
                                         float scale, int causal, const usp_posdesc* qpos, const usp_posdesc* kpos,
-                                        int first, int last, int o_dtype, void* stream) {
+                                        int first, int last, int o_dtype, void* stream) try {
   if (!q || !k || !v || !state) return USP_ERR_NULL;
   if (last && (!o || !lse)) return USP_ERR_NULL;
   if (bs < 1 || Lq < 1 || Lk < 1 || hq < 1 || hkv < 1) return USP_ERR_SHAPE;
@@ -169,6 +174,8 @@ extern "C" int usp_block_attn_fwd_state(const void* q, const void* k, const void
   const RingState rs = {(float*)state, first ? 1 : 0, last ? 1 : 0};
   return launch_block_attn_fwd(q, k, v, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal ? 1 : 0, qd, kd, USP_BF16, o_dtype,
                                (hipStream_t)stream, &rs);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 namespace {
@@ -181,17 +188,21 @@ int ring_attn_fwd_impl(const void* q, const void* const* k_blocks, const void* c
 extern "C" int usp_ring_attn_fwd(const void* q, const void* const* k_blocks, const void* const* v_blocks,
                                  const usp_posdesc* kpos_blocks, int n_blocks, void* o, float* lse, int bs, int64_t Lq,
                                  int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc* qpos,
-                                 int in_dtype, int o_dtype, void* stream) {
+                                 int in_dtype, int o_dtype, void* stream) try {
   return ring_attn_fwd_impl(q, k_blocks, v_blocks, kpos_blocks, n_blocks, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal,
                             qpos, in_dtype, o_dtype, stream, false);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 extern "C" int usp_ring_attn_fwd_vt(const void* q, const void* const* k_blocks, const void* const* vt_blocks,
                                     const usp_posdesc* kpos_blocks, int n_blocks, void* o, float* lse, int bs,
                                     int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
-                                    const usp_posdesc* qpos, void* stream) {
+                                    const usp_posdesc* qpos, void* stream) try {
   return ring_attn_fwd_impl(q, k_blocks, vt_blocks, kpos_blocks, n_blocks, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal,
                             qpos, USP_BF16, USP_BF16, stream, true);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 namespace {
@@ -233,7 +244,7 @@ extern "C" int usp_ring_attn_fwd_partials(const void* q, const void* const* k_bl
                                           const usp_posdesc* kpos_blocks, const int32_t* lk_blocks, int n_blocks,
                                           float* const* o_parts, float* const* lse_parts, int bs, int64_t Lq,
                                           int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
-                                          const usp_posdesc* qpos, void* stream) {
+                                          const usp_posdesc* qpos, void* stream) try {
   if (!q || !k_blocks || !v_blocks || !o_parts || !lse_parts) return USP_ERR_NULL;
   if (n_blocks < 1 || n_blocks > USP_MAX_RING_BLOCKS) return USP_ERR_UNSUPPORTED;
   if (bs < 1 || Lq < 1 || Lk < 1 || hq < 1 || hkv < 1) return USP_ERR_SHAPE;
@@ -260,6 +271,8 @@ extern "C" int usp_ring_attn_fwd_partials(const void* q, const void* const* k_bl
   if (scale == 0.0f) scale = 1.0f / sqrtf((float)hs);
   return launch_attn_fwd_partials(q, k_blocks, v_blocks, kd, lk, n_blocks, o_parts, lse_parts, bs, Lq, Lk, hq, hkv, hs,
                                   scale, causal ? 1 : 0, qd, (hipStream_t)stream);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 extern "C" int usp_lse_merge(const void* const* o_parts, const float* const* lse_parts, int n_parts, void* o_out,
@@ -647,11 +660,13 @@ int stage_kv_blocks(const usp_problem& p, const void* k, const void* v, char* k_
 
 }  // namespace
 
-extern "C" size_t usp_attn_fwd_workspace_bytes(const usp_problem* p, int n_ranks) {
+extern "C" size_t usp_attn_fwd_workspace_bytes(const usp_problem* p, int n_ranks) try {
   if (usp_validate(p) != USP_OK || n_ranks < 1) return 0;
   // one rank touches one Ulysses column; a wider range may straddle ring rows, so size for all U
   const int cols = n_ranks == 1 ? 1 : p->ulysses;
   return plan_fwd(*p, cols).total;
+} catch (...) {
+  return 0;
 }
 
 namespace {
@@ -849,8 +864,10 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
 }  // namespace
 
 extern "C" int usp_attn_fwd(const usp_problem* p, const void* q, const void* k, const void* v, void* o, float* lse,
-                            int rank_begin, int rank_end, void* workspace, size_t workspace_bytes, void* stream) {
+                            int rank_begin, int rank_end, void* workspace, size_t workspace_bytes, void* stream) try {
   return attn_fwd_impl(p, q, k, v, o, lse, rank_begin, rank_end, workspace, workspace_bytes, stream);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -879,7 +896,7 @@ void* scratch_on_current_device() {
 }  // namespace
 
 extern "C" int usp_attn_fwd_noalloc(const usp_problem* p, const void* q, const void* k, const void* v, void* o,
-                                    float* lse, int rank_begin, int rank_end, void* stream) {
+                                    float* lse, int rank_begin, int rank_end, void* stream) try {
   int st = usp_validate(p);
   if (st != USP_OK) return st;
   const int N = p->ulysses * p->ring;
@@ -893,6 +910,8 @@ extern "C" int usp_attn_fwd_noalloc(const usp_problem* p, const void* q, const v
   if (!ptr) return USP_ERR_LAUNCH;
   // every region of the workspace is written by a kernel of the call before a kernel reads it: nothing to clear
   return attn_fwd_impl(p, q, k, v, o, lse, rank_begin, rank_end, ptr, USP_NOALLOC_SCRATCH_BYTES, stream, heavy_fits);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 extern "C" int usp_attn_delta(const void* o, const void* d_o, float* delta, int bs, int64_t L, int h, int hs,
@@ -908,7 +927,7 @@ extern "C" int usp_attn_delta(const void* o, const void* d_o, float* delta, int 
 extern "C" int usp_block_attn_bwd(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                                   const float* delta, float* dq, float* dk, float* dv, int bs, int64_t Lq, int64_t Lk,
                                   int hq, int hkv, int hs, float scale, int causal, const usp_posdesc* qpos,
-                                  const usp_posdesc* kpos, int accumulate, void* stream) {
+                                  const usp_posdesc* kpos, int accumulate, void* stream) try {
   if (!q || !k || !v || !d_o || !lse || !delta || !dq || !dk || !dv) return USP_ERR_NULL;
   if (bs < 1 || Lq < 1 || Lk < 1 || hq < 1 || hkv < 1) return USP_ERR_SHAPE;
   if (hq % hkv) return USP_ERR_DEGREE;
@@ -925,6 +944,8 @@ extern "C" int usp_block_attn_bwd(const void* q, const void* k, const void* v, c
   if (scale == 0.0f) scale = 1.0f / sqrtf((float)hs);
   return launch_block_attn_bwd(q, k, v, d_o, lse, delta, dq, dk, dv, bs, Lq, Lk, hq, hkv, hs, scale, causal ? 1 : 0,
                                qd, kd, accumulate ? 1 : 0, accumulate ? 1 : 0, (hipStream_t)stream);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1109,7 +1130,7 @@ extern "C" size_t usp_attn_bwd_workspace_bytes_with_ds(const usp_problem* p, int
 
 extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, const void* v, const void* o,
                             const float* lse, const void* d_o, void* dq, void* dk, void* dv, int rank_begin,
-                            int rank_end, void* workspace, size_t workspace_bytes, void* stream_) {
+                            int rank_end, void* workspace, size_t workspace_bytes, void* stream_) try {
   int st = usp_validate(p);
   if (st != USP_OK) return st;
   if (p->dtype != USP_BF16) return USP_ERR_DTYPE;
@@ -1322,6 +1343,8 @@ extern "C" int usp_attn_bwd(const usp_problem* p, const void* q, const void* k, 
       n_convert = 0;
     }
   return n_convert ? launch_bwd_convert(convert, n_convert, p->dtype, stream) : USP_OK;
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 extern "C" int usp_ring_attn_bwd(const void* q, const void* const* k_blocks, const void* const* v_blocks,
@@ -1329,7 +1352,7 @@ extern "C" int usp_ring_attn_bwd(const void* q, const void* const* k_blocks, con
                                  const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks,
                                  int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                                  const usp_posdesc* qpos, int accumulate_dq, const int* accumulate_dkdv,
-                                 void* stream) {
+                                 void* stream) try {
   if (!q || !k_blocks || !v_blocks || !d_o || !lse || !delta || !dq || !dk_blocks || !dv_blocks || !accumulate_dkdv)
     return USP_ERR_NULL;
   if (n_blocks < 1 || n_blocks > USP_MAX_RING_BLOCKS) return USP_ERR_UNSUPPORTED;
@@ -1357,6 +1380,8 @@ extern "C" int usp_ring_attn_bwd(const void* q, const void* const* k_blocks, con
   return launch_ring_attn_bwd(q, k_blocks, v_blocks, kd, n_blocks, d_o, lse, delta, dq, dk_blocks, dv_blocks, bs, Lq,
                               Lk, hq, hkv, hs, scale, causal ? 1 : 0, qd, accumulate_dq ? 1 : 0, acc,
                               (hipStream_t)stream);
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
 
 namespace {
@@ -1405,7 +1430,7 @@ extern "C" int usp_ring_attn_bwd_ws(const void* q, const void* const* k_blocks, 
                                     const float* delta, float* dq, float* const* dk_blocks, float* const* dv_blocks,
                                     int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int hs, float scale, int causal,
                                     const usp_posdesc* qpos, int accumulate_dq, const int* accumulate_dkdv,
-                                    void* workspace, size_t workspace_bytes, void* stream_) {
+                                    void* workspace, size_t workspace_bytes, void* stream_) try {
   if (!q || !k_blocks || !v_blocks || !d_o || !lse || !delta || !dq || !dk_blocks || !dv_blocks || !accumulate_dkdv)
     return USP_ERR_NULL;
   if (n_blocks < 1 || n_blocks > USP_MAX_RING_BLOCKS) return USP_ERR_UNSUPPORTED;
@@ -1473,4 +1498,6 @@ extern "C" int usp_ring_attn_bwd_ws(const void* q, const void* const* k_blocks, 
       if (st != USP_OK) return st;
     }
   return USP_OK;
+} catch (...) {
+  return USP_ERR_LAUNCH;
 }
