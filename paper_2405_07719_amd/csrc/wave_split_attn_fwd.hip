@@ -89,19 +89,22 @@ __device__ inline BlockRows block_rows(const void* t, int esize, int hs, int bs,
                    shard_bytes - run_bytes};
 }
 
-// One 32-key tile of such rows.  All 32 of them inside one shard (always, when bs = 1) are read through a buffer
-// descriptor: the lane's byte offset is the same for every tile, the row within the tile goes into the scalar offset.
-// (With a 64-bit row address per load the address arithmetic took as long as the products.)  A tile that crosses from one
-// shard into the next, which lie bs entries apart, finds each row on its own, and so does the last, ragged one, where a row
-// past the last key is that key's again (the mask hides it): a buffer's range check does not cover the scalar offset.
+// One 32-key tile of such rows.  Inside one shard (always, when bs = 1) it is read through a buffer descriptor whose extent
+// ends with the last valid row: rows past it read as zeros.  The row within the tile is part of the vector offset, which
+// the descriptor's range check covers (the scalar offset it does not).  Row addresses of 64 bits took as long as the products
+// (and cost the ragged last tile 1 to 3 us at L = 250 to 2000: fp32, head size 64, L = 248 10.8 us for 10.0).  A tile that
+// crosses from one shard into the next, which lie bs entries apart, finds each row on its own, clamped to the last.
+// kScalarStep: the row goes into the scalar offset instead, and a ragged tile, too, finds its rows on its own (bf16 at head
+// size 64, whose 128 registers hold no offset per load: L = 1024 18.25 us, with the vector offset 19.1).
+template <bool kScalarStep>
 struct Tile {
   BlockRows rows;
   int key0, last;       // first key; last valid row of the tile
-  bool whole;           // 32 rows inside one shard
+  bool whole;           // read through the descriptor
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ Tile(const BlockRows& r, int key0_, int len, int row_len) : rows(r), key0(key0_) {
     last = min(kTile, len - key0) - 1;
-    whole = last == kTile - 1 && (r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last));
+    whole = (!kScalarStep || last == kTile - 1) && (r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last));
     rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)r.row(key0), 0, last * (int)r.row_bytes + row_len, kRawBufferFlags);
   }
   // t[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
@@ -112,9 +115,10 @@ struct Tile {
     const int at = lane_row * (int)rows.row_bytes + col;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
+      const int row = step(i) * (int)rows.row_bytes, voff = kScalarStep ? at : at + row, soff = kScalarStep ? row : 0;
       if constexpr (!kWhole) t[i] = *(const VAny*)(rows.row(key0 + min(lane_row + step(i), last)) + col);
-      else if constexpr (sizeof(V) == 16) t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, step(i) * (int)rows.row_bytes, 0));
-      else t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, step(i) * (int)rows.row_bytes, 0));
+      else if constexpr (sizeof(V) == 16) t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
+      else t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
     }
   }
 };
@@ -130,6 +134,7 @@ template <int HS> struct Operands<__bf16, HS> {
   static constexpr int KSTR = HS * 2 + 48, VSTR = HS * 2 + 64;
   static constexpr int kLdsPerWave = kTile * VSTR;
   static constexpr int TL = kTile * CPR / 64;            // 16-byte loads per lane of a tile
+  typedef Tile<HS == 64> KvTile;
   bf16x8 q[KSTEPS];
   u32x4 k[TL], v[TL];
 
@@ -137,8 +142,8 @@ template <int HS> struct Operands<__bf16, HS> {
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = *(const bf16x8_any*)(row + 32 * ks + 16 * hl);
   }
-  template <bool kWhole> __device__ static void load_rows(u32x4 (&t)[TL], const Tile& tile, int lane) {
-    tile.load<kWhole>(t, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  template <bool kWhole> __device__ static void load_rows(u32x4 (&t)[TL], const KvTile& tile, int lane) {
+    tile.template load<kWhole>(t, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
   template <int STR> __device__ static void stash_rows(char* lds, const u32x4 (&t)[TL], int lane) {
 #pragma unroll
@@ -148,7 +153,7 @@ template <int HS> struct Operands<__bf16, HS> {
     }
     __builtin_amdgcn_wave_barrier();   // this wave's own LDS accesses stay in this order
   }
-  template <bool kWhole> __device__ void load_tile(const Tile& kt, const Tile& vt, int lane) {
+  template <bool kWhole> __device__ void load_tile(const KvTile& kt, const KvTile& vt, int lane) {
     load_rows<kWhole>(k, kt, lane);
     load_rows<kWhole>(v, vt, lane);
   }
@@ -204,6 +209,7 @@ template <int HS> struct Operands<float, HS> {
   static constexpr int KSTR = HS * 4 + 16;               // an odd number of 16-byte chunks
   static constexpr int kLdsPerWave = kTile * KSTR;
   static constexpr int TL = kTile * CPR / 64;
+  typedef Tile<false> KvTile;
   typedef float vrow __attribute__((ext_vector_type(DB)));
   f32x4 q[KC];           // dims 8 c + 4 (lane half) .. + 3: the product's two k indices are the lane halves
   f32x4 k[TL];           // a tile's K rows on their way to LDS
@@ -213,12 +219,12 @@ template <int HS> struct Operands<float, HS> {
 #pragma unroll
     for (int c = 0; c < KC; ++c) q[c] = *(const f32x4_any*)(row + 32 * c + 16 * hl);
   }
-  template <bool kWhole> __device__ void load_tile(const Tile& kt, const Tile& vt, int lane) {
-    kt.load<kWhole>(k, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  template <bool kWhole> __device__ void load_tile(const KvTile& kt, const KvTile& vt, int lane) {
+    kt.template load<kWhole>(k, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
     if constexpr (HS == 64) load_v<kWhole>(vt, lane);
   }
-  template <bool kWhole> __device__ void load_v(const Tile& vt, int lane) {
-    vt.load<kWhole>(v, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
+  template <bool kWhole> __device__ void load_v(const KvTile& vt, int lane) {
+    vt.template load<kWhole>(v, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
   }
   __device__ void stash_k(char* lds, int lane) {
 #pragma unroll
@@ -343,7 +349,7 @@ void wave_split_attn_fwd(const WsArgs a) {
     const BlockRows vr = block_rows(a.v, sizeof(T), HS, a.bs, a.n_k, a.kv_heads, blk * a.U, b, u * a.hkv + kvh);
     for (; turn < nt; turn += kWaves) {
       const int key0 = (turn < na ? tr.a0 + turn : tr.b0 + (turn - na)) * kTile;
-      const Tile kt(kr, key0, a.Lk, HS * (int)sizeof(T)), vt(vr, key0, a.Lk, HS * (int)sizeof(T));
+      const typename Op::KvTile kt(kr, key0, a.Lk, HS * (int)sizeof(T)), vt(vr, key0, a.Lk, HS * (int)sizeof(T));
       if (kt.whole) op.template load_tile<true>(kt, vt, lane);   // (K and V are cut into shards alike)
       else op.template load_tile<false>(kt, vt, lane);
       op.stash_k(lds, lane);
