@@ -18,8 +18,8 @@
 // the waves with a run-time bound alone cost 15 %: eight LDS reads, each waited for).  Large ones: every workgroup reads
 // all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the 256-row kernel: 0.54 PFLOP/s at
 // L = 8192, where that one has 0.71 (K fragments loaded straight from their rows, 32 lines per instruction, had 0.39).
-// Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at fp32 rate, 104
-// TFLOP/s at L = 2048, head size 128 (154 is what a large fp32 matrix product reaches); one thread per row on the vector
+// Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at fp32 rate, 124
+// TFLOP/s at L = 2048, eight heads of size 128, no mask (154 is what a large fp32 matrix product reaches); one thread per row on the vector
 // ALU, as it was before, took 1230 us for the four ranks of L = 256 that take 9 us here, and the four bf16 ranks of
 // L = 1024 took 121 us in nine launches where this is one of 12 us.
 #include <algorithm>
