@@ -13,15 +13,17 @@
 //     out: A operand of S^T = K Q^T, lane = key).  bf16: V rows follow through the same tile and come back by transpose
 //     reads.  fp32: v_mfma_f32_32x32x2_f32 takes ONE value per lane and product, so V needs no transposition at all:
 //     product i multiplies the two keys that the lane halves hold in score register i with 32 head dims, lane = dim.
-// What bounds it.  Small problems: the chain of latencies of one workgroup (arguments, Q, K and V, two products, merge,
-// store: 6 us), so the prologue has no divisions, the merge no dependent LDS reads, a tile's loads no branches (loops over
-// the waves with a run-time bound alone cost 15 %: eight LDS reads, each waited for).  Large ones: every workgroup reads
-// all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the 256-row kernel: 0.54 PFLOP/s at
-// L = 8192, where that one has 0.71 (K fragments loaded straight from their rows, 32 lines per instruction, had 0.39).
-// Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at fp32 rate, 124
-// TFLOP/s at L = 2048, eight heads of size 128, no mask (154 is what a large fp32 matrix product reaches); one thread per row on the vector
-// ALU, as it was before, took 1230 us for the four ranks of L = 256 that take 9 us here, and the four bf16 ranks of
-// L = 1024 took 121 us in nine launches where this is one of 12 us.
+// What bounds it.  Small problems: the chain of one workgroup.  Time stamps in a workgroup of one tile per wave (fp32, head
+// size 64, 19 thousand cycles): 5 to 7 thousand before the first product, most of it loads waiting to issue: what a CU loads
+// goes through one path of 64 bytes a cycle, and the eight waves each loaded all of Q (a third of everything) and had their
+// V in front of the others' K.  So Q is loaded once and shared through LDS, V is asked for behind the barrier that this
+// needs anyway, and the next tile's K and V while a tile is worked on (a tile of a walk took 3.3 thousand cycles with its
+// loads waited for).  All that does not depend on the workgroup is worked out on the host.  Together: four fp32 ranks of
+// L = 256 9.3 -> 8.6 us, four bf16 ranks of L = 1024 12.1 -> 10.9, one of eight ranks of L = 2048 (32 heads on 8) 18.7 ->
+// 16.6, all eight 90.6 -> 79.0, fp32 at L = 2048 (eight heads of size 64, two ranks a ring) 47.1 -> 43.0.
+// Large problems: every workgroup reads all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the
+// 256-row kernel.  Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at
+// fp32 rate, 125 TFLOP/s at L = 2048, four heads of size 128, no mask (154 is what a large fp32 matrix product reaches).
 #include <algorithm>
 
 #include "attn_device.h"
@@ -35,10 +37,40 @@ using namespace dev;
 constexpr int kWaves = 8, kRows = 32, kTile = 32;
 
 // The caller's tensors lie on an element's alignment, no more is claimed (this chip's wide accesses take any address).
-typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 
+// Where the positions of ring block r begin: those of its two runs are start0 + r step0 .. and start1 - r step1 ..
+// (Algorithm 2: chunks r and 2R-1-r of 2R, or block r of R; one given block: steps of 0; no mask: one run from 0).
+struct BlockPositions {
+  int start0, step0, len0, start1, step1, len1;
+  __device__ PosDesc32 of(int r) const { return PosDesc32{start0 + r * step0, len0, start1 - r * step1, len1}; }
+};
+
+// The keys of a ring block (one batch entry) lie in the shards [U][bs][n][heads][hs], row j at j rows and (j / n) jumps from
+// the block's first.  Tiles are numbered shard by shard and none crosses from one shard into the next, so that every tile is
+// read through buffer descriptors (K, V) whose extent ends with its last row: rows past it read as zeros.  The row within the
+// tile is part of the vector offset, which the descriptor's range check covers (the scalar offset it does not).  With a
+// second path for tiles that cross, and a branch round the loads where there is no next tile, every wait for one tile's loads
+// was a wait for all that were in flight.  With a batch of one a block is one run of n = Lk rows.
+struct KeyTiles {
+  FastDiv by_n, by_tiles;      // rows of a shard; tiles of a shard
+  int one;                     // a single run of rows
+  __device__ int upto(int keys) const {   // tiles that hold the first `keys` keys
+    if (one) return (unsigned)(keys + kTile - 1) / kTile;
+    const int shard = by_n.split(keys);
+    return shard * (int)by_tiles.d + (int)((unsigned)(keys + kTile - 1) / kTile);
+  }
+  __device__ int of(int key) const {
+    if (one) return (unsigned)key / kTile;
+    const int shard = by_n.split(key);
+    return shard * (int)by_tiles.d + (int)((unsigned)key / kTile);
+  }
+};
+
+// Everything that does not depend on the workgroup is worked out on the host: of the 19 thousand cycles that a workgroup of
+// one tile per wave took, 6 thousand went by before its first product, in 500 instructions of addresses and positions.
 struct WsArgs {
   const void* q;
   const void* k;
@@ -50,11 +82,15 @@ struct WsArgs {
   int U, R, rank_begin, n_ranks;
   int first_wg;               // work items before this launch's first (0 but for 2^32 threads and more; a second grid
                               // dimension instead: 12.37 us for 12.17)
-  FastDiv n_q, n_k;           // rows of a Q and of a K/V shard
+  FastDiv n_q;                // rows of a Q shard
+  KeyTiles tiles;
   FastDiv by_hkv, by_bs, by_ranks, by_g, by_U;
   int Lq, Lk;                 // rows of a ring block
-  int n_qtiles, causal, split;
-  PosDesc32 qpos, kpos;       // split < 0: the one block's positions as given, else by Algorithm 2 from the ring rank
+  int n_qtiles, causal;
+  // elements from one ring block to the next, from one batch entry to the next, and what rows of the next shard lie further
+  // on than the next row would (0: a batch of one)
+  uint64_t q_ring, q_run, q_jump, kv_ring, kv_run, kv_jump;
+  BlockPositions qpos, kpos;
   float scale, scale_log2;
   // Running state of a ring that delivers its blocks one per call (STATE instances), in the 256-row kernel's records
   // (block_attn_fwd.hip): per 32 rows of a (batch, head) the O^T accumulator as [hs / 8][64 lanes][4], m, and l, per lane.
@@ -62,63 +98,37 @@ struct WsArgs {
   int state_first, state_last, state_records;   // records of a (batch, head)
 };
 
-// Algorithm 2 for ring rank r: chunks r and 2R-1-r of 2R, or block r of R
-__device__ inline PosDesc32 block_positions(const WsArgs& a, const PosDesc32& given, int len, int r) {
-  if (a.split < 0) return given;
-  if (a.split == USP_SPLIT_ZIGZAG) {
-    const int c = len / 2;
-    return PosDesc32{r * c, c, (2 * a.R - 1 - r) * c, c};
-  }
-  return PosDesc32{r * len, len, 0, 0};
-}
+__device__ inline uint64_t times(int n, uint64_t x) { return (uint64_t)(uint32_t)n * x; }
 
-// The rows of a ring block (one batch entry, one head) inside the shards [U][bs][n][heads][hs]: row j lies at
-// base + j row_bytes + (j / n) jump, and jump is 0 when bs = 1.
-struct BlockRows {
-  const char* base;
-  FastDiv n;
-  uint32_t row_bytes;
-  int64_t jump;
-  __device__ const char* row(int j) const { return base + (int64_t)j * row_bytes + (int64_t)n.div(j) * jump; }
-};
-
-__device__ inline BlockRows block_rows(const void* t, int esize, int hs, int bs, FastDiv n, int heads, int first_shard, int b, int head) {
-  const uint32_t row_bytes = (uint32_t)heads * hs * esize;
-  const int64_t run_bytes = (int64_t)n.d * row_bytes, shard_bytes = bs * run_bytes;
-  return BlockRows{(const char*)t + first_shard * shard_bytes + b * run_bytes + (int64_t)head * hs * esize, n, row_bytes,
-                   shard_bytes - run_bytes};
-}
-
-// One 32-key tile of such rows.  Inside one shard (always, when bs = 1) it is read through a buffer descriptor whose extent
-// ends with the last valid row: rows past it read as zeros.  The row within the tile is part of the vector offset, which
-// the descriptor's range check covers (the scalar offset it does not).  Row addresses of 64 bits took as long as the products
-// (and cost the ragged last tile 1 to 3 us at L = 250 to 2000: fp32, head size 64, L = 248 10.8 us for 10.0).  A tile that
-// crosses from one shard into the next, which lie bs entries apart, finds each row on its own, clamped to the last.
-// kScalarStep: the row goes into the scalar offset instead, and a ragged tile, too, finds its rows on its own (bf16 at head
-// size 64, whose 128 registers hold no offset per load: L = 1024 18.25 us, with the vector offset 19.1).
-template <bool kScalarStep>
 struct Tile {
-  BlockRows rows;
-  int key0, last;       // first key; last valid row of the tile
-  bool whole;           // read through the descriptor
-  __amdgpu_buffer_rsrc_t rsrc;
-  __device__ Tile(const BlockRows& r, int key0_, int len, int row_len) : rows(r), key0(key0_) {
-    last = min(kTile, len - key0) - 1;
-    whole = (!kScalarStep || last == kTile - 1) && (r.jump == 0 || r.n.div(key0) == r.n.div(key0 + last));
-    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)r.row(key0), 0, last * (int)r.row_bytes + row_len, kRawBufferFlags);
+  uint64_t at;          // bytes from the tensor's begin to the tile's first row
+  int row_bytes, extent;
+  int key0, end;        // its keys
+  // (!exists: no tile; its loads find nothing in range and give zeros)
+  __device__ Tile(const KeyTiles& tiles, bool exists, int t, int Lk, uint64_t block, uint64_t jump, int row_bytes_, int row_len) : row_bytes(row_bytes_) {
+    key0 = t * kTile;
+    end = min(key0 + kTile, Lk);
+    at = block;
+    if (!tiles.one) {
+      const int shard = tiles.by_tiles.split(t);
+      key0 = shard * (int)tiles.by_n.d + t * kTile;
+      end = min(key0 + kTile, (shard + 1) * (int)tiles.by_n.d);
+      at += times(shard, jump);
+    }
+    at += (uint64_t)(uint32_t)key0 * (uint32_t)row_bytes;
+    extent = exists ? (end - 1 - key0) * row_bytes + row_len : 0;
   }
-  // t[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
-  template <bool kWhole, typename V, int N, typename Step>
-  __device__ void load(V (&t)[N], int lane_row, Step step, int col) const {
+  // x[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
+  template <typename V, int N, typename Step>
+  __device__ void load(V (&x)[N], const void* tensor, int lane_row, Step step, int col) const {
     static_assert(sizeof(V) == 16 || sizeof(V) == 8, "");
-    typedef V VAny __attribute__((aligned(2)));
-    const int at = lane_row * (int)rows.row_bytes + col;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((char*)tensor + at, 0, extent, kRawBufferFlags);
+    const int voff0 = lane_row * row_bytes + col;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int row = step(i) * (int)rows.row_bytes, voff = kScalarStep ? at : at + row, soff = kScalarStep ? row : 0;
-      if constexpr (!kWhole) t[i] = *(const VAny*)(rows.row(key0 + min(lane_row + step(i), last)) + col);
-      else if constexpr (sizeof(V) == 16) t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
-      else t[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
+      const int voff = voff0 + step(i) * row_bytes;
+      if constexpr (sizeof(V) == 16) x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 0, 0));
+      else x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, 0, 0));
     }
   }
 };
@@ -129,21 +139,28 @@ template <typename T, int HS> struct Operands;
 template <int HS> struct Operands<__bf16, HS> {
   static constexpr int KSTEPS = HS / 16, DB = HS / 32, CPR = HS / 8;
   static constexpr int kWavesPerSimd = HS == 64 ? 4 : 2;   // head size 64: two workgroups to a CU
+  // Q fragments: kept in registers, or, where four waves to a SIMD leave none to spare, read from LDS for every tile.
+  static constexpr bool kQInRegs = HS == 128;
+  static constexpr bool kAhead = true;     // a tile's K and V are asked for while the tile before is worked on
   // Rows of the wave's LDS tile.  K: an odd number of 16-byte chunks, no bank conflicts on the fragment reads; V: an odd
   // multiple of 64 bytes, none on the transpose reads.  K and V take turns in one tile (a wave's LDS accesses are in order).
-  static constexpr int KSTR = HS * 2 + 48, VSTR = HS * 2 + 64;
+  static constexpr int KSTR = HS * 2 + 48, VSTR = HS * 2 + 64, QSTR = HS * 2 + 16;
   static constexpr int kLdsPerWave = kTile * VSTR;
   static constexpr int TL = kTile * CPR / 64;            // 16-byte loads per lane of a tile
-  typedef Tile<HS == 64> KvTile;
-  bf16x8 q[KSTEPS];
+  bf16x8 q[kQInRegs ? KSTEPS : 1];
   u32x4 k[TL], v[TL];
 
-  __device__ void load_q(const char* row, int hl) {
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = *(const bf16x8_any*)(row + 32 * ks + 16 * hl);
+  __device__ static bf16x8 q_at(const char* q_lds, int lane, int ks) {
+    return *(const bf16x8*)(q_lds + (lane & 31) * QSTR + 32 * ks + 16 * (lane >> 5));
   }
-  template <bool kWhole> __device__ static void load_rows(u32x4 (&t)[TL], const KvTile& tile, int lane) {
-    tile.template load<kWhole>(t, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  __device__ void read_q(const char* q_lds, int lane) {
+    if constexpr (kQInRegs) {
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = q_at(q_lds, lane, ks);
+    }
+  }
+  __device__ static void load_rows(u32x4 (&t)[TL], const void* tensor, const Tile& tile, int lane) {
+    tile.load(t, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
   template <int STR> __device__ static void stash_rows(char* lds, const u32x4 (&t)[TL], int lane) {
 #pragma unroll
@@ -153,20 +170,18 @@ template <int HS> struct Operands<__bf16, HS> {
     }
     __builtin_amdgcn_wave_barrier();   // this wave's own LDS accesses stay in this order
   }
-  template <bool kWhole> __device__ void load_tile(const KvTile& kt, const KvTile& vt, int lane) {
-    load_rows<kWhole>(k, kt, lane);
-    load_rows<kWhole>(v, vt, lane);
-  }
+  __device__ void load_k(const void* tensor, const Tile& t, int lane) { load_rows(k, tensor, t, lane); }
+  __device__ void load_v(const void* tensor, const Tile& t, int lane) { load_rows(v, tensor, t, lane); }
   __device__ void stash_k(char* lds, int lane) { stash_rows<KSTR>(lds, k, lane); }
   // S^T = K Q^T; leaves V in the LDS tile
-  __device__ f32x16 scores(char* lds, int lane) {
+  __device__ f32x16 scores(char* lds, const char* q_lds, int lane) {
     f32x16 s;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = 0.f;
     const char* row = lds + (lane & 31) * KSTR + 16 * (lane >> 5);
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks)
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(row + 32 * ks), q[ks], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(row + 32 * ks), kQInRegs ? q[kQInRegs ? ks : 0] : q_at(q_lds, lane, ks), s, 0, 0, 0);
     __builtin_amdgcn_wave_barrier();
     stash_rows<VSTR>(lds, v, lane);
     return s;
@@ -206,25 +221,26 @@ template <int HS> struct Operands<__bf16, HS> {
 template <int HS> struct Operands<float, HS> {
   static constexpr int DB = HS / 32, KC = HS / 8, CPR = HS / 4;
   static constexpr int kWavesPerSimd = 2;
-  static constexpr int KSTR = HS * 4 + 16;               // an odd number of 16-byte chunks
+  // (Head size 128: Q, K, V and O are all the registers.  With Q read from LDS for every tile there is room for the next K, and
+  // it was slower: 72.4 us for 68.7 at L = 2048, four heads, no mask.)
+  static constexpr bool kAhead = HS == 64;
+  static constexpr int KSTR = HS * 4 + 16, QSTR = KSTR;  // an odd number of 16-byte chunks
   static constexpr int kLdsPerWave = kTile * KSTR;
   static constexpr int TL = kTile * CPR / 64;
-  typedef Tile<false> KvTile;
   typedef float vrow __attribute__((ext_vector_type(DB)));
   f32x4 q[KC];           // dims 8 c + 4 (lane half) .. + 3: the product's two k indices are the lane halves
   f32x4 k[TL];           // a tile's K rows on their way to LDS
   vrow v[16];            // V of the key that score register i of this lane half holds, dims DB l32 .. + DB - 1
 
-  __device__ void load_q(const char* row, int hl) {
+  __device__ void read_q(const char* q_lds, int lane) {
 #pragma unroll
-    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4_any*)(row + 32 * c + 16 * hl);
+    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(q_lds + (lane & 31) * QSTR + 32 * c + 16 * (lane >> 5));
   }
-  template <bool kWhole> __device__ void load_tile(const KvTile& kt, const KvTile& vt, int lane) {
-    kt.template load<kWhole>(k, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
-    if constexpr (HS == 64) load_v<kWhole>(vt, lane);
+  __device__ void load_k(const void* tensor, const Tile& t, int lane) {
+    t.load(k, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
-  template <bool kWhole> __device__ void load_v(const KvTile& vt, int lane) {
-    vt.template load<kWhole>(v, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
+  __device__ void load_v(const void* tensor, const Tile& t, int lane) {
+    t.load(v, tensor, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
   }
   __device__ void stash_k(char* lds, int lane) {
 #pragma unroll
@@ -234,7 +250,7 @@ template <int HS> struct Operands<float, HS> {
     }
     __builtin_amdgcn_wave_barrier();
   }
-  __device__ f32x16 scores(char* lds, int lane) {
+  __device__ f32x16 scores(char* lds, const char*, int lane) {
     f32x16 s;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = 0.f;
@@ -276,7 +292,8 @@ template <int HS> struct Operands<float, HS> {
 
 template <typename T, int HS>
 constexpr size_t lds_bytes() {
-  const size_t states = (size_t)kWaves * kRows * (HS + 4) * sizeof(float), tiles = (size_t)kWaves * Operands<T, HS>::kLdsPerWave;
+  const size_t states = (size_t)kWaves * kRows * (HS + 4) * sizeof(float);
+  const size_t tiles = (size_t)kWaves * Operands<T, HS>::kLdsPerWave + kRows * Operands<T, HS>::QSTR;
   return (states > tiles ? states : tiles);
 }
 
@@ -302,14 +319,28 @@ void wave_split_attn_fwd(const WsArgs a) {
   const int r = a.by_U.split(u);
   const int h = kvh * a.g + hg;
   const int row0 = (a.causal ? a.n_qtiles - 1 - t : t) * kRows, row1 = min(a.Lq, row0 + kRows);
-  const PosDesc32 qpos = block_positions(a, a.qpos, a.Lq, r);
-  const int qmin = a.causal ? pos_min(qpos, row0, row1) : 0;
-  const int my_row = min(row0 + l32, a.Lq - 1);
-  const int qp = a.causal ? pos_of(qpos, my_row) : 0;
+  constexpr int kNever = 0x7ffffffe;   // no mask: a query after every key
+  const PosDesc32 qpos = a.qpos.of(r);
+  const int qmin = a.causal ? pos_min(qpos, row0, row1) : kNever, qmax = a.causal ? pos_max(qpos, row0, row1) : kNever;
 
   Op op;
-  const BlockRows qr = block_rows(a.q, sizeof(T), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
-  op.load_q(qr.row(my_row), hl);
+  // (element offsets: Q and O lie alike, whatever their types; K and V too)
+  const uint64_t q_at = times(r, a.q_ring) + times(b, a.q_run) + (uint32_t)((u * a.hq + h) * HS);
+  const uint64_t kv_at = times(b, a.kv_run) + (uint32_t)((u * a.hkv + kvh) * HS);
+  auto q_row = [&](int j) { return q_at + (uint64_t)(uint32_t)j * (uint32_t)(a.q_heads * HS) + (a.q_jump ? times(a.n_q.div(j), a.q_jump) : 0); };
+  // Q is read once and shared through LDS: loaded by every wave for itself, it was a third of what a workgroup with one tile
+  // per wave moves through the CU's load path (64 bytes a cycle), ahead of all of its K.
+  constexpr int QCH = HS * (int)sizeof(T) / 16, QL = kRows * QCH / (kWaves * 64);   // 16-byte chunks of a row; of a thread
+  char* const q_lds = smem + kWaves * Op::kLdsPerWave;
+  u32x4 qreg[QL > 0 ? QL : 1];
+  const bool q_loader = QL > 0 || (int)threadIdx.x < kRows * QCH;
+  if (q_loader) {
+#pragma unroll
+    for (int i = 0; i < (QL > 0 ? QL : 1); ++i) {
+      const int ch = (int)threadIdx.x + i * (kWaves * 64), row = min(row0 + ch / QCH, a.Lq - 1);
+      qreg[i] = *(const u32x4_any*)((const char*)a.q + q_row(row) * sizeof(T) + (ch % QCH) * 16);
+    }
+  }
 
   f32x16 o[DB];
 #pragma unroll
@@ -318,14 +349,30 @@ void wave_split_attn_fwd(const WsArgs a) {
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
   float m = -INFINITY, l = 0.f;
 
+  // The walk over the blocks' visible tiles, this wave's every eighth.  (Algorithm 1 step 5: step i visits block (r - i) mod R.)
+  // Of every ascending run of key positions the visible ones are a prefix: of tiles 0 .. and of tiles from the second run's on.
+  int step = -1, kstart0 = 0, kstart1 = 0, na = 0, skip = 0, nt = 0;
+  uint64_t block_at = 0;
+  auto visible = [&](int blk) {
+    const PosDesc32 kp = a.kpos.of(blk);
+    kstart0 = kp.start0;
+    kstart1 = kp.start1;
+    const int c0 = min(max(qmax - kp.start0, -1), kp.len0 - 1) + 1, c1 = min(max(qmax - kp.start1, -1), kp.len1 - 1) + 1;
+    na = a.tiles.upto(c0);
+    const int b0 = max(a.tiles.of(kp.len0), na);
+    skip = b0 - na;
+    nt = na + (c1 > 0 ? max(a.tiles.upto(kp.len0 + c1) - b0, 0) : 0);
+  };
+
   // The state enters with the merge, as a ninth wave's would, and leaves from there: nothing of it is held meanwhile.
   float* rec = nullptr;
   __shared__ float m_state_s[kRows], f_state_s[kRows];
   if constexpr (STATE) {
     rec = a.state + ((size_t)(b * a.hq + h) * a.state_records + row0 / kRows) * (HS * kRows + 128);
     if (!a.state_first && !a.state_last) {   // rows that see nothing of this block: their state stays as it is
-      const TileRanges tr = visible_key_tiles<kTile>(a.causal, qpos, a.kpos, a.Lk, row0, row1);
-      if (tr.a1 - tr.a0 + tr.b1 - tr.b0 == 0) return;   // workgroup-uniform
+      visible(0);
+      if (nt == 0) return;   // workgroup-uniform
+      nt = 0;                // (the walk has not begun)
     }
     if (threadIdx.x < kRows) m_state_s[threadIdx.x] = a.state_first ? -INFINITY : rec[HS * kRows + threadIdx.x];
   }
@@ -340,68 +387,97 @@ void wave_split_attn_fwd(const WsArgs a) {
   constexpr bool kShareFirst = sizeof(T) == 2;
   constexpr float kRescaleThreshold = kShareFirst ? 8.f : 0.f;   // log2 units
   bool shared_first = !kShareFirst;   // wave-uniform: every wave passes the one barrier exactly once
-  for (int i = 0; i < a.R; ++i) {
-    const int blk = r - i < 0 ? r - i + a.R : r - i;   // Algorithm 1 step 5: step i visits block (r - i) mod R
-    const PosDesc32 kpos = block_positions(a, a.kpos, a.Lk, blk);
-    const TileRanges tr = visible_key_tiles<kTile>(a.causal, qpos, kpos, a.Lk, row0, row1);
-    const int na = tr.a1 - tr.a0, nt = na + (tr.b1 - tr.b0);
-    const BlockRows kr = block_rows(a.k, sizeof(T), HS, a.bs, a.n_k, a.kv_heads, blk * a.U, b, u * a.hkv + kvh);
-    const BlockRows vr = block_rows(a.v, sizeof(T), HS, a.bs, a.n_k, a.kv_heads, blk * a.U, b, u * a.hkv + kvh);
-    for (; turn < nt; turn += kWaves) {
-      const int key0 = (turn < na ? tr.a0 + turn : tr.b0 + (turn - na)) * kTile;
-      const typename Op::KvTile kt(kr, key0, a.Lk, HS * (int)sizeof(T)), vt(vr, key0, a.Lk, HS * (int)sizeof(T));
-      if (kt.whole) op.template load_tile<true>(kt, vt, lane);   // (K and V are cut into shards alike)
-      else op.template load_tile<false>(kt, vt, lane);
-      op.stash_k(lds, lane);
-      if constexpr (sizeof(T) == 4 && HS == 128) {
-        if (kt.whole) op.template load_v<true>(vt, lane);
-        else op.template load_v<false>(vt, lane);
-      }   // K, V, Q and O together are more than the registers
-      f32x16 s = op.scores(lds, lane);
-      const bool need_mask = key0 + kTile > a.Lk || (a.causal && pos_max(kpos, key0, min(a.Lk, key0 + kTile)) > qmin);
-      if (need_mask) {
+  auto next_tile = [&]() {   // of the walk; false: it has ended
+    while (turn >= nt) {
+      turn -= nt;
+      if (++step >= a.R) return false;
+      const int blk = r - step + (r < step ? a.R : 0);
+      visible(blk);
+      block_at = kv_at + times(blk, a.kv_ring);
+    }
+    return true;
+  };
+  const int row_bytes = a.kv_heads * HS * (int)sizeof(T);
+  auto tile_now = [&](bool exists) {
+    return Tile(a.tiles, exists, turn < na ? turn : turn + skip, a.Lk, block_at * sizeof(T), a.kv_jump * sizeof(T), row_bytes, HS * (int)sizeof(T));
+  };
+  bool more = next_tile();
+  // Loads of a tile to come are always issued, with or without one: with a branch round them, what waits for older loads would
+  // have to wait for all.
+  Tile tile = tile_now(more);
+  if (Op::kAhead) op.load_k(a.k, tile, lane);
+  if (q_loader) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int key = key0 + 8 * (e >> 2) + 4 * hl + (e & 3);
-          const bool vis = key < a.Lk && (!a.causal || pos_of(kpos, key) <= qp);
-          s[e] = vis ? s[e] : -INFINITY;
-        }
-      }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
-      mx = both_halves_max(mx);
-      if (!shared_first) {
-        int t = lane;   // places in LDS derived here, from a lane index the compiler cannot see through: kept, they are spilled
-        asm volatile("" : "+v"(t));
-        if (wave < 2 && t < 32) first_s[wave][t] = (wave == 0 || i == 0) ? mx : -INFINITY;
-        __syncthreads();
-        m = fmaxf(first_s[0][t & 31], first_s[1][t & 31]);
-        if constexpr (STATE) {   // (a row that has a state goes on from its maximum)
-          const float ms = m_state_s[t & 31];
-          m = ms > -INFINITY ? ms : m;
-        }
-        shared_first = true;
-      }
-      if (__any((mx - m) * a.scale_log2 > kRescaleThreshold)) {   // (m = -inf and a key: inf; no key at all: NaN, no)
-        const float m_new = fmaxf(m, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - (m_new == -INFINITY ? 0.f : m_new * a.scale_log2));   // m = -inf -> 0
-        l *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-        m = m_new;
-      }
-      const float mc = m == -INFINITY ? 0.f : m * a.scale_log2;
+    for (int i = 0; i < (QL > 0 ? QL : 1); ++i) {
+      const int ch = (int)threadIdx.x + i * (kWaves * 64);
+      *(u32x4*)(q_lds + (ch / QCH) * Op::QSTR + (ch % QCH) * 16) = qreg[i];
+    }
+  }
+  __syncthreads();
+  if (Op::kAhead) op.load_v(a.v, tile, lane);   // (behind every wave's K)
+  op.read_q(q_lds, lane);
+  while (more) {
+    const int key0 = tile.key0, key_end = tile.end, start0 = kstart0, start1 = kstart1;
+    const bool first_block = step == 0;
+    const bool need_mask = key_end - key0 < kTile || pos_max(PosDesc32{start0, a.kpos.len0, start1, a.kpos.len1}, key0, key_end) > qmin;
+    if (!Op::kAhead) op.load_k(a.k, tile, lane);
+    op.stash_k(lds, lane);
+    if (!Op::kAhead) op.load_v(a.v, tile, lane);
+    turn += kWaves;
+    more = next_tile();
+    tile = tile_now(more);
+    if (Op::kAhead) op.load_k(a.k, tile, lane);
+    f32x16 s = op.scores(lds, q_lds, lane);
+    if (sizeof(T) == 2) op.load_v(a.v, tile, lane);   // (V has gone to LDS)
+    if (need_mask) {
+      // key key0 + 4 hl + c (c = 0 .. 27, known at compile time) is visible if c does not exceed this row's bound in the run
+      // that the key belongs to; worked out here, from a lane index the compiler cannot see through, and not kept
+      int t = lane;
+      asm volatile("" : "+v"(t));
+      const int first = key0 + 4 * (t >> 5);
+      const int qp = a.causal ? pos_of(qpos, min(row0 + (t & 31), a.Lq - 1)) : kNever;
+      const int in_run0 = a.kpos.len0 - first;
+      const int bound0 = min(qp - start0, key_end - 1) - first, bound1 = min(qp - start1, key_end - 1 - a.kpos.len0) + in_run0;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.scale_log2, -mc));
-        l += s[e];
+        const int c = 8 * (e >> 2) + (e & 3);
+        s[e] = c <= (c < in_run0 ? bound0 : bound1) ? s[e] : -INFINITY;
       }
-      op.accumulate(s, o, lds, lane);
     }
-    turn -= nt;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
+    mx = both_halves_max(mx);
+    if (!shared_first) {
+      int t = lane;   // places in LDS derived here, from a lane index the compiler cannot see through: kept, they are spilled
+      asm volatile("" : "+v"(t));
+      if (wave < 2 && t < 32) first_s[wave][t] = (wave == 0 || first_block) ? mx : -INFINITY;
+      __syncthreads();
+      m = fmaxf(first_s[0][t & 31], first_s[1][t & 31]);
+      if constexpr (STATE) {   // (a row that has a state goes on from its maximum)
+        const float ms = m_state_s[t & 31];
+        m = ms > -INFINITY ? ms : m;
+      }
+      shared_first = true;
+    }
+    if (__any((mx - m) * a.scale_log2 > kRescaleThreshold)) {   // (m = -inf and a key: inf; no key at all: NaN, no)
+      const float m_new = fmaxf(m, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - (m_new == -INFINITY ? 0.f : m_new * a.scale_log2));   // m = -inf -> 0
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+      m = m_new;
+    }
+    const float mc = m == -INFINITY ? 0.f : m * a.scale_log2;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.scale_log2, -mc));
+      l += s[e];
+    }
+    op.accumulate(s, o, lds, lane);
+    if (Op::kAhead && sizeof(T) == 4) op.load_v(a.v, tile, lane);
   }
   if (!shared_first) {   // no tile for this wave
     if (wave < 2 && lane < 32) first_s[wave][lane] = -INFINITY;
@@ -466,7 +542,6 @@ void wave_split_attn_fwd(const WsArgs a) {
     }
   }
   __syncthreads();
-  const BlockRows orow = block_rows(a.o, sizeof(OutT), HS, a.bs, a.n_q, a.q_heads, r * a.U, b, u * a.hq + h);
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
     const int rr = pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, c = (int)threadIdx.x % PER_ROW;
@@ -483,7 +558,7 @@ void wave_split_attn_fwd(const WsArgs a) {
     }
     sum *= inv_s[rr];
     if (row0 + rr < a.Lq) {
-      OutT* dst = (OutT*)orow.row(row0 + rr) + 4 * c;
+      OutT* dst = (OutT*)a.o + q_row(row0 + rr) + 4 * c;
       if constexpr (sizeof(OutT) == 4) *(f32x4_any*)dst = sum;
       else *(u32x2_any*)dst = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
     }
@@ -506,11 +581,22 @@ int launch_typed(WsArgs a, int64_t grid, hipStream_t stream) {
   return USP_OK;
 }
 
-int launch(WsArgs a, int hs, int in_dtype, int o_dtype, hipStream_t stream) {
+int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipStream_t stream) {
   a.g = a.hq / a.hkv;
   a.by_hkv = fast_div(a.hkv); a.by_bs = fast_div(a.bs); a.by_ranks = fast_div(a.n_ranks);
   a.by_g = fast_div(a.g); a.by_U = fast_div(a.U);
   a.n_qtiles = (a.Lq + kRows - 1) / kRows;
+  auto strides = [&](int heads, const FastDiv& n, uint64_t& ring, uint64_t& run, uint64_t& jump) {
+    run = (uint64_t)n.d * heads * hs;
+    ring = run * a.bs * a.U;
+    jump = run * (a.bs - 1);
+  };
+  strides(a.q_heads, a.n_q, a.q_ring, a.q_run, a.q_jump);
+  strides(a.kv_heads, n_k, a.kv_ring, a.kv_run, a.kv_jump);
+  a.tiles.one = a.kv_jump == 0;
+  a.tiles.by_n = n_k;
+  a.tiles.by_tiles = fast_div((n_k.d + kTile - 1) / kTile);
+  if (!a.causal) a.kpos = BlockPositions{0, 0, a.Lk, 0, 0, 0};
   a.scale_log2 = a.scale * 1.4426950408889634f;
   const int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * a.n_ranks;
   if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
@@ -535,11 +621,13 @@ int launch_wave_split_usp_fwd(const usp_problem& p, const void* q, const void* k
   a.bs = p.bs; a.hq = p.hc / p.ulysses; a.hkv = p.hk / p.ulysses;
   a.q_heads = p.hc; a.kv_heads = p.hk;
   a.U = p.ulysses; a.R = p.ring; a.rank_begin = rank_begin; a.n_ranks = rank_end - rank_begin;
-  a.n_q = a.n_k = fast_div(p.L / ((int64_t)p.ulysses * p.ring));
+  a.n_q = fast_div(p.L / ((int64_t)p.ulysses * p.ring));
   a.Lq = a.Lk = (int)(p.L / p.ring);
-  a.causal = p.causal ? 1 : 0; a.split = p.split;
+  a.causal = p.causal ? 1 : 0;
+  const int c = a.Lq / 2;
+  a.qpos = a.kpos = p.split == USP_SPLIT_ZIGZAG ? BlockPositions{0, c, c, (2 * p.ring - 1) * c, c, c} : BlockPositions{0, a.Lq, a.Lq, 0, 0, 0};
   a.scale = scale;
-  return launch(a, p.hs, p.dtype, p.dtype, stream);
+  return launch(a, a.n_q, p.hs, p.dtype, p.dtype, stream);
 }
 
 int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
@@ -550,16 +638,16 @@ int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, voi
   a.bs = bs; a.hq = a.q_heads = hq; a.hkv = a.kv_heads = hkv;
   a.U = a.R = a.n_ranks = 1;
   a.Lq = (int)Lq; a.n_q = fast_div(Lq);
-  a.Lk = (int)Lk; a.n_k = fast_div(Lk);
-  a.causal = causal; a.split = -1;
+  a.Lk = (int)Lk;
+  a.causal = causal;
   if (state) {
     a.state = state->state; a.state_first = state->first; a.state_last = state->last;
     a.state_records = (int)((Lq + 255) / 256) * 8;
   }
-  a.qpos = PosDesc32{(int)qpos.start0, (int)qpos.len0, (int)qpos.start1, (int)qpos.len1};
-  a.kpos = PosDesc32{(int)kpos.start0, (int)kpos.len0, (int)kpos.start1, (int)kpos.len1};
+  a.qpos = BlockPositions{(int)qpos.start0, 0, (int)qpos.len0, (int)qpos.start1, 0, (int)qpos.len1};
+  a.kpos = BlockPositions{(int)kpos.start0, 0, (int)kpos.len0, (int)kpos.start1, 0, (int)kpos.len1};
   a.scale = scale;
-  return launch(a, hs, in_dtype, o_dtype, stream);
+  return launch(a, fast_div(Lk), hs, in_dtype, o_dtype, stream);
 }
 
 }  // namespace usp

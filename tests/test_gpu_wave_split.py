@@ -40,6 +40,23 @@ def test_all_ranks_match_the_oracle(usp, dtype, bs, L, hc, hk, hs, U, R, causal,
         assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
 
 
+@pytest.mark.parametrize("dtype", [tl.BF16, tl.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("bs,L,hc,hk,hs,U,R,causal,zigzag", [
+    (2, 330, 4, 2, 64, 1, 5, True, True),           # shards of 66 rows: the second run begins inside a shard's second tile
+    (2, 1056, 4, 4, 128, 4, 1, True, True),         # shards of 264: nine tiles each, the last of eight rows
+    (3, 1188, 2, 2, 128, 2, 2, False, False),       # shards of 297 without a mask: every ragged tile is masked
+    (2, 2112, 4, 2, 64, 2, 3, True, False),         # more tiles than waves in every block, shards of 352 = 11 tiles
+    (1, 1036, 4, 2, 64, 2, 1, True, True),          # one run of rows: a batch of one, the last tile of twelve rows
+])
+def test_tiles_end_with_their_shard(usp, dtype, bs, L, hc, hk, hs, U, R, causal, zigzag):
+    """No key tile crosses from one shard of a batch into the next, and the next tile is asked for while one is worked on."""
+    prob = tl.Problem(970 + L, bs, L, hc, hk, hs, U, R, causal, zigzag, dtype)
+    o, lse = _run_usp_fwd(usp, prob)
+    ref_o, tol = _check_against_reference(prob, o, lse)
+    for rank in range(prob.N):
+        assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
+
+
 def test_a_rank_range_writes_only_its_slices(usp):
     """bs = 2, ranks 1 and 2 of four: their head slices, everything else as it was; the other ranks' LSE too."""
     prob = tl.Problem(951, 2, 160, 4, 2, 64, 2, 2, True, True, tl.FP32)
