@@ -44,6 +44,7 @@ class UspError(RuntimeError):
 
 
 _lib = None
+_torch_cuda = _raw_stream = _raw_device = None   # set by load(); None: this torch has no such functions
 
 
 def load():
@@ -57,7 +58,11 @@ def load():
     # torch first: it ships a HIP runtime of its own, and the tensors and streams passed in belong to that one.
     # Loaded after torch, the library binds to the runtime already in the process; loaded before it, the library
     # would bring in the system's copy, torch its own, and launches on torch's buffers fail ("HIP launch error").
-    import torch  # noqa: F401
+    import torch
+    global _torch_cuda, _raw_stream, _raw_device
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _raw_device = getattr(torch._C, "_cuda_getDevice", None)
+    _torch_cuda = torch.cuda if _raw_stream is not None and _raw_device is not None else None
     lib = C.CDLL(LIB_PATH)
     P, I, L, F, V = C.POINTER, C.c_int, C.c_int64, C.c_float, C.c_void_p
     lib.usp_status_str.restype = C.c_char_p
@@ -117,6 +122,12 @@ def _ptr(x):
 def _stream(stream):
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
+    # The handle of torch's current stream, without the Stream object that torch.cuda.current_stream() makes first: that took
+    # 2.7 us of the 8.3 us that a call kept the host busy, longer than its launch, and longer than the GPU takes for the
+    # shortest calls.
+    cuda = _torch_cuda
+    if cuda is not None and cuda.is_initialized():
+        return _raw_stream(_raw_device())
     import torch
     return torch.cuda.current_stream().cuda_stream
 
