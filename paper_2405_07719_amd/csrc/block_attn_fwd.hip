@@ -22,6 +22,7 @@
 //     counters in device memory, heaviest query tiles first (descending local index under a
 //     causal mask), KV group fastest; a workgroup prefers the items whose KV heads its XCD's L2
 //     already serves (attn_device.h).  K/V tiles are fetched through buffer descriptors.
+#include <algorithm>
 #include <numeric>
 #include <type_traits>
 
@@ -86,6 +87,13 @@ struct AttnArgs {
   int state_first, state_last;
 };
 
+// The arguments of a launch whose items are listed (instance STATE): the query tiles that its middle steps walk.
+constexpr int kMaxListed = 1024;
+struct ListedArgs : AttnArgs {
+  int n_listed;                  // 0: every tile, in the usual order
+  uint32_t list[kMaxListed / 2];   // tile numbers, two to a word
+};
+
 // floats of one 32-row state record: the O^T accumulator (hs / 32 x 16 registers x 64 lanes), then m and l per lane
 constexpr size_t state_record_floats(int hs) { return (size_t)(hs / 32) * 16 * 64 + 2 * 64; }
 
@@ -124,7 +132,8 @@ __device__ inline size_t qo_offset(const Args& a, int b, int row, int h, int hs)
 // LDS pipe, which issues a read every ~7 cycles whatever its width, was the busiest unit of the kernel.
 template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(NWAVES * 64, NWAVES * 64), amdgpu_waves_per_eu(WPE, WPE)))
-void block_attn_fwd_mfma(const AttnArgs) {
+void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) {
+  using Args = std::conditional_t<STATE, ListedArgs, AttnArgs>;
   static_assert(!STATE || NQB == 1, "the state record is laid out for one 32-row block per wave");
   static_assert(!MIXED || (!STATE && sizeof(OutT) == 2), "the mixed launch writes bf16 results and fp32 partials");
   static_assert(!VT || KT == 64, "the transposed V layout is made of 64-key tiles");
@@ -160,7 +169,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
   __shared__ unsigned empty_queues;   // thread 0's record of the item queues it has found empty
   int turn = 0;
   if (threadIdx.x == 0) {
-    auto ap0 = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    auto ap0 = (const __attribute__((address_space(4))) Args*)__builtin_amdgcn_kernarg_segment_ptr();
     // the first item is given, not drawn
     next_item[0] = ItemQueues{ap0->ticket_slot, ap0->n_items, (int)gridDim.x, ap0->n_queues}.first_item(blockIdx.x);
     empty_queues = 0;
@@ -170,14 +179,16 @@ void block_attn_fwd_mfma(const AttnArgs) {
     // compiler cannot see through.  Read once, everything derived from them (reciprocals of the item decode, strides,
     // flags) would be hoisted out of the item loop and held in scalar registers across it; there are not enough,
     // and the overflow goes to lanes of a vector register that the tile loop cannot spare.
-    auto ap = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    auto ap = (const __attribute__((address_space(4))) Args*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(ap));
     const int n_items = ap->n_items;
+    // Every item given, none left to draw: no counter is touched.  (Looking for one took 3 to 5 us at the end of a launch.)
+    const bool drawing = !STATE || n_items > (int)gridDim.x;
     __syncthreads();   // the previous item is done with LDS, and next_item[turn] has been written
     int w = __builtin_amdgcn_readfirstlane(next_item[turn]);
     turn ^= 1;
     if (w >= n_items) {
-      if (threadIdx.x == 0) ItemQueues{ap->ticket_slot, n_items, (int)gridDim.x, ap->n_queues}.leave();
+      if (drawing && threadIdx.x == 0) ItemQueues{ap->ticket_slot, n_items, (int)gridDim.x, ap->n_queues}.leave();
       break;
     }
     ItemArgs a;
@@ -213,7 +224,10 @@ void block_attn_fwd_mfma(const AttnArgs) {
       t += ap->n_split_tiles;
     }
     // (a mixed launch counts its tiles from the last one down whatever the mask: its cut tiles are the last rows)
-    const int qtile = (a.causal || MIXED) ? a.n_qtiles - 1 - t : t;
+    int qtile = (a.causal || MIXED) ? a.n_qtiles - 1 - t : t;
+    if constexpr (STATE) {
+      if (ap->n_listed) qtile = (int)((ap->list[t >> 1] >> (16 * (t & 1))) & 0xffffu);
+    }
     const int b = group / a.hkv, kvh = group % a.hkv;
     const int h = kvh * a.g + hg;
 
@@ -233,7 +247,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
       // split half of a rank's rows see nothing of most blocks): the rows' state stays as it is, so it is neither
       // read nor written back, and the item ends here.  (The first step writes the initial state, the last one the
       // output: those walk every item.)
-      if (!ap->state_first && !ap->state_last) {
+      if (!ap->state_first && !ap->state_last && !ap->n_listed) {
         bool any = false;
         for (int blk = 0; blk < a.n_blocks; ++blk) {
           const PosDesc32 kp = {ap->kpos[blk].start0, ap->kpos[blk].len0, ap->kpos[blk].start1, ap->kpos[blk].len1};
@@ -243,9 +257,8 @@ void block_attn_fwd_mfma(const AttnArgs) {
         if (!any) {   // workgroup-uniform
           if (threadIdx.x == 0) {
             const ItemQueues queues = {ap->ticket_slot, n_items, (int)gridDim.x, ap->n_queues};
-            const unsigned own_ticket = queues.begin(empty_queues);
             unsigned empty = empty_queues;
-            next_item[turn] = queues.finish(own_ticket, empty);
+            next_item[turn] = drawing ? queues.finish(queues.begin(empty), empty) : n_items;
             empty_queues = empty;
           }
           continue;
@@ -299,20 +312,33 @@ void block_attn_fwd_mfma(const AttnArgs) {
       float* const st = ap->state;
       {
         st_rec = st + ((((size_t)b * a.hq + h) * a.n_qtiles + qtile) * NWAVES + wave) * state_record_floats(HS);
-        if (!ap->state_first) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const f32x4 v4 = *(const f32x4*)(st_rec + ((db * 4 + j) * 64 + lane) * 4);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) oacc[0][db][4 * j + e] = v4[e];
-            }
-          m_run[0] = st_rec[DB * 16 * 64 + lane];
-          l_run[0] = st_rec[DB * 16 * 64 + 64 + lane];
-        }
       }
     }
+    // (the first step's loads find an empty range and give zeros: no branch, no second copy of the accumulators)
+    auto state_rsrc = [&]() {
+      return __builtin_amdgcn_make_buffer_rsrc((void*)st_rec, 0, ap->state_first ? 0 : (int)(state_record_floats(HS) * sizeof(float)), kRawBufferFlags);
+    };
+    auto load_state_sums = [&]() {   // m (-inf: no state yet) and l
+      const __amdgpu_buffer_rsrc_t rec = state_rsrc();
+      const uint32_t m = __builtin_amdgcn_raw_buffer_load_b32(rec, lane * 4, DB * 4096, 0);
+      const uint32_t l = __builtin_amdgcn_raw_buffer_load_b32(rec, lane * 4, DB * 4096 + 256, 0);
+      m_run[0] = ap->state_first ? -INFINITY : __builtin_bit_cast(float, m);
+      l_run[0] = __builtin_bit_cast(float, l);
+    };
+    auto load_state_acc = [&]() {
+      const __amdgpu_buffer_rsrc_t rec = state_rsrc();
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const u32x4 v4 = __builtin_amdgcn_raw_buffer_load_b128(rec, lane * 16, (db * 4 + j) * 1024, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t x = v4[e];
+            oacc[0][db][4 * j + e] = __builtin_bit_cast(float, x);
+          }
+        }
+    };
 
     // wave-level bounds for the mask decision
     const int wave_row1 = min(row_end, wave_row0 + NQB * 32);
@@ -530,13 +556,14 @@ void block_attn_fwd_mfma(const AttnArgs) {
 
     const std::integral_constant<bool, true> steady;
     const std::integral_constant<bool, false> draining;
+    if constexpr (STATE) blk0 = 0, blk1 = 1;
     for (int blk = blk0; blk < blk1; ++blk) {
       if (per_block || MIXED) Lk_b = ap->lk_blk[blk];
       kpos = PosDesc32{ap->kpos[blk].start0, ap->kpos[blk].len0, ap->kpos[blk].start1, ap->kpos[blk].len1};
       tr = visible_key_tiles<KT>(a.causal, a.qpos, kpos, Lk_b, tile_row0, tile_row1);
       na = tr.a1 - tr.a0;
       nt = na + (tr.b1 - tr.b0);
-      if (nt == 0) continue;         // nothing of this block is visible to the query tile (workgroup-uniform)
+      if (!STATE && nt == 0) continue;   // nothing of this block is visible to the query tile (workgroup-uniform)
       {
         // Tiles that need no mask: full tiles that lie wholly in one ascending run of the key positions and whose
         // last key no row of this wave precedes.  In walk order they form a run at the start of each visible range.
@@ -561,14 +588,29 @@ void block_attn_fwd_mfma(const AttnArgs) {
       full_tiles = Lk_b / KT;
       full_extent = (KT - 1) * (int)row_bytes + HS * 2;
       ragged_extent = (Lk_b - full_tiles * KT - 1) * (int)row_bytes + HS * 2;   // (not used when there is no ragged tile)
-      fetch(kg, tile_of(0), kreg);
-      fetch_v(vg, tile_of(0), vreg);
-      stash(kbuf, KSTR, kreg);
-      stash_v(vbuf, vreg);
       v_tile = tile_of(1);
-      if (nt > 1) {
-        fetch(kg, tile_of(1), kreg);
-        stash(kbuf + KBYTES, KSTR, kreg);
+      if constexpr (STATE) {
+        // Loads return in their order: K(0) and K(1) go ahead of the state, 128 KiB per workgroup, 34 to 68 MiB that all
+        // workgroups ask for at once and that took 11 us to arrive, and V(0), first wanted after the softmax, behind it.
+        load_state_sums();
+        if (nt > 0) {
+          fetch(kg, tile_of(0), kreg);
+          fetch(kg, nt > 1 ? v_tile : tile_of(0), vreg);
+        }
+        load_state_acc();
+        if (nt == 0) continue;
+        stash(kbuf, KSTR, kreg);
+        stash(kbuf + KBYTES, KSTR, vreg);
+        fetch_v(vg, tile_of(0), vreg);
+      } else {
+        fetch(kg, tile_of(0), kreg);
+        fetch_v(vg, tile_of(0), vreg);
+        stash(kbuf, KSTR, kreg);
+        stash_v(vbuf, vreg);
+        if (nt > 1) {
+          fetch(kg, v_tile, kreg);
+          stash(kbuf + KBYTES, KSTR, kreg);
+        }
       }
       __syncthreads();
       f32x16 s0[NQB][KB], s1[NQB][KB];   // scores of the current and of the next tile
@@ -580,6 +622,13 @@ void block_attn_fwd_mfma(const AttnArgs) {
 #pragma unroll
         for (int kbk = 0; kbk < KB; ++kbk) asm volatile("" : "=v"(s1[qb][kbk]));
       qk(kbuf, s0);
+      if constexpr (STATE) {   // the state has to have arrived before the loop (see settle), and V(0) be in LDS
+#pragma unroll
+        for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(oacc[0][db]));
+        settle(m_run[0]);
+        settle(l_run[0]);
+        stash_v(vbuf, vreg);
+      }
       __syncthreads();   // step 0 overwrites K buffer 0 with tile 2: every wave must have read tile 0 first
 
       int it = 0;
@@ -600,7 +649,7 @@ void block_attn_fwd_mfma(const AttnArgs) {
 
     const ItemQueues queues = {ap->ticket_slot, n_items, (int)gridDim.x, ap->n_queues};
     unsigned own_ticket = kNoDraw;
-    if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
+    if (drawing && threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
     // ---- epilogue: normalise, write O (a row that saw no key at all: l = 0 -> O = 0, LSE = -inf)
     // ---- write O (this lane: query l32, dims 32 db + 8 j + 4 hl + 0..3) and LSE
     if (STATE && !ap->state_last) {
@@ -666,22 +715,62 @@ void block_attn_fwd_mfma(const AttnArgs) {
     }
     if (threadIdx.x == 0) {   // waits for the draw only: the stores were issued after it
       unsigned empty = empty_queues;
-      next_item[turn] = queues.finish(own_ticket, empty);
+      next_item[turn] = drawing ? queues.finish(own_ticket, empty) : n_items;
       empty_queues = empty;
     }
   }   // next work item
 }
 
+// smallest and largest position of the rows [a, b) (pos_min and pos_max of attn_device.h, on the host)
+inline int64_t host_pos_min(const PosDesc32& d, int64_t a, int64_t b) {
+  int64_t m = INT64_MAX;
+  if (a < d.len0) m = d.start0 + a;
+  if (b > d.len0) m = std::min(m, d.start1 + std::max<int64_t>(a, d.len0) - d.len0);
+  return m;
+}
+inline int64_t host_pos_max(const PosDesc32& d, int64_t a, int64_t b) {
+  int64_t m = INT64_MIN;
+  if (a < d.len0) m = d.start0 + std::min<int64_t>(b, d.len0) - 1;
+  if (b > d.len0) m = std::max(m, d.start1 + b - 1 - d.len0);
+  return m;
+}
+
 template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
-int launch_mfma(AttnArgs a, hipStream_t stream) {
+int launch_mfma(const AttnArgs& args, hipStream_t stream) {
   constexpr int BM = NWAVES * NQB * 32;
   constexpr int KSTR = HS * 2 + 48, VSTR = VT ? KT * 2 + 16 : HS * 2 + 64;
   constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR));
   static_assert(BM == 256, "RowTiles");
+  std::conditional_t<STATE, ListedArgs, AttnArgs> a;
+  static_cast<AttnArgs&>(a) = args;
+  if (STATE && a.n_blocks != 1) return USP_ERR_UNSUPPORTED;
   const RowTiles tiles(usp_posdesc{a.qpos.start0, a.qpos.len0, a.qpos.start1, a.qpos.len1}, a.Lq, a.causal && !STATE);
   a.n_qtiles = tiles.n;
   a.tiles_run0 = tiles.in_run0;
   int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * (a.per_block ? a.n_blocks : 1);
+  if constexpr (STATE) {
+    // A middle step of a step-by-step ring leaves the rows that see nothing of its block as they are (under the zigzag split
+    // half of a rank's rows see nothing of most blocks): their tiles are no items.  Drawn and put back, they were 8 to 12 us
+    // at the end of such a step of L = 32768, ring 8.
+    a.n_listed = 0;
+    if (a.causal && !a.state_first && !a.state_last && a.n_qtiles <= kMaxListed) {
+      int n = 0;
+      for (int t = a.n_qtiles - 1; t >= 0; --t) {   // heaviest first
+        const int r0 = t * BM, r1 = std::min(a.Lq, r0 + BM);
+        bool sees = false;
+        for (int j = 0; j < a.n_blocks; ++j) sees = sees || host_pos_max(a.qpos, r0, r1) >= host_pos_min(a.kpos[j], 0, a.Lk);
+        if (!sees) continue;
+        if (n % 2 == 0) a.list[n / 2] = 0;
+        a.list[n / 2] |= (uint32_t)t << (16 * (n % 2));
+        ++n;
+      }
+      if (n == 0) return USP_OK;
+      if (n < a.n_qtiles) {
+        a.n_listed = n;
+        grid = (int64_t)n * a.hq * a.bs;
+      }
+    }
+  }
   if constexpr (MIXED) {
     if (a.n_split_tiles < 0 || a.n_split_tiles > a.n_qtiles) return USP_ERR_UNSUPPORTED;
     const int64_t split = (int64_t)a.n_split_tiles * a.hq * a.bs * a.n_blocks;

@@ -487,3 +487,41 @@ def test_ring_attn_fwd_vt_equals_row_major_v(usp, name, bs, L, hq, hkv, hs, R, r
     assert torch.equal(l0.view(torch.int32), l1.view(torch.int32))
     tl.assert_lse_close(tl.to_f64(l1), ref_l, 1e-3)
     assert tl.max_abs(tl.to_f64(o1), ref_o) <= 2e-2
+
+
+@pytest.mark.parametrize("hs,hq,hkv,runs,blocks", [
+    (128, 8, 2, ((0, 2048), (14336, 2048)), ((0, 2048, 14336, 2048), (2048, 2048, 12288, 2048), (4096, 4096, 0, 0), (12288, 2100, 0, 0))),
+    (128, 4, 4, ((3000, 900), (9000, 1300)), ((0, 3000, 0, 0), (3000, 900, 9000, 1300), (9500, 2200, 0, 0), (2900, 3500, 0, 0))),
+    (64, 8, 1, ((5000, 700), (100, 1500)), ((0, 1600, 0, 0), (5000, 2200, 0, 0), (1000, 100, 5100, 2100), (0, 2200, 0, 0))),
+    (64, 1, 1, ((0, 1024 * 256 + 40), (0, 0)), ((0, 4000, 0, 0), (200000, 4000, 0, 0), (262100, 4000, 0, 0))),
+], ids=["live_half", "ragged_runs", "first_run_later", "more_tiles_than_are_listed"])
+def test_state_steps_walk_only_tiles_that_see_the_block(usp, hs, hq, hkv, runs, blocks):
+    """Steps in which all, some, one or none of the 256-row query tiles see the block, against the one-launch loop over the
+    same blocks: the same weights (maxima and roundings follow the same walk), sums in fp32 in the same order."""
+    (s0, n0), (s1, n1) = runs
+    Lq, R = n0 + n1, len(blocks)
+    gen = torch.Generator(device="cuda").manual_seed(Lq)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    Lk = blocks[0][1] + blocks[0][3]
+    q = normal(1, Lq, hq, hs)
+    qd = usp.usp_posdesc(s0, n0, s1, n1)
+    o = torch.full((1, Lq, hq, hs), float("nan"), device="cuda")
+    lse = torch.full((1, hq, Lq), float("nan"), device="cuda")
+    kd = [usp.usp_posdesc(a, min(n, Lk), b, max(0, Lk - min(n, Lk))) for a, n, b, m in blocks]
+    kb, vb = [normal(1, Lk, hkv, hs) for _ in blocks], [normal(1, Lk, hkv, hs) for _ in blocks]
+    state = torch.full((usp.usp_block_attn_fwd_state_bytes(1, Lq, hq, hs),), 0xFF, dtype=torch.uint8, device="cuda")
+    for i in range(R):
+        usp.usp_block_attn_fwd_state(q, kb[i], vb[i], state, o, lse, 1, Lq, Lk, hq, hkv, hs, 0.0, True, qd, kd[i], i == 0,
+                                     i == R - 1, tl.FP32)
+    o1, lse1 = torch.empty_like(o), torch.empty_like(lse)
+    usp.usp_ring_attn_fwd(q, kb, vb, kd, o1, lse1, 1, Lq, Lk, hq, hkv, hs, 0.0, True, qd, tl.BF16, tl.FP32)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isinf(lse), torch.isinf(lse1)) and not torch.isnan(lse).any()
+    seen = ~torch.isinf(lse)
+    assert (lse[seen] - lse1[seen]).abs().max().item() <= 1e-4
+    # (a call that goes to the kernel for short blocks moves on from other maxima: a bf16 rounding of a weight, 2^-9, apart)
+    assert ((o - o1).norm() / o1.norm()).item() <= 2 ** -8
+    assert o[~seen.transpose(1, 2)].abs().sum().item() == 0
