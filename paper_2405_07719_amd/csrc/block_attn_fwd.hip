@@ -79,6 +79,7 @@ struct AttnArgs {
   int lk_blk[kMaxBlocks];
   void* o_part[kMaxBlocks];
   float* lse_part[kMaxBlocks];
+  int part_row0[kMaxBlocks];   // a partial result holds the rows from here on (of every batch entry)
   // Running state of a ring that delivers its blocks one per call (launch_block_attn_fwd_state): the online-softmax
   // state of every query row (running maximum m, sum l, unnormalised O^T accumulator) in the kernel's own register
   // layout, one record of state_record_floats() per 32-row block of a (batch, head): read at the start of an item
@@ -87,11 +88,11 @@ struct AttnArgs {
   int state_first, state_last;
 };
 
-// The arguments of a launch whose items are listed (instance STATE): the query tiles that its middle steps walk.
-constexpr int kMaxListed = 1024;
+// The arguments of a launch whose items are listed.  Instance STATE: the query tiles that its middle steps walk.  Instance
+// MIXED: a tile and the piece of the keys (listed_item()), heaviest first, every entry once per head and batch entry.
 struct ListedArgs : AttnArgs {
-  int n_listed;                  // 0: every tile, in the usual order
-  uint32_t list[kMaxListed / 2];   // tile numbers, two to a word
+  int n_listed;                         // 0: every tile, in the usual order
+  uint32_t list[kMaxListedItems / 2];   // two to a word
 };
 
 // floats of one 32-row state record: the O^T accumulator (hs / 32 x 16 registers x 64 lanes), then m and l per lane
@@ -132,8 +133,8 @@ __device__ inline size_t qo_offset(const Args& a, int b, int row, int h, int hs)
 // LDS pipe, which issues a read every ~7 cycles whatever its width, was the busiest unit of the kernel.
 template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(NWAVES * 64, NWAVES * 64), amdgpu_waves_per_eu(WPE, WPE)))
-void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) {
-  using Args = std::conditional_t<STATE, ListedArgs, AttnArgs>;
+void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs>) {
+  using Args = std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs>;
   static_assert(!STATE || NQB == 1, "the state record is laid out for one 32-row block per wave");
   static_assert(!MIXED || (!STATE && sizeof(OutT) == 2), "the mixed launch writes bf16 results and fp32 partials");
   static_assert(!VT || KT == 64, "the transposed V layout is made of 64-key tiles");
@@ -208,15 +209,30 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: keep what derives from it in scalar registers
     const int l32 = lane & 31, hl = lane >> 5;
     bool per_block = ap->per_block != 0;
+    bool listed = false;
     if constexpr (MIXED) {
-      per_block = w < ap->n_split_items;     // the split items come first
-      if (!per_block) w -= ap->n_split_items;
+      listed = ap->n_listed > 0;
+      if (!listed) {
+        per_block = w < ap->n_split_items;     // the split items come first
+        if (!per_block) w -= ap->n_split_items;
+      }
     }
     const int group = w % n_groups; w /= n_groups;
     const int hg = w % a.g;
     int t = w / a.g;
     int blk0 = 0, blk1 = a.n_blocks;         // the blocks this item walks
-    if (per_block) {
+    int entry = 0;
+    if constexpr (STATE || MIXED) {
+      if (STATE ? ap->n_listed > 0 : listed) entry = (int)((ap->list[t >> 1] >> (16 * (t & 1))) & 0xffffu);
+    }
+    if (MIXED && listed) {
+      const int piece = entry >> kListedTileBits;
+      per_block = piece != kListedWhole;
+      if (per_block) {
+        blk0 = piece;
+        blk1 = blk0 + 1;
+      }
+    } else if (per_block) {
       blk0 = t % a.n_blocks;
       blk1 = blk0 + 1;
       t /= a.n_blocks;
@@ -225,9 +241,8 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) 
     }
     // (a mixed launch counts its tiles from the last one down whatever the mask: its cut tiles are the last rows)
     int qtile = (a.causal || MIXED) ? a.n_qtiles - 1 - t : t;
-    if constexpr (STATE) {
-      if (ap->n_listed) qtile = (int)((ap->list[t >> 1] >> (16 * (t & 1))) & 0xffffu);
-    }
+    if constexpr (STATE) qtile = ap->n_listed ? entry : qtile;
+    if constexpr (MIXED) qtile = listed ? entry & ((1 << kListedTileBits) - 1) : qtile;
     const int b = group / a.hkv, kvh = group % a.hkv;
     const int h = kvh * a.g + hg;
 
@@ -671,7 +686,8 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) 
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
         const int qrow = wave_row0 + qb * 32 + l32;
         if (qrow < row_end) {
-          float* dst = (float*)ap->o_part[blk0] + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
+          const int row0 = ap->part_row0[blk0], part_rows = a.Lq - row0;
+          float* dst = (float*)ap->o_part[blk0] + (((size_t)b * part_rows + (qrow - row0)) * a.hq + h) * HS + 4 * hl;
 #pragma unroll
           for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -681,7 +697,7 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE, ListedArgs, AttnArgs>) 
               *(f32x4*)(dst + db * 32 + j * 8) = v4;
             }
           if (hl == 0)
-            ap->lse_part[blk0][((size_t)b * a.hq + h) * a.Lq + qrow] = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
+            ap->lse_part[blk0][((size_t)b * a.hq + h) * part_rows + (qrow - row0)] = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
         }
       }
     } else
@@ -736,33 +752,34 @@ inline int64_t host_pos_max(const PosDesc32& d, int64_t a, int64_t b) {
 }
 
 template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
-int launch_mfma(const AttnArgs& args, hipStream_t stream) {
+int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed = nullptr, int n_listed = 0) {
   constexpr int BM = NWAVES * NQB * 32;
   constexpr int KSTR = HS * 2 + 48, VSTR = VT ? KT * 2 + 16 : HS * 2 + 64;
   constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR));
   static_assert(BM == 256, "RowTiles");
-  std::conditional_t<STATE, ListedArgs, AttnArgs> a;
+  std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs> a;
   static_cast<AttnArgs&>(a) = args;
   if (STATE && a.n_blocks != 1) return USP_ERR_UNSUPPORTED;
   const RowTiles tiles(usp_posdesc{a.qpos.start0, a.qpos.len0, a.qpos.start1, a.qpos.len1}, a.Lq, a.causal && !STATE);
   a.n_qtiles = tiles.n;
   a.tiles_run0 = tiles.in_run0;
   int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * (a.per_block ? a.n_blocks : 1);
+  [[maybe_unused]] auto put = [&](int at, uint32_t entry) {
+    if constexpr (STATE || MIXED) a.list[at / 2] = at % 2 ? a.list[at / 2] | entry << 16 : entry;
+  };
+  if constexpr (STATE || MIXED) a.n_listed = 0;
   if constexpr (STATE) {
     // A middle step of a step-by-step ring leaves the rows that see nothing of its block as they are (under the zigzag split
     // half of a rank's rows see nothing of most blocks): their tiles are no items.  Drawn and put back, they were 8 to 12 us
     // at the end of such a step of L = 32768, ring 8.
-    a.n_listed = 0;
-    if (a.causal && !a.state_first && !a.state_last && a.n_qtiles <= kMaxListed) {
+    if (a.causal && !a.state_first && !a.state_last && a.n_qtiles <= kMaxListedItems) {
       int n = 0;
       for (int t = a.n_qtiles - 1; t >= 0; --t) {   // heaviest first
         const int r0 = t * BM, r1 = std::min(a.Lq, r0 + BM);
         bool sees = false;
         for (int j = 0; j < a.n_blocks; ++j) sees = sees || host_pos_max(a.qpos, r0, r1) >= host_pos_min(a.kpos[j], 0, a.Lk);
         if (!sees) continue;
-        if (n % 2 == 0) a.list[n / 2] = 0;
-        a.list[n / 2] |= (uint32_t)t << (16 * (n % 2));
-        ++n;
+        put(n++, (uint32_t)t);
       }
       if (n == 0) return USP_OK;
       if (n < a.n_qtiles) {
@@ -777,6 +794,17 @@ int launch_mfma(const AttnArgs& args, hipStream_t stream) {
     grid = split + (int64_t)(a.n_qtiles - a.n_split_tiles) * a.hq * a.bs;
     if (split > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
     a.n_split_items = (int)split;
+    if (n_listed > 0) {
+      if (n_listed > kMaxListedItems) return USP_ERR_UNSUPPORTED;
+      for (int j = 0; j < n_listed; ++j) {
+        const int tile = listed[j] & ((1 << kListedTileBits) - 1), piece = listed[j] >> kListedTileBits;
+        if (tile >= a.n_qtiles) return USP_ERR_UNSUPPORTED;
+        if (piece != kListedWhole && (piece >= a.n_blocks || tiles.begin(tile) < a.part_row0[piece])) return USP_ERR_UNSUPPORTED;
+        put(j, listed[j]);
+      }
+      a.n_listed = n_listed;
+      grid = (int64_t)n_listed * a.hq * a.bs;
+    }
   }
   if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
   auto kern = block_attn_fwd_mfma<HS, NQB, NWAVES, KT, WPE, OutT, STATE, VT, MIXED>;
@@ -823,6 +851,7 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
     a.lk_blk[j] = (int)Lk;
     a.o_part[j] = nullptr;
     a.lse_part[j] = nullptr;
+    a.part_row0[j] = 0;
   }
   a.bs = bs; a.hq = hq; a.hkv = hkv; a.g = hq / hkv;
   a.Lq = (int)Lq; a.Lk = (int)Lk;
@@ -903,6 +932,8 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
     if (a.lk_blk[j] < 1 || a.lk_blk[j] > Lk) return USP_ERR_SHAPE;
     a.o_part[j] = o_parts[jj];
     a.lse_part[j] = lse_parts[jj];
+    a.part_row0[j] = mixed && mixed->part_row0 ? (int)mixed->part_row0[jj] : 0;
+    if (a.part_row0[j] < 0 || a.part_row0[j] > Lq) return USP_ERR_SHAPE;
   }
   a.n_blocks = n_blocks;
   a.per_block = 1;
@@ -924,11 +955,12 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
     a.lse = mixed->lse;
     a.per_block = 0;
     a.n_split_tiles = mixed->n_split_tiles;
+    auto go = [&](auto launch) { return launch(a, stream, mixed->listed, mixed->n_listed); };
     if (mixed->v_transposed)
-      return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, __bf16, false, true, true>(a, stream)
-                       : launch_mfma<64, 1, 8, 64, 2, __bf16, false, true, true>(a, stream);
-    return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, __bf16, false, false, true>(a, stream)
-                     : launch_mfma<64, 1, 8, 64, 2, __bf16, false, false, true>(a, stream);
+      return hs == 128 ? go(launch_mfma<128, 1, 8, 64, 2, __bf16, false, true, true>)
+                       : go(launch_mfma<64, 1, 8, 64, 2, __bf16, false, true, true>);
+    return hs == 128 ? go(launch_mfma<128, 1, 8, 64, 2, __bf16, false, false, true>)
+                     : go(launch_mfma<64, 1, 8, 64, 2, __bf16, false, false, true>);
   }
   return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, float>(a, stream) : launch_mfma<64, 1, 8, 64, 2, float>(a, stream);
 }

@@ -26,6 +26,7 @@ struct MergeArgs {
   // SEQ instances: o_out is the first sequence-layout shard of the rank's Ulysses group, [U][bs][rows_per_shard]
   // [seq_heads][hs]; the rank's heads begin at seq_head0 (Algorithm 1's last all-to-all rides on the merge's stores)
   int rows_per_shard, seq_heads, seq_head0;
+  int part_row0[USP_MAX_RING_BLOCKS];   // SEQ instances of up to eight parts: the first row that a part holds
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -63,10 +64,29 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(MergeArgs a) {
     // loads of O first, weights while they are in flight
     f32x4 x[NP];
     float l[NP];
+    if constexpr (SEQ) {
+      // A row that a part does not hold, for it sees none of the part's keys, counts for nothing there.  Its loads go to the
+      // first part, which every row has, a second time: no branch stands between the loads, and the lines are there already.
+      bool holds[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) x[p] = load4((const PartT*)a.o[p] + off);
+      for (int p = 0; p < NP; ++p) {
+        holds[p] = i >= a.part_row0[p];
+        const int64_t r0 = (holds[p] ? a.part_row0[p] : a.part_row0[0]), before = (b + 1) * r0 * a.hq;   // rows times heads that are not there
+        x[p] = load4((const PartT*)(holds[p] ? a.o[p] : a.o[0]) + off - before * a.hs);
+      }
 #pragma unroll
-    for (int p = 0; p < NP; ++p) l[p] = a.lse[p][li];
+      for (int p = 0; p < NP; ++p) {
+        const int64_t r0 = (holds[p] ? a.part_row0[p] : a.part_row0[0]);
+        l[p] = (holds[p] ? a.lse[p] : a.lse[0])[li - ((int64_t)b * a.hq + h + 1) * r0];
+      }
+#pragma unroll
+      for (int p = 0; p < NP; ++p) l[p] = holds[p] ? l[p] : -INFINITY;
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) x[p] = load4((const PartT*)a.o[p] + off);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) l[p] = a.lse[p][li];
+    }
     float m = -INFINITY;
 #pragma unroll
     for (int p = 0; p < NP; ++p) m = fmaxf(m, l[p]);
@@ -126,13 +146,15 @@ void launch_typed(const MergeArgs& a, dim3 grid, hipStream_t stream) {
 
 int launch_lse_merge(const void* const* o_parts, const float* const* lse_parts, int n_parts, void* o_out,
                      float* lse_out, int bs, int64_t Lq, int hq, int hs, int part_dtype, int out_dtype,
-                     hipStream_t stream, const SeqLayoutIO* seq, int64_t row0) {
+                     hipStream_t stream, const SeqLayoutIO* seq, int64_t row0, const int64_t* part_row0) {
   if (row0 < 0 || row0 >= Lq) return USP_ERR_UNSUPPORTED;
+  if (part_row0 && (!seq || n_parts > 8 || part_row0[0] > row0)) return USP_ERR_UNSUPPORTED;
   MergeArgs a;
   a.rows_per_shard = seq ? seq->rows_per_shard : 0;
   a.seq_heads = seq ? seq->heads : 0;
   a.seq_head0 = seq ? seq->head0 : 0;
   if (seq && part_dtype != USP_FP32) return USP_ERR_UNSUPPORTED;
+  for (int i = 0; i < USP_MAX_RING_BLOCKS; ++i) a.part_row0[i] = part_row0 && i < n_parts ? (int)part_row0[i] : 0;
   for (int i = 0; i < n_parts; ++i) {
     a.o[i] = o_parts[i];
     a.lse[i] = lse_parts[i];

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <string.h>
 #include <vector>
@@ -379,6 +380,15 @@ constexpr int kMaxHeavyPieces = USP_MAX_RING_BLOCKS;
 struct HeavyPieces { int n; int64_t first[kMaxHeavyPieces], last[kMaxHeavyPieces]; int block[kMaxHeavyPieces]; };
 struct HeavyChoice { int tiles, pieces; };   // tiles == 0: nothing is cut this way
 
+// What a rank's launch runs: a list of items (listed_item()), heaviest first, over the pieces hp of the keys.  Piece j's
+// partial result holds the rows from row0[j] on; the rows from merge_row0 on are merged.  No items: not planned this way.
+struct ItemPlan {
+  HeavyPieces hp;
+  int64_t row0[kMaxHeavyPieces];
+  int64_t merge_row0;
+  std::vector<uint16_t> items;
+};
+
 // The pieces of a ring rank's keys, in the order its ring loop visits them: piece j = keys [first, last) of the block
 // of ring step block[j].  R = 1: `pieces` equal parts of the one block (multiples of 64 keys); R > 1: the blocks.
 HeavyPieces heavy_pieces(const usp_problem& p, int pieces) {
@@ -404,8 +414,9 @@ usp_posdesc piece_of(const usp_posdesc& d, int64_t a, int64_t b) {
   return usp_posdesc{d.start0 + a, n0, d.start1, (b - a) - n0};
 }
 
-// What ring rank r cuts ({0, 0}: nothing, the launch is key_splits()' business).  (Worked out once per problem:
-// heavy_choice() below keeps the answers.)
+// What ring rank r cuts ({0, 0}: nothing, the launch is key_splits()' business): the room for partial results that the
+// workspace has, and the cut itself where work_out_items() has none.  (Worked out once per problem: rank_plans() below keeps
+// the answers.)
 HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   const HeavyChoice none = {0, 0};
   if (!ring_in_one_launch(p)) return none;
@@ -501,36 +512,183 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   return best;
 }
 
+// The launch of ring rank r within the room that the plan has for partial results (that of choice, or of key_splits()): which
+// tiles are cut, into which pieces, by playing the launch through for a number of cuts.  Items are dealt heaviest first, a
+// tile's pieces that it sees nothing of are none, and a partial result holds only the rows that see its piece, so that the
+// room for three whole ones is room for four or five.  Measured against equal pieces for the last tiles, every pair of tile and
+// piece an item (an empty one took 9 us to write zeros), whole usp_attn_fwd of one rank, us: 32/8 heads, U 8: L = 6144 68.6 ->
+// 65.6, 8192 95.2 -> 91.1, 10240 145 -> 129, 12288 180 -> 168, 16384 272 -> 272, 20480 425 -> 403, 24576 593 -> 570; U 4 x R 2,
+// L = 16384 333 -> 287; U 8 x R 2, L = 40960 1001 -> 820; R 8, L = 8192 129 -> 111; head size 64, U 8, L = 12288 118 -> 106.
+// Without a mask (all pieces seen, all items alike) no difference.  The answer is within the room that callers have been told.
+constexpr int kMaxMergeRowParts = 8;   // (launch_lse_merge)
+ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) {
+  ItemPlan best;
+  best.hp.n = 0;
+  best.merge_row0 = 0;
+  const int64_t Lq = p.L / p.ring;
+  const int room = std::max(key_splits(p) * p.ring, choice.tiles > 0 ? choice.pieces : 0);   // partial results of all rows
+  if (room == 0 || !ring_in_one_launch(p)) return best;
+  usp_posdesc qd;
+  ring_block_desc(p, r, &qd);
+  const RowTiles rows(qd, Lq, p.causal);
+  const int T = rows.n, n = (p.hc / p.ulysses) * p.bs;
+  if (T > kMaxListedItems || (int64_t)T * n > 4 * kPlanCUs) return best;
+  // us of an item besides its tiles, of a tile of 64 keys, of a whole item's step to the next piece; read off time stamps
+  const double kItem = 9.0, kTile = p.hs == 128 ? 1.78 : 1.15, kCross = 3.0;
+  auto pos_of = [&](int64_t i) { return i < qd.len0 ? qd.start0 + i : qd.start1 + (i - qd.len0); };
+  std::vector<int64_t> qmax(T);
+  for (int i = 0; i < T; ++i) {
+    const int64_t a = rows.begin(i), b = rows.end(i);
+    qmax[i] = std::max(pos_of(a), pos_of(b - 1));
+    if (a < qd.len0 && b > qd.len0) qmax[i] = std::max({qmax[i], pos_of(qd.len0 - 1), pos_of(qd.len0)});
+  }
+  struct Item { double us; uint16_t entry; };
+  std::vector<Item> list;
+  std::vector<int> sees;   // [tile][piece]: tiles of 64 keys that query tile i walks in piece j
+  std::vector<double> free_at;
+  double best_us = 1e30;
+  auto look = [&](const HeavyPieces& hp) {
+    sees.assign((size_t)T * hp.n, 0);
+    for (int j = 0; j < hp.n; ++j) {
+      usp_posdesc kd;
+      ring_block_desc(p, ((r - hp.block[j]) % p.ring + p.ring) % p.ring, &kd);
+      const usp_posdesc pd = piece_of(kd, hp.first[j], hp.last[j]);
+      for (int i = 0; i < T; ++i) {
+        const int64_t c0 = p.causal ? std::clamp<int64_t>(qmax[i] - pd.start0 + 1, 0, pd.len0) : pd.len0;
+        const int64_t c1 = p.causal ? std::clamp<int64_t>(qmax[i] - pd.start1 + 1, 0, pd.len1) : pd.len1;
+        sees[(size_t)i * hp.n + j] = (int)((c0 + 63) / 64 + (c1 + 63) / 64);
+      }
+    }
+  };
+  // the last k tiles cut into hp (looked at before)
+  auto consider = [&](const HeavyPieces& hp, int k) {
+    if (k < 1 || k > T) return;
+    int64_t row0[kMaxHeavyPieces], held = 0;
+    for (int j = 0; j < hp.n; ++j) {
+      int first = T - k;
+      while (first < T && sees[(size_t)first * hp.n + j] == 0) ++first;
+      for (int i = first; i < T; ++i)
+        if (sees[(size_t)i * hp.n + j] == 0) return;   // (never: what sees a piece is a run of rows up to the last)
+      row0[j] = first < T ? rows.begin(first) : Lq;
+      held += Lq - row0[j];
+    }
+    const int64_t cut_row0 = rows.begin(T - k);
+    if (row0[0] > cut_row0 || held > room * Lq) return;
+    double work = 0.0;
+    list.clear();
+    for (int i = 0; i < T; ++i) {
+      double sum = 0.0;
+      int walked = 0;
+      for (int j = 0; j < hp.n; ++j) {
+        const int tiles = sees[(size_t)i * hp.n + j];
+        if (tiles == 0) continue;
+        sum += tiles;
+        ++walked;
+        if (i >= T - k) list.push_back({kItem + kTile * tiles, listed_item(i, j)});
+      }
+      if (i < T - k) list.push_back({kItem + kTile * sum + kCross * std::max(0, walked - 1), listed_item(i, kListedWhole)});
+    }
+    if ((int)list.size() > kMaxListedItems) return;
+    for (const Item& it : list) work += it.us;
+    const double merge_us = 10.0 + ((double)held * 8.0 + (double)(Lq - cut_row0) * 2.0) * n * p.hs / 5.0e6;
+    if (work * n / kPlanCUs + merge_us >= best_us) return;
+    std::stable_sort(list.begin(), list.end(), [](const Item& a, const Item& b) { return a.us > b.us; });
+    free_at.clear();   // a min-heap of the workgroups' finish times
+    double end = 0.0;
+    for (const Item& it : list)
+      for (int c = 0; c < n; ++c) {
+        if ((int)free_at.size() < kPlanCUs) {
+          free_at.push_back(it.us);
+          if ((int)free_at.size() == kPlanCUs) std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
+          end = std::max(end, it.us);
+          continue;
+        }
+        std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+        free_at.back() += it.us;
+        end = std::max(end, free_at.back());
+        if (end + merge_us >= best_us) return;
+        std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+      }
+    if (end + merge_us >= best_us) return;
+    best_us = end + merge_us;
+    best.hp = hp;
+    std::copy(row0, row0 + hp.n, best.row0);
+    best.merge_row0 = cut_row0;
+    best.items.clear();
+    for (const Item& it : list) best.items.push_back(it.entry);
+  };
+  auto cut_last = [&](const HeavyPieces& hp) {
+    look(hp);
+    for (int part = 1; part <= 32; ++part) {
+      const int k = std::max(1, T * part / 32);
+      if (part == 1 || k != std::max(1, T * (part - 1) / 32)) consider(hp, k);
+    }
+  };
+  if (p.ring > 1) {   // the blocks, whole or in as many pieces as key_splits() has them
+    for (int m = 1; m * p.ring <= kMaxMergeRowParts && m <= std::max(1, key_splits(p)); ++m) {
+      HeavyPieces hp;
+      hp.n = 0;
+      const int64_t piece = ((Lq + m - 1) / m + 63) / 64 * 64;
+      for (int i = 0; i < p.ring; ++i)
+        for (int64_t a = 0; a < Lq; a += piece, ++hp.n) {
+          hp.first[hp.n] = a; hp.last[hp.n] = std::min(Lq, a + piece); hp.block[hp.n] = i;
+        }
+      cut_last(hp);
+    }
+    return best;
+  }
+  for (int pieces = 2; pieces <= 4; ++pieces) cut_last(heavy_pieces(p, pieces));
+  if (p.causal) {
+    // pieces of so many keys that every item is about as long; tiles that see no more than one piece are whole
+    const int tiles = (int)((Lq + 63) / 64);
+    const int shortest = std::max(4, (tiles + kMaxMergeRowParts - 1) / kMaxMergeRowParts);
+    for (int step = 0, q = tiles - 1; q >= shortest && step < 64; ++step, q -= std::max(1, tiles / 64)) {
+      HeavyPieces hp;
+      hp.n = 0;
+      for (int64_t a = 0; a < Lq; a += 64 * q, ++hp.n) {
+        hp.first[hp.n] = a; hp.last[hp.n] = std::min(Lq, a + 64 * q); hp.block[hp.n] = 0;
+      }
+      look(hp);
+      int k = 0;
+      while (k < T && hp.n > 1 && sees[(size_t)(T - 1 - k) * hp.n + 1] > 0) ++k;
+      consider(hp, k);
+    }
+  }
+  return best;
+}
+
 // (the scale plays no part in how a problem is cut)
 bool same_problem(const usp_problem& a, const usp_problem& b) {
   return a.bs == b.bs && a.L == b.L && a.hc == b.hc && a.hk == b.hk && a.hs == b.hs && a.ulysses == b.ulysses &&
          a.ring == b.ring && a.causal == b.causal && a.split == b.split && a.dtype == b.dtype;
 }
 
-// Playing a launch through takes the host 0.1-0.3 ms per ring rank, as long as a short launch itself: the answers
+// Playing launches through takes the host 0.2-1 ms per ring rank, as long as a short launch itself: the answers
 // for the last problems seen are kept (every ring rank's, worked out at the first question about the problem).
-HeavyChoice heavy_choice(const usp_problem& p, int r) {
-  struct Entry { usp_problem p; std::vector<HeavyChoice> per_rank; };
+struct RankPlan { HeavyChoice choice; ItemPlan plan; };
+std::shared_ptr<const std::vector<RankPlan>> rank_plans(const usp_problem& p) {
+  struct Entry { usp_problem p; std::shared_ptr<const std::vector<RankPlan>> ranks; };
   static std::mutex mu;
   static std::vector<Entry> seen;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : seen)
-    if (same_problem(e.p, p)) return e.per_rank[r];
+    if (same_problem(e.p, p)) return e.ranks;
   if (seen.size() >= 64) seen.erase(seen.begin());
-  Entry e{p, {}};
-  for (int rr = 0; rr < p.ring; ++rr) e.per_rank.push_back(work_out_heavy_choice(p, rr));
-  seen.push_back(e);
-  return seen.back().per_rank[r];
+  auto ranks = std::make_shared<std::vector<RankPlan>>();
+  for (int r = 0; r < p.ring; ++r) {
+    const HeavyChoice c = work_out_heavy_choice(p, r);
+    ranks->push_back({c, work_out_items(p, r, c)});
+  }
+  seen.push_back({p, ranks});
+  return ranks;
 }
 
 // The most pieces any ring rank of the problem cuts its heaviest tiles into (0: no rank does): the workspace holds as
 // many partial results.
 int heavy_max_pieces(const usp_problem& p) {
   int m = 0;
-  for (int r = 0; r < p.ring; ++r) {
-    const HeavyChoice c = heavy_choice(p, r);
-    if (c.tiles > 0) m = std::max(m, c.pieces);
-  }
+  for (const RankPlan& r : *rank_plans(p))
+    if (r.choice.tiles > 0) m = std::max(m, r.choice.pieces);
   return m;
 }
 
@@ -734,6 +892,7 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   auto k_block = [&](int s, int u) { return kv_block(f.k_in_place, k, f.k_head, f.kv_block_bytes, s, u); };
   auto v_block = [&](int s, int u) { return kv_block(f.v_in_place, v, f.v_head, f.v_block_bytes, s, u); };
 
+  const auto plans = rank_plans(*p);
   for (int rank = rank_begin; rank < rank_end; ++rank) {
     const int r = rank / U, u = rank % U;
     // Step 2: Q of this rank to head layout (the one-launch ring loop reads the shards itself).
@@ -759,18 +918,20 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
       // row once, so it does that straight from / to the sequence-layout shards of the Ulysses group.
       const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq, kv_pitch};
       const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * es;
-      const HeavyChoice heavy = allow_heavy ? heavy_choice(*p, r) : HeavyChoice{0, 0};
-      if (heavy.tiles > 0) {
-        // Medium length: the last `heavy` query tiles as one item per piece of the keys (the halves of the one block, or
-        // the ring blocks), with partial results; every other tile a whole item of the same launch that writes its
-        // finished rows itself.  Then the merge of the cut rows, straight to the sequence-layout shards.
-        const HeavyPieces hp = heavy_pieces(*p, heavy.pieces);
+      const RankPlan& cut = (*plans)[r];
+      const bool by_list = allow_heavy && !cut.plan.items.empty();
+      if (by_list || (allow_heavy && cut.choice.tiles > 0)) {
+        // Short and medium lengths: the heaviest query tiles as one item per piece of the keys that they see (pieces of the
+        // one block, or the ring blocks), with partial results; every other tile a whole item of the same launch that writes
+        // its finished rows itself.  Then the merge of the cut rows, straight to the sequence-layout shards.
+        const HeavyPieces hp = by_list ? cut.plan.hp : heavy_pieces(*p, cut.choice.pieces);
         const void* kp[kMaxHeavyPieces];
         const void* vp[kMaxHeavyPieces];
         usp_posdesc pd[kMaxHeavyPieces];
         int lk[kMaxHeavyPieces];
         float* o_ptrs[kMaxHeavyPieces];
         float* l_ptrs[kMaxHeavyPieces];
+        size_t held = 0;   // rows of partial results before this one
         for (int n = 0; n < hp.n; ++n) {
           const size_t row_off = (size_t)hp.first[n] * kv_pitch * p->hs * es;
           kp[n] = (const char*)kb[hp.block[n]] + row_off;
@@ -778,17 +939,28 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
           vp[n] = (const char*)vb[hp.block[n]] + (f.v_transposed ? (size_t)(hp.first[n] / 64) * p->hs * 64 * es : row_off);
           pd[n] = piece_of(kds[hp.block[n]], hp.first[n], hp.last[n]);
           lk[n] = (int)(hp.last[n] - hp.first[n]);
-          o_ptrs[n] = (float*)(ws + f.o_parts + (size_t)n * f.part_o_bytes);
-          l_ptrs[n] = (float*)(ws + f.lse_parts + (size_t)n * f.part_lse_bytes);
+          if (by_list) {   // one behind the other
+            o_ptrs[n] = (float*)(ws + f.o_parts) + held * hq * p->hs;
+            l_ptrs[n] = (float*)(ws + f.lse_parts) + held * hq;
+            held += (size_t)p->bs * (Lq - cut.plan.row0[n]);
+          } else {
+            o_ptrs[n] = (float*)(ws + f.o_parts + (size_t)n * f.part_o_bytes);
+            l_ptrs[n] = (float*)(ws + f.lse_parts + (size_t)n * f.part_lse_bytes);
+          }
         }
-        const MixedLaunch mixed = {(char*)o + group_off, lse_rank, heavy.tiles, f.v_transposed};
+        MixedLaunch mixed = {(char*)o + group_off, lse_rank, by_list ? 0 : cut.choice.tiles, f.v_transposed};
+        if (by_list) {
+          mixed.listed = cut.plan.items.data();
+          mixed.n_listed = (int)cut.plan.items.size();
+          mixed.part_row0 = cut.plan.row0;
+        }
         st = launch_attn_fwd_partials((const char*)q + group_off, kp, vp, pd, lk, hp.n, o_ptrs, l_ptrs, p->bs, Lq, Lq, hq,
                                       hkv, p->hs, scale, p->causal ? 1 : 0, qd, stream, &seq, &mixed);
         if (st != USP_OK) return st;
         const RowTiles rows(qd, Lq, p->causal);
-        const int64_t row0 = rows.begin(rows.n - heavy.tiles);
+        const int64_t row0 = by_list ? cut.plan.merge_row0 : rows.begin(rows.n - cut.choice.tiles);
         st = launch_lse_merge((const void* const*)o_ptrs, (const float* const*)l_ptrs, hp.n, (char*)o + group_off, lse_rank,
-                              p->bs, Lq, hq, p->hs, USP_FP32, p->dtype, stream, &seq, row0);
+                              p->bs, Lq, hq, p->hs, USP_FP32, p->dtype, stream, &seq, row0, mixed.part_row0);
         if (st != USP_OK) return st;
         continue;
       }
@@ -1101,7 +1273,7 @@ BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   return best;
 }
 
-// Playing the cuts of a problem through takes the host 0.1 ms, 0.7 at most: the last answers are kept, as heavy_choice() keeps its.
+// Playing the cuts of a problem through takes the host 0.1 ms, 0.7 at most: the last answers are kept, as rank_plans() keeps its.
 BwdCut bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   struct Entry { usp_problem p; int r; BwdCut cut; };   // (`most` follows from the problem)
   static std::mutex mu;

@@ -123,9 +123,10 @@ int launch_layout_a2a_multi(const usp_problem& p, int heads, int dir, int n_tens
 // pointers at the rank's first KV head; 0: dense.
 struct SeqLayoutIO { int rows_per_shard, heads, head0, kv_heads = 0; };
 // row0 > 0: only the rows [row0, Lq) of every batch are merged (and written); the tensors keep their full shapes.
+// part_row0 (with seq): part j holds, of every batch entry, the rows from part_row0[j] on, the first part all that are merged.
 int launch_lse_merge(const void* const* o_parts, const float* const* lse_parts, int n_parts, void* o_out,
                      float* lse_out, int bs, int64_t Lq, int hq, int hs, int part_dtype, int out_dtype,
-                     hipStream_t stream, const SeqLayoutIO* seq = nullptr, int64_t row0 = 0);
+                     hipStream_t stream, const SeqLayoutIO* seq = nullptr, int64_t row0 = 0, const int64_t* part_row0 = nullptr);
 // Optional: the running online-softmax state of a ring that delivers its blocks one call at a time (bf16 instance):
 // attn_fwd_state_bytes() bytes in the kernel's own layout; first: the state is not read (the call starts it);
 // last: the state is not written, the call writes the normalised O and the LSE instead.
@@ -153,7 +154,21 @@ int launch_layout_a2a_vt(const usp_problem& p, int heads, const void* src, void*
 // then hold the rows of the cut tiles only, to be merged over that row range.
 // v_transposed: the V pointers are pieces of blocks in key-tile-transposed layout (each begins at a tile of 64 keys of
 // its block; Lk, the batch stride in rows, then also gives the number of tiles per head of a whole block).
-struct MixedLaunch { void* o; float* lse; int n_split_tiles; bool v_transposed; };
+// listed, n_listed: the launch's items (listed_item(), at most kMaxListedItems), heaviest first, each to run for every head
+// and batch entry; pieces that a tile sees nothing of are not among them.  Without a list every one of the last
+// n_split_tiles tiles has an item per piece.  part_row0: the first row that the piece's partial result holds (null: 0).
+struct MixedLaunch {
+  void* o;
+  float* lse;
+  int n_split_tiles;
+  bool v_transposed;
+  const uint16_t* listed = nullptr;
+  int n_listed = 0;
+  const int64_t* part_row0 = nullptr;
+};
+constexpr int kMaxListedItems = 1024, kListedTileBits = 11, kListedWhole = 31;
+constexpr uint16_t listed_item(int tile, int piece) { return (uint16_t)(piece << kListedTileBits | tile); }   // piece kListedWhole: all of them
+static_assert(kMaxListedItems <= 1 << kListedTileBits && USP_MAX_RING_BLOCKS < kListedWhole, "every tile and piece has a number");
 int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const void* const* v_blocks,
                              const usp_posdesc* kpos_blocks, const int* lk_blocks, int n_blocks, float* const* o_parts,
                              float* const* lse_parts, int bs, int64_t Lq, int64_t Lk, int hq, int hkv, int hs,

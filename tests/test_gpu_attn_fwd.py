@@ -235,3 +235,38 @@ def test_usp_fwd_rejects_bad_arguments(usp):
     bad = usp.problem(1, 1024, 8, 4, 128, 8, 1, True)            # U = 8 > hk = 4
     assert usp.usp_validate(bad) == 3
     assert usp.usp_attn_fwd_workspace_bytes(bad, 1) == 0
+
+
+@pytest.mark.parametrize("bs,L,hq,hkv,hs,R,rank,causal,zigzag", [
+    (1, 4096, 4, 1, 128, 1, 0, True, True),          # the shortest that is cut this way
+    (1, 8192, 4, 4, 64, 1, 0, True, True),           # head size 64, a piece per few tiles
+    (2, 9000, 2, 1, 128, 1, 0, True, False),         # a batch of two: partial results of fewer rows, one behind the other
+    (1, 12500, 4, 1, 128, 1, 0, True, True),         # ragged last tile and last piece
+    (1, 20480, 4, 1, 128, 1, 0, False, True),        # no mask: every piece is seen
+    (1, 16384, 8, 2, 128, 2, 1, True, True),         # ring blocks, a rank whose second run begins inside a 256-row tile or not
+    (1, 8240, 8, 8, 128, 4, 2, True, True),          # runs of 1030 rows: tiles that end with their run
+    (1, 16384, 8, 8, 64, 8, 3, True, True),          # eight blocks, the most that one merge takes this way
+    (2, 16384, 4, 2, 128, 4, 3, True, False),        # contiguous blocks: the last rank sees all, whole and cut tiles
+])
+def test_listed_items_match_the_uncut_launch(usp, bs, L, hq, hkv, hs, R, rank, causal, zigzag):
+    """Lengths at which some query tiles are cut into pieces of the keys that they see, each a listed item with a partial
+    result that holds only the rows that see the piece, against one uncut launch over the same blocks.  Workspace and outputs
+    begin as NaN.  A piece's weights are rounded to bf16 relative to its own maxima: 2^-9 per weight."""
+    p = usp.problem(bs, L, hq, hkv, hs, 1, R, causal, usp.USP_SPLIT_ZIGZAG if zigzag else usp.USP_SPLIT_CONTIG, usp.USP_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(L + hs)
+    q = torch.randn((R, bs, L // R, hq, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k, v = (torch.randn((R, bs, L // R, hkv, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    ws = torch.full((max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)),), 0xFF, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((R, bs, hq, L // R), float("nan"), device="cuda")
+    usp.usp_attn_fwd(p, q, k, v, o, lse, rank, rank + 1, ws)
+    order = [(rank - i) % R for i in range(R)]
+    pos = [usp.usp_local_positions(p, s, 0)[1] for s in range(R)]
+    o1, lse1 = torch.empty_like(q[rank]), torch.empty_like(lse[rank])
+    usp.usp_ring_attn_fwd(q[rank], [k[s] for s in order], [v[s] for s in order], [pos[s] for s in order], o1, lse1, bs, L // R,
+                          L // R, hq, hkv, hs, 0.0, causal, pos[rank], tl.BF16, tl.BF16)
+    torch.cuda.synchronize()
+    assert (lse[rank] - lse1).abs().max().item() <= 1e-4
+    diff = (o[rank].float() - o1.float()).norm(dim=-1) / o1.float().norm(dim=-1)
+    assert diff.max().item() <= 2 ** -6, diff.max().item()      # row by row: 2^-9 of P and of O, four times over
+    assert (o[rank].float() - o1.float()).norm().item() <= 2 ** -8 * o1.float().norm().item()
