@@ -2,7 +2,7 @@
 // Algorithm 1 (all-to-alls, blocks, merge) for a range of virtual ranks in a single launch, for the problems where
 // launches and latency are the time rather than the matrix core, and for fp32 data of every size.
 //
-//   * A workgroup owns 32 query rows of one (rank, batch, head).  Its waves take the visible 32-key tiles of all K/V
+//   * A workgroup owns 32 query rows (16 in small fp32 grids) of one (rank, batch, head).  Its waves take the visible 32-key tiles of all K/V
 //     blocks in turn (tile j of the walk to wave j mod 8), each with an online-softmax state of its own, and combine the
 //     eight states through LDS at the end: the key split and its merge cost two barriers instead of fp32 partials in
 //     memory and a launch.  A rank of 512 rows is 16 workgroups per head here where the 256-row kernel has 2.
@@ -19,7 +19,7 @@
 // V in front of the others' K.  So Q is loaded once and shared through LDS, V is asked for behind the barrier that this
 // needs anyway, and the next tile's K and V while a tile is worked on (a tile of a walk took 3.3 thousand cycles with its
 // loads waited for).  All that does not depend on the workgroup is worked out on the host.  Together: four fp32 ranks of
-// L = 256 9.3 -> 8.6 us, four bf16 ranks of L = 1024 12.1 -> 10.9, one of eight ranks of L = 2048 (32 heads on 8) 18.7 ->
+// L = 256 9.3 -> 8.6 us (6.5 with 16 rows per workgroup, see launch()), four bf16 ranks of L = 1024 12.1 -> 10.9, one of eight ranks of L = 2048 (32 heads on 8) 18.7 ->
 // 16.6, all eight 90.6 -> 79.0, fp32 at L = 2048 (eight heads of size 64, two ranks a ring) 47.1 -> 43.0.
 // Large problems: every workgroup reads all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the
 // 256-row kernel.  Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at
@@ -34,7 +34,7 @@ namespace {
 
 using namespace dev;
 
-constexpr int kWaves = 8, kRows = 32, kTile = 32;
+constexpr int kWaves = 8, kTile = 32;
 
 // The caller's tensors lie on an element's alignment, no more is claimed (this chip's wide accesses take any address).
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
@@ -134,9 +134,45 @@ struct Tile {
 };
 
 // ---- operands of one data type: the fragments of Q and of a 32-key tile, and the two products -------------------
-template <typename T, int HS> struct Operands;
+// What a 32-row workgroup's lanes hold: lane = row l32 (column of S^T and O^T); score e is key first_key() + key_step(e).
+struct Rows32 {
+  static constexpr int kRows = 32, kScores = 16;
+  typedef f32x16 Scores;
+  typedef f32x16 Acc;
+  static __device__ int row_of(int lane) { return lane & 31; }
+  static __device__ int first_key(int lane) { return 4 * (lane >> 5); }
+  static constexpr __device__ int key_step(int e) { return 8 * (e >> 2) + (e & 3); }
+  static __device__ float max_of_row(float x) { return both_halves_max(x); }
+  static __device__ float sum_of_row(float x) { return both_halves_sum(x); }
+};
+// ... and a 16-row one's (fp32): four lanes to a row, 16 lanes apart.
+struct Rows16 {
+  static constexpr int kRows = 16, kScores = 8;
+  typedef float Scores __attribute__((ext_vector_type(8)));
+  typedef f32x4 Acc;
+  static __device__ int row_of(int lane) { return lane & 15; }
+  static __device__ int first_key(int lane) { return 4 * (lane >> 4); }
+  static constexpr __device__ int key_step(int e) { return 16 * (e >> 2) + (e & 3); }
+  static __device__ u32x2 other(float x) {   // x of this quarter and of the one 16 lanes off
+    const uint32_t xi = __builtin_bit_cast(uint32_t, x);
+    return __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
+  }
+  static __device__ float max_of_row(float x) {
+    const u32x2 r = other(x);
+    const uint32_t a = r[0], b = r[1];
+    return both_halves_max(fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)));
+  }
+  static __device__ float sum_of_row(float x) {
+    const u32x2 r = other(x);
+    const uint32_t a = r[0], b = r[1];
+    return both_halves_sum(__builtin_bit_cast(float, a) + __builtin_bit_cast(float, b));
+  }
+};
 
-template <int HS> struct Operands<__bf16, HS> {
+template <typename T, int HS, int ROWS> struct Operands;
+
+template <int HS> struct Operands<__bf16, HS, 32> : Rows32 {
+  static constexpr int kBlocks = HS / 32;   // accumulators
   static constexpr int KSTEPS = HS / 16, DB = HS / 32, CPR = HS / 8;
   static constexpr int kWavesPerSimd = HS == 64 ? 4 : 2;   // head size 64: two workgroups to a CU
   // Q fragments: kept in registers, or, where four waves to a SIMD leave none to spare, read from LDS for every tile.
@@ -214,11 +250,12 @@ template <int HS> struct Operands<__bf16, HS> {
     return f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
   }
   static constexpr int kGroups = DB * 4;   // groups of four dims per lane
-  static __device__ int group_dim(int gi, int hl) { return dim4(gi / 4, gi % 4, hl); }
+  static __device__ int group_dim(int gi, int lane) { return dim4(gi / 4, gi % 4, lane >> 5); }
   static __device__ f32x4 group(const f32x16 (&o)[DB], int gi) { return out4(o, gi / 4, gi % 4); }
 };
 
-template <int HS> struct Operands<float, HS> {
+template <int HS> struct Operands<float, HS, 32> : Rows32 {
+  static constexpr int kBlocks = HS / 32;
   static constexpr int DB = HS / 32, KC = HS / 8, CPR = HS / 4;
   static constexpr int kWavesPerSimd = 2;
   // (Head size 128: Q, K, V and O are all the registers.  With Q read from LDS for every tile there is room for the next K, and
@@ -280,8 +317,8 @@ template <int HS> struct Operands<float, HS> {
   }
   // register i of block db is head dim DB (row i of the product) + db
   static constexpr int kGroups = DB * 4;
-  static __device__ int group_dim(int gi, int hl) {
-    const int r = DB == 4 ? gi : 2 * gi;                 // the product rows of this group: one (DB = 4) or two (DB = 2)
+  static __device__ int group_dim(int gi, int lane) {
+    const int hl = lane >> 5, r = DB == 4 ? gi : 2 * gi;                 // the product rows of this group: one (DB = 4) or two (DB = 2)
     return DB * (8 * (r >> 2) + 4 * hl + (r & 3));
   }
   static __device__ f32x4 group(const f32x16 (&o)[DB], int gi) {
@@ -290,21 +327,92 @@ template <int HS> struct Operands<float, HS> {
   }
 };
 
-template <typename T, int HS>
+// fp32, 16 rows per workgroup, v_mfma_f32_16x16x4_f32: for grids that leave half the chip idle, and where the matrix core at
+// fp32 rate is the longest part of a workgroup's time (rule in launch()).  Four k indices: the lane quarters.
+template <int HS> struct Operands<float, HS, 16> : Rows16 {
+  static constexpr int NB = HS / 16, VH = NB / 4, KC = HS / 16, CPR = HS / 4;
+  static constexpr int kBlocks = NB;
+  static constexpr int kWavesPerSimd = 2;
+  static constexpr bool kAhead = true;
+  static constexpr int KSTR = HS * 4 + 16, QSTR = KSTR;
+  static constexpr int kLdsPerWave = kTile * KSTR;
+  static constexpr int TL = kTile * CPR / 64;
+  f32x4 q[KC];           // dims 16 c + 4 (lane quarter) .. + 3
+  f32x4 k[TL];
+  f32x4 v[VH][8];        // V of the key of score e, dims NB (lane & 15) + 4 half .. + 3
+
+  __device__ void read_q(const char* q_lds, int lane) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(q_lds + (lane & 15) * QSTR + 64 * c + 16 * (lane >> 4));
+  }
+  __device__ void load_k(const void* tensor, const Tile& t, int lane) {
+    t.load(k, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  }
+  __device__ void load_v(const void* tensor, const Tile& t, int lane) {
+#pragma unroll
+    for (int half = 0; half < VH; ++half)
+      t.load(v[half], tensor, first_key(lane), [](int e) { return key_step(e); }, (lane & 15) * (NB * 4) + 16 * half);
+  }
+  __device__ void stash_k(char* lds, int lane) {
+#pragma unroll
+    for (int c = 0; c < TL; ++c) {
+      const int ch = lane + 64 * c;
+      *(f32x4*)(lds + (ch / CPR) * KSTR + (ch % CPR) * 16) = k[c];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ Scores scores(char* lds, const char*, int lane) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;   // keys 0 .. 15 and 16 .. 31
+    const char* row = lds + (lane & 15) * KSTR + 16 * (lane >> 4);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const f32x4 k0 = *(const f32x4*)(row + 64 * c), k1 = *(const f32x4*)(row + 16 * KSTR + 64 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a0 = k0[e], a1 = k1[e], qa = q[c][e];
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, qa, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, qa, s1, 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    return __builtin_shufflevector(s0, s1, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+  __device__ void accumulate(const Scores& p, Acc (&o)[NB], const char*, int) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float pe = p[e];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float va = v[nb / 4][e][nb % 4];
+        o[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(va, pe, o[nb], 0, 0, 0);
+      }
+    }
+  }
+  // register i of block nb is head dim NB (4 (lane quarter) + i) + nb
+  static constexpr int kGroups = NB;
+  static __device__ int group_dim(int gi, int lane) { return NB * (4 * (lane >> 4) + gi / VH) + 4 * (gi % VH); }
+  static __device__ f32x4 group(const Acc (&o)[NB], int gi) {
+    const int i = gi / VH, b = 4 * (gi % VH);
+    return f32x4{o[b][i], o[b + 1][i], o[b + 2][i], o[b + 3][i]};
+  }
+};
+
+template <typename T, int HS, int ROWS>
 constexpr size_t lds_bytes() {
-  const size_t states = (size_t)kWaves * kRows * (HS + 4) * sizeof(float);
-  const size_t tiles = (size_t)kWaves * Operands<T, HS>::kLdsPerWave + kRows * Operands<T, HS>::QSTR;
+  const size_t states = (size_t)kWaves * ROWS * (HS + 4) * sizeof(float);
+  const size_t tiles = (size_t)kWaves * Operands<T, HS, ROWS>::kLdsPerWave + ROWS * Operands<T, HS, ROWS>::QSTR;
   return (states > tiles ? states : tiles);
 }
 
-template <typename T, int HS, typename OutT, bool STATE = false>
-__global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS>::kWavesPerSimd, Operands<T, HS>::kWavesPerSimd)))
+template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32>
+__global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS, ROWS>::kWavesPerSimd, Operands<T, HS, ROWS>::kWavesPerSimd)))
 void wave_split_attn_fwd(const WsArgs a) {
-  using Op = Operands<T, HS>;
-  constexpr int DB = HS / 32, OSTR = HS + 4;   // floats between the rows of a state in LDS: an odd number of 16 B chunks
+  using Op = Operands<T, HS, ROWS>;
+  static_assert(!STATE || ROWS == 32, "the state's records are of 32 rows");
+  constexpr int NB = Op::kBlocks, kRows = ROWS, OSTR = HS + 4;   // floats between the rows of a state in LDS: an odd number of 16 B chunks
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows], inv_s[kRows], first_s[2][kRows];
-  const int lane = threadIdx.x & 63, l32 = lane & 31, hl = lane >> 5;
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
   // KV group fastest (neighbouring workgroups go to different XCDs: one XCD's L2 then holds few KV heads), then head,
@@ -342,11 +450,11 @@ void wave_split_attn_fwd(const WsArgs a) {
     }
   }
 
-  f32x16 o[DB];
+  typename Op::Acc o[NB];
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+    for (int i = 0; i < (int)(sizeof(o[0]) / 4); ++i) o[nb][i] = 0.f;
   float m = -INFINITY, l = 0.f;
 
   // The walk over the blocks' visible tiles, this wave's every eighth.  (Algorithm 1 step 5: step i visits block (r - i) mod R.)
@@ -427,27 +535,27 @@ void wave_split_attn_fwd(const WsArgs a) {
     more = next_tile();
     tile = tile_now(more);
     if (Op::kAhead) op.load_k(a.k, tile, lane);
-    f32x16 s = op.scores(lds, q_lds, lane);
+    typename Op::Scores s = op.scores(lds, q_lds, lane);
     if (sizeof(T) == 2) op.load_v(a.v, tile, lane);   // (V has gone to LDS)
     if (need_mask) {
-      // key key0 + 4 hl + c (c = 0 .. 27, known at compile time) is visible if c does not exceed this row's bound in the run
+      // key key0 + first_key() + c (c known at compile time) is visible if c does not exceed this row's bound in the run
       // that the key belongs to; worked out here, from a lane index the compiler cannot see through, and not kept
       int t = lane;
       asm volatile("" : "+v"(t));
-      const int first = key0 + 4 * (t >> 5);
-      const int qp = a.causal ? pos_of(qpos, min(row0 + (t & 31), a.Lq - 1)) : kNever;
+      const int first = key0 + Op::first_key(t);
+      const int qp = a.causal ? pos_of(qpos, min(row0 + Op::row_of(t), a.Lq - 1)) : kNever;
       const int in_run0 = a.kpos.len0 - first;
       const int bound0 = min(qp - start0, key_end - 1) - first, bound1 = min(qp - start1, key_end - 1 - a.kpos.len0) + in_run0;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int c = 8 * (e >> 2) + (e & 3);
+      for (int e = 0; e < Op::kScores; ++e) {
+        const int c = Op::key_step(e);
         s[e] = c <= (c < in_run0 ? bound0 : bound1) ? s[e] : -INFINITY;
       }
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
-    mx = both_halves_max(mx);
+    for (int e = 0; e < Op::kScores; ++e) mx = fmaxf(mx, s[e]);
+    mx = Op::max_of_row(mx);
     if (!shared_first) {
       int t = lane;   // places in LDS derived here, from a lane index the compiler cannot see through: kept, they are spilled
       asm volatile("" : "+v"(t));
@@ -465,14 +573,14 @@ void wave_split_attn_fwd(const WsArgs a) {
       const float alpha = __builtin_amdgcn_exp2f(m * a.scale_log2 - (m_new == -INFINITY ? 0.f : m_new * a.scale_log2));   // m = -inf -> 0
       l *= alpha;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+        for (int e = 0; e < (int)(sizeof(o[0]) / 4); ++e) o[nb][e] *= alpha;
       m = m_new;
     }
     const float mc = m == -INFINITY ? 0.f : m * a.scale_log2;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
+    for (int e = 0; e < Op::kScores; ++e) {
       s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.scale_log2, -mc));
       l += s[e];
     }
@@ -487,7 +595,7 @@ void wave_split_attn_fwd(const WsArgs a) {
   // ---- the waves' states are combined: common maximum, scaled outputs side by side in LDS, summed row by row
   int end_lane = lane;   // (a lane index of its own for the epilogue: what derives from it is not kept across the loop)
   asm volatile("" : "+v"(end_lane));
-  constexpr int PER_ROW = HS / 4, ROWS_PER_PASS = kWaves * 64 / PER_ROW, PASSES = kRows / ROWS_PER_PASS;
+  constexpr int PER_ROW = HS / 4, ROWS_PER_PASS = kWaves * 64 / PER_ROW, PASSES = (kRows + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
   // where the record holds dims 4 c .. 4 c + 3 of row rr: this thread's part of the last step
   auto rec_at = [&](int rr, int c) { return rec + ((c >> 1) * 64 + (c & 1) * 32 + rr) * 4; };
   f32x4 o_state[STATE ? PASSES : 1];
@@ -498,30 +606,31 @@ void wave_split_attn_fwd(const WsArgs a) {
         o_state[pass] = *(const f32x4*)rec_at(pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, (int)threadIdx.x % PER_ROW);
     }
   }
-  l = both_halves_sum(l);
-  if (end_lane < 32) {
-    m_s[wave][(end_lane & 31)] = m;
-    l_s[wave][(end_lane & 31)] = l;
+  const int end_row = Op::row_of(end_lane);
+  l = Op::sum_of_row(l);
+  if (end_lane < kRows) {
+    m_s[wave][end_row] = m;
+    l_s[wave][end_row] = l;
   }
   __syncthreads();
   // (every loop over the waves is unrolled, all its LDS reads in flight at once: a wave that had no tile adds zeros)
   float mw[kWaves], m_all = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][(end_lane & 31)];
+  for (int j = 0; j < kWaves; ++j) mw[j] = m_s[j][end_row];
 #pragma unroll
   for (int j = 0; j < kWaves; ++j) m_all = fmaxf(m_all, mw[j]);
   if constexpr (STATE) m_all = fmaxf(m_all, m_state_s[end_lane & 31]);
   const float mc = m_all == -INFINITY ? 0.f : m_all * a.scale_log2;
   {
     const float f = __builtin_amdgcn_exp2f(m * a.scale_log2 - mc);
-    float* dst = (float*)smem + (wave * kRows + (end_lane & 31)) * OSTR;
+    float* dst = (float*)smem + (wave * kRows + end_row) * OSTR;
 #pragma unroll
-    for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, end_lane >> 5)) = Op::group(o, gi) * f;
+    for (int gi = 0; gi < Op::kGroups; ++gi) *(f32x4*)(dst + Op::group_dim(gi, end_lane)) = Op::group(o, gi) * f;
   }
-  if (wave == 0 && (STATE || end_lane < 32)) {
+  if (wave == 0 && (STATE || end_lane < kRows)) {
     float tot = 0.f;
 #pragma unroll
-    for (int j = 0; j < kWaves; ++j) tot += l_s[j][(end_lane & 31)] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
+    for (int j = 0; j < kWaves; ++j) tot += l_s[j][end_row] * __builtin_amdgcn_exp2f(mw[j] * a.scale_log2 - mc);
     if constexpr (STATE) {
       float f = 0.f;
       float* const lane_rec = rec + HS * kRows;   // m of 64 lanes, l of 64 lanes: a row's l is the sum of its two
@@ -536,15 +645,16 @@ void wave_split_attn_fwd(const WsArgs a) {
       }
     }
     if (!STATE || a.state_last) {
-      inv_s[(end_lane & 31)] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
-      if (row0 + (end_lane & 31) < a.Lq)
-        a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + (end_lane & 31)] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
+      inv_s[end_row] = tot > 0.f ? 1.f / tot : 0.f;   // a row that saw no key: O = 0, LSE = -inf
+      if (row0 + end_row < a.Lq)
+        a.lse[(((int64_t)rank * a.bs + b) * a.hq + h) * a.Lq + row0 + end_row] = tot > 0.f ? m_all * a.scale + logf(tot) : -INFINITY;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
     const int rr = pass * ROWS_PER_PASS + (int)threadIdx.x / PER_ROW, c = (int)threadIdx.x % PER_ROW;
+    if (kRows % ROWS_PER_PASS && rr >= kRows) break;
     const float* src = (const float*)smem + rr * OSTR + 4 * c;
     f32x4 sum = *(const f32x4*)src;
 #pragma unroll
@@ -565,10 +675,10 @@ void wave_split_attn_fwd(const WsArgs a) {
   }
 }
 
-template <typename T, int HS, typename OutT, bool STATE = false>
+template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32>
 int launch_typed(WsArgs a, int64_t grid, hipStream_t stream) {
-  constexpr size_t lds = lds_bytes<T, HS>();
-  auto kern = wave_split_attn_fwd<T, HS, OutT, STATE>;
+  constexpr size_t lds = lds_bytes<T, HS, ROWS>();
+  auto kern = wave_split_attn_fwd<T, HS, OutT, STATE, ROWS>;
   static LdsLimitRaised lds_limit;   // per kernel instance
   if (!raise_dynamic_lds_limit((const void*)kern, lds, lds_limit)) return USP_ERR_LAUNCH;
   const int64_t at_once = max_workgroups(kWaves * 64);
@@ -585,7 +695,14 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
   a.g = a.hq / a.hkv;
   a.by_hkv = fast_div(a.hkv); a.by_bs = fast_div(a.bs); a.by_ranks = fast_div(a.n_ranks);
   a.by_g = fast_div(a.g); a.by_U = fast_div(a.U);
-  a.n_qtiles = (a.Lq + kRows - 1) / kRows;
+  // fp32: 16 rows per workgroup where workgroups of 32 leave half of the CUs idle, or, under a causal mask, hold them with
+  // items of very different lengths.  Measured, 32 and 16 rows, us (in brackets workgroups of 32): four ranks of L = 256, no
+  // mask (32) 8.6, 6.5; L = 512, head size 128 (64) 21, 13.5; L = 1024, no mask, head size 128 (128) 36.6, 22.6; causal, L =
+  // 1024, head size 64 (256) 21.2, 17.5, head size 128 (256) 37.1, 36.1; no mask, L = 2048, head size 128 (256) 68.7, 75.7;
+  // causal, L = 2048, head size 64 (512) 43.0, 50.0.
+  const int64_t heads = (int64_t)a.hq * a.bs * a.n_ranks;
+  const int rows = in_dtype == USP_FP32 && (a.Lq + 31) / 32 * heads <= (a.causal ? kPlanCUs : kPlanCUs / 2) ? 16 : 32;
+  a.n_qtiles = (a.Lq + rows - 1) / rows;
   auto strides = [&](int heads, const FastDiv& n, uint64_t& ring, uint64_t& run, uint64_t& jump) {
     run = (uint64_t)n.d * heads * hs;
     ring = run * a.bs * a.U;
@@ -598,11 +715,15 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
   a.tiles.by_tiles = fast_div((n_k.d + kTile - 1) / kTile);
   if (!a.causal) a.kpos = BlockPositions{0, 0, a.Lk, 0, 0, 0};
   a.scale_log2 = a.scale * 1.4426950408889634f;
-  const int64_t grid = (int64_t)a.n_qtiles * a.hq * a.bs * a.n_ranks;
+  const int64_t grid = (int64_t)a.n_qtiles * heads;
   if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
   if (a.state) {   // bf16 data
     if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<__bf16, 128, float, true>(a, grid, stream) : launch_typed<__bf16, 128, __bf16, true>(a, grid, stream);
     return o_dtype == USP_FP32 ? launch_typed<__bf16, 64, float, true>(a, grid, stream) : launch_typed<__bf16, 64, __bf16, true>(a, grid, stream);
+  }
+  if (in_dtype == USP_FP32 && rows == 16) {
+    if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<float, 128, float, false, 16>(a, grid, stream) : launch_typed<float, 128, __bf16, false, 16>(a, grid, stream);
+    return o_dtype == USP_FP32 ? launch_typed<float, 64, float, false, 16>(a, grid, stream) : launch_typed<float, 64, __bf16, false, 16>(a, grid, stream);
   }
   if (in_dtype == USP_FP32) {
     if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<float, 128, float>(a, grid, stream) : launch_typed<float, 128, __bf16>(a, grid, stream);

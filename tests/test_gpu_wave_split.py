@@ -57,6 +57,25 @@ def test_tiles_end_with_their_shard(usp, dtype, bs, L, hc, hk, hs, U, R, causal,
         assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
 
 
+@pytest.mark.parametrize("hs", [64, 128])
+@pytest.mark.parametrize("bs,L,hc,hk,U,R,causal,zigzag", [
+    (1, 6, 2, 1, 1, 1, True, True),                 # fewer rows than a workgroup's 16
+    (1, 2048, 4, 4, 1, 1, True, True),              # 256 workgroups of 32 rows: the last size with 16 under a mask
+    (1, 2080, 4, 4, 1, 1, True, True),              # ... and the first with 32
+    (1, 1024, 4, 2, 1, 1, False, True),             # 128: the last with 16 without a mask
+    (1, 1048, 4, 2, 1, 1, False, True),             # ... and the first with 32 (ragged: 24 rows in the last)
+    (2, 204, 4, 2, 2, 1, True, False),              # shards of 102 rows, row tiles that cross from one into the next
+    (1, 536, 2, 2, 1, 4, True, True),               # runs of 67 positions inside a 16-row tile, rows past the last
+])
+def test_fp32_rows_of_a_workgroup(usp, bs, L, hc, hk, hs, U, R, causal, zigzag):
+    """Both sides of the line between 16 and 32 rows per workgroup, and the remainders of 16 rows."""
+    prob = tl.Problem(990 + L, bs, L, hc, hk, hs, U, R, causal, zigzag, tl.FP32)
+    o, lse = _run_usp_fwd(usp, prob)
+    ref_o, tol = _check_against_reference(prob, o, lse)
+    for rank in range(prob.N):
+        assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
+
+
 def test_a_rank_range_writes_only_its_slices(usp):
     """bs = 2, ranks 1 and 2 of four: their head slices, everything else as it was; the other ranks' LSE too."""
     prob = tl.Problem(951, 2, 160, 4, 2, 64, 2, 2, True, True, tl.FP32)
