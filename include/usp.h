@@ -208,10 +208,10 @@ int usp_ring_attn_fwd_partials(const void* q, const void* const* k_blocks, const
  * usp_ring_attn_fwd (all blocks are resident on the one GPU); with more blocks one usp_block_attn_fwd per ring step
  * with fp32 partials, then usp_lse_merge.  fp32 data, and the shortest bf16 sequences, run all ranks of the range in one
  * launch that reads and writes the shards directly (the workspace is then checked, but used only where o or lse lies over
- * an input).  Short sequences (fewer query tiles x heads than keep 256 CUs busy for as long as the last tile takes) run the
- * single launch of usp_ring_attn_fwd_partials over two to eight parts of the keys, then usp_lse_merge; a little longer
- * (more than one work item per CU, the heaviest still longer than a CU's share) only the last query tiles of a causal rank
- * are cut so, in the same launch as the whole ones, and the merge covers their rows; the workspace query knows.
+ * an input).  Short sequences (fewer query tiles x heads than keep 256 CUs busy for as long as the last tile takes), and those
+ * a little longer (more than one work item per CU, the heaviest still longer than a CU's share), run one launch in which the
+ * last query tiles are cut into items over two to eight parts of the keys that they see, beside whole items for the other
+ * tiles, then the merge of the cut rows; the workspace query knows.
  *   q, o: seq layout with hc heads; k, v: seq layout with hk heads (ALL N shards must be
  *   present: the ring reads the other ring ranks' K/V where hardware would receive them);
  *   lse: [N][bs][hc/U][L/R] float, written for the ranks in range.
