@@ -196,6 +196,25 @@ inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
   return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
 }
 
+// Whether tiles cross from one shard of n rows into the next.  By shards there are more of them, and emptier ones: with eight
+// shards of 34 rows 16 for 9.  At head size 128 and 32 rows per workgroup fewer tiles are always the faster walk; elsewhere where
+// they are so many fewer that it makes up for the rows' offsets: in rounds of the eight waves, and half in tiles, for the waves
+// share what loads.  (In 32 bits: the offset of a tile's last row, jumps included.)  Measured, by shards and crossing, us, a batch
+// of two: 32/8 heads, one rank of U 8 x R 4, shards of 34 rows 18.7, 12.2, of 24 rows 12.3, 9.9; U 4 x R 2, 16/8 heads, all ranks,
+// shards of 130 43.3, 40.8, of 330 150.7, 147.0; fp32, eight heads, U 8 x R 2, all ranks, shards of 34 72.6, 51.4, of 520 4637,
+// 4382; head size 64, U 8 x R 4, shards of 34 116, 72; U 2 x R 2, shards of 66 8.15, 8.55, of 130 13.1, 13.6; fp32, U 2, L = 3852
+// 533, 575; fp32, 16 rows per workgroup, U 2 x R 2, shards of 34 9.7, 10.2, of 130 47.4, 51.3.
+constexpr int kWaveSplitWaves = 8, kWaveSplitTile = 32;
+enum Cross { kNoCross, kOneCross, kAnyCross };   // kOneCross: a tile crosses once at most
+inline Cross wave_split_crossing(int64_t n, int U, int R, int bs, int64_t row_bytes, bool always) {
+  constexpr int T = kWaveSplitTile, W = kWaveSplitWaves;
+  if (bs == 1 || U == 1 || n % T == 0 || (T + (n + T) * (bs - 1)) * row_bytes >= (int64_t)1 << 31) return kNoCross;
+  auto cost = [](int64_t tiles) { return 2.0 + (double)((tiles + W - 1) / W) + (double)tiles / W; };
+  const int64_t by_shard = (int64_t)R * U * ((n + T - 1) / T), crossing = R * ((U * n + T - 1) / T);
+  if (cost(by_shard) <= (always ? 1.0 : 1.07) * cost(crossing)) return kNoCross;
+  return n < T ? kAnyCross : kOneCross;
+}
+
 // One tensor of the launch that prepares a backward: rows [r0, r0 + n_rings) x columns [c0, c0 + n_cols) of ring blocks of the
 // sequence layout [N][bs][L/U][heads][hs].  dst: their copy in [block][bs][head][row][hs]; o (src is dO): D_i of their rows,
 // [block][bs][head][row] fp32 at delta.

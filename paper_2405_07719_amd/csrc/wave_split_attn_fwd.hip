@@ -34,7 +34,7 @@ namespace {
 
 using namespace dev;
 
-constexpr int kWaves = 8, kTile = 32;
+constexpr int kWaves = kWaveSplitWaves, kTile = kWaveSplitTile;
 
 // The caller's tensors lie on an element's alignment, no more is claimed (this chip's wide accesses take any address).
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
@@ -49,14 +49,15 @@ struct BlockPositions {
 };
 
 // The keys of a ring block (one batch entry) lie in the shards [U][bs][n][heads][hs], row j at j rows and (j / n) jumps from
-// the block's first.  Tiles are numbered shard by shard and none crosses from one shard into the next, so that every tile is
-// read through buffer descriptors (K, V) whose extent ends with its last row: rows past it read as zeros.  The row within the
-// tile is part of the vector offset, which the descriptor's range check covers (the scalar offset it does not).  With a
-// second path for tiles that cross, and a branch round the loads where there is no next tile, every wait for one tile's loads
-// was a wait for all that were in flight.  With a batch of one a block is one run of n = Lk rows.
+// the block's first.  Every tile is read through buffer descriptors (K, V) whose extent ends with its last row: rows past it
+// read as zeros.  The row within the tile is part of the vector offset, which the descriptor's range check covers (the scalar
+// offset it does not).  With a second path for tiles that cross from one shard into the next, and a branch round the loads
+// where there is no next tile, every wait for one tile's loads was a wait for all that were in flight.  So either tiles are
+// numbered shard by shard and none crosses, or, in instances of their own, all may: see wave_split_crossing().  With a batch
+// of one a block is one run of n = Lk rows.
 struct KeyTiles {
   FastDiv by_n, by_tiles;      // rows of a shard; tiles of a shard
-  int one;                     // a single run of rows
+  int one;                     // tiles are numbered through: a single run of rows, or tiles that cross
   __device__ int upto(int keys) const {   // tiles that hold the first `keys` keys
     if (one) return (unsigned)(keys + kTile - 1) / kTile;
     const int shard = by_n.split(keys);
@@ -100,33 +101,59 @@ struct WsArgs {
 
 __device__ inline uint64_t times(int n, uint64_t x) { return (uint64_t)(uint32_t)n * x; }
 
-struct Tile {
+template <int CROSS> struct Tile {
   uint64_t at;          // bytes from the tensor's begin to the tile's first row
   int row_bytes, extent;
   int key0, end;        // its keys
+  int cross, jump;      // kOneCross: rows from `cross` on lie `jump` bytes further on
+  int row_at;           // kAnyCross: bytes from there to row lane % 32, handed from lane to lane where the rows are loaded
   // (!exists: no tile; its loads find nothing in range and give zeros)
-  __device__ Tile(const KeyTiles& tiles, bool exists, int t, int Lk, uint64_t block, uint64_t jump, int row_bytes_, int row_len) : row_bytes(row_bytes_) {
+  __device__ Tile(const KeyTiles& tiles, bool exists, int t, int Lk, uint64_t block, uint64_t jump_, int row_bytes_, int row_len, int lane) : row_bytes(row_bytes_) {
     key0 = t * kTile;
     end = min(key0 + kTile, Lk);
     at = block;
+    if constexpr (CROSS != kNoCross) {
+      int in_shard = key0;
+      at += times(tiles.by_n.split(in_shard), jump_) + (uint64_t)(uint32_t)key0 * (uint32_t)row_bytes;
+      jump = (int)jump_;
+      cross = (int)tiles.by_n.d - in_shard;
+      const int last = end - 1 - key0;
+      extent = last * row_bytes + row_len;
+      if constexpr (CROSS == kOneCross) {
+        extent += last >= cross ? jump : 0;
+      } else {
+        extent += tiles.by_n.div(in_shard + last) * jump;
+        row_at = (lane % kTile) * row_bytes + tiles.by_n.div(in_shard + lane % kTile) * jump;
+      }
+      extent = exists ? extent : 0;
+      return;
+    }
     if (!tiles.one) {
       const int shard = tiles.by_tiles.split(t);
       key0 = shard * (int)tiles.by_n.d + t * kTile;
       end = min(key0 + kTile, (shard + 1) * (int)tiles.by_n.d);
-      at += times(shard, jump);
+      at += times(shard, jump_);
     }
     at += (uint64_t)(uint32_t)key0 * (uint32_t)row_bytes;
     extent = exists ? (end - 1 - key0) * row_bytes + row_len : 0;
   }
-  // x[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i)
-  template <typename V, int N, typename Step>
+  // x[i] = 16 bytes (8: V of the fp32 kernel at head size 64) at byte `col` of row lane_row + step(i).  kApart: tiles that do
+  // not cross have their loads to themselves, for instances that wait for all of a tile's loads anyway.
+  template <bool kApart = false, typename V, int N, typename Step>
   __device__ void load(V (&x)[N], const void* tensor, int lane_row, Step step, int col) const {
+    if (kApart && CROSS == kOneCross && cross >= kTile) load_from<kNoCross>(x, tensor, lane_row, step, col);
+    else load_from<CROSS>(x, tensor, lane_row, step, col);
+  }
+  template <int HOW, typename V, int N, typename Step>
+  __device__ void load_from(V (&x)[N], const void* tensor, int lane_row, Step step, int col) const {
     static_assert(sizeof(V) == 16 || sizeof(V) == 8, "");
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((char*)tensor + at, 0, extent, kRawBufferFlags);
     const int voff0 = lane_row * row_bytes + col;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int voff = voff0 + step(i) * row_bytes;
+      int voff = voff0 + step(i) * row_bytes;
+      if constexpr (HOW == kOneCross) voff += lane_row >= cross - step(i) ? jump : 0;
+      if constexpr (HOW == kAnyCross) voff = __builtin_amdgcn_ds_bpermute((lane_row + step(i)) * 4, row_at) + col;
       if constexpr (sizeof(V) == 16) x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 0, 0));
       else x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, 0, 0));
     }
@@ -169,9 +196,9 @@ struct Rows16 {
   }
 };
 
-template <typename T, int HS, int ROWS> struct Operands;
+template <typename T, int HS, int ROWS, int CROSS> struct Operands;
 
-template <int HS> struct Operands<__bf16, HS, 32> : Rows32 {
+template <int HS, int CROSS> struct Operands<__bf16, HS, 32, CROSS> : Rows32 {
   static constexpr int kBlocks = HS / 32;   // accumulators
   static constexpr int KSTEPS = HS / 16, DB = HS / 32, CPR = HS / 8;
   static constexpr int kWavesPerSimd = HS == 64 ? 4 : 2;   // head size 64: two workgroups to a CU
@@ -195,7 +222,7 @@ template <int HS> struct Operands<__bf16, HS, 32> : Rows32 {
       for (int ks = 0; ks < KSTEPS; ++ks) q[ks] = q_at(q_lds, lane, ks);
     }
   }
-  __device__ static void load_rows(u32x4 (&t)[TL], const void* tensor, const Tile& tile, int lane) {
+  template <typename Tile> __device__ static void load_rows(u32x4 (&t)[TL], const void* tensor, const Tile& tile, int lane) {
     tile.load(t, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
   template <int STR> __device__ static void stash_rows(char* lds, const u32x4 (&t)[TL], int lane) {
@@ -206,8 +233,8 @@ template <int HS> struct Operands<__bf16, HS, 32> : Rows32 {
     }
     __builtin_amdgcn_wave_barrier();   // this wave's own LDS accesses stay in this order
   }
-  __device__ void load_k(const void* tensor, const Tile& t, int lane) { load_rows(k, tensor, t, lane); }
-  __device__ void load_v(const void* tensor, const Tile& t, int lane) { load_rows(v, tensor, t, lane); }
+  template <typename Tile> __device__ void load_k(const void* tensor, const Tile& t, int lane) { load_rows(k, tensor, t, lane); }
+  template <typename Tile> __device__ void load_v(const void* tensor, const Tile& t, int lane) { load_rows(v, tensor, t, lane); }
   __device__ void stash_k(char* lds, int lane) { stash_rows<KSTR>(lds, k, lane); }
   // S^T = K Q^T; leaves V in the LDS tile
   __device__ f32x16 scores(char* lds, const char* q_lds, int lane) {
@@ -254,7 +281,7 @@ template <int HS> struct Operands<__bf16, HS, 32> : Rows32 {
   static __device__ f32x4 group(const f32x16 (&o)[DB], int gi) { return out4(o, gi / 4, gi % 4); }
 };
 
-template <int HS> struct Operands<float, HS, 32> : Rows32 {
+template <int HS, int CROSS> struct Operands<float, HS, 32, CROSS> : Rows32 {
   static constexpr int kBlocks = HS / 32;
   static constexpr int DB = HS / 32, KC = HS / 8, CPR = HS / 4;
   static constexpr int kWavesPerSimd = 2;
@@ -264,20 +291,25 @@ template <int HS> struct Operands<float, HS, 32> : Rows32 {
   static constexpr int KSTR = HS * 4 + 16, QSTR = KSTR;  // an odd number of 16-byte chunks
   static constexpr int kLdsPerWave = kTile * KSTR;
   static constexpr int TL = kTile * CPR / 64;
+  // (... and where the rows' offsets want registers, most of Q is read from LDS for every tile.)
+  static constexpr int kQInRegs = HS == 128 && CROSS == kAnyCross ? KC - 10 : KC;
   typedef float vrow __attribute__((ext_vector_type(DB)));
-  f32x4 q[KC];           // dims 8 c + 4 (lane half) .. + 3: the product's two k indices are the lane halves
+  f32x4 q[kQInRegs];     // dims 8 c + 4 (lane half) .. + 3: the product's two k indices are the lane halves
   f32x4 k[TL];           // a tile's K rows on their way to LDS
   vrow v[16];            // V of the key that score register i of this lane half holds, dims DB l32 .. + DB - 1
 
+  __device__ static f32x4 q_at(const char* q_lds, int lane, int c) {
+    return *(const f32x4*)(q_lds + (lane & 31) * QSTR + 32 * c + 16 * (lane >> 5));
+  }
   __device__ void read_q(const char* q_lds, int lane) {
 #pragma unroll
-    for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(q_lds + (lane & 31) * QSTR + 32 * c + 16 * (lane >> 5));
+    for (int c = 0; c < kQInRegs; ++c) q[c] = q_at(q_lds, lane, c);
   }
-  __device__ void load_k(const void* tensor, const Tile& t, int lane) {
-    t.load(k, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
+  template <typename Tile> __device__ void load_k(const void* tensor, const Tile& t, int lane) {
+    t.template load<!kAhead>(k, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
-  __device__ void load_v(const void* tensor, const Tile& t, int lane) {
-    t.load(v, tensor, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
+  template <typename Tile> __device__ void load_v(const void* tensor, const Tile& t, int lane) {
+    t.template load<!kAhead>(v, tensor, 4 * (lane >> 5), [](int i) { return 8 * (i >> 2) + (i & 3); }, (lane & 31) * (DB * 4));
   }
   __device__ void stash_k(char* lds, int lane) {
 #pragma unroll
@@ -287,17 +319,17 @@ template <int HS> struct Operands<float, HS, 32> : Rows32 {
     }
     __builtin_amdgcn_wave_barrier();
   }
-  __device__ f32x16 scores(char* lds, const char*, int lane) {
+  __device__ f32x16 scores(char* lds, const char* q_lds, int lane) {
     f32x16 s;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = 0.f;
     const char* row = lds + (lane & 31) * KSTR + 16 * (lane >> 5);
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      const f32x4 kc = *(const f32x4*)(row + 32 * c);
+      const f32x4 kc = *(const f32x4*)(row + 32 * c), qc = c < kQInRegs ? q[c < kQInRegs ? c : 0] : q_at(q_lds, lane, c);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float ka = kc[e], qa = q[c][e];
+        const float ka = kc[e], qa = qc[e];
         s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka, qa, s, 0, 0, 0);
       }
     }
@@ -329,7 +361,7 @@ template <int HS> struct Operands<float, HS, 32> : Rows32 {
 
 // fp32, 16 rows per workgroup, v_mfma_f32_16x16x4_f32: for grids that leave half the chip idle, and where the matrix core at
 // fp32 rate is the longest part of a workgroup's time (rule in launch()).  Four k indices: the lane quarters.
-template <int HS> struct Operands<float, HS, 16> : Rows16 {
+template <int HS, int CROSS> struct Operands<float, HS, 16, CROSS> : Rows16 {
   static constexpr int NB = HS / 16, VH = NB / 4, KC = HS / 16, CPR = HS / 4;
   static constexpr int kBlocks = NB;
   static constexpr int kWavesPerSimd = 2;
@@ -345,10 +377,10 @@ template <int HS> struct Operands<float, HS, 16> : Rows16 {
 #pragma unroll
     for (int c = 0; c < KC; ++c) q[c] = *(const f32x4*)(q_lds + (lane & 15) * QSTR + 64 * c + 16 * (lane >> 4));
   }
-  __device__ void load_k(const void* tensor, const Tile& t, int lane) {
+  template <typename Tile> __device__ void load_k(const void* tensor, const Tile& t, int lane) {
     t.load(k, tensor, lane / CPR, [](int c) { return c * (64 / CPR); }, (lane % CPR) * 16);
   }
-  __device__ void load_v(const void* tensor, const Tile& t, int lane) {
+  template <typename Tile> __device__ void load_v(const void* tensor, const Tile& t, int lane) {
 #pragma unroll
     for (int half = 0; half < VH; ++half)
       t.load(v[half], tensor, first_key(lane), [](int e) { return key_step(e); }, (lane & 15) * (NB * 4) + 16 * half);
@@ -400,14 +432,14 @@ template <int HS> struct Operands<float, HS, 16> : Rows16 {
 template <typename T, int HS, int ROWS>
 constexpr size_t lds_bytes() {
   const size_t states = (size_t)kWaves * ROWS * (HS + 4) * sizeof(float);
-  const size_t tiles = (size_t)kWaves * Operands<T, HS, ROWS>::kLdsPerWave + ROWS * Operands<T, HS, ROWS>::QSTR;
+  const size_t tiles = (size_t)kWaves * Operands<T, HS, ROWS, kNoCross>::kLdsPerWave + ROWS * Operands<T, HS, ROWS, kNoCross>::QSTR;
   return (states > tiles ? states : tiles);
 }
 
-template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32>
-__global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS, ROWS>::kWavesPerSimd, Operands<T, HS, ROWS>::kWavesPerSimd)))
+template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32, int CROSS = kNoCross>
+__global__ __attribute__((amdgpu_flat_work_group_size(kWaves * 64, kWaves * 64), amdgpu_waves_per_eu(Operands<T, HS, ROWS, CROSS>::kWavesPerSimd, Operands<T, HS, ROWS, CROSS>::kWavesPerSimd)))
 void wave_split_attn_fwd(const WsArgs a) {
-  using Op = Operands<T, HS, ROWS>;
+  using Op = Operands<T, HS, ROWS, CROSS>;
   static_assert(!STATE || ROWS == 32, "the state's records are of 32 rows");
   constexpr int NB = Op::kBlocks, kRows = ROWS, OSTR = HS + 4;   // floats between the rows of a state in LDS: an odd number of 16 B chunks
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -507,12 +539,12 @@ void wave_split_attn_fwd(const WsArgs a) {
   };
   const int row_bytes = a.kv_heads * HS * (int)sizeof(T);
   auto tile_now = [&](bool exists) {
-    return Tile(a.tiles, exists, turn < na ? turn : turn + skip, a.Lk, block_at * sizeof(T), a.kv_jump * sizeof(T), row_bytes, HS * (int)sizeof(T));
+    return Tile<CROSS>(a.tiles, exists, turn < na ? turn : turn + skip, a.Lk, block_at * sizeof(T), a.kv_jump * sizeof(T), row_bytes, HS * (int)sizeof(T), lane);
   };
   bool more = next_tile();
   // Loads of a tile to come are always issued, with or without one: with a branch round them, what waits for older loads would
   // have to wait for all.
-  Tile tile = tile_now(more);
+  Tile<CROSS> tile = tile_now(more);
   if (Op::kAhead) op.load_k(a.k, tile, lane);
   if (q_loader) {
 #pragma unroll
@@ -675,10 +707,10 @@ void wave_split_attn_fwd(const WsArgs a) {
   }
 }
 
-template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32>
+template <typename T, int HS, typename OutT, bool STATE = false, int ROWS = 32, int CROSS = kNoCross>
 int launch_typed(WsArgs a, int64_t grid, hipStream_t stream) {
   constexpr size_t lds = lds_bytes<T, HS, ROWS>();
-  auto kern = wave_split_attn_fwd<T, HS, OutT, STATE, ROWS>;
+  auto kern = wave_split_attn_fwd<T, HS, OutT, STATE, ROWS, CROSS>;
   static LdsLimitRaised lds_limit;   // per kernel instance
   if (!raise_dynamic_lds_limit((const void*)kern, lds, lds_limit)) return USP_ERR_LAUNCH;
   const int64_t at_once = max_workgroups(kWaves * 64);
@@ -689,6 +721,16 @@ int launch_typed(WsArgs a, int64_t grid, hipStream_t stream) {
     if (st != USP_OK) return st;
   }
   return USP_OK;
+}
+
+// (a whole forward of several shards: its results are of the inputs' type)
+template <int CROSS>
+int launch_crossing(const WsArgs& a, int hs, int in_dtype, int rows, int64_t grid, hipStream_t stream) {
+  if (in_dtype == USP_FP32 && rows == 16)
+    return hs == 128 ? launch_typed<float, 128, float, false, 16, CROSS>(a, grid, stream) : launch_typed<float, 64, float, false, 16, CROSS>(a, grid, stream);
+  if (in_dtype == USP_FP32)
+    return hs == 128 ? launch_typed<float, 128, float, false, 32, CROSS>(a, grid, stream) : launch_typed<float, 64, float, false, 32, CROSS>(a, grid, stream);
+  return hs == 128 ? launch_typed<__bf16, 128, __bf16, false, 32, CROSS>(a, grid, stream) : launch_typed<__bf16, 64, __bf16, false, 32, CROSS>(a, grid, stream);
 }
 
 int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipStream_t stream) {
@@ -710,7 +752,8 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
   };
   strides(a.q_heads, a.n_q, a.q_ring, a.q_run, a.q_jump);
   strides(a.kv_heads, n_k, a.kv_ring, a.kv_run, a.kv_jump);
-  a.tiles.one = a.kv_jump == 0;
+  const Cross cross = wave_split_crossing(n_k.d, a.U, a.R, a.bs, (int64_t)a.kv_heads * hs * dtype_size(in_dtype), hs == 128 && rows == 32);
+  a.tiles.one = a.kv_jump == 0 || cross != kNoCross;
   a.tiles.by_n = n_k;
   a.tiles.by_tiles = fast_div((n_k.d + kTile - 1) / kTile);
   if (!a.causal) a.kpos = BlockPositions{0, 0, a.Lk, 0, 0, 0};
@@ -721,6 +764,8 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
     if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<__bf16, 128, float, true>(a, grid, stream) : launch_typed<__bf16, 128, __bf16, true>(a, grid, stream);
     return o_dtype == USP_FP32 ? launch_typed<__bf16, 64, float, true>(a, grid, stream) : launch_typed<__bf16, 64, __bf16, true>(a, grid, stream);
   }
+  if (cross == kOneCross) return launch_crossing<kOneCross>(a, hs, in_dtype, rows, grid, stream);
+  if (cross == kAnyCross) return launch_crossing<kAnyCross>(a, hs, in_dtype, rows, grid, stream);
   if (in_dtype == USP_FP32 && rows == 16) {
     if (hs == 128) return o_dtype == USP_FP32 ? launch_typed<float, 128, float, false, 16>(a, grid, stream) : launch_typed<float, 128, __bf16, false, 16>(a, grid, stream);
     return o_dtype == USP_FP32 ? launch_typed<float, 64, float, false, 16>(a, grid, stream) : launch_typed<float, 64, __bf16, false, 16>(a, grid, stream);

@@ -49,8 +49,31 @@ def test_all_ranks_match_the_oracle(usp, dtype, bs, L, hc, hk, hs, U, R, causal,
     (1, 1036, 4, 2, 64, 2, 1, True, True),          # one run of rows: a batch of one, the last tile of twelve rows
 ])
 def test_tiles_end_with_their_shard(usp, dtype, bs, L, hc, hk, hs, U, R, causal, zigzag):
-    """No key tile crosses from one shard of a batch into the next, and the next tile is asked for while one is worked on."""
+    """Key tiles at the ends of shards: numbered shard by shard, or crossing once (head size 128, 32 rows per workgroup)."""
     prob = tl.Problem(970 + L, bs, L, hc, hk, hs, U, R, causal, zigzag, dtype)
+    o, lse = _run_usp_fwd(usp, prob)
+    ref_o, tol = _check_against_reference(prob, o, lse)
+    for rank in range(prob.N):
+        assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
+
+
+# shards of few rows, whose tiles cross: how often at most (tests/test_wave_split_host.py asks the library's rule)
+CROSSING = [
+    (2, 96, 4, 4, 128, 4, 4, True, True, 2),        # shards of 6 rows: a tile spans six shards; runs of 12 positions
+    (3, 80, 8, 8, 64, 8, 1, False, False, 2),       # of 10 without a mask, a ragged last tile
+    (2, 320, 8, 8, 128, 8, 4, False, True, 2),      # of 10, in fp32 with 32 rows per workgroup
+    (2, 320, 8, 8, 64, 8, 4, False, True, 2),
+    (2, 272, 8, 8, 128, 8, 1, True, True, 1),       # of 34: crossings move through the tile, two rows a shard
+    (2, 1088, 8, 8, 64, 8, 4, True, True, 1),       # of 34, more tiles than waves, runs that end inside a tile
+    (4, 1088, 8, 8, 128, 8, 4, False, False, 1),
+    (2, 1280, 4, 4, 64, 4, 8, True, False, 1),      # of 40: tiles that begin where a shard does
+]
+
+
+@pytest.mark.parametrize("dtype", [tl.BF16, tl.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("bs,L,hc,hk,hs,U,R,causal,zigzag,cross", CROSSING)
+def test_tiles_cross_from_one_shard_into_the_next(usp, dtype, bs, L, hc, hk, hs, U, R, causal, zigzag, cross):
+    prob = tl.Problem(930 + L + hs, bs, L, hc, hk, hs, U, R, causal, zigzag, dtype)
     o, lse = _run_usp_fwd(usp, prob)
     ref_o, tol = _check_against_reference(prob, o, lse)
     for rank in range(prob.N):

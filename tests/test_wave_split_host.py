@@ -1,0 +1,59 @@
+"""The rule by which the key tiles of the forward that splits keys over waves cross from one shard into the next: compiled from
+the library's internal header and checked on the CPU."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from tests.test_gpu_wave_split import CROSSING
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = """
+#include "usp_internal.h"
+extern "C" int cross(int64_t n, int U, int R, int bs, int64_t row_bytes, int always) {
+  return usp::wave_split_crossing(n, U, R, bs, row_bytes, always != 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def cross(tmp_path_factory):
+    where = tmp_path_factory.mktemp("wave_split")
+    src, lib = where / "cross.cpp", where / "cross.so"
+    src.write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2405_07719_amd", "csrc"), str(src), "-o",
+                    str(lib), "-Wl,--unresolved-symbols=ignore-all"], check=True)
+    f = ctypes.CDLL(str(lib)).cross
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    return f
+
+
+@pytest.mark.parametrize("case", CROSSING)
+def test_the_gpu_cases_cross(cross, case):
+    """... whatever the data type and the rows per workgroup."""
+    bs, L, hc, hk, hs, U, R, causal, zigzag, how = case
+    for always in (0, 1):
+        assert cross(L // (U * R), U, R, bs, hk * hs * 4, always) == how
+
+
+def test_short_shards_cross(cross):
+    """Eight shards of 34 rows are nine tiles and not sixteen; a batch of one, whole tiles and one shard have nothing to cross."""
+    assert cross(34, 8, 1, 2, 2048, 1) == cross(34, 8, 1, 2, 2048, 0) == 1
+    assert cross(24, 8, 4, 2, 2048, 1) == cross(24, 8, 4, 2, 2048, 0) == 2
+    assert cross(34, 8, 1, 1, 2048, 1) == 0
+    assert cross(64, 8, 1, 2, 2048, 1) == 0
+    assert cross(34, 1, 8, 2, 2048, 1) == 0
+    assert cross(66, 2, 2, 2, 2048, 0) == 0      # ten tiles for twelve: not at head size 64
+
+
+def test_offsets_stay_within_32_bits(cross):
+    """The last row of a tile lies at most 31 rows and (31 + n - 1) // n jumps of n (bs - 1) rows from its first."""
+    for n in [1, 2, 3, 7, 31, 33, 100, 1000, 4097, 100001]:
+        for row_bytes in [128, 2048, 16384]:
+            for bs in [2, 3, 9, 100, 1000, 20000]:
+                if cross(n, 8, 8, bs, row_bytes, 1):
+                    jumps = (31 + n - 1) // n
+                    assert (31 + jumps * n * (bs - 1)) * row_bytes + row_bytes < 2 ** 31
+    assert cross(33, 8, 8, 2, 2048, 1) == 1 and cross(100001, 8, 8, 20, 2048, 1) == 0
