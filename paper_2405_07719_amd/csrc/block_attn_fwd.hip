@@ -580,20 +580,11 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
       nt = na + (tr.b1 - tr.b0);
       if (!STATE && nt == 0) continue;   // nothing of this block is visible to the query tile (workgroup-uniform)
       {
-        // Tiles that need no mask: full tiles that lie wholly in one ascending run of the key positions and whose
-        // last key no row of this wave precedes.  In walk order they form a run at the start of each visible range.
-        const int full = Lk_b / KT;
-        int fa = full, tb0 = 0, tb1 = 0;
-        if (a.causal && wave_live) {
-          int64_t c0 = (int64_t)wave_qmin - kpos.start0 + 1; c0 = c0 < 0 ? 0 : (c0 > kpos.len0 ? kpos.len0 : c0);
-          int64_t c1 = (int64_t)wave_qmin - kpos.start1 + 1; c1 = c1 < 0 ? 0 : (c1 > kpos.len1 ? kpos.len1 : c1);
-          fa = (int)(c0 / KT);
-          tb0 = (int)(((int64_t)kpos.len0 + KT - 1) / KT);
-          tb1 = (int)(((int64_t)kpos.len0 + c1) / KT);
-        }
-        free_a = min(min(fa, full), na);
-        free_b0 = na + max(tb0, tr.b0) - tr.b0;
-        free_b1 = na + min(min(tb1, full), tr.b1) - tr.b0;
+        const UnmaskedTiles unmasked = unmasked_key_tiles(KT, a.causal, wave_live, MIXED, wave_qmin, kpos.start0, kpos.len0, kpos.start1,
+                                                          kpos.len1, Lk_b, na, tr.b0, tr.b1);
+        free_a = unmasked.a;
+        free_b0 = unmasked.b0;
+        free_b1 = unmasked.b1;
       }
       kg = (const char*)ap->k[blk] + kv_head_off;
       vg = (const char*)ap->v[blk] + (VT ? vt_head_off : kv_head_off);
