@@ -221,6 +221,19 @@ inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
   return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
 }
 
+// Rows per workgroup of an fp32 launch: 16 where workgroups of 32 leave half of the CUs idle, or, under a causal mask, hold them
+// with items of very different lengths: then only with walks of a twelfth as many key tiles as there are workgroups, for twice
+// as many of these do not fit the chip at once and each has its own first loads and merge.  Measured, 32 and 16 rows, us (in
+// brackets workgroups of 32, and tiles): no mask, four ranks of L = 256 (32) 8.6, 6.5; L = 512, head size 128 (64) 21, 13.5;
+// L = 1024, head size 128 (128) 36.6, 22.6; L = 2048, head size 128 (256) 68.7, 75.7; causal, head size 64, L = 128 (144, 4) 7.3,
+// 9.4, L = 256 (256, 8) 9.4, 10.9, four ring ranks (144, 8) 9.8, 11.3; L = 384 (144, 12) 10.9, 9.3, (252, 12) 11.2, 12.8; L = 512
+// (192, 16) 13.1, 11.5, (256, 16) 13.1, 12.7, with four ring ranks 13.5, 15.0; L = 768 (240, 24) 17.3, 15.0, with four 17.95, 17.96;
+// L = 1024 (256, 32) 21.3, 17.2; head size 128 the same within 0.1 of the ratio; L = 2048 (512, 64) 43.0, 50.0.
+inline int wave_split_fp32_rows(int64_t Lq, int64_t heads, int64_t key_tiles, int causal) {
+  const int64_t wgs = (Lq + 31) / 32 * heads;
+  return wgs <= kPlanCUs / 2 || (causal && wgs <= kPlanCUs && wgs <= 12 * key_tiles) ? 16 : 32;
+}
+
 // Whether tiles cross from one shard of n rows into the next.  By shards there are more of them, and emptier ones: with eight
 // shards of 34 rows 16 for 9.  At head size 128 and 32 rows per workgroup fewer tiles are always the faster walk; elsewhere where
 // they are so many fewer that it makes up for the rows' offsets: in rounds of the eight waves, and half in tiles, for the waves

@@ -737,13 +737,8 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
   a.g = a.hq / a.hkv;
   a.by_hkv = fast_div(a.hkv); a.by_bs = fast_div(a.bs); a.by_ranks = fast_div(a.n_ranks);
   a.by_g = fast_div(a.g); a.by_U = fast_div(a.U);
-  // fp32: 16 rows per workgroup where workgroups of 32 leave half of the CUs idle, or, under a causal mask, hold them with
-  // items of very different lengths.  Measured, 32 and 16 rows, us (in brackets workgroups of 32): four ranks of L = 256, no
-  // mask (32) 8.6, 6.5; L = 512, head size 128 (64) 21, 13.5; L = 1024, no mask, head size 128 (128) 36.6, 22.6; causal, L =
-  // 1024, head size 64 (256) 21.2, 17.5, head size 128 (256) 37.1, 36.1; no mask, L = 2048, head size 128 (256) 68.7, 75.7;
-  // causal, L = 2048, head size 64 (512) 43.0, 50.0.
   const int64_t heads = (int64_t)a.hq * a.bs * a.n_ranks;
-  const int rows = in_dtype == USP_FP32 && (a.Lq + 31) / 32 * heads <= (a.causal ? kPlanCUs : kPlanCUs / 2) ? 16 : 32;
+  const int rows = in_dtype == USP_FP32 ? wave_split_fp32_rows(a.Lq, heads, (int64_t)a.R * ((a.Lk + kTile - 1) / kTile), a.causal) : 32;
   a.n_qtiles = (a.Lq + rows - 1) / rows;
   auto strides = [&](int heads, const FastDiv& n, uint64_t& ring, uint64_t& run, uint64_t& jump) {
     run = (uint64_t)n.d * heads * hs;

@@ -1,5 +1,5 @@
-"""The rule by which the key tiles of the forward that splits keys over waves cross from one shard into the next: compiled from
-the library's internal header and checked on the CPU."""
+"""Rules of the forward that splits keys over waves: where its key tiles cross from one shard into the next, and how many rows an
+fp32 workgroup has.  Compiled from the library's internal header and checked on the CPU."""
 import ctypes
 import os
 import subprocess
@@ -14,20 +14,27 @@ SOURCE = """
 extern "C" int cross(int64_t n, int U, int R, int bs, int64_t row_bytes, int always) {
   return usp::wave_split_crossing(n, U, R, bs, row_bytes, always != 0);
 }
+extern "C" int rows(int64_t Lq, int64_t heads, int64_t key_tiles, int causal) { return usp::wave_split_fp32_rows(Lq, heads, key_tiles, causal); }
 """
 
 
 @pytest.fixture(scope="module")
-def cross(tmp_path_factory):
+def lib(tmp_path_factory):
     where = tmp_path_factory.mktemp("wave_split")
     src, lib = where / "cross.cpp", where / "cross.so"
     src.write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2405_07719_amd", "csrc"), str(src), "-o",
                     str(lib), "-Wl,--unresolved-symbols=ignore-all"], check=True)
-    f = ctypes.CDLL(str(lib)).cross
-    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
-    return f
+    lib = ctypes.CDLL(str(lib))
+    lib.cross.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    return lib
+
+
+@pytest.fixture(scope="module")
+def cross(lib):
+    return lib.cross
 
 
 @pytest.mark.parametrize("case", CROSSING)
@@ -57,3 +64,13 @@ def test_offsets_stay_within_32_bits(cross):
                     jumps = (31 + n - 1) // n
                     assert (31 + jumps * n * (bs - 1)) * row_bytes + row_bytes < 2 ** 31
     assert cross(33, 8, 8, 2, 2048, 1) == 1 and cross(100001, 8, 8, 20, 2048, 1) == 0
+
+
+@pytest.mark.parametrize("L,heads,R,causal,want", [
+    (256, 4, 1, 0, 16), (1024, 4, 1, 0, 16), (1024, 5, 1, 0, 32),       # up to 128 workgroups of 32 rows
+    (128, 36, 1, 1, 32), (104, 64, 4, 1, 32), (18, 256, 16, 1, 32),     # short walks under a mask: not above 128
+    (64, 64, 1, 1, 16), (384, 12, 1, 1, 16), (512, 12, 1, 1, 16), (512, 16, 1, 1, 32), (1024, 8, 1, 1, 16), (1024, 9, 1, 1, 32),
+])
+def test_rows_of_an_fp32_workgroup(lib, L, heads, R, causal, want):
+    """L rows of each ring rank; `heads` of all ranks and batch entries."""
+    assert lib.rows(L, heads, R * -(-L // 32), causal) == want
