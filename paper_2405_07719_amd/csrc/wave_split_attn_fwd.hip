@@ -747,7 +747,7 @@ int launch(WsArgs a, const FastDiv& n_k, int hs, int in_dtype, int o_dtype, hipS
   };
   strides(a.q_heads, a.n_q, a.q_ring, a.q_run, a.q_jump);
   strides(a.kv_heads, n_k, a.kv_ring, a.kv_run, a.kv_jump);
-  const Cross cross = wave_split_crossing(n_k.d, a.U, a.R, a.bs, (int64_t)a.kv_heads * hs * dtype_size(in_dtype), hs == 128 && rows == 32);
+  const Cross cross = wave_split_crossing(n_k.d, a.U, a.R, a.bs, (int64_t)a.kv_heads * hs * dtype_size(in_dtype), in_dtype, hs, rows);
   a.tiles.one = a.kv_jump == 0 || cross != kNoCross;
   a.tiles.by_n = n_k;
   a.tiles.by_tiles = fast_div((n_k.d + kTile - 1) / kTile);
