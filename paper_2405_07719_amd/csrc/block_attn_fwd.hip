@@ -878,15 +878,7 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
 int launch_block_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
                           int64_t Lk, int hq, int hkv, int hs, float scale, int causal, const usp_posdesc& qpos,
                           const usp_posdesc& kpos, int in_dtype, int o_dtype, hipStream_t stream, const RingState* state) {
-  // fp32 has the one kernel.  bf16: the launch of 256-row items takes 6 us and its longest item (1.75 us per 64 keys at
-  // head size 128), or its work at 1.1 (0.8) PFLOP/s; short blocks, whose items are few and long, are faster with their
-  // keys split over the waves of a workgroup.  Measured, the ring of 32/8 heads, one call per block and the merge, 256-row
-  // items against waves: 8 blocks of 256 keys 145 / 74 us, of 512 keys 178 / 126, 2 blocks of 1024 keys 78 / 83; head size
-  // 64: 8 blocks of 512 keys 132 / 73, 2 of 1024 56 / 56.  With the running state (either kernel reads and writes the
-  // same records): 16 heads, 8 blocks of 452 keys 200 / 78, of 1024 keys 233 / 143; head size 64: 164 / 70, 170 / 78.
-  const double flop = 4.0 * hs * bs * hq * (double)Lq * (double)Lk * (causal ? 0.5 : 1.0);
-  if (in_dtype == USP_FP32 || wave_split_us(Lq, bs * hq, hs, flop) <
-                                  6.0 + std::max(1.75 * (double)Lk / 64 * (hs / 128.0), flop / (hs == 128 ? 1.1e9 : 0.8e9)))
+  if (block_goes_to_waves(bs, Lq, Lk, hq, hs, causal, in_dtype))
     return launch_wave_split_block_fwd(q, k, v, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal, qpos, kpos, in_dtype, o_dtype,
                                        stream, state);
   return launch_ring_attn_fwd(q, &k, &v, &kpos, 1, o, lse, bs, Lq, Lk, hq, hkv, hs, scale, causal, qpos, in_dtype,

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "usp.h"
@@ -219,6 +220,19 @@ int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, voi
 inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
   const int64_t wgs = (rows + 31) / 32 * heads, round = hs == 64 ? 2 * kPlanCUs : kPlanCUs;
   return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
+}
+
+// Where one block of keys goes, to the waves of a workgroup or to 256-row items.
+// fp32 has the one kernel.  bf16: the launch of 256-row items takes 6 us and its longest item (1.75 us per 64 keys at
+// head size 128), or its work at 1.1 (0.8) PFLOP/s; short blocks, whose items are few and long, are faster with their
+// keys split over the waves of a workgroup.  Measured, the ring of 32/8 heads, one call per block and the merge, 256-row
+// items against waves: 8 blocks of 256 keys 145 / 74 us, of 512 keys 178 / 126, 2 blocks of 1024 keys 78 / 83; head size
+// 64: 8 blocks of 512 keys 132 / 73, 2 of 1024 56 / 56.  With the running state (either kernel reads and writes the
+// same records): 16 heads, 8 blocks of 452 keys 200 / 78, of 1024 keys 233 / 143; head size 64: 164 / 70, 170 / 78.
+inline bool block_goes_to_waves(int bs, int64_t Lq, int64_t Lk, int hq, int hs, int causal, int dtype) {
+  const double flop = 4.0 * hs * bs * hq * (double)Lq * (double)Lk * (causal ? 0.5 : 1.0);
+  return dtype == USP_FP32 || wave_split_us(Lq, bs * hq, hs, flop) <
+                                  6.0 + std::max(1.75 * (double)Lk / 64 * (hs / 128.0), flop / (hs == 128 ? 1.1e9 : 0.8e9));
 }
 
 // Rows per workgroup of an fp32 launch: 16 where workgroups of 32 leave half of the CUs idle, or, under a causal mask, hold them
