@@ -7,6 +7,7 @@
 #include <functional>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string.h>
 #include <vector>
 
@@ -414,8 +415,47 @@ usp_posdesc piece_of(const usp_posdesc& d, int64_t a, int64_t b) {
   return usp_posdesc{d.start0 + a, n0, d.start1, (b - a) - n0};
 }
 
+// A launch played through on the host: kPlanCUs workgroups, the one that is free first takes the next item, every item for
+// `heads` heads and batch entries one behind the other.  As many workgroups as heads and workgroups have a common divisor
+// always do the same, and one plays for all of them.
+class PlayedLaunch {
+ public:
+  explicit PlayedLaunch(int heads) : alike_(std::gcd(heads, kPlanCUs)), workgroups_(kPlanCUs / alike_), copies_(heads / alike_) {}
+  // an item of `us` for every head; false if one is not done before `limit`
+  bool give(double us, double limit) {
+    for (int c = 0; c < copies_; ++c) {
+      const double done = give_one(us);
+      end_ = std::max(end_, done);
+      if (done >= limit) return false;
+    }
+    return true;
+  }
+  double end() const { return end_; }
+
+ private:
+  double give_one(double us) {
+    if (n_ < workgroups_) {
+      free_at_[n_++] = us;
+      if (n_ == workgroups_) std::make_heap(free_at_, free_at_ + n_, std::greater<double>());
+      return us;
+    }
+    const double done = free_at_[0] + us;
+    int at = 0;   // the first one's new place in the heap
+    for (int child; (child = 2 * at + 1) < n_; at = child) {
+      if (child + 1 < n_ && free_at_[child + 1] < free_at_[child]) ++child;
+      if (free_at_[child] >= done) break;
+      free_at_[at] = free_at_[child];
+    }
+    free_at_[at] = done;
+    return done;
+  }
+  int alike_, workgroups_, copies_, n_ = 0;
+  double end_ = 0.0;
+  double free_at_[kPlanCUs];
+};
+
 // What ring rank r cuts ({0, 0}: nothing, the launch is key_splits()' business): the room for partial results that the
-// workspace has, and the cut itself where work_out_items() has none.  (Worked out once per problem: rank_plans() below keeps
+// workspace has, and the cut itself where work_out_items() has none.  (Worked out once per problem: plans_of() below keeps
 // the answers.)
 HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   const HeavyChoice none = {0, 0};
@@ -433,25 +473,10 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   if (!p.causal && items <= kPlanCUs) return none;
   const double kItem = 8.0, kTile = 1.85, kCross = 3.0;
   auto pos_of = [&](int64_t i) { return i < qd.len0 ? qd.start0 + i : qd.start1 + (i - qd.len0); };
-  auto play = [&](const std::vector<double>& w) {
-    std::vector<double> free_at;   // a min-heap of the workgroups' finish times
-    free_at.reserve(kPlanCUs);
-    size_t j = 0;
-    for (; j < w.size() && (int)j < kPlanCUs; ++j) free_at.push_back(w[j]);
-    std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
-    for (; j < w.size(); ++j) {
-      std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
-      free_at.back() += w[j];
-      std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
-    }
-    double end = 0.0;
-    for (double t : free_at) end = std::max(end, t);
-    return end;
-  };
-  // time of the launch with the last k query tiles cut into the pieces hp (k = T: every tile, k = 0: none)
-  auto launch_time = [&](const HeavyPieces& hp, int k) {
-    // 64-key tiles of piece j that query tile i walks: under kpos <= qpos the visible keys of each run are a prefix of it
-    std::vector<double> tiles((size_t)T * hp.n);
+  // 64-key tiles of piece j that query tile i walks: under kpos <= qpos the visible keys of each run are a prefix of it
+  std::vector<double> tiles;
+  auto look = [&](const HeavyPieces& hp) {
+    tiles.resize((size_t)T * hp.n);
     for (int j = 0; j < hp.n; ++j) {
       usp_posdesc kd;
       ring_block_desc(p, ((r - hp.block[j]) % p.ring + p.ring) % p.ring, &kd);
@@ -465,12 +490,11 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
         tiles[(size_t)i * hp.n + j] = (double)((c0 + 63) / 64 + (c1 + 63) / 64);
       }
     }
-    std::vector<double> w;
-    w.reserve((size_t)items + (size_t)k * n * hp.n);
-    for (int t = 0; t < k; ++t)
-      for (int j = 0; j < hp.n; ++j)
-        for (int h = 0; h < n; ++h) w.push_back(kItem + kTile * tiles[(size_t)(T - 1 - t) * hp.n + j]);
-    for (int t = k; t < T; ++t) {
+  };
+  // time of the launch with the last k query tiles cut into the pieces hp, looked at before (k = T: every tile, k = 0: none);
+  // `limit` if it is that or more
+  auto launch_time = [&](const HeavyPieces& hp, int k, double limit) {
+    auto whole = [&](int t) {
       double sum = 0.0;
       int walked = 0;
       for (int j = 0; j < hp.n; ++j) {
@@ -479,18 +503,28 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
       }
       // (the one-launch ring loop pays the change of block too, so it is charged whether or not anything is cut)
       const double cross = (p.ring > 1 || k > 0) ? kCross * std::max(0, walked - 1) : 0.0;
-      for (int h = 0; h < n; ++h) w.push_back(kItem + kTile * sum + cross);
-    }
-    double us = play(w);
-    if (k > 0) {
-      const double cut_rows = (double)(Lq - rows.begin(T - k)) * n;
-      us += 10.0 + cut_rows * p.hs * (hp.n * 2.0 * 4.0 + 2.0) / 5.0e6;   // the fp32 partials written and read, bf16 out
-    }
-    return us;
+      return kItem + kTile * sum + cross;
+    };
+    const double cut_rows = (double)(Lq - rows.begin(T - k)) * n;
+    const double merge_us = k > 0 ? 10.0 + cut_rows * p.hs * (hp.n * 2.0 * 4.0 + 2.0) / 5.0e6 : 0.0;   // the fp32 partials written and read, bf16 out
+    double work = 0.0;   // less than a fair share of it is not possible
+    for (int t = 0; t < k; ++t)
+      for (int j = 0; j < hp.n; ++j) work += kItem + kTile * tiles[(size_t)(T - 1 - t) * hp.n + j];
+    for (int t = k; t < T; ++t) work += whole(t);
+    if (work * n / kPlanCUs * (1.0 - 1e-9) + merge_us >= limit) return limit;
+    PlayedLaunch launch(n);
+    for (int t = 0; t < k; ++t)
+      for (int j = 0; j < hp.n; ++j)
+        if (!launch.give(kItem + kTile * tiles[(size_t)(T - 1 - t) * hp.n + j], limit - merge_us)) return limit;
+    for (int t = k; t < T; ++t)
+      if (!launch.give(whole(t), limit - merge_us)) return limit;
+    return launch.end() + merge_us;
   };
   // what the launch costs as key_splits() has it: whole, or every tile in so many pieces per block
   const int splits = key_splits(p);
-  const double as_is_us = splits > 0 ? launch_time(heavy_pieces(p, splits), T) : launch_time(heavy_pieces(p, 2), 0);
+  const HeavyPieces as_is = heavy_pieces(p, splits > 0 ? splits : 2);
+  look(as_is);
+  const double as_is_us = launch_time(as_is, splits > 0 ? T : 0, 1e30);
   // A cut has to pay for itself: 3 % by this model when the pieces are parts of one block and the launch was whole,
   // where the model's choice was the measured optimum at every length tried; 8 % when they are ring blocks of unequal
   // visible parts, where it promises 5 % more than is measured (the uncut launch's long tail runs on few CUs at a
@@ -501,10 +535,11 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
   for (int pieces = 2; pieces <= (p.ring == 1 ? 4 : 2); ++pieces) {   // (R > 1: the blocks, one pass)
     if (p.ring == 1 && Lq / pieces < 1024) break;
     const HeavyPieces hp = heavy_pieces(p, pieces);
+    look(hp);
     for (int part = 1; part < 32; ++part) {   // k in steps of T / 32
       const int k = std::max(1, T * part / 32);
       if (part > 1 && k == std::max(1, T * (part - 1) / 32)) continue;
-      const double us = launch_time(hp, k);
+      const double us = launch_time(hp, k, best_us);
       if (us < best_us) { best = HeavyChoice{k, hp.n}; best_us = us; }
     }
   }
@@ -545,19 +580,40 @@ ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) 
   struct Item { double us; uint16_t entry; };
   std::vector<Item> list;
   std::vector<int> sees;   // [tile][piece]: tiles of 64 keys that query tile i walks in piece j
-  std::vector<double> free_at;
+  std::vector<double> whole(T), cut(T), longest(T + 1);   // us of tile i's one item, of its items per piece, the longest item from i on if cut
+  std::vector<double> whole_before(T + 1), cut_from(T + 1);
+  int first_seeing[kMaxHeavyPieces];   // the query tile from which on the piece is seen
   double best_us = 1e30;
   auto look = [&](const HeavyPieces& hp) {
-    sees.assign((size_t)T * hp.n, 0);
+    sees.resize((size_t)T * hp.n);
+    std::fill(whole.begin(), whole.end(), 0.0);
+    std::fill(cut.begin(), cut.end(), 0.0);
+    std::fill(longest.begin(), longest.end(), 0.0);
     for (int j = 0; j < hp.n; ++j) {
       usp_posdesc kd;
       ring_block_desc(p, ((r - hp.block[j]) % p.ring + p.ring) % p.ring, &kd);
       const usp_posdesc pd = piece_of(kd, hp.first[j], hp.last[j]);
-      for (int i = 0; i < T; ++i) {
+      first_seeing[j] = T;
+      for (int i = T - 1; i >= 0; --i) {   // (rows stand in ascending order: what sees a piece is a run of tiles up to the last)
         const int64_t c0 = p.causal ? std::clamp<int64_t>(qmax[i] - pd.start0 + 1, 0, pd.len0) : pd.len0;
         const int64_t c1 = p.causal ? std::clamp<int64_t>(qmax[i] - pd.start1 + 1, 0, pd.len1) : pd.len1;
-        sees[(size_t)i * hp.n + j] = (int)((c0 + 63) / 64 + (c1 + 63) / 64);
+        const int n_tiles = (int)((c0 + 63) / 64 + (c1 + 63) / 64);
+        sees[(size_t)i * hp.n + j] = n_tiles;
+        if (n_tiles == 0) continue;
+        first_seeing[j] = i;
+        whole[i] += kTile * n_tiles + kCross;
+        cut[i] += kItem + kTile * n_tiles;
+        longest[i] = std::max(longest[i], kItem + kTile * n_tiles);
       }
+    }
+    whole_before[0] = cut_from[T] = 0.0;
+    for (int i = 0; i < T; ++i) {
+      whole[i] = kItem + std::max(0.0, whole[i] - kCross);
+      whole_before[i + 1] = whole_before[i] + whole[i];
+    }
+    for (int i = T - 1; i >= 0; --i) {
+      cut_from[i] = cut_from[i + 1] + cut[i];
+      longest[i] = std::max(longest[i], longest[i + 1]);
     }
   };
   // the last k tiles cut into hp (looked at before)
@@ -565,52 +621,32 @@ ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) 
     if (k < 1 || k > T) return;
     int64_t row0[kMaxHeavyPieces], held = 0;
     for (int j = 0; j < hp.n; ++j) {
-      int first = T - k;
-      while (first < T && sees[(size_t)first * hp.n + j] == 0) ++first;
-      for (int i = first; i < T; ++i)
-        if (sees[(size_t)i * hp.n + j] == 0) return;   // (never: what sees a piece is a run of rows up to the last)
+      const int first = std::max(T - k, first_seeing[j]);
       row0[j] = first < T ? rows.begin(first) : Lq;
       held += Lq - row0[j];
     }
     const int64_t cut_row0 = rows.begin(T - k);
     if (row0[0] > cut_row0 || held > room * Lq) return;
-    double work = 0.0;
-    list.clear();
-    for (int i = 0; i < T; ++i) {
-      double sum = 0.0;
-      int walked = 0;
-      for (int j = 0; j < hp.n; ++j) {
-        const int tiles = sees[(size_t)i * hp.n + j];
-        if (tiles == 0) continue;
-        sum += tiles;
-        ++walked;
-        if (i >= T - k) list.push_back({kItem + kTile * tiles, listed_item(i, j)});
-      }
-      if (i < T - k) list.push_back({kItem + kTile * sum + kCross * std::max(0, walked - 1), listed_item(i, kListedWhole)});
-    }
-    if ((int)list.size() > kMaxListedItems) return;
-    for (const Item& it : list) work += it.us;
     const double merge_us = 10.0 + ((double)held * 8.0 + (double)(Lq - cut_row0) * 2.0) * n * p.hs / 5.0e6;
-    if (work * n / kPlanCUs + merge_us >= best_us) return;
+    // no sooner than a fair share, and than the longest item
+    if ((whole_before[T - k] + cut_from[T - k]) * n / kPlanCUs * (1.0 - 1e-9) + merge_us >= best_us || longest[T - k] + merge_us >= best_us ||
+        (k < T && whole[T - k - 1] + merge_us >= best_us))
+      return;
+    list.clear();
+    for (int i = 0; i < T - k; ++i) list.push_back({whole[i], listed_item(i, kListedWhole)});
+    for (int i = T - k; i < T; ++i)
+      for (int j = 0; j < hp.n; ++j)
+        if (const int n_tiles = sees[(size_t)i * hp.n + j]) list.push_back({kItem + kTile * n_tiles, listed_item(i, j)});
+    if ((int)list.size() > kMaxListedItems) return;
     std::stable_sort(list.begin(), list.end(), [](const Item& a, const Item& b) { return a.us > b.us; });
-    free_at.clear();   // a min-heap of the workgroups' finish times
-    double end = 0.0;
+    // of the first m kPlanCUs + 1 items some workgroup has m + 1, none shorter than the last of these
+    for (size_t m = 1; m * kPlanCUs < list.size() * n; ++m)
+      if ((m + 1) * list[m * kPlanCUs / n].us + merge_us >= best_us) return;
+    PlayedLaunch launch(n);
     for (const Item& it : list)
-      for (int c = 0; c < n; ++c) {
-        if ((int)free_at.size() < kPlanCUs) {
-          free_at.push_back(it.us);
-          if ((int)free_at.size() == kPlanCUs) std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
-          end = std::max(end, it.us);
-          continue;
-        }
-        std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
-        free_at.back() += it.us;
-        end = std::max(end, free_at.back());
-        if (end + merge_us >= best_us) return;
-        std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
-      }
-    if (end + merge_us >= best_us) return;
-    best_us = end + merge_us;
+      if (!launch.give(it.us, best_us - merge_us)) return;
+    if (launch.end() + merge_us >= best_us) return;
+    best_us = launch.end() + merge_us;
     best.hp = hp;
     std::copy(row0, row0 + hp.n, best.row0);
     best.merge_row0 = cut_row0;
@@ -663,32 +699,54 @@ bool same_problem(const usp_problem& a, const usp_problem& b) {
          a.ring == b.ring && a.causal == b.causal && a.split == b.split && a.dtype == b.dtype;
 }
 
-// Playing launches through takes the host 0.2-1 ms per ring rank, as long as a short launch itself: the answers
-// for the last problems seen are kept (every ring rank's, worked out at the first question about the problem).
-struct RankPlan { HeavyChoice choice; ItemPlan plan; };
-std::shared_ptr<const std::vector<RankPlan>> rank_plans(const usp_problem& p) {
-  struct Entry { usp_problem p; std::shared_ptr<const std::vector<RankPlan>> ranks; };
-  static std::mutex mu;
-  static std::vector<Entry> seen;
-  std::lock_guard<std::mutex> lock(mu);
-  for (const Entry& e : seen)
-    if (same_problem(e.p, p)) return e.ranks;
-  if (seen.size() >= 64) seen.erase(seen.begin());
-  auto ranks = std::make_shared<std::vector<RankPlan>>();
-  for (int r = 0; r < p.ring; ++r) {
-    const HeavyChoice c = work_out_heavy_choice(p, r);
-    ranks->push_back({c, work_out_items(p, r, c)});
+// Playing launches through takes the host 10 to 400 us per ring rank (L = 8192, U 8, 25 us for the choice and 80 for the items;
+// 16384, U 4 x R 2, 28 for the items; 24576, U 8, 100 and 380; no mask, 17776, 120 and 330): the answers for the last problems
+// asked about are kept.  Every ring rank's choice is worked out at the first question about the problem, for the workspace
+// depends on all; a ring rank's items when it is first launched by them, or, where it is the only one, asked about.  Nobody waits for another problem's answers.
+struct Plans {
+  usp_problem p;
+  std::vector<HeavyChoice> choices;
+  std::mutex mu;
+  std::vector<std::unique_ptr<const ItemPlan>> items;
+  const ItemPlan& items_of(int r) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!items[r]) items[r] = std::make_unique<const ItemPlan>(work_out_items(p, r, choices[r]));
+    return *items[r];
   }
-  seen.push_back({p, ranks});
-  return ranks;
+};
+std::shared_ptr<Plans> plans_of(const usp_problem& p) {
+  static std::mutex mu;
+  static std::vector<std::shared_ptr<Plans>> seen;   // the last asked about is last
+  auto find = [&]() -> std::shared_ptr<Plans> {
+    for (auto it = seen.rbegin(); it != seen.rend(); ++it)
+      if (same_problem((*it)->p, p)) {
+        std::rotate(it.base() - 1, it.base(), seen.end());
+        return seen.back();
+      }
+    return nullptr;
+  };
+  {
+    std::lock_guard<std::mutex> lock(mu);
+    if (auto known = find()) return known;
+  }
+  auto plans = std::make_shared<Plans>();
+  plans->p = p;
+  for (int r = 0; r < p.ring; ++r) plans->choices.push_back(work_out_heavy_choice(p, r));
+  plans->items.resize(p.ring);
+  std::lock_guard<std::mutex> lock(mu);
+  if (auto known = find()) return known;
+  if (seen.size() >= 64) seen.erase(seen.begin());
+  seen.push_back(plans);
+  return plans;
 }
 
 // The most pieces any ring rank of the problem cuts its heaviest tiles into (0: no rank does): the workspace holds as
 // many partial results.
 int heavy_max_pieces(const usp_problem& p) {
+  if (!ring_in_one_launch(p)) return 0;
   int m = 0;
-  for (const RankPlan& r : *rank_plans(p))
-    if (r.choice.tiles > 0) m = std::max(m, r.choice.pieces);
+  for (const HeavyChoice& c : plans_of(p)->choices)
+    if (c.tiles > 0) m = std::max(m, c.pieces);
   return m;
 }
 
@@ -822,7 +880,10 @@ extern "C" size_t usp_attn_fwd_workspace_bytes(const usp_problem* p, int n_ranks
   if (usp_validate(p) != USP_OK || n_ranks < 1) return 0;
   // one rank touches one Ulysses column; a wider range may straddle ring rows, so size for all U
   const int cols = n_ranks == 1 ? 1 : p->ulysses;
-  return plan_fwd(*p, cols).total;
+  const size_t bytes = plan_fwd(*p, cols).total;
+  // (one ring rank: its items are the ones that will be launched, so they are worked out here and not in the first call)
+  if (p->ring == 1 && ring_in_one_launch(*p) && !short_in_one_launch(*p, n_ranks)) plans_of(*p)->items_of(0);
+  return bytes;
 } catch (...) {
   return 0;
 }
@@ -892,7 +953,7 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
   auto k_block = [&](int s, int u) { return kv_block(f.k_in_place, k, f.k_head, f.kv_block_bytes, s, u); };
   auto v_block = [&](int s, int u) { return kv_block(f.v_in_place, v, f.v_head, f.v_block_bytes, s, u); };
 
-  const auto plans = rank_plans(*p);
+  const auto plans = allow_heavy && ring_in_one_launch(*p) ? plans_of(*p) : nullptr;
   for (int rank = rank_begin; rank < rank_end; ++rank) {
     const int r = rank / U, u = rank % U;
     // Step 2: Q of this rank to head layout (the one-launch ring loop reads the shards itself).
@@ -918,13 +979,14 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
       // row once, so it does that straight from / to the sequence-layout shards of the Ulysses group.
       const SeqLayoutIO seq = {(int)(p->L / N), p->hc, u * hq, kv_pitch};
       const size_t group_off = (size_t)r * U * p->bs * (p->L / N) * p->hc * p->hs * es;
-      const RankPlan& cut = (*plans)[r];
-      const bool by_list = allow_heavy && !cut.plan.items.empty();
-      if (by_list || (allow_heavy && cut.choice.tiles > 0)) {
+      const ItemPlan* const list = plans ? &plans->items_of(r) : nullptr;
+      const HeavyChoice choice = plans ? plans->choices[r] : HeavyChoice{0, 0};
+      const bool by_list = list && !list->items.empty();
+      if (by_list || choice.tiles > 0) {
         // Short and medium lengths: the heaviest query tiles as one item per piece of the keys that they see (pieces of the
         // one block, or the ring blocks), with partial results; every other tile a whole item of the same launch that writes
         // its finished rows itself.  Then the merge of the cut rows, straight to the sequence-layout shards.
-        const HeavyPieces hp = by_list ? cut.plan.hp : heavy_pieces(*p, cut.choice.pieces);
+        const HeavyPieces hp = by_list ? list->hp : heavy_pieces(*p, choice.pieces);
         const void* kp[kMaxHeavyPieces];
         const void* vp[kMaxHeavyPieces];
         usp_posdesc pd[kMaxHeavyPieces];
@@ -942,23 +1004,23 @@ int attn_fwd_impl(const usp_problem* p, const void* q, const void* k, const void
           if (by_list) {   // one behind the other
             o_ptrs[n] = (float*)(ws + f.o_parts) + held * hq * p->hs;
             l_ptrs[n] = (float*)(ws + f.lse_parts) + held * hq;
-            held += (size_t)p->bs * (Lq - cut.plan.row0[n]);
+            held += (size_t)p->bs * (Lq - list->row0[n]);
           } else {
             o_ptrs[n] = (float*)(ws + f.o_parts + (size_t)n * f.part_o_bytes);
             l_ptrs[n] = (float*)(ws + f.lse_parts + (size_t)n * f.part_lse_bytes);
           }
         }
-        MixedLaunch mixed = {(char*)o + group_off, lse_rank, by_list ? 0 : cut.choice.tiles, f.v_transposed};
+        MixedLaunch mixed = {(char*)o + group_off, lse_rank, by_list ? 0 : choice.tiles, f.v_transposed};
         if (by_list) {
-          mixed.listed = cut.plan.items.data();
-          mixed.n_listed = (int)cut.plan.items.size();
-          mixed.part_row0 = cut.plan.row0;
+          mixed.listed = list->items.data();
+          mixed.n_listed = (int)list->items.size();
+          mixed.part_row0 = list->row0;
         }
         st = launch_attn_fwd_partials((const char*)q + group_off, kp, vp, pd, lk, hp.n, o_ptrs, l_ptrs, p->bs, Lq, Lq, hq,
                                       hkv, p->hs, scale, p->causal ? 1 : 0, qd, stream, &seq, &mixed);
         if (st != USP_OK) return st;
         const RowTiles rows(qd, Lq, p->causal);
-        const int64_t row0 = by_list ? cut.plan.merge_row0 : rows.begin(rows.n - cut.choice.tiles);
+        const int64_t row0 = by_list ? list->merge_row0 : rows.begin(rows.n - choice.tiles);
         st = launch_lse_merge((const void* const*)o_ptrs, (const float* const*)l_ptrs, hp.n, (char*)o + group_off, lse_rank,
                               p->bs, Lq, hq, p->hs, USP_FP32, p->dtype, stream, &seq, row0, mixed.part_row0);
         if (st != USP_OK) return st;
@@ -1273,7 +1335,7 @@ BwdCut work_out_bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   return best;
 }
 
-// Playing the cuts of a problem through takes the host 0.1 ms, 0.7 at most: the last answers are kept, as rank_plans() keeps its.
+// Playing the cuts of a problem through takes the host 0.1 ms, 0.7 at most: the last answers are kept, as plans_of() keeps its.
 BwdCut bwd_cut(const usp_problem& p, int r, const BwdCut& most) {
   struct Entry { usp_problem p; int r; BwdCut cut; };   // (`most` follows from the problem)
   static std::mutex mu;

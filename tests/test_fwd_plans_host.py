@@ -1,0 +1,64 @@
+"""How the forward of a rank is cut, on the CPU: which answers are worked out and when, and the launches played through."""
+import heapq
+import random
+
+import pytest
+
+import paper_2405_07719_amd as usp
+from tests.host_side import HostSide, problem
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    return HostSide(tmp_path_factory.mktemp("host_side"))
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 6, 12, 32, 96, 256, 300, 512])
+def test_one_workgroup_plays_for_all_alike(host, heads):
+    """The end of a launch is that of 256 workgroups, the first one that is free taking the next item, to the last bit: the
+    same sums in the same order."""
+    rng = random.Random(heads)
+    for n in [1, 2, 7, 40, 150]:
+        us = [rng.choice([9.0, 10.78, 23.5, rng.uniform(8, 200)]) for _ in range(n)]
+        for items in (us, sorted(us, reverse=True)):
+            free, end = [0.0] * 256, 0.0
+            for x in items:
+                for _ in range(heads):
+                    done = heapq.heappop(free) + x
+                    end = max(end, done)
+                    heapq.heappush(free, done)
+            assert host.played(heads, items) == end
+
+
+def test_items_are_listed_for_the_ranks_that_are_launched(host):
+    """... and not for a workspace query about several ring ranks, a problem that goes to the one short launch, or ranks that nobody asked for."""
+    p = problem(1, 16384, 32, 8, 128, 4, 2)
+    assert host.query(p) > 0 and host.ranks_listed(p) == 0
+    assert host.forward(p, 5, 6)["kind"] == "listed" and host.ranks_listed(p) == 1
+    assert host.forward(p, 6, 7)["kind"] == "listed" and host.ranks_listed(p) == 1      # the same ring rank
+    assert host.forward(p, 0, 8)["launches"] == 8 and host.ranks_listed(p) == 2
+    one = problem(1, 8192, 32, 8, 128, 8, 1)
+    assert host.query(one) > 0 and host.ranks_listed(one) == 1                          # there is no other ring rank
+    short = problem(1, 2048, 32, 8, 128, 8, 1)
+    assert host.forward(short, 0, 1)["kind"] == "waves" and host.ranks_listed(short) == 0
+    many = problem(1, 2 * 17 * 4096, 32, 8, 128, 1, 17)      # more blocks than one launch takes
+    assert host.forward(many, 0, 1)["kind"] == "blocks" and host.ranks_listed(many) == 0
+
+
+def test_answers_are_kept_for_the_last_problems(host):
+    """64 of them, whichever were asked about last."""
+    kept = problem(1, 16384, 32, 8, 128, 4, 2, zigzag=False)
+    assert host.forward(kept, 7, 8)["kind"] == "listed" and host.ranks_listed(kept) == 1
+    for i in range(100):
+        host.query(problem(1, 6144 + 16 * i, 32, 8, 128, 8, 1))
+        assert host.ranks_listed(kept) == 1
+    for i in range(64):
+        host.query(problem(1, 6144 + 16 * i, 16, 8, 128, 8, 1))
+    assert host.ranks_listed(kept) == 0
+
+
+@pytest.mark.parametrize("dtype", [usp.USP_BF16, usp.USP_FP32])
+def test_the_same_launch_every_time(host, dtype):
+    for p in [problem(1, 8192, 32, 8, 128, 8, 1, dtype=dtype), problem(2, 4608, 8, 2, 64, 1, 2, dtype=dtype)]:
+        first = host.forward(p, 0, 1)
+        assert host.forward(p, 0, 1) == first
