@@ -212,6 +212,8 @@ int usp_ring_attn_fwd_partials(const void* q, const void* const* k_blocks, const
  * a little longer (more than one work item per CU, the heaviest still longer than a CU's share), run one launch in which the
  * last query tiles are cut into items over two to eight parts of the keys that they see, beside whole items for the other
  * tiles, then the merge of the cut rows; the workspace query knows.
+ * Which of these a rank takes, and how a launch sums, goes by the size of the call: a rank's last bits may depend on the ranks
+ * that it is launched with.
  *   q, o: seq layout with hc heads; k, v: seq layout with hk heads (ALL N shards must be
  *   present: the ring reads the other ring ranks' K/V where hardware would receive them);
  *   lse: [N][bs][hc/U][L/R] float, written for the ranks in range.

@@ -99,6 +99,18 @@ def test_fp32_rows_of_a_workgroup(usp, bs, L, hc, hk, hs, U, R, causal, zigzag):
         assert tl.max_abs(o[rank], ref_o[rank]) <= tol, rank
 
 
+@pytest.mark.parametrize("hs", [64, 128])
+def test_fp32_rank_alone_and_among_all(usp, hs):
+    """A rank's workgroups have 16 rows where it runs alone (64 of 32 rows) and 32 among all four (256): its rows are summed in
+    another order.  Each sum is within the oracle test's tolerance of the exact one, so the two are within twice that."""
+    prob = tl.Problem(960 + hs, 1, 1024, 8, 8, hs, 1, 4, False, True, tl.FP32)
+    o, lse = _run_usp_fwd(usp, prob)
+    o1, lse1 = _run_usp_fwd(usp, prob, 2, 3)
+    assert tl.max_abs(o[2], o1[2]) <= 2 * 2e-5 and tl.max_abs(lse[2], lse1[2]) <= 2 * 2e-5
+    ref_o, tol = _check_against_reference(prob, o1, lse1, ranks=[2])
+    assert tl.max_abs(o1[2], ref_o[2]) <= tol
+
+
 def test_a_rank_range_writes_only_its_slices(usp):
     """bs = 2, ranks 1 and 2 of four: their head slices, everything else as it was; the other ranks' LSE too."""
     prob = tl.Problem(951, 2, 160, 4, 2, 64, 2, 2, True, True, tl.FP32)
