@@ -6,6 +6,7 @@ import pytest
 
 import paper_2405_07719_amd as usp
 from tests.host_side import HostSide, problem
+from tests.test_gpu_attn_fwd import CUT, MODEL_SHAPES
 
 
 @pytest.fixture(scope="module")
@@ -62,3 +63,27 @@ def test_the_same_launch_every_time(host, dtype):
     for p in [problem(1, 8192, 32, 8, 128, 8, 1, dtype=dtype), problem(2, 4608, 8, 2, 64, 1, 2, dtype=dtype)]:
         first = host.forward(p, 0, 1)
         assert host.forward(p, 0, 1) == first
+
+
+@pytest.mark.parametrize("case", CUT)
+def test_the_gpu_cases_take_their_launch(host, case):
+    *shape, rank, causal, zigzag, launch, parts = case
+    got = host.forward(problem(*shape, causal, zigzag), rank, rank + 1)
+    assert (got["kind"], got["parts"]) == (launch, parts), got
+
+
+def test_the_gpu_cases_cover_every_cut(host):
+    """Lists with and without whole items, parts of the same and of different rows, two to eight parts, one and several batch
+    entries; the older cuts that rings of 9 to 16 blocks take."""
+    listed = []
+    for *shape, rank, causal, zigzag, launch, parts in CUT:
+        got = host.forward(problem(*shape, causal, zigzag), rank, rank + 1)
+        listed += [(got["parts"], got["whole"] > 0, got["different_rows"], shape[0] > 1, shape[5] > 1)] if launch == "listed" else []
+    assert {2, 3, 4, 8} <= {x[0] for x in listed}
+    assert {(w, d) for _, w, d, _, _ in listed} == {(False, 0), (False, 1), (True, 0), (True, 1)}
+    assert any(b and u and d for _, _, d, b, u in listed)
+    assert {c[-2] for c in CUT} == {"waves", "listed", "last tiles cut", "every tile cut", "blocks"}
+    shapes = {name: host.forward(problem(*shape, causal=causal), 0, shape[5] * shape[6])["kind"] for name, *shape, causal in MODEL_SHAPES}
+    assert {n for n, kind in shapes.items() if kind == "listed"} == {
+        "key_split_3_pieces_noncausal", "heavy_tiles_cut_head_size_64", "heavy_tiles_cut_batch_of_two", "heavy_tiles_cut_ring_of_two",
+        "heavy_tiles_cut_short_four_pieces", "tiles_cut_noncausal_to_fill_the_last_round"}

@@ -174,26 +174,30 @@ def test_usp_fwd_causal_gqa_all_factorisations(usp, U, R, zigzag):
         assert tl.max_abs(o[rank], ref_o[rank]) <= to, rank
 
 
-@pytest.mark.parametrize("name,bs,L,hc,hk,hs,U,R,causal", [
+MODEL_SHAPES = [
     ("mha_llama2_like", 1, 1024, 8, 8, 128, 4, 2, True),          # MHA: one KV head per query head
     ("mqa_ring_only", 1, 1024, 8, 1, 128, 1, 4, True),            # MQA: Ulysses cannot split the single KV head, the ring can
     ("noncausal_visual_tokens", 1, 1536, 8, 4, 128, 2, 2, False),  # bidirectional, length not a power of two
     ("head_size_64", 2, 768, 8, 4, 64, 2, 2, True),
     ("gqa_group_of_eight", 1, 1024, 16, 2, 128, 2, 2, True),
-    ("ring_of_32_stepwise_path", 1, 2048, 4, 2, 128, 1, 32, True),  # more blocks than one launch takes: per-step launches + merge
-    # short sequences, few work items: the K/V blocks are cut into pieces that run as work items of their own
-    ("key_split_3_pieces_across_zigzag_runs", 1, 6144, 4, 2, 128, 1, 2, True),   # Lq 3072: pieces of 1024, runs of 1536
+    ("ring_of_32_stepwise_path", 1, 2048, 4, 2, 128, 1, 32, True),  # more blocks than the ring loop of 256-row items takes, short enough for one launch
+    # short sequences, few work items: query tiles are cut into pieces of the keys that run as work items of their own (which launch
+    # each of these takes: tests/test_fwd_plans_host.py)
+    ("key_split_3_pieces_across_zigzag_runs", 1, 6144, 4, 2, 128, 1, 2, True),   # Lq 3072, runs of 1536
     ("key_split_3_pieces_noncausal", 1, 4096, 8, 4, 128, 2, 1, False),
-    ("key_split_4_pieces_batch_of_two", 2, 4096, 4, 2, 128, 2, 1, True),   # ratio 8: four pieces of 1024 keys
+    ("key_split_4_pieces_batch_of_two", 2, 4096, 4, 2, 128, 2, 1, True),   # a batch of two
     ("key_split_head_size_64", 1, 2048, 4, 2, 64, 2, 1, True),
-    # medium length, more than one work item per CU but the heaviest longer than a CU's share: only the last query
-    # tiles are cut in two (partial results, merged over their rows), the others stay whole items of the same launch
-    ("heavy_tiles_cut_head_size_64", 1, 5120, 16, 4, 64, 1, 1, True),      # 5 of 20 tiles cut
-    ("heavy_tiles_cut_batch_of_two", 2, 4608, 8, 2, 128, 1, 1, True),      # 6 of 18 tiles cut
+    # medium length, more than one work item per CU but the heaviest longer than a CU's share: only the last query tiles are cut
+    # (partial results, merged over their rows), the others stay whole items of the same launch
+    ("heavy_tiles_cut_head_size_64", 1, 5120, 16, 4, 64, 1, 1, True),
+    ("heavy_tiles_cut_batch_of_two", 2, 4608, 8, 2, 128, 1, 1, True),
     ("heavy_tiles_cut_ring_of_two", 1, 9216, 16, 4, 128, 1, 2, True),      # the pieces are the two ring blocks
-    ("heavy_tiles_cut_short_four_pieces", 1, 6144, 8, 2, 128, 2, 1, True), # fewer items than CUs: 18 of 24 tiles in 4 pieces
+    ("heavy_tiles_cut_short_four_pieces", 1, 6144, 8, 2, 128, 2, 1, True),   # fewer whole items than CUs
     ("tiles_cut_noncausal_to_fill_the_last_round", 1, 5120, 16, 4, 128, 1, 1, False),   # 320 equal items on 256 CUs
-])
+]
+
+
+@pytest.mark.parametrize("name,bs,L,hc,hk,hs,U,R,causal", MODEL_SHAPES)
 def test_usp_fwd_other_model_shapes(usp, name, bs, L, hc, hk, hs, U, R, causal):
     prob = tl.Problem(300 + len(name), bs, L, hc, hk, hs, U, R, causal, True, tl.BF16)
     o, lse = _run_usp_fwd(usp, prob)
@@ -237,36 +241,72 @@ def test_usp_fwd_rejects_bad_arguments(usp):
     assert usp.usp_attn_fwd_workspace_bytes(bad, 1) == 0
 
 
-@pytest.mark.parametrize("bs,L,hq,hkv,hs,R,rank,causal,zigzag", [
-    (1, 4096, 4, 1, 128, 1, 0, True, True),          # the shortest that is cut this way
-    (1, 8192, 4, 4, 64, 1, 0, True, True),           # head size 64, a piece per few tiles
-    (2, 9000, 2, 1, 128, 1, 0, True, False),         # a batch of two: partial results of fewer rows, one behind the other
-    (1, 12500, 4, 1, 128, 1, 0, True, True),         # ragged last tile and last piece
-    (1, 20480, 4, 1, 128, 1, 0, False, True),        # no mask: every piece is seen
-    (1, 16384, 8, 2, 128, 2, 1, True, True),         # ring blocks, a rank whose second run begins inside a 256-row tile or not
-    (1, 8240, 8, 8, 128, 4, 2, True, True),          # runs of 1030 rows: tiles that end with their run
-    (1, 16384, 8, 8, 64, 8, 3, True, True),          # eight blocks, the most that one merge takes this way
-    (2, 16384, 4, 2, 128, 4, 3, True, False),        # contiguous blocks: the last rank sees all, whole and cut tiles
-])
-def test_listed_items_match_the_uncut_launch(usp, bs, L, hq, hkv, hs, R, rank, causal, zigzag):
-    """Lengths at which some query tiles are cut into pieces of the keys that they see, each a listed item with a partial
-    result that holds only the rows that see the piece, against one uncut launch over the same blocks.  Workspace and outputs
-    begin as NaN.  A piece's weights are rounded to bf16 relative to its own maxima: 2^-9 per weight."""
-    p = usp.problem(bs, L, hq, hkv, hs, 1, R, causal, usp.USP_SPLIT_ZIGZAG if zigzag else usp.USP_SPLIT_CONTIG, usp.USP_BF16)
+# What one rank of usp_attn_fwd launches last, as tests/test_fwd_plans_host.py asks the library's host side: "listed" (whole items
+# and pieces that are seen, of so many parts of the keys), "last tiles cut" and "every tile cut" (rings of 9 to 16 blocks, which no
+# list covers), "blocks" (longer rings), "waves" (the short one-launch forward, here for the lengths just below the listed ones).
+CUT = [  # bs, L, hc, hk, hs, U, R, rank, causal, zigzag, launch, parts
+    (1, 4096, 4, 1, 128, 1, 1, 0, True, True, "waves", 0),              # four heads: just too short to be cut
+    (1, 8192, 4, 4, 64, 1, 1, 0, True, True, "listed", 4),              # head size 64, a piece per few tiles
+    (2, 9000, 2, 1, 128, 1, 1, 0, True, False, "listed", 4),            # a batch of two: partial results of fewer rows, one behind the other
+    (1, 12500, 4, 1, 128, 1, 1, 0, True, True, "listed", 3),            # ragged last tile and last piece
+    (1, 20480, 4, 1, 128, 1, 1, 0, False, True, "listed", 4),           # no mask: every piece is seen
+    (1, 16384, 8, 2, 128, 1, 2, 1, True, True, "listed", 2),            # ring blocks, a rank whose second run begins inside a 256-row tile or not
+    (1, 8240, 8, 8, 128, 1, 4, 2, True, True, "listed", 4),             # runs of 1030 rows: tiles that end with their run
+    (1, 16384, 8, 8, 64, 1, 8, 3, True, True, "waves", 0),              # eight heads of eight blocks, head size 64: too short
+    (2, 16384, 4, 2, 128, 1, 4, 3, True, False, "listed", 4),           # contiguous blocks, the last rank: every tile sees and is cut into all
+    (1, 8192, 32, 8, 128, 1, 8, 0, True, True, "listed", 8),            # eight parts of the same rows, the most that one merge takes, beside whole items
+    (2, 4224, 16, 8, 128, 1, 8, 6, True, True, "listed", 8),            # ... of different rows, in a batch of two
+    (1, 5312, 16, 4, 128, 1, 8, 0, False, False, "listed", 8),          # ... without a mask
+    (1, 4448, 32, 1, 128, 1, 8, 5, True, False, "listed", 8),           # two blocks that no row sees
+    (1, 9216, 16, 4, 128, 1, 2, 1, True, True, "listed", 2),            # whole items that walk both ring blocks, and cut ones
+    (1, 6976, 16, 8, 128, 2, 1, 1, True, True, "listed", 3),            # Ulysses 2, waves without rows in the last query tile
+    (2, 9232, 16, 8, 128, 8, 1, 5, True, False, "listed", 4),           # Ulysses 8, a batch of two: K and V staged
+    (2, 8320, 32, 32, 64, 8, 2, 3, True, True, "listed", 2),            # Ulysses 8 x ring 2, tiles that end with their run, waves without rows
+    (1, 37674, 16, 4, 128, 1, 9, 8, True, True, "last tiles cut", 9),   # one tile
+    (2, 37332, 8, 8, 64, 1, 9, 1, True, True, "last tiles cut", 9),     # nine tiles, a batch of two
+    (2, 41688, 16, 4, 64, 2, 9, 6, False, False, "last tiles cut", 9),
+    (2, 7620, 8, 8, 128, 1, 10, 5, True, True, "every tile cut", 10),
+    (1, 10134, 8, 8, 128, 1, 9, 4, True, False, "every tile cut", 9),
+    (1, 15600, 16, 8, 64, 2, 12, 21, False, True, "every tile cut", 12),
+    (2, 6840, 32, 8, 64, 1, 20, 4, False, True, "blocks", 0),           # more blocks than one launch takes: a launch each, and the merge
+    (1, 14976, 16, 8, 128, 2, 32, 48, False, True, "blocks", 0),
+]
+
+
+@pytest.mark.parametrize("bs,L,hc,hk,hs,U,R,rank,causal,zigzag,launch,parts", CUT)
+def test_cut_forwards_match_the_uncut_launch(usp, bs, L, hc, hk, hs, U, R, rank, causal, zigzag, launch, parts):
+    """Lengths at which some query tiles are cut into pieces of the keys, against one uncut launch over the same blocks.
+    Workspace and outputs begin as NaN; what belongs to other ranks stays so.  A piece's weights are rounded to bf16 relative to
+    its own maxima: 2^-9 per weight."""
+    p = usp.problem(bs, L, hc, hk, hs, U, R, causal, usp.USP_SPLIT_ZIGZAG if zigzag else usp.USP_SPLIT_CONTIG, usp.USP_BF16)
     gen = torch.Generator(device="cuda").manual_seed(L + hs)
-    q = torch.randn((R, bs, L // R, hq, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
-    k, v = (torch.randn((R, bs, L // R, hkv, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    N, hq, hkv, Lq = U * R, hc // U, hk // U, L // R
+    r, u = divmod(rank, U)
+    q = torch.randn((N, bs, L // N, hc, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k, v = (torch.randn((N, bs, L // N, hk, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+
+    def head(t, s, heads):      # ring block s of t in head layout, the rank's heads
+        block = t[s * U:(s + 1) * U].transpose(0, 1).reshape(bs, Lq, t.shape[3], hs)
+        return block[:, :, u * heads:(u + 1) * heads].contiguous()
+
     ws = torch.full((max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)),), 0xFF, dtype=torch.uint8, device="cuda")
     o = torch.full_like(q, float("nan"))
-    lse = torch.full((R, bs, hq, L // R), float("nan"), device="cuda")
+    lse = torch.full((N, bs, hq, Lq), float("nan"), device="cuda")
     usp.usp_attn_fwd(p, q, k, v, o, lse, rank, rank + 1, ws)
-    order = [(rank - i) % R for i in range(R)]
+    order = [(r - i) % R for i in range(R)]
     pos = [usp.usp_local_positions(p, s, 0)[1] for s in range(R)]
-    o1, lse1 = torch.empty_like(q[rank]), torch.empty_like(lse[rank])
-    usp.usp_ring_attn_fwd(q[rank], [k[s] for s in order], [v[s] for s in order], [pos[s] for s in order], o1, lse1, bs, L // R,
-                          L // R, hq, hkv, hs, 0.0, causal, pos[rank], tl.BF16, tl.BF16)
+    o1 = torch.empty((bs, Lq, hq, hs), device="cuda", dtype=torch.bfloat16)
+    lse1 = torch.empty((bs, hq, Lq), device="cuda")
+    kb, vb = ([head(t, s, hkv) for s in order] for t in (k, v))
+    if launch == "blocks":      # (no mask: all blocks as one)
+        assert not causal
+        kb, vb, order = [torch.cat(kb, dim=1)], [torch.cat(vb, dim=1)], []
+    usp.usp_ring_attn_fwd(head(q, r, hq), kb, vb, [pos[s] for s in order] if causal else None, o1, lse1, bs, Lq, kb[0].shape[1], hq, hkv, hs,
+                          0.0, causal, pos[r] if causal else None, tl.BF16, tl.BF16)
     torch.cuda.synchronize()
+    got = head(o, r, hq).float()
+    assert torch.isnan(o).sum().item() == o.numel() - got.numel() and torch.isnan(lse).sum().item() == lse.numel() - lse1.numel()
     assert (lse[rank] - lse1).abs().max().item() <= 1e-4
-    diff = (o[rank].float() - o1.float()).norm(dim=-1) / o1.float().norm(dim=-1)
+    diff = (got - o1.float()).norm(dim=-1) / o1.float().norm(dim=-1)
     assert diff.max().item() <= 2 ** -6, diff.max().item()      # row by row: 2^-9 of P and of O, four times over
-    assert (o[rank].float() - o1.float()).norm().item() <= 2 ** -8 * o1.float().norm().item()
+    assert (got - o1.float()).norm().item() <= 2 ** -8 * o1.float().norm().item()
