@@ -95,6 +95,8 @@ class HostSide:
         self.lib.usp_attn_fwd_workspace_bytes.restype = ctypes.c_size_t
         self.lib.played.restype = ctypes.c_double
 
+    long = staticmethod(ctypes.c_int64)
+
     def query(self, p, n_ranks=1):
         return self.lib.usp_attn_fwd_workspace_bytes(ctypes.byref(p), n_ranks)
 

@@ -7,6 +7,7 @@ import pytest
 import paper_2405_07719_amd as usp
 from tests.host_side import HostSide, problem
 from tests.test_gpu_attn_fwd import CUT, MODEL_SHAPES
+from tests.test_gpu_ring import STATE_STEPS
 
 
 @pytest.fixture(scope="module")
@@ -87,3 +88,25 @@ def test_the_gpu_cases_cover_every_cut(host):
     assert {n for n, kind in shapes.items() if kind == "listed"} == {
         "key_split_3_pieces_noncausal", "heavy_tiles_cut_head_size_64", "heavy_tiles_cut_batch_of_two", "heavy_tiles_cut_ring_of_two",
         "heavy_tiles_cut_short_four_pieces", "tiles_cut_noncausal_to_fill_the_last_round"}
+
+
+@pytest.mark.parametrize("case", STATE_STEPS, ids=[c[0] for c in STATE_STEPS])
+def test_the_gpu_state_steps_go_to_256_row_items(host, case):
+    """... with as many query tiles that see the block as the case says: rows of 256 in a row, as the state's records are."""
+    name, bs, hs, hq, hkv, rows, blocks, tiles = case
+    Lq, Lk = rows[1] + rows[3], blocks[0][1] + blocks[0][3]
+    assert all(b[1] + b[3] == Lk for b in blocks)
+    assert not host.lib.block_goes_to_waves(bs, host.long(Lq), host.long(Lk), hq, hs, 1, usp.USP_BF16)
+    q = [rows[0] + i if i < rows[1] else rows[2] + i - rows[1] for i in range(Lq)]
+    starts = [min([b[0]] * (b[1] > 0) + [b[2]] * (b[3] > 0)) for b in blocks]
+    assert [sum(max(q[t:t + 256]) >= s for t in range(0, Lq, 256)) for s in starts[1:-1]] == tiles
+
+
+def test_the_gpu_state_steps_cover_every_list():
+    """All tiles, some, one, none; an odd number; as many items as CUs, fewer, and more."""
+    items, counts = set(), set()
+    for name, bs, hs, hq, hkv, rows, blocks, tiles in STATE_STEPS:
+        n = -(-(rows[1] + rows[3]) // 256)
+        counts |= {"all" if t == n else "none" if t == 0 else "odd" if t % 2 else "even" for t in tiles}
+        items |= {(t * hq * bs > 256) - (t * hq * bs < 256) for t in tiles if 0 < t < n}
+    assert counts == {"all", "none", "odd", "even"} and items == {-1, 0, 1}

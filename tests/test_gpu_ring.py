@@ -496,8 +496,9 @@ def test_ring_attn_fwd_vt_equals_row_major_v(usp, name, bs, L, hq, hkv, hs, R, r
     (64, 1, 1, ((0, 1024 * 256 + 40), (0, 0)), ((0, 4000, 0, 0), (200000, 4000, 0, 0), (262100, 4000, 0, 0))),
 ], ids=["live_half", "ragged_runs", "first_run_later", "more_tiles_than_are_listed"])
 def test_state_steps_walk_only_tiles_that_see_the_block(usp, hs, hq, hkv, runs, blocks):
-    """Steps in which all, some, one or none of the 256-row query tiles see the block, against the one-launch loop over the
-    same blocks: the same weights (maxima and roundings follow the same walk), sums in fp32 in the same order."""
+    """Steps in which all, some, one or none of the rows see the block, against the one-launch loop over the same blocks.  The
+    first three go to the kernel that splits a workgroup's keys over its waves, the last to the one of 256-row items, with more
+    query tiles than a launch lists; STATE_STEPS below has those that it lists."""
     (s0, n0), (s1, n1) = runs
     Lq, R = n0 + n1, len(blocks)
     gen = torch.Generator(device="cuda").manual_seed(Lq)
@@ -525,3 +526,55 @@ def test_state_steps_walk_only_tiles_that_see_the_block(usp, hs, hq, hkv, runs, 
     # (a call that goes to the kernel for short blocks moves on from other maxima: a bf16 rounding of a weight, 2^-9, apart)
     assert ((o - o1).norm() / o1.norm()).item() <= 2 ** -8
     assert o[~seen.transpose(1, 2)].abs().sum().item() == 0
+
+
+# Rings whose steps go to 256-row items (tests/test_fwd_plans_host.py asks the library's rule), with the query tiles that see the
+# block in every middle step: positions of the rows, then of every block's keys, two runs each.
+STATE_STEPS = [
+    # a rank of a zigzag ring: all of 16 tiles; 13, an odd number and more items than CUs; none, no launch; one; the later run's
+    # eight, an item for every one of 256 CUs
+    ("zigzag_rank", 1, 128, 32, 8, (4096, 2048, 26624, 2048),
+     [(4096, 2048, 26624, 2048), (2048, 2048, 28672, 2048), (5000, 4096, 0, 0), (30000, 4096, 0, 0), (28600, 4096, 0, 0),
+      (14336, 2048, 16384, 2048), (0, 2048, 30720, 2048)], [16, 13, 0, 1, 8]),
+    ("zigzag_rank_head_size_64", 1, 64, 32, 8, (4096, 2048, 26624, 2048),
+     [(4096, 2048, 26624, 2048), (2048, 2048, 28672, 2048), (5000, 4096, 0, 0), (30000, 4096, 0, 0), (28600, 4096, 0, 0),
+      (14336, 2048, 16384, 2048), (0, 2048, 30720, 2048)], [16, 13, 0, 1, 8]),
+    # a batch of two, runs and blocks that end inside a tile: a tile of both runs' rows, few items, a last tile of 216 rows
+    ("ragged_batch_of_two", 2, 128, 16, 8, (1000, 1900, 20000, 1900),
+     [(1000, 1900, 20000, 1900), (21500, 3800, 0, 0), (2500, 3700, 21890, 100), (2899, 1000, 9000, 2800), (0, 1000, 18000, 2800)], [2, 10, 8]),
+    # positions descend from run to run: the first tiles see the block, and the last do not
+    ("later_run_first", 1, 128, 32, 4, (30000, 2304, 100, 1800),
+     [(0, 4104, 0, 0), (20000, 4104, 0, 0), (31000, 4104, 0, 0), (1000, 4104, 0, 0)], [9, 6]),
+]
+
+
+@pytest.mark.parametrize("o_dtype", [tl.BF16, tl.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("name,bs,hs,hq,hkv,rows,blocks,tiles", STATE_STEPS, ids=[c[0] for c in STATE_STEPS])
+def test_state_steps_list_the_tiles_that_see_the_block(usp, name, bs, hs, hq, hkv, rows, blocks, tiles, o_dtype):
+    """Against the one-launch loop over the same blocks, whose walk has the same maxima and roundings.  The state begins as NaN,
+    which the first step does not read; tiles that are not listed keep theirs."""
+    Lq, Lk = rows[1] + rows[3], blocks[0][1] + blocks[0][3]
+    gen = torch.Generator(device="cuda").manual_seed(Lq + hs)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    q, qd = normal(bs, Lq, hq, hs), usp.usp_posdesc(*rows)
+    kd = [usp.usp_posdesc(*b) for b in blocks]
+    kb, vb = [normal(bs, Lk, hkv, hs) for _ in blocks], [normal(bs, Lk, hkv, hs) for _ in blocks]
+    odt = torch.float32 if o_dtype == tl.FP32 else torch.bfloat16
+    o, lse = torch.full((bs, Lq, hq, hs), float("nan"), device="cuda", dtype=odt), torch.full((bs, hq, Lq), float("nan"), device="cuda")
+    state = torch.full((usp.usp_block_attn_fwd_state_bytes(bs, Lq, hq, hs),), 0xFF, dtype=torch.uint8, device="cuda")
+    for i in range(len(blocks)):
+        usp.usp_block_attn_fwd_state(q, kb[i], vb[i], state, o, lse, bs, Lq, Lk, hq, hkv, hs, 0.0, True, qd, kd[i], i == 0,
+                                     i == len(blocks) - 1, o_dtype)
+    o1, lse1 = torch.empty_like(o), torch.empty_like(lse)
+    usp.usp_ring_attn_fwd(q, kb, vb, kd, o1, lse1, bs, Lq, Lk, hq, hkv, hs, 0.0, True, qd, tl.BF16, o_dtype)
+    torch.cuda.synchronize()
+    assert not torch.isnan(lse).any() and not torch.isnan(o.float()).any()
+    assert torch.equal(torch.isinf(lse), torch.isinf(lse1))
+    seen = ~torch.isinf(lse)
+    assert (lse[seen] - lse1[seen]).abs().max().item() <= 1e-4
+    diff = (o.float() - o1.float()).norm(dim=-1) / o1.float().norm(dim=-1).clamp_min(1e-30)
+    assert diff.max().item() <= 2 ** -6 and ((o.float() - o1.float()).norm() / o1.float().norm()).item() <= 2 ** -8
+    assert o[~seen.transpose(1, 2)].float().abs().sum().item() == 0
