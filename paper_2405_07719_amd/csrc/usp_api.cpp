@@ -551,10 +551,13 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
 // tiles are cut, into which pieces, by playing the launch through for a number of cuts.  Items are dealt heaviest first, a
 // tile's pieces that it sees nothing of are none, and a partial result holds only the rows that see its piece, so that the
 // room for three whole ones is room for four or five.  Measured against equal pieces for the last tiles, every pair of tile and
-// piece an item (an empty one took 9 us to write zeros), whole usp_attn_fwd of one rank, us: 32/8 heads, U 8: L = 6144 68.6 ->
-// 65.6, 8192 95.2 -> 91.1, 10240 145 -> 129, 12288 180 -> 168, 16384 272 -> 272, 20480 425 -> 403, 24576 593 -> 570; U 4 x R 2,
-// L = 16384 333 -> 287; U 8 x R 2, L = 40960 1001 -> 820; R 8, L = 8192 129 -> 111; head size 64, U 8, L = 12288 118 -> 106.
-// Without a mask (all pieces seen, all items alike) no difference.  The answer is within the room that callers have been told.
+// piece an item (an empty one took 9 us to write zeros), whole usp_attn_fwd of one rank, us: 32/8 heads, U 8: L = 6144 70.9 ->
+// 65.9, 8192 97.2 -> 90.6, 10240 147 -> 127, 12288 181 -> 168, 16384 275 -> 274, 20480 428 -> 405, 24576 594 -> 569; U 4 x R 2,
+// L = 16384, rank 0 292 -> 278, 7 337 -> 287; U 8 x R 2, L = 40960, rank 0 1000 -> 828, 8 820 -> 826; R 8, L = 8192, rank 0 131 -> 118,
+// 7 133 -> 132; head size 64, U 8, L = 12288 119 -> 105.  500 random ranks 1.09 times as fast, five of them slower by more than
+// 2 % (rings of four and eight contiguous blocks, whose equal items just do not fit the CUs once more; a head size 128 without a
+// mask, whole items first).  Without a mask (all pieces seen, all items alike) no difference.  The answer is within the room that
+// callers have been told.
 constexpr int kMaxMergeRowParts = 8;   // (launch_lse_merge)
 ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) {
   ItemPlan best;
@@ -752,10 +755,12 @@ int heavy_max_pieces(const usp_problem& p) {
 
 // Short sequences: whether all ranks of a range go through the one launch of wave_split_attn_fwd.hip instead of two to
 // four launches per rank, one rank after the other.  Those take at least 30 us (25 at head size 64) per rank and run at
-// 1.15 (0.8) PFLOP/s beyond that, the one launch as wave_split_us() says.  Measured, per-rank launches against the one:
-// 32/8 heads, U 8, one rank: L = 1024 45 / 13 us, 2048 46 / 19, 4096 52 / 39, 6144 72 / 80; without a mask L = 3072
-// 50 / 47, 4096 59 / 63; U 1 (32 heads): L = 1024 41 / 37, 1536 55 / 62; head size 64, U 8: L = 4096 39 / 23, 6144 51 / 42;
-// all four ranks of 8/4 heads, U 2 x R 2: L = 1024 121 / 13, 4096 182 / 74.
+// 1.15 (0.8) PFLOP/s beyond that, the one launch as wave_split_us() says.  Measured, per-rank launches against the one, us:
+// 32/8 heads, U 8, one rank: L = 1024 37 / 11, 2048 34 / 18, 3072 37 / 24, 4096 43 / 37, 5120 54 / 59, 6144 68 / 79; without a mask
+// L = 3072 45 / 45, 4096 57 / 64; batch of two L = 2048 42 / 23, 4096 71 / 73; U 1 (32 heads): L = 1024 39 / 31, 1536 52 / 53; head
+// size 64, U 8: L = 4096 34 / 23, 6144 47 / 43, 8192 65 / 70, without a mask L = 4096 41 / 36, 6144 67 / 74; all four ranks of 8/4
+// heads, U 2 x R 2: L = 1024 116 / 12, 4096 176 / 73.  (Two near the line that it has on the other side: batch of two, L = 3072
+// 53 / 47; head size 64, U 1, L = 2048 52 / 43.)
 bool short_in_one_launch(const usp_problem& p, int n_ranks) {
   const int64_t Lq = p.L / p.ring;
   const int heads = p.bs * (p.hc / p.ulysses);

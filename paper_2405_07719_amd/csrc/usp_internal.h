@@ -215,8 +215,8 @@ int launch_wave_split_block_fwd(const void* q, const void* k, const void* v, voi
                                 const RingState* state = nullptr);
 // Time of such a launch, in us: rounds of one workgroup (32 rows of a head; two at head size 64) per CU, 4 us each for its
 // first loads and the merge of its waves, and 0.6 PFLOP/s, where reading every key for only 32 rows leaves it.  Measured
-// (this formula): one rank of four heads, causal, L = 4096 38 us (41), 8192 128 (134); 32 heads, L = 1024 37 (34),
-// 2048 92 (93); four heads of size 64, L = 4096 23 (22), 6144 42 (44).
+// (this formula): one rank of four heads, causal, L = 4096 34 us (41), 8192 116 (134); 32 heads, L = 1024 31 (34),
+// 2048 80 (93); four heads of size 64, L = 4096 22 (22), 6144 40 (44).
 inline double wave_split_us(int64_t rows, int heads, int hs, double flop) {
   const int64_t wgs = (rows + 31) / 32 * heads, round = hs == 64 ? 2 * kPlanCUs : kPlanCUs;
   return 4.0 + 4.0 * (double)((wgs + round - 1) / round) + flop / 0.6e9;
@@ -252,11 +252,11 @@ inline int wave_split_fp32_rows(int64_t Lq, int64_t heads, int64_t key_tiles, in
 // shards of 34 rows 16 for 9.  They cross where that makes up for the rows' offsets, counted in rounds of the eight waves and half
 // in tiles, for the waves share what loads: at head size 128 and 32 rows per workgroup always, in bf16 at head size 64 for a
 // twentieth, else for more.  (In 32 bits: the offset of a tile's last row, jumps included.)  Measured, by shards and crossing, us,
-// a batch of two: 32/8 heads, one rank of U 8 x R 4, shards of 34 rows 18.7, 12.2, of 24 rows 12.3, 9.9; U 4 x R 2, 16/8 heads, all
-// ranks, shards of 130 43.3, 40.8, of 330 150.7, 147.0; fp32, eight heads, U 8 x R 2, all ranks, shards of 34 72.6, 51.4, of 520
-// 4637, 4382; bf16, head size 64, U 8 x R 2, one rank, shards of 100 13.1, 10.5, of 266 30.3, 29.3, U 2 x R 2, all ranks, of 66 8.15,
-// 8.55, of 130 13.1, 13.6; fp32, head size 64, U 8 x R 4, all ranks, of 34 116, 72, U 8 x R 2, one rank, of 200 35.8, 34.9, of 266
-// 78, 81; fp32, 16 rows per workgroup, U 2 x R 2, of 34 9.7, 10.2, of 130 47.4, 51.3.
+// a batch of two: 32/8 heads, one rank of U 8 x R 4, shards of 34 rows 18.9, 12.4, of 24 rows 12.5, 10.4; U 4 x R 2, 16/8 heads, all
+// ranks, shards of 130 43.4, 41.2, of 330 150.6, 148.0; fp32, eight heads, U 8 x R 2, all ranks, shards of 34 72.5, 50.1, of 520
+// 4648, 4421; bf16, head size 64, U 8 x R 2, one rank, shards of 100 13.1, 10.5, of 266 30.0, 29.4, U 2 x R 2, all ranks, of 66 8.4,
+// 8.7, of 130 13.2, 13.5; fp32, head size 64, U 8 x R 4, all ranks, of 34 116, 73, U 8 x R 2, one rank, of 200 36.2, 35.2, of 266
+// 78.3, 80.5; fp32, 16 rows per workgroup, U 2 x R 2, of 34 9.8, 10.1, of 130 47.7, 49.3.
 constexpr int kWaveSplitWaves = 8, kWaveSplitTile = 32;
 enum Cross { kNoCross, kOneCross, kAnyCross };   // kOneCross: a tile crosses once at most
 inline Cross wave_split_crossing(int64_t n, int U, int R, int bs, int64_t row_bytes, int dtype, int hs, int rows) {

@@ -101,29 +101,35 @@ struct WsArgs {
 
 __device__ inline uint64_t times(int n, uint64_t x) { return (uint64_t)(uint32_t)n * x; }
 
-template <int CROSS> struct Tile {
+// What a tile that crosses knows besides: rows from `cross` on lie `jump` bytes further on; or, for any number of crossings, the
+// bytes from the tile's first row to row lane % 32, handed from lane to lane where the rows are loaded.
+template <int CROSS> struct Crossing {};
+template <> struct Crossing<kOneCross> { int cross, jump; };
+template <> struct Crossing<kAnyCross> { int row_at; };
+template <int CROSS> struct Tile : Crossing<CROSS> {
   uint64_t at;          // bytes from the tensor's begin to the tile's first row
   int row_bytes, extent;
   int key0, end;        // its keys
-  int cross, jump;      // kOneCross: rows from `cross` on lie `jump` bytes further on
-  int row_at;           // kAnyCross: bytes from there to row lane % 32, handed from lane to lane where the rows are loaded
   // (!exists: no tile; its loads find nothing in range and give zeros)
-  __device__ Tile(const KeyTiles& tiles, bool exists, int t, int Lk, uint64_t block, uint64_t jump_, int row_bytes_, int row_len, int lane) : row_bytes(row_bytes_) {
+  __device__ Tile(const KeyTiles& tiles, bool exists, int t, int Lk, uint64_t block, uint64_t jump_, int row_bytes_, int row_len) : row_bytes(row_bytes_) {
     key0 = t * kTile;
     end = min(key0 + kTile, Lk);
     at = block;
     if constexpr (CROSS != kNoCross) {
       int in_shard = key0;
       at += times(tiles.by_n.split(in_shard), jump_) + (uint64_t)(uint32_t)key0 * (uint32_t)row_bytes;
-      jump = (int)jump_;
-      cross = (int)tiles.by_n.d - in_shard;
-      const int last = end - 1 - key0;
+      const int last = end - 1 - key0, jump = (int)jump_;
       extent = last * row_bytes + row_len;
       if constexpr (CROSS == kOneCross) {
-        extent += last >= cross ? jump : 0;
+        this->cross = (int)tiles.by_n.d - in_shard;
+        this->jump = jump;
+        extent += last >= this->cross ? jump : 0;
       } else {
         extent += tiles.by_n.div(in_shard + last) * jump;
-        row_at = (lane % kTile) * row_bytes + tiles.by_n.div(in_shard + lane % kTile) * jump;
+        // (the thread's number, not a lane index from the caller: that, passed through, made every instance longer by 10 to 30
+        // instructions; four bf16 ranks of L = 1024 10.93 us for 10.87)
+        const int row = (int)threadIdx.x % kTile;
+        this->row_at = row * row_bytes + tiles.by_n.div(in_shard + row) * jump;
       }
       extent = exists ? extent : 0;
       return;
@@ -141,8 +147,13 @@ template <int CROSS> struct Tile {
   // not cross have their loads to themselves, for instances that wait for all of a tile's loads anyway.
   template <bool kApart = false, typename V, int N, typename Step>
   __device__ void load(V (&x)[N], const void* tensor, int lane_row, Step step, int col) const {
-    if (kApart && CROSS == kOneCross && cross >= kTile) load_from<kNoCross>(x, tensor, lane_row, step, col);
-    else load_from<CROSS>(x, tensor, lane_row, step, col);
+    if constexpr (kApart && CROSS == kOneCross) {
+      if (this->cross >= kTile) {
+        load_from<kNoCross>(x, tensor, lane_row, step, col);
+        return;
+      }
+    }
+    load_from<CROSS>(x, tensor, lane_row, step, col);
   }
   template <int HOW, typename V, int N, typename Step>
   __device__ void load_from(V (&x)[N], const void* tensor, int lane_row, Step step, int col) const {
@@ -152,8 +163,8 @@ template <int CROSS> struct Tile {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       int voff = voff0 + step(i) * row_bytes;
-      if constexpr (HOW == kOneCross) voff += lane_row >= cross - step(i) ? jump : 0;
-      if constexpr (HOW == kAnyCross) voff = __builtin_amdgcn_ds_bpermute((lane_row + step(i)) * 4, row_at) + col;
+      if constexpr (HOW == kOneCross) voff += lane_row >= this->cross - step(i) ? this->jump : 0;
+      if constexpr (HOW == kAnyCross) voff = __builtin_amdgcn_ds_bpermute((lane_row + step(i)) * 4, this->row_at) + col;
       if constexpr (sizeof(V) == 16) x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 0, 0));
       else x[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, 0, 0));
     }
@@ -539,7 +550,7 @@ void wave_split_attn_fwd(const WsArgs a) {
   };
   const int row_bytes = a.kv_heads * HS * (int)sizeof(T);
   auto tile_now = [&](bool exists) {
-    return Tile<CROSS>(a.tiles, exists, turn < na ? turn : turn + skip, a.Lk, block_at * sizeof(T), a.kv_jump * sizeof(T), row_bytes, HS * (int)sizeof(T), lane);
+    return Tile<CROSS>(a.tiles, exists, turn < na ? turn : turn + skip, a.Lk, block_at * sizeof(T), a.kv_jump * sizeof(T), row_bytes, HS * (int)sizeof(T));
   };
   bool more = next_tile();
   // Loads of a tile to come are always issued, with or without one: with a branch round them, what waits for older loads would
