@@ -250,12 +250,12 @@ inline int wave_split_fp32_rows(int64_t Lq, int64_t heads, int64_t key_tiles, in
 
 // Whether tiles cross from one shard of n rows into the next.  By shards there are more of them, and emptier ones: with eight
 // shards of 34 rows 16 for 9.  They cross where that makes up for the rows' offsets, counted in rounds of the eight waves and half
-// in tiles, for the waves share what loads: at head size 128 and 32 rows per workgroup always, in bf16 at head size 64 for a
-// twentieth, else for more.  (In 32 bits: the offset of a tile's last row, jumps included.)  Measured, by shards and crossing, us,
+// in tiles, for the waves share what loads: at head size 128 and 32 rows per workgroup always, in bf16 at head size 64 with four
+// shards and more always and with fewer for a twentieth, else for more.  (In 32 bits: the offset of a tile's last row, jumps included.)  Measured, by shards and crossing, us,
 // a batch of two: 32/8 heads, one rank of U 8 x R 4, shards of 34 rows 18.9, 12.4, of 24 rows 12.5, 10.4; U 4 x R 2, 16/8 heads, all
 // ranks, shards of 130 43.4, 41.2, of 330 150.6, 148.0; fp32, eight heads, U 8 x R 2, all ranks, shards of 34 72.5, 50.1, of 520
-// 4648, 4421; bf16, head size 64, U 8 x R 2, one rank, shards of 100 13.1, 10.5, of 266 30.0, 29.4, U 2 x R 2, all ranks, of 66 8.4,
-// 8.7, of 130 13.2, 13.5; fp32, head size 64, U 8 x R 4, all ranks, of 34 116, 73, U 8 x R 2, one rank, of 200 36.2, 35.2, of 266
+// 4648, 4421; bf16, head size 64, one rank, U 8 x R 2, shards of 100 13.1, 10.5, of 266 30.0, 29.4, U 4 x R 2, contiguous, of 130 10.9,
+// 10.2, of 236 16.9, 15.6, U 4, of 130 7.1, 7.4, U 2 x R 2, all ranks, of 66 8.4, 8.7, of 130 13.2, 13.5; fp32, head size 64, U 8 x R 4, all ranks, of 34 116, 73, U 8 x R 2, one rank, of 200 36.2, 35.2, of 266
 // 78.3, 80.5; fp32, 16 rows per workgroup, U 2 x R 2, of 34 9.8, 10.1, of 130 47.7, 49.3.
 constexpr int kWaveSplitWaves = 8, kWaveSplitTile = 32;
 enum Cross { kNoCross, kOneCross, kAnyCross };   // kOneCross: a tile crosses once at most
@@ -264,7 +264,7 @@ inline Cross wave_split_crossing(int64_t n, int U, int R, int bs, int64_t row_by
   if (bs == 1 || U == 1 || n % T == 0 || (T + (n + T) * (bs - 1)) * row_bytes >= (int64_t)1 << 31) return kNoCross;
   auto cost = [](int64_t tiles) { return 2.0 + (double)((tiles + W - 1) / W) + (double)tiles / W; };
   const int64_t by_shard = (int64_t)R * U * ((n + T - 1) / T), crossing = R * ((U * n + T - 1) / T);
-  const double offsets = hs == 128 && rows == 32 ? 1.0 : dtype == USP_BF16 ? 1.05 : 1.07;
+  const double offsets = (hs == 128 && rows == 32) || (dtype == USP_BF16 && U >= 4) ? 1.0 : dtype == USP_BF16 ? 1.05 : 1.07;
   if (cost(by_shard) <= offsets * cost(crossing)) return kNoCross;
   return n < T ? kAnyCross : kOneCross;
 }
