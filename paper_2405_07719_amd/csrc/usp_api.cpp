@@ -554,10 +554,10 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
 // piece an item (an empty one took 9 us to write zeros), whole usp_attn_fwd of one rank, us: 32/8 heads, U 8: L = 6144 70.9 ->
 // 65.9, 8192 97.2 -> 90.6, 10240 147 -> 127, 12288 181 -> 168, 16384 275 -> 274, 20480 428 -> 405, 24576 594 -> 569; U 4 x R 2,
 // L = 16384, rank 0 292 -> 278, 7 337 -> 287; U 8 x R 2, L = 40960, rank 0 1000 -> 828, 8 820 -> 826; R 8, L = 8192, rank 0 131 -> 118,
-// 7 133 -> 132; head size 64, U 8, L = 12288 119 -> 105.  500 random ranks 1.09 times as fast, five of them slower by more than
-// 2 % (rings of four and eight contiguous blocks, whose equal items just do not fit the CUs once more; a head size 128 without a
-// mask, whole items first).  Without a mask (all pieces seen, all items alike) no difference.  The answer is within the room that
-// callers have been told.
+// 7 133 -> 132; head size 64, U 8, L = 12288 119 -> 105.  500 random ranks 1.09 times as fast, three of them slower by more than
+// 2 %; known to be slower: rings of four and eight contiguous blocks whose equal items just do not fit the CUs once more (32/1 heads,
+// R 4, L = 3776 82 -> 84; R 8, 4448 82 -> 91), and without a mask 18 tiles of 16 heads (U 2, L = 4444 180 -> 185).  The answer is
+// within the room that callers have been told.
 constexpr int kMaxMergeRowParts = 8;   // (launch_lse_merge)
 ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) {
   ItemPlan best;

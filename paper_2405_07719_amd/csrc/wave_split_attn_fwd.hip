@@ -19,8 +19,8 @@
 // V in front of the others' K.  So Q is loaded once and shared through LDS, V is asked for behind the barrier that this
 // needs anyway, and the next tile's K and V while a tile is worked on (a tile of a walk took 3.3 thousand cycles with its
 // loads waited for).  All that does not depend on the workgroup is worked out on the host.  Together: four fp32 ranks of
-// L = 256 9.3 -> 8.6 us (6.5 with 16 rows per workgroup, see launch()), four bf16 ranks of L = 1024 12.1 -> 10.9, one of eight ranks of L = 2048 (32 heads on 8) 18.7 ->
-// 16.6, all eight 90.6 -> 79.0, fp32 at L = 2048 (eight heads of size 64, two ranks a ring) 47.1 -> 43.0.
+// L = 256 9.3 -> 8.6 us (6.5 with 16 rows per workgroup, wave_split_fp32_rows()), four bf16 ranks of L = 1024 12.1 -> 10.9, one of
+// eight ranks of L = 2048 (32 heads on 8) 18.7 -> 16.6, all eight 90.6 -> 79.0, fp32 at L = 2048 (eight heads of size 64, two ranks a ring) 47.1 -> 43.0.
 // Large problems: every workgroup reads all its keys for only 32 rows, eight times the L2 and LDS traffic per product of the
 // 256-row kernel.  Where the line between the two lies is in usp_api.cpp (short_in_one_launch).  fp32: the matrix core at
 // fp32 rate, 125 TFLOP/s at L = 2048, four heads of size 128, no mask (154 is what a large fp32 matrix product reaches).
@@ -371,7 +371,7 @@ template <int HS, int CROSS> struct Operands<float, HS, 32, CROSS> : Rows32 {
 };
 
 // fp32, 16 rows per workgroup, v_mfma_f32_16x16x4_f32: for grids that leave half the chip idle, and where the matrix core at
-// fp32 rate is the longest part of a workgroup's time (rule in launch()).  Four k indices: the lane quarters.
+// fp32 rate is the longest part of a workgroup's time (rule in wave_split_fp32_rows()).  Four k indices: the lane quarters.
 template <int HS, int CROSS> struct Operands<float, HS, 16, CROSS> : Rows16 {
   static constexpr int NB = HS / 16, VH = NB / 4, KC = HS / 16, CPR = HS / 4;
   static constexpr int kBlocks = NB;
