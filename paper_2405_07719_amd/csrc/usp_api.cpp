@@ -556,7 +556,7 @@ HeavyChoice work_out_heavy_choice(const usp_problem& p, int r) {
 // L = 16384, rank 0 292 -> 278, 7 337 -> 287; U 8 x R 2, L = 40960, rank 0 1000 -> 828, 8 820 -> 826; R 8, L = 8192, rank 0 131 -> 118,
 // 7 133 -> 132; head size 64, U 8, L = 12288 119 -> 105.  500 random ranks 1.09 times as fast, three of them slower by more than
 // 2 %; known to be slower: rings of four and eight contiguous blocks whose equal items just do not fit the CUs once more (32/1 heads,
-// R 4, L = 3776 82 -> 84; R 8, 4448 82 -> 91), and without a mask 18 tiles of 16 heads (U 2, L = 4444 180 -> 185).  The answer is
+// R 4, L = 3776 82 -> 84; R 8, 4448 82 -> 86 to 91), and without a mask 18 tiles of 16 heads (U 2, L = 4444 180 -> 185).  The answer is
 // within the room that callers have been told.
 constexpr int kMaxMergeRowParts = 8;   // (launch_lse_merge)
 ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) {
