@@ -154,6 +154,49 @@ __device__ inline float both_halves_sum(float x) {
   return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
 }
 
+// The caller's tensors lie anywhere (a view may begin at any element): accesses that claim no more than an element's
+// alignment.  On this chip they are the same 16-byte instructions, which take any address.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// A wave's 32 finished rows (accumulators acc[db]: this lane has dims 32 db + 8 j + 4 hl .. + 3 of row lane % 32), times f,
+// to memory in whole 128-byte lines.  put(i, row, col, values) stores 16 bytes of the wave's row `row` = 8 i + lane / 8 from
+// element `col` on; eight neighbouring lanes share a line, an instruction has eight rows.
+// Stored from where the products leave them, every instruction touches 32 rows in pieces of 8 or 16 bytes, and the address
+// path of a CU takes a cycle and more for each: 128 such instructions end every item (256 rows at head size 128), 3 to 4 us
+// that its CU does nothing else in.  The exchange through LDS is private to the wave (its instructions keep their order there, so
+// no barrier); the tiles that a workgroup keeps in LDS are no longer read when an item ends.  One rank of eight, us, pieces ->
+// lines: forward of L = 8192 88.1 -> 86.2; backward of L = 2048 65.4 -> 64.2, 8192 275.5 -> 273.1, 32768 3335 -> 3304.
+constexpr int kRowsLdsStride = 144;                    // a line, and one 16-byte chunk more: rows begin in all banks
+constexpr int kRowsLdsBytes = 32 * kRowsLdsStride;     // of one wave
+template <typename OutT, int DB, typename Put>
+__device__ inline void put_rows(char* wave_lds, int lane, const f32x16 (&acc)[DB], float f, Put put) {
+  constexpr bool F32 = sizeof(OutT) == 4;
+  constexpr int DBL = F32 ? 1 : 2;   // 32-dim blocks to a line
+  static_assert(DB % DBL == 0, "whole lines");
+  char* const mine = wave_lds + (lane & 31) * kRowsLdsStride + (lane >> 5) * (F32 ? 16 : 8);
+  const char* const theirs = wave_lds + (lane >> 3) * kRowsLdsStride + (lane & 7) * 16;
+#pragma unroll
+  for (int d0 = 0; d0 < DB; d0 += DBL) {
+#pragma unroll
+    for (int d = 0; d < DBL; ++d)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x16& x = acc[d0 + d];
+        const f32x4 v = {x[4 * j] * f, x[4 * j + 1] * f, x[4 * j + 2] * f, x[4 * j + 3] * f};
+        if constexpr (F32) *(u32x4*)(mine + 32 * j) = __builtin_bit_cast(u32x4, v);
+        else *(u32x2*)(mine + 64 * d + 16 * j) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+      }
+    // (the reads below are of other lanes' writes: the order stays as it is written)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      put(i, 8 * i + (lane >> 3), (d0 * 32) + (lane & 7) * (16 / (int)sizeof(OutT)), *(const u32x4*)(theirs + 8 * i * kRowsLdsStride));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+}
+
 // ---- persistent workgroups that draw their work items from counters ------------------------------------------
 // The hardware deals the workgroups of a grid to the eight XCDs round robin, i.e. every XCD gets the same share,
 // but the XCDs do not run at one speed (each settles at its own clock under the power limit: per-tile times

@@ -164,17 +164,6 @@ __device__ inline void pack_b_operand(const float (&x)[16], bf16x8& lo, bf16x8& 
   hi = __builtin_bit_cast(bf16x8, b);
 }
 
-// a lane's part of a finished row (dims 32 db + 8 j + 4 hl .. + 3, dst at 4 hl), times f, as bf16
-template <int DB>
-__device__ inline void store_bf16_row(__bf16* dst, const f32x16 (&x)[DB], float f) {
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *(u32x2*)(dst + db * 32 + j * 8) = u32x2{pack_bf16(x[db][4 * j] * f, x[db][4 * j + 1] * f),
-                                               pack_bf16(x[db][4 * j + 2] * f, x[db][4 * j + 3] * f)};
-}
-
 // -------------------------------------------------------------------------------------------------
 // What the MFMA kernels need that the caller does not hold, in ONE launch: D_i = sum_e dO_ie O_ie of every query row
 // ([block][bs][heads][L] fp32), and, for tensors that they do not read in place, copies of Q, dO, K and V in head layout
@@ -196,8 +185,6 @@ struct PrepareJob {
 constexpr int kMaxPrepareJobs = 4;
 struct PrepareArgs { PrepareJob job[kMaxPrepareJobs]; int n_jobs; };
 
-// The caller's tensors lie anywhere (a view may begin at any element): loads that claim no more than an element's alignment.
-// On this chip they are the same 16-byte instructions, which take any address.
 typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
 
 template <int HS>
@@ -253,6 +240,36 @@ struct NextItem {
   }
 };
 
+// The end of an item: a wave's finished rows to memory (put_rows), `rows` of them, `pitch` elements apart.  Derived anew from a
+// thread index that the compiler cannot see through, so that nothing of it is kept across the tile loop.
+struct EndOfItem {
+  int lane;
+  char* wave_lds;
+  // lds: room for the eight waves' rows, which nobody reads any more (every step ends on a barrier)
+  __device__ explicit EndOfItem(char* lds) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    wave_lds = lds + __builtin_amdgcn_readfirstlane(tid >> 6) * kRowsLdsBytes;
+  }
+  template <int DB>
+  __device__ void put_bf16(const f32x16 (&x)[DB], float f, __bf16* dst, size_t pitch, int rows) const {
+    put_rows<__bf16>(wave_lds, lane, x, f, [&](int, int r, int col, u32x4 v) {
+      if (r < rows) *(u32x4_any*)(dst + r * pitch + col) = v;
+    });
+  }
+  template <int DB>
+  __device__ void put_f32(const f32x16 (&x)[DB], float f, float* dst, size_t pitch, int rows, bool add) const {
+    put_rows<float>(wave_lds, lane, x, f, [&](int, int r, int col, u32x4 v) {
+      if (r >= rows) return;
+      f32x4_any* d = (f32x4_any*)(dst + r * pitch + col);
+      f32x4 v4 = __builtin_bit_cast(f32x4, v);
+      if (add) v4 += *d;
+      *d = v4;
+    });
+  }
+};
+
 // One work item (number w among the dQ items) of a persistent workgroup.  Item order as the forward kernel's: KV group
 // fastest, then head within group, then query tile, heavy first.
 template <int HS>
@@ -264,6 +281,7 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
   constexpr int STAGE = 2 * KT * USTR;              // K, V
   static_assert(KT * CPR <= NT, "one chunk per thread and tensor");
   static_assert(2 * STAGE <= 256 * USTR, "the two stages lie in the dK/dV items' V rows");
+  static_assert(8 * kRowsLdsBytes <= 256 * USTR, "and so do the waves' finished rows");
     DqItemArgs a;
     a.q = ap->q; a.d_o = ap->d_o; a.lse = ap->lse; a.delta = ap->delta; a.dq = ap->dq;
     a.bs = ap->bs; a.hq = ap->hq; a.hkv = ap->hkv; a.g = ap->g;
@@ -445,20 +463,13 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
     }   // blocks
 
     const unsigned own_ticket = next.begin();
-    if (qrow < row_end && ap->dq_heads) {
-      store_bf16_row((__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + qrow) * ap->dq_heads + h) * HS + 4 * hl, dq, a.scale);
-    } else if (qrow < row_end) {
-      float* dst = a.dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          f32x4 v4 = {dq[db][4 * j] * a.scale, dq[db][4 * j + 1] * a.scale, dq[db][4 * j + 2] * a.scale,
-                      dq[db][4 * j + 3] * a.scale};
-          f32x4* d = (f32x4*)(dst + db * 32 + j * 8);
-          if (a.accumulate) v4 += *d;
-          *d = v4;
-        }
+    const EndOfItem end(lds);
+    if (ap->dq_heads) {
+      __bf16* const dst = (__bf16*)a.dq + (((size_t)(qblk * a.bs + b) * a.Lq + wave_row0) * ap->dq_heads + h) * HS;
+      end.put_bf16(dq, a.scale, dst, (size_t)ap->dq_heads * HS, row_end - wave_row0);
+    } else {
+      float* const dst = a.dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * a.Lq + wave_row0) * a.hq + h) * HS;
+      end.put_f32(dq, a.scale, dst, (size_t)a.hq * HS, row_end - wave_row0, a.accumulate != 0);
     }
     next.finish(own_ticket);
 }
@@ -485,6 +496,7 @@ void bwd_dq_ds_kernel(const BwdArgs) {
   constexpr int CPT = KT * CPR / NT;                // 16 B chunks of K per thread and step
   constexpr int STAGE = KT * USTR;
   static_assert(KT * CPR % NT == 0, "whole chunks per thread");
+  static_assert(8 * kRowsLdsBytes <= 2 * STAGE, "the waves' finished rows fit where the K rows were");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* const lds = smem;                           // [2][STAGE]  K
   char* const ds_all = smem + 2 * STAGE;            // [8 waves][NB blocks] of kDsBlockLds bytes
@@ -625,22 +637,13 @@ void bwd_dq_ds_kernel(const BwdArgs) {
 
     unsigned own_ticket = kNoDraw;
     if (threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
-    if (qrow < Lq && ap->dq_heads) {
-      store_bf16_row((__bf16*)ap->dq + (((size_t)b * Lq + qrow) * ap->dq_heads + h) * HS + 4 * hl, dq, ap->scale);
-    } else if (qrow < Lq) {
-      const float scale = ap->scale;
-      const int accumulate = ap->accumulate;
-      float* dst = ap->dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * Lq + qrow) * hq + h) * HS + 4 * hl;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          f32x4 v4 = {dq[db][4 * j] * scale, dq[db][4 * j + 1] * scale, dq[db][4 * j + 2] * scale,
-                      dq[db][4 * j + 3] * scale};
-          f32x4* d = (f32x4*)(dst + db * 32 + j * 8);
-          if (accumulate) v4 += *d;
-          *d = v4;
-        }
+    const EndOfItem end(lds);
+    if (ap->dq_heads) {
+      __bf16* const dst = (__bf16*)ap->dq + (((size_t)b * Lq + wave_row0) * ap->dq_heads + h) * HS;
+      end.put_bf16(dq, ap->scale, dst, (size_t)ap->dq_heads * HS, Lq - wave_row0);
+    } else {
+      float* const dst = ap->dq + (size_t)kslice * ap->dq_part_stride + (((size_t)b * Lq + wave_row0) * hq + h) * HS;
+      end.put_f32(dq, ap->scale, dst, (size_t)hq * HS, Lq - wave_row0, ap->accumulate != 0);
     }
     if (threadIdx.x == 0) {
       unsigned empty = empty_queues;
@@ -665,6 +668,7 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
   constexpr int STAGE = 2 * QT * USTR;     // Q, dO (each row carries its statistic in the padding, see below)
   constexpr int XOFF = HS * 2;             // byte offset, inside a row, of the extra k-step that holds the statistic
   static_assert(QT * CPR <= NT, "one chunk per thread and tensor");
+  static_assert(8 * kRowsLdsBytes <= BN * USTR, "the waves' finished rows fit where the V rows were");
   static_assert(XOFF + 32 <= USTR, "the extra k-step lives in the row padding");
   char* const v_s = smem;                  // [BN][USTR]: the workgroup's V rows, resident for the whole item
   char* const lds = smem + BN * USTR;      // [2][STAGE]
@@ -965,43 +969,35 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
     }   // query blocks
 
     const unsigned own_ticket = next.begin();
-    if (key_ok && ap->dkdv_heads) {
-      const size_t off = (((size_t)b * a.Lk + key) * ap->dkdv_heads + kvh) * HS + 4 * hl;
-      store_bf16_row((__bf16*)ap->dk[blk] + off, dk, a.scale);
-      store_bf16_row((__bf16*)ap->dv[blk] + off, dv, 1.f);
-    } else if (key_ok) {
+    const EndOfItem end(smem);   // (where the V rows were: the padding behind the query rows keeps its zeros)
+    if (ap->dkdv_heads) {
+      const size_t off = (((size_t)b * a.Lk + wave_key0) * ap->dkdv_heads + kvh) * HS;
+      const size_t pitch = (size_t)ap->dkdv_heads * HS;
+      end.put_bf16(dk, a.scale, (__bf16*)ap->dk[blk] + off, pitch, key_end - wave_key0);
+      end.put_bf16(dv, 1.f, (__bf16*)ap->dv[blk] + off, pitch, key_end - wave_key0);
+    } else {
       const size_t part_stride = ap->dkdv_part_stride;   // > 0: every (head split, query slice) has its own copy
-      const size_t off = (size_t)(hsplit * q_splits + qs) * part_stride + (((size_t)b * a.Lk + key) * a.hkv + kvh) * HS + 4 * hl;
-      float* dkp = ap->dk[blk] + off;
-      float* dvp = ap->dv[blk] + off;
+      const size_t part = (size_t)(hsplit * q_splits + qs) * part_stride;
       if (n_hsplit > 1 && part_stride == 0) {
+        if (key_ok) {
+          const size_t off = (((size_t)b * a.Lk + key) * a.hkv + kvh) * HS + 4 * hl;
+          float* dkp = ap->dk[blk] + off;
+          float* dvp = ap->dv[blk] + off;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+          for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-              atomicAdd(dkp + db * 32 + j * 8 + tt, dk[db][4 * j + tt] * a.scale);
-              atomicAdd(dvp + db * 32 + j * 8 + tt, dv[db][4 * j + tt]);
-            }
+              for (int tt = 0; tt < 4; ++tt) {
+                atomicAdd(dkp + db * 32 + j * 8 + tt, dk[db][4 * j + tt] * a.scale);
+                atomicAdd(dvp + db * 32 + j * 8 + tt, dv[db][4 * j + tt]);
+              }
+        }
       } else {
         const bool add = ap->acc_dkdv[blk] != 0;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            f32x4 k4 = {dk[db][4 * j] * a.scale, dk[db][4 * j + 1] * a.scale, dk[db][4 * j + 2] * a.scale,
-                        dk[db][4 * j + 3] * a.scale};
-            f32x4 v4 = {dv[db][4 * j], dv[db][4 * j + 1], dv[db][4 * j + 2], dv[db][4 * j + 3]};
-            f32x4* kd = (f32x4*)(dkp + db * 32 + j * 8);
-            f32x4* vd = (f32x4*)(dvp + db * 32 + j * 8);
-            if (add) {
-              k4 += *kd;
-              v4 += *vd;
-            }
-            *kd = k4;
-            *vd = v4;
-          }
+        const size_t off = part + (((size_t)b * a.Lk + wave_key0) * a.hkv + kvh) * HS;
+        end.put_f32(dk, a.scale, ap->dk[blk] + off, (size_t)a.hkv * HS, key_end - wave_key0, add);
+        end.put_f32(dv, 1.f, ap->dv[blk] + off, (size_t)a.hkv * HS, key_end - wave_key0, add);
       }
     }
 

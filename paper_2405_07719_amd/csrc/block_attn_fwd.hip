@@ -152,6 +152,10 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   constexpr int VT_TILE_BYTES = HS * KT * 2;   // one transposed tile in global memory: [HS][KT] bf16, contiguous
   constexpr int CHUNKS = KT * HS / 8;      // 16 B chunks per tile (K and V alike)
   constexpr int CPT = CHUNKS / NT;         // chunks per thread
+  // Finished rows leave in whole lines (put_rows).  Only where items are short and many end in fp32 partial results: L = 8192
+  // of Ulysses 8 88.1 -> 86.2 us; in the uncut instances, whose items are 100 us and more, nothing was gained (L = 32768 971
+  // and 972 us) and the registers that it takes at the end changed the tile loop's (L = 212992 0.5 % slower).
+  constexpr bool LINES = MIXED;
   constexpr float kRescaleThreshold = 8.0f;   // in log2 units: P stays below 2^8
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
 
@@ -658,6 +662,12 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
     if (drawing && threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
     // ---- epilogue: normalise, write O (a row that saw no key at all: l = 0 -> O = 0, LSE = -inf)
     // ---- write O (this lane: query l32, dims 32 db + 8 j + 4 hl + 0..3) and LSE
+    static_assert(!LINES || NWAVES * kRowsLdsBytes <= 2 * (KBYTES + VBYTES), "the waves' rows fit where the tiles were");
+    int end_tid = threadIdx.x;
+    if constexpr (LINES) asm volatile("" : "+v"(end_tid));   // (what the rows' exchange derives from it is not kept across the tile loop either)
+    const int end_lane = end_tid & 63;
+    // (every step ends on a barrier: the tiles are no longer read)
+    char* const wave_lds = smem + __builtin_amdgcn_readfirstlane(end_tid >> 6) * kRowsLdsBytes;
     if (STATE && !ap->state_last) {
       // not the last ring step: the state goes back as it is (each store instruction of a wave fills 1 KiB)
 #pragma unroll
@@ -676,44 +686,50 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         const float l_tot = both_halves_sum(l_run[qb]);
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
         const int qrow = wave_row0 + qb * 32 + l32;
-        if (qrow < row_end) {
-          const int row0 = ap->part_row0[blk0], part_rows = a.Lq - row0;
-          float* dst = (float*)ap->o_part[blk0] + (((size_t)b * part_rows + (qrow - row0)) * a.hq + h) * HS + 4 * hl;
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const f32x4 v4 = {oacc[qb][db][4 * j] * inv, oacc[qb][db][4 * j + 1] * inv, oacc[qb][db][4 * j + 2] * inv,
-                                oacc[qb][db][4 * j + 3] * inv};
-              *(f32x4*)(dst + db * 32 + j * 8) = v4;
-            }
-          if (hl == 0)
-            ap->lse_part[blk0][((size_t)b * a.hq + h) * part_rows + (qrow - row0)] = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
-        }
+        const int row0 = ap->part_row0[blk0], part_rows = a.Lq - row0;
+        if (qrow < row_end && hl == 0)
+          ap->lse_part[blk0][((size_t)b * a.hq + h) * part_rows + (qrow - row0)] = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
+        const int base = wave_row0 + qb * 32;
+        float* const dst = (float*)ap->o_part[blk0] + (((size_t)b * part_rows + (base - row0)) * a.hq + h) * HS;
+        put_rows<float>(wave_lds, end_lane, oacc[qb], inv, [&](int, int r, int col, u32x4 v) {
+          if (base + r < row_end) *(u32x4*)(dst + (size_t)r * a.hq * HS + col) = v;
+        });
       }
     } else
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       const float l_tot = both_halves_sum(l_run[qb]);
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-      const int qrow = wave_row0 + qb * 32 + l32;
+      const int base = wave_row0 + qb * 32, qrow = base + l32;
+      if constexpr (LINES) {
+        // (where a row of O lies is worked out once, by the lane that has the row, and handed to those that store it)
+        const long long at = (long long)qo_offset(a, b, min(qrow, row_end - 1), h, HS);
+        long long row_at[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row_at[i] = __shfl(at, 8 * i + (end_lane >> 3));
+        put_rows<OutT>(wave_lds, end_lane, oacc[qb], inv, [&](int i, int r, int col, u32x4 v) {
+          if (base + r < row_end) *(u32x4_any*)((OutT*)a.o + row_at[i] + col) = v;
+        });
+      }
       if (qrow < row_end) {
-        OutT* dst = (per_block && !MIXED) ? (OutT*)ap->o_part[blk0] + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl
-                              : (OutT*)a.o + qo_offset(a, b, qrow, h, HS) + 4 * hl;
+        if constexpr (!LINES) {
+          OutT* dst = per_block ? (OutT*)ap->o_part[blk0] + (((size_t)b * a.Lq + qrow) * a.hq + h) * HS + 4 * hl
+                                : (OutT*)a.o + qo_offset(a, b, qrow, h, HS) + 4 * hl;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+          for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            f32x4 v4 = {oacc[qb][db][4 * j] * inv, oacc[qb][db][4 * j + 1] * inv, oacc[qb][db][4 * j + 2] * inv,
-                        oacc[qb][db][4 * j + 3] * inv};
-            OutT* d = dst + db * 32 + j * 8;
-            if constexpr (sizeof(OutT) == 4) {
-              *(f32x4*)d = v4;
-            } else {
-              u32x2 pk = {pack_bf16(v4[0], v4[1]), pack_bf16(v4[2], v4[3])};
-              *(u32x2*)d = pk;
+            for (int j = 0; j < 4; ++j) {
+              f32x4 v4 = {oacc[qb][db][4 * j] * inv, oacc[qb][db][4 * j + 1] * inv, oacc[qb][db][4 * j + 2] * inv,
+                          oacc[qb][db][4 * j + 3] * inv};
+              OutT* d = dst + db * 32 + j * 8;
+              if constexpr (sizeof(OutT) == 4) {
+                *(f32x4*)d = v4;
+              } else {
+                u32x2 pk = {pack_bf16(v4[0], v4[1]), pack_bf16(v4[2], v4[3])};
+                *(u32x2*)d = pk;
+              }
             }
-          }
+        }
         if (hl == 0) {
           const float lse = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
           ((per_block && !MIXED) ? ap->lse_part[blk0] : a.lse)[((size_t)b * a.hq + h) * a.Lq + qrow] = lse;
