@@ -676,7 +676,12 @@ ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) 
     }
     return best;
   }
-  for (int pieces = 2; pieces <= 4; ++pieces) cut_last(heavy_pieces(p, pieces));
+  // Without a mask all items are as long, and what is left of a last round is dealt out in pieces: in eight it ends sooner than in
+  // four (70 tiles of four heads are 256 items and 24 more, which as 96 pieces kept 96 CUs for a quarter of an item, as 192 pieces
+  // 192 of them for an eighth).  us, up to four pieces -> up to eight: U 8: L = 17776 612 -> 579 (head size 64 384 -> 363), 16704
+  // 563 -> 521, 25728 1209 -> 1195; U 4, L = 9000 332 -> 312; U 2, head size 64, 5216 146 -> 141; U 1, 16 heads, 4368 175 -> 167; of 24
+  // lengths the others as before.  With a mask the lengths below are tried instead.
+  for (int pieces = p.causal ? 4 : kMaxMergeRowParts; pieces >= 2; --pieces) cut_last(heavy_pieces(p, pieces));
   if (p.causal) {
     // pieces of so many keys that every item is about as long; tiles that see no more than one piece are whole
     const int tiles = (int)((Lq + 63) / 64);
