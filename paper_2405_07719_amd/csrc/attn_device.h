@@ -197,6 +197,32 @@ __device__ inline void put_rows(char* wave_lds, int lane, const f32x16 (&acc)[DB
   }
 }
 
+// The other way: a wave's 32 rows of HS bf16 from memory in whole lines, as the products' operands want them (f[ks]: this lane
+// has dims 16 ks + 8 hl .. + 7 of row lane % 32).  load(i, row, col) gives the 16 bytes from element `col` on of row `row` =
+// 8 i + lane / 8.  Loaded as they are wanted, an instruction touches 32 rows: 64 of them, the Q of a workgroup, keep the address
+// path of its CU busy for 1.5 us.  The backward's items, whole backward of one rank, us: Ulysses 8, L = 1024 58.4 -> 56.5, 2048
+// 64.3 -> 62.8, 4096 111.6 -> 109.5, 12288 547 -> 544; Ulysses 2 x ring 4, 4096 120.5 -> 118.2.  (The cut forward was 2 % slower
+// with it, its Q behind the first tiles of K and V: L = 8192 88.8 -> 91.1.)
+template <int HS, typename Load>
+__device__ inline void get_rows(char* wave_lds, int lane, bf16x8 (&f)[HS / 16], Load load) {
+  u32x4 raw[HS / 64][4];
+#pragma unroll
+  for (int c = 0; c < HS / 64; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) raw[c][i] = load(i, 8 * i + (lane >> 3), 64 * c + (lane & 7) * 8);
+  char* const mine = wave_lds + (lane >> 3) * kRowsLdsStride + (lane & 7) * 16;
+  const char* const wanted = wave_lds + (lane & 31) * kRowsLdsStride + (lane >> 5) * 16;
+#pragma unroll
+  for (int c = 0; c < HS / 64; ++c) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(u32x4*)(mine + 8 * i * kRowsLdsStride) = raw[c][i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (as in put_rows)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[4 * c + k] = __builtin_bit_cast(bf16x8, *(const u32x4*)(wanted + 32 * k));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+}
+
 // ---- persistent workgroups that draw their work items from counters ------------------------------------------
 // The hardware deals the workgroups of a grid to the eight XCDs round robin, i.e. every XCD gets the same share,
 // but the XCDs do not run at one speed (each settles at its own clock under the power limit: per-tile times

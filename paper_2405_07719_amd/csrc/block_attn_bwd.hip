@@ -240,6 +240,10 @@ struct NextItem {
   }
 };
 
+// LDS of a dK/dV item: 256 rows of V and two stages of 32 rows of Q and dO, 48 bytes of padding each.  Behind it the waves of
+// either kind of item exchange the rows that they hold in registers (get_rows).
+constexpr int dkdv_lds_bytes(int hs) { return (256 + 4 * 32) * (hs * 2 + 48); }
+
 // The end of an item: a wave's finished rows to memory (put_rows), `rows` of them, `pitch` elements apart.  Derived anew from a
 // thread index that the compiler cannot see through, so that nothing of it is kept across the tile loop.
 struct EndOfItem {
@@ -327,12 +331,14 @@ __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next
 
     bf16x8 qf[KSTEPS], dof[KSTEPS];
     {
-      const size_t off = (size_t)((qblk * a.bs + b) * a.q_rb + (int64_t)rr * a.q_row + (int64_t)h * a.q_head) * HS + 8 * hl;
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        qf[ks] = *(const bf16x8*)((const __bf16*)a.q + off + 16 * ks);
-        dof[ks] = *(const bf16x8*)((const __bf16*)a.d_o + off + 16 * ks);
-      }
+      const size_t off = (size_t)((qblk * a.bs + b) * a.q_rb + (int64_t)wave_row0 * a.q_row + (int64_t)h * a.q_head) * HS;
+      char* const rows_lds = lds + dkdv_lds_bytes(HS) + wave * kRowsLdsBytes;
+      const int last = row_end - 1 - wave_row0;   // (negative: this wave has no rows; it loads the tile's last one)
+      auto row_of = [&](const void* t) {
+        return [=](int, int r, int col) { return *(const u32x4_any*)((const __bf16*)t + off + (int64_t)min(r, last) * a.q_row * HS + col); };
+      };
+      get_rows<HS>(rows_lds, lane, qf, row_of(a.q));
+      get_rows<HS>(rows_lds, lane, dof, row_of(a.d_o));
     }
     const size_t stat = ((size_t)(qblk * a.bs + b) * a.hq + h) * a.Lq + rr;
     const float lse = a.lse[stat];
@@ -716,9 +722,11 @@ __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& ne
     // do not fit 256 VGPRs: the spills' reloads share the counter of the prefetch loads and stall on them).
     bf16x8 kf[KSTEPS];
     {
-      const size_t off = (size_t)(b * a.kv_rb + (int64_t)kk * a.kv_row + (int64_t)kvh * a.kv_head) * HS + 8 * hl;
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = *(const bf16x8*)((const __bf16*)ap->k[blk] + off + 16 * ks);
+      const __bf16* const kg = (const __bf16*)ap->k[blk] + (size_t)(b * a.kv_rb + (int64_t)wave_key0 * a.kv_row + (int64_t)kvh * a.kv_head) * HS;
+      const int last = key_end - 1 - wave_key0;   // (negative: this wave has no keys; it loads the tile's last one)
+      get_rows<HS>(smem + dkdv_lds_bytes(HS) + wave * kRowsLdsBytes, lane, kf, [&](int, int r, int col) {
+        return *(const u32x4_any*)(kg + (int64_t)min(r, last) * a.kv_row * HS + col);
+      });
       const char* vg = (const char*)((const __bf16*)ap->v[blk] + (size_t)(b * a.kv_rb + (int64_t)kvh * a.kv_head) * HS);
       const uint32_t v_row_bytes = (uint32_t)a.kv_row * HS * 2;
 #pragma unroll
@@ -1118,8 +1126,7 @@ __global__ __launch_bounds__(256) void bwd_convert_kernel(const ConvertArgs a) {
 
 template <int HS, bool PAIR>
 int launch_bwd(const BwdArgs& a, int64_t grid, hipStream_t stream) {
-  constexpr int USTR = HS * 2 + 48;
-  constexpr size_t lds = 256 * USTR + 2 * (2 * 32 * USTR);
+  constexpr size_t lds = dkdv_lds_bytes(HS) + 8 * kRowsLdsBytes;
   static LdsLimitRaised lds_limit;   // per kernel instance
   if (!raise_dynamic_lds_limit((const void*)bwd_kernel<HS, PAIR>, lds, lds_limit)) return USP_ERR_LAUNCH;
   hipLaunchKernelGGL((bwd_kernel<HS, PAIR>), dim3((unsigned)grid), dim3(512), lds, stream, a);
