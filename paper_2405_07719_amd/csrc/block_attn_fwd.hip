@@ -124,7 +124,7 @@ __device__ inline size_t qo_offset(const Args& a, int b, int row, int h, int hs)
 
 // -------------------------------------------------------------------------------------------
 // bf16 MFMA kernel, software pipelined: while the softmax of key tile j runs on the vector ALU,
-// the matrix core already computes the scores of tile j+1, then P(j) V(j).
+// the matrix core already computes the scores of tile j+1, then P(j) V(j) (at head size 64 P(j) V(j) comes a tile later).
 // -------------------------------------------------------------------------------------------
 // VT: the V blocks come in key-tile-transposed layout (usp.h: USP_SEQ_TO_HEAD_VT): per (batch, KV head) tiles of 64
 // keys stored [hs][64 keys], the keys of each group of 16 in the order 0-3, 8-11, 4-7, 12-15.  The A operand of
@@ -157,6 +157,16 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   // and 972 us) and the registers that it takes at the end changed the tile loop's (L = 212992 0.5 % slower).
   constexpr bool LINES = MIXED;
   constexpr float kRescaleThreshold = 8.0f;   // in log2 units: P stays below 2^8
+  // Head size 64: half the products to as many weights, and registers to spare.  The vector ALU is the busier unit (a wave issues
+  // an instruction of it every eight cycles at most, two waves one every four), so P V runs a tile behind, under the next tile's
+  // weights like that tile's scores, and no row maxima are formed while a tile's weights stay within their bound (their sum,
+  // which is formed anyway, tells).  One rank of Ulysses 8, us: L = 32768 601 -> 586, 65536 without a mask 4720 -> 4650, 17776
+  // without a mask 371 -> 357; ring 8, 32768 610 -> 598, its eight steps with a state 667 -> 656.  The products spread evenly between the
+  // weights' instructions instead of where the compiler leaves them: 5 % slower.  At head size 128, where the products take longer
+  // than the weights, it fits the registers and is 1.5 to 4 % slower (L = 32768 963 -> 981, 212992 19990 -> 20770).
+  constexpr bool TRAILING = HS == 64;
+  constexpr float kSumLimit = 256.f;          // of a lane's weights of a tile: P stays below 2^8 here too
+  static_assert(!TRAILING || NQB == 1, "one 32-row block per wave");
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
 
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -358,6 +368,8 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
           }
         }
     };
+
+    float neg_mc = INFINITY;   // TRAILING: -m in the exponent's units; no maximum yet: every weight overflows, and asks for one
 
     // wave-level bounds for the mask decision
     const int wave_row1 = min(row_end, wave_row0 + NQB * 32);
@@ -573,6 +585,93 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
       __syncthreads();
     };
 
+    // ---- TRAILING: one step on tile `it`, whose scores are in s_cur; the scores of tile it + 1 go to s_next, P(it - 1) V(it - 1)
+    //      to the accumulators, P(it) to p_cur
+    auto products_v = [&](int it, const bf16x8 (&p)[PS]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < PS; ++s)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          bf16x8 vf;
+          if constexpr (VT) {
+            vf = *(const bf16x8*)(vbuf + (it & 1) * VBYTES + (db * 32 + l32) * VSTR + 32 * s + 16 * hl);
+          } else {
+            const char* p0 = vbuf + (it & 1) * VBYTES + v_lane_off + (16 * s) * VSTR + db * 64;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * VSTR));
+            vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          }
+          oacc[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[s], oacc[0][db], 0, 0, 0);
+        }
+    };
+    auto trailing_step = [&](auto steady_tag, int it, f32x16 (&s_cur)[NQB][KB], f32x16 (&s_next)[NQB][KB], const bf16x8 (&p_prev)[PS],
+                             bf16x8 (&p_cur)[PS]) __attribute__((always_inline)) {
+      constexpr bool STEADY = decltype(steady_tag)::value;   // a tile before, a next one and one after that exist
+      const bool has1 = STEADY || it + 1 < nt;
+      const bool has2 = STEADY || it + 2 < nt;
+      if (!(it < free_a || (it >= free_b0 && it < free_b1))) {
+        const int key0 = tile_of(it) * KT;
+        const int qp = a.causal ? pos_of(a.qpos, min(wave_row0 + l32, row_end - 1)) : 0;
+#pragma unroll
+        for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int key = key0 + kbk * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
+            const int kp = a.causal ? pos_of(kpos, key) : 0;
+            const bool vis = key < Lk_b && (!a.causal || kp <= qp);
+            s_cur[0][kbk][i] = vis ? s_cur[0][kbk][i] : -INFINITY;
+          }
+      }
+      if (has2) fetch(kg, tile_of(it + 2), kreg);
+      fetch_v(vg, tile_of(it), vreg);
+      __builtin_amdgcn_sched_barrier(0);   // (as in step)
+
+      if (has1) qk(kbuf + ((it + 1) & 1) * KBYTES, s_next);
+      if (STEADY || it > 0) products_v(it - 1, p_prev);
+      auto weights = [&](float n) __attribute__((always_inline)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            u32x4 pk;
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) {
+              const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[0][kbk][half * 8 + 2 * pr], a.scale_log2, n));
+              const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[0][kbk][half * 8 + 2 * pr + 1], a.scale_log2, n));
+              sum += p0 + p1;
+              pk[pr] = pack_bf16(p0, p1);
+            }
+            p_cur[kbk * 2 + half] = __builtin_bit_cast(bf16x8, pk);
+          }
+        return sum;
+      };
+      float sum = weights(neg_mc);
+      if (__any(!(sum <= kSumLimit))) {   // a weight out of bounds, a row's first keys (infinity, or NaN where masked): with the maxima, once more
+        float x = -INFINITY;
+#pragma unroll
+        for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) x = fmaxf(x, s_cur[0][kbk][i]);
+        const float m_new = fmaxf(m_run[0], both_halves_max(x));
+        const float mcn = (m_new == -INFINITY) ? 0.f : m_new * a.scale_log2;
+        const float alpha = __builtin_amdgcn_exp2f(m_run[0] * a.scale_log2 - mcn);   // m_run = -inf -> 0
+        m_run[0] = m_new;
+        neg_mc = (m_new == -INFINITY) ? INFINITY : -mcn;
+        l_run[0] *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[0][db][i] *= alpha;
+        sum = weights(-mcn);
+      }
+      l_run[0] += sum;
+      // K(it+2) replaces K(it), V(it) replaces V(it-2)
+      if (has2) stash(kbuf + (it & 1) * KBYTES, KSTR, kreg);
+      stash_v(vbuf + (it & 1) * VBYTES, vreg);
+      __syncthreads();
+    };
+
     const std::integral_constant<bool, true> steady;
     const std::integral_constant<bool, false> draining;
     if constexpr (STATE) blk0 = 0, blk1 = 1;
@@ -599,6 +698,52 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
       full_extent = (KT - 1) * (int)row_bytes + HS * 2;
       ragged_extent = (Lk_b - full_tiles * KT - 1) * (int)row_bytes + HS * 2;   // (not used when there is no ragged tile)
       v_tile = tile_of(1);
+      if constexpr (TRAILING) {
+        if constexpr (STATE) load_state_sums();   // (K(0) and K(1) ahead of the accumulators, see below)
+        if (nt > 0) {
+          fetch(kg, tile_of(0), kreg);
+          if (nt > 1) fetch(kg, v_tile, vreg);
+        }
+        if constexpr (STATE) load_state_acc();
+        if (nt == 0) continue;
+        stash(kbuf, KSTR, kreg);
+        if (nt > 1) stash(kbuf + KBYTES, KSTR, vreg);
+        __syncthreads();
+        f32x16 s0[NQB][KB], s1[NQB][KB];   // scores of the current and of the next tile
+        bf16x8 p0[PS], p1[PS];             // weights of the tile before and of the current one
+#pragma unroll
+        for (int kbk = 0; kbk < KB; ++kbk) asm volatile("" : "=v"(s1[0][kbk]));   // (undefined, and says so: see below)
+#pragma unroll
+        for (int ks = 0; ks < PS; ++ks) asm volatile("" : "=v"(p0[ks]), "=v"(p1[ks]));
+        qk(kbuf, s0);
+        if constexpr (STATE) {
+#pragma unroll
+          for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(oacc[0][db]));
+          settle(m_run[0]);
+          settle(l_run[0]);
+          neg_mc = (m_run[0] == -INFINITY) ? INFINITY : -m_run[0] * a.scale_log2;
+        }
+        __syncthreads();   // step 0 overwrites K buffer 0 with tile 2
+        int it = 0;
+        auto one = [&]() __attribute__((always_inline)) {
+          trailing_step(draining, it, s0, s1, p0, p1);
+#pragma unroll
+          for (int ks = 0; ks < PS; ++ks) p0[ks] = p1[ks];
+          if (it + 1 < nt) {
+#pragma unroll
+            for (int kbk = 0; kbk < KB; ++kbk) s0[0][kbk] = s1[0][kbk];
+          }
+          ++it;
+        };
+        one();
+        for (; it + 3 < nt; it += 2) {
+          trailing_step(steady, it, s0, s1, p0, p1);
+          trailing_step(steady, it + 1, s1, s0, p1, p0);
+        }
+        while (it < nt) one();
+        products_v(nt - 1, p0);   // (the next block's first V tile is stored two barriers from here)
+        continue;
+      }
       if constexpr (STATE) {
         // Loads return in their order: K(0) and K(1) go ahead of the state, 128 KiB per workgroup, 34 to 68 MiB that all
         // workgroups ask for at once and that took 11 us to arrive, and V(0), first wanted after the softmax, behind it.
@@ -662,12 +807,12 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
     if (drawing && threadIdx.x == 0) own_ticket = queues.begin(empty_queues);
     // ---- epilogue: normalise, write O (a row that saw no key at all: l = 0 -> O = 0, LSE = -inf)
     // ---- write O (this lane: query l32, dims 32 db + 8 j + 4 hl + 0..3) and LSE
-    static_assert(!LINES || NWAVES * kRowsLdsBytes <= 2 * (KBYTES + VBYTES), "the waves' rows fit where the tiles were");
+    static_assert(!LINES || TRAILING || NWAVES * kRowsLdsBytes <= 2 * (KBYTES + VBYTES), "the waves' rows fit where the tiles were");
     int end_tid = threadIdx.x;
     if constexpr (LINES) asm volatile("" : "+v"(end_tid));   // (what the rows' exchange derives from it is not kept across the tile loop either)
     const int end_lane = end_tid & 63;
-    // (every step ends on a barrier: the tiles are no longer read)
-    char* const wave_lds = smem + __builtin_amdgcn_readfirstlane(end_tid >> 6) * kRowsLdsBytes;
+    // (every step ends on a barrier: the tiles are no longer read; but the last P V of TRAILING comes behind it)
+    char* const wave_lds = smem + (TRAILING ? 2 * (KBYTES + VBYTES) : 0) + __builtin_amdgcn_readfirstlane(end_tid >> 6) * kRowsLdsBytes;
     if (STATE && !ap->state_last) {
       // not the last ring step: the state goes back as it is (each store instruction of a wave fills 1 KiB)
 #pragma unroll
@@ -762,7 +907,7 @@ template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STAT
 int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed = nullptr, int n_listed = 0) {
   constexpr int BM = NWAVES * NQB * 32;
   constexpr int KSTR = HS * 2 + 48, VSTR = VT ? KT * 2 + 16 : HS * 2 + 64;
-  constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR));
+  constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR)) + (MIXED && HS == 64 ? NWAVES * kRowsLdsBytes : 0);
   static_assert(BM == 256, "RowTiles");
   std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs> a;
   static_cast<AttnArgs&>(a) = args;
