@@ -124,14 +124,14 @@ __device__ inline size_t qo_offset(const Args& a, int b, int row, int h, int hs)
 
 // -------------------------------------------------------------------------------------------
 // bf16 MFMA kernel, software pipelined: while the softmax of key tile j runs on the vector ALU,
-// the matrix core already computes the scores of tile j+1, then P(j) V(j) (at head size 64 P(j) V(j) comes a tile later).
+// the matrix core already computes the scores of tile j+1, then P(j) V(j) (TRAILING: P(j) V(j) a tile later).
 // -------------------------------------------------------------------------------------------
 // VT: the V blocks come in key-tile-transposed layout (usp.h: USP_SEQ_TO_HEAD_VT): per (batch, KV head) tiles of 64
 // keys stored [hs][64 keys], the keys of each group of 16 in the order 0-3, 8-11, 4-7, 12-15.  The A operand of
 // O^T = V^T P^T (rows = head dims, 8 keys per lane) is then ONE 16-byte row read per product instead of two LDS
 // transpose reads: 32 LDS reads per step and wave (the minimum: one fragment per product) instead of 48, and the
 // LDS pipe, which issues a read every ~7 cycles whatever its width, was the busiest unit of the kernel.
-template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
+template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false, bool TRAILING = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(NWAVES * 64, NWAVES * 64), amdgpu_waves_per_eu(WPE, WPE)))
 void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs>) {
   using Args = std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs>;
@@ -157,16 +157,15 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   // and 972 us) and the registers that it takes at the end changed the tile loop's (L = 212992 0.5 % slower).
   constexpr bool LINES = MIXED;
   constexpr float kRescaleThreshold = 8.0f;   // in log2 units: P stays below 2^8
-  // Head size 64: half the products to as many weights, and registers to spare.  The vector ALU is the busier unit (a wave issues
+  // TRAILING (head size 64, blocks of kTrailingKeys keys and more): half the products to as many weights, and registers to spare.  The vector ALU is the busier unit (a wave issues
   // an instruction of it every eight cycles at most, two waves one every four), so P V runs a tile behind, under the next tile's
   // weights like that tile's scores, and no row maxima are formed while a tile's weights stay within their bound (their sum,
   // which is formed anyway, tells).  One rank of Ulysses 8, us: L = 32768 601 -> 586, 65536 without a mask 4720 -> 4650, 17776
   // without a mask 371 -> 357; ring 8, 32768 610 -> 598, its eight steps with a state 667 -> 656.  The products spread evenly between the
   // weights' instructions instead of where the compiler leaves them: 5 % slower.  At head size 128, where the products take longer
   // than the weights, it fits the registers and is 1.5 to 4 % slower (L = 32768 963 -> 981, 212992 19990 -> 20770).
-  constexpr bool TRAILING = HS == 64;
   constexpr float kSumLimit = 256.f;          // of a lane's weights of a tile: P stays below 2^8 here too
-  static_assert(!TRAILING || NQB == 1, "one 32-row block per wave");
+  static_assert(!TRAILING || (HS == 64 && NQB == 1), "one 32-row block per wave");
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
 
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -647,6 +646,18 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         return sum;
       };
       float sum = weights(neg_mc);
+      if constexpr (STEADY) {
+        // Operand reads eight ahead of the products, then four by four: left alone, ten of the sixteen come in one burst of all
+        // eight waves, behind the barrier.  1 to 1.5 % (the lengths above, us: 562 -> 557, 4328 -> 4262, 344.5 -> 339.5, 573 ->
+        // 569, 636 -> 628); one by one 2 % slower than left alone, pairs six ahead in between.
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+      }
       if (__any(!(sum <= kSumLimit))) {   // a weight out of bounds, a row's first keys (infinity, or NaN where masked): with the maxima, once more
         float x = -INFINITY;
 #pragma unroll
@@ -903,11 +914,11 @@ inline int64_t host_pos_max(const PosDesc32& d, int64_t a, int64_t b) {
   return m;
 }
 
-template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
+template <int HS, int NQB, int NWAVES, int KT, int WPE, typename OutT, bool STATE = false, bool VT = false, bool MIXED = false, bool TRAILING = false>
 int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed = nullptr, int n_listed = 0) {
   constexpr int BM = NWAVES * NQB * 32;
   constexpr int KSTR = HS * 2 + 48, VSTR = VT ? KT * 2 + 16 : HS * 2 + 64;
-  constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR)) + (MIXED && HS == 64 ? NWAVES * kRowsLdsBytes : 0);
+  constexpr size_t lds = 2 * ((size_t)KT * KSTR + (VT ? (size_t)HS * VSTR : (size_t)KT * VSTR)) + (MIXED && TRAILING ? NWAVES * kRowsLdsBytes : 0);
   static_assert(BM == 256, "RowTiles");
   std::conditional_t<STATE || MIXED, ListedArgs, AttnArgs> a;
   static_cast<AttnArgs&>(a) = args;
@@ -959,7 +970,7 @@ int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed
     }
   }
   if (grid > 0x7fffffffll) return USP_ERR_UNSUPPORTED;
-  auto kern = block_attn_fwd_mfma<HS, NQB, NWAVES, KT, WPE, OutT, STATE, VT, MIXED>;
+  auto kern = block_attn_fwd_mfma<HS, NQB, NWAVES, KT, WPE, OutT, STATE, VT, MIXED, TRAILING>;
   static LdsLimitRaised lds_limit;   // per kernel instance
   if (!raise_dynamic_lds_limit((const void*)kern, lds, lds_limit)) return USP_ERR_LAUNCH;
   // one workgroup per CU (its registers and LDS fill a CU), fewer when there are fewer items
@@ -969,6 +980,17 @@ int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed
   const int n_wgs = (int)std::min<int64_t>(grid, compute_units());
   hipLaunchKernelGGL(kern, dim3((unsigned)n_wgs), dim3(NWAVES * 64), lds, stream, a);
   return launch_status();
+}
+
+// Head size 64: every block fills and drains the pipeline of TRAILING, which is a tile longer, with steps that copy scores and
+// weights.  A ring of short blocks loses by it what its long ones gain: one rank, us, without / with: R 4, 962 keys a block 76.2 /
+// 79.8, R 8, 1502 keys 128.5 / 132.3, R 4, 1646 keys 101.5 / 104.0, ring steps with a state, 834 keys 86.6 / 88.5; 1760 keys 47.0 / 46.4,
+// 3600 51.7 / 51.2, 4096 611 / 597.  (The sets swapped from step to step instead of copied: 79.8 -> 77.2, but L = 32768 583 -> 593.)
+constexpr int64_t kTrailingKeys = 2048;
+template <typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
+int launch_mfma_64(const AttnArgs& a, hipStream_t stream, const uint16_t* listed = nullptr, int n_listed = 0) {
+  return a.Lk >= kTrailingKeys ? launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED, true>(a, stream, listed, n_listed)
+                               : launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED>(a, stream, listed, n_listed);
 }
 
 }  // namespace
@@ -1019,21 +1041,21 @@ int launch_ring_attn_fwd(const void* q, const void* const* k_blocks, const void*
   if (v_transposed) {   // V blocks in key-tile-transposed layout (bf16 in and out)
     if (o_dtype != USP_BF16) return USP_ERR_DTYPE;
     return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, __bf16, false, true>(a, stream)
-                     : launch_mfma<64, 1, 8, 64, 2, __bf16, false, true>(a, stream);
+                     : launch_mfma_64<__bf16, false, true>(a, stream);
   }
   if (a.state) {   // the instance that reads and writes the running state of a step-by-step ring
     if (hs == 128)
       return o_dtype == USP_FP32 ? launch_mfma<128, 1, 8, 64, 2, float, true>(a, stream)
                                  : launch_mfma<128, 1, 8, 64, 2, __bf16, true>(a, stream);
-    return o_dtype == USP_FP32 ? launch_mfma<64, 1, 8, 64, 2, float, true>(a, stream)
-                               : launch_mfma<64, 1, 8, 64, 2, __bf16, true>(a, stream);
+    return o_dtype == USP_FP32 ? launch_mfma_64<float, true>(a, stream)
+                               : launch_mfma_64<__bf16, true>(a, stream);
   }
   // 256 query rows per workgroup (8 waves x 32), 64-key tiles, two waves per SIMD
   if (hs == 128)
     return o_dtype == USP_FP32 ? launch_mfma<128, 1, 8, 64, 2, float>(a, stream)
                                : launch_mfma<128, 1, 8, 64, 2, __bf16>(a, stream);
-  if (o_dtype == USP_FP32) return launch_mfma<64, 1, 8, 64, 2, float>(a, stream);
-  return launch_mfma<64, 1, 8, 64, 2, __bf16>(a, stream);
+  if (o_dtype == USP_FP32) return launch_mfma_64<float>(a, stream);
+  return launch_mfma_64<__bf16>(a, stream);
 }
 
 int launch_block_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int bs, int64_t Lq,
@@ -1102,11 +1124,11 @@ int launch_attn_fwd_partials(const void* q, const void* const* k_blocks, const v
     auto go = [&](auto launch) { return launch(a, stream, mixed->listed, mixed->n_listed); };
     if (mixed->v_transposed)
       return hs == 128 ? go(launch_mfma<128, 1, 8, 64, 2, __bf16, false, true, true>)
-                       : go(launch_mfma<64, 1, 8, 64, 2, __bf16, false, true, true>);
+                       : go(launch_mfma_64<__bf16, false, true, true>);
     return hs == 128 ? go(launch_mfma<128, 1, 8, 64, 2, __bf16, false, false, true>)
-                     : go(launch_mfma<64, 1, 8, 64, 2, __bf16, false, false, true>);
+                     : go(launch_mfma_64<__bf16, false, false, true>);
   }
-  return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, float>(a, stream) : launch_mfma<64, 1, 8, 64, 2, float>(a, stream);
+  return hs == 128 ? launch_mfma<128, 1, 8, 64, 2, float>(a, stream) : launch_mfma_64<float>(a, stream);
 }
 
 }  // namespace usp

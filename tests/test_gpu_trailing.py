@@ -1,6 +1,6 @@
-"""The forward at head size 64, whose second product runs a tile behind and which forms row maxima only where the weights leave
-their bound: one to seven key tiles and ragged ones, scores that grow and fall by thousands of powers of two from tile to tile,
-rows that see nothing, several blocks, the running state; V as rows and as transposed tiles.  Against double precision."""
+"""The forward at head size 64, whose second product runs a tile behind in blocks of 2048 keys and more, and which forms row
+maxima there only where the weights leave their bound: one to seven key tiles and ragged ones, scores that grow and fall by
+thousands of powers of two from tile to tile, rows that see nothing, several blocks, the running state.  Against double precision."""
 import pytest
 import torch
 
@@ -33,19 +33,12 @@ STEPS = {"even": [1.0] * 7, "growing": [0.01, 0.3, 1, 10, 100, 300, 1000], "fall
          "up and down": [0.0, 50, 0.1, 500, 0.0, 5000, 1.0]}
 
 
-@pytest.mark.parametrize("how", STEPS)
-@pytest.mark.parametrize("Lk", [1, 64, 65, 128, 192, 250, 256, 320, 447])
-@pytest.mark.parametrize("causal", [False, True])
-def test_one_block_and_two(Lk, how, causal):
-    hq, hkv, Lq = 4, 2, 300
-    gen = torch.Generator(device="cuda").manual_seed(Lk)
-    q = torch.randn((Lq, hq, HS), generator=gen, device="cuda").bfloat16()
-    k, v = (torch.randn((2, Lk, hkv, HS), generator=gen, device="cuda").bfloat16() for _ in range(2))
-    k = (k.float() * torch.tensor(STEPS[how], device="cuda").repeat_interleave(64)[:Lk, None, None]).bfloat16()
-    # the rows begin inside the first block's keys, so that some see little; the second block lies ahead of many of them
+def rings(k, v, q, qd, causal, how):
+    """One block, and two; the second lies behind the first."""
+    Lk, Lq, hq, hkv = k.shape[1], q.shape[0], q.shape[1], k.shape[2]
+    k = (k.float() * torch.tensor(STEPS[how], device="cuda").repeat_interleave(64).repeat(-(-Lk // 448))[:Lk, None, None]).bfloat16()
     first, second = usp.usp_posdesc(5, Lk, 0, 0), usp.usp_posdesc(Lk + 5, Lk, 0, 0)
-    qd = usp.usp_posdesc(0, Lq, 0, 0)
-    qpos, kpos = torch.arange(Lq).cuda(), torch.arange(2 * Lk).cuda() + 5
+    qpos, kpos = torch.arange(qd.start0, qd.start0 + Lq).cuda(), torch.arange(2 * Lk).cuda() + 5
     for n in (1, 2):
         o, lse = torch.full((1, Lq, hq, HS), float("nan"), device="cuda").bfloat16(), torch.full((1, hq, Lq), float("nan"), device="cuda")
         ks, vs = [k[j].contiguous()[None] for j in range(n)], [v[j].contiguous()[None] for j in range(n)]
@@ -53,9 +46,34 @@ def test_one_block_and_two(Lk, how, causal):
         compare(o[0], lse[0], *reference(q, k[:n].flatten(0, 1), v[:n].flatten(0, 1), qpos, kpos[:n * Lk], causal))
 
 
+def draw(seed, Lq, Lk):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.randn((Lq, 4, HS), generator=gen, device="cuda").bfloat16()
+    return q, *(torch.randn((2, Lk, 2, HS), generator=gen, device="cuda").bfloat16() for _ in range(2))
+
+
+# short blocks (the loop without the tile behind) and long ones, whole and ragged; the rows begin ahead of the first key
 @pytest.mark.parametrize("how", STEPS)
-def test_running_state_and_whole_forward(how):
-    L, R, h = 2 * 2 * 1100, 2, 4
+@pytest.mark.parametrize("Lk", [1, 65, 192, 320, 447, 2048, 2049, 2300])
+@pytest.mark.parametrize("causal", [False, True])
+def test_one_block_and_two(Lk, how, causal):
+    q, k, v = draw(Lk, 300, Lk)
+    rings(k, v, q, usp.usp_posdesc(0, 300, 0, 0), causal, how)
+
+
+# long blocks of which the last row sees one to seven tiles, up to a key past a tile
+@pytest.mark.parametrize("how", STEPS)
+@pytest.mark.parametrize("seen", [1, 63, 64, 65, 128, 130, 192, 200, 256, 300, 320, 447])
+def test_few_tiles_of_a_long_block(seen, how):
+    Lq = min(seen + 5, 290)
+    q, k, v = draw(seen, Lq, 2100)
+    rings(k, v, q, usp.usp_posdesc(seen + 5 - Lq, Lq, 0, 0), True, how)
+
+
+@pytest.mark.parametrize("how", STEPS)
+@pytest.mark.parametrize("L", [4400, 2200])
+def test_running_state_and_whole_forward(L, how):
+    R, h = 2, 4
     gen = torch.Generator(device="cuda").manual_seed(7)
     p = usp.problem(1, L, h, h, HS, 1, R, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
     q, k, v = (torch.randn((R, 1, L // R, h, HS), generator=gen, device="cuda") for _ in range(3))
