@@ -18,6 +18,11 @@ CALIB_SOURCES = ["calib_mfma.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU forms
+    # Loops begin on a line of the instruction cache.  The attention kernels' tile loops, instruction for instruction the
+    # same, differ by up to 3.5 % with where they lie, and every change ahead of them moved them (head size 64, no mask, us,
+    # the same loop as it fell / aligned: Ulysses 8, L = 10000 168.9 / 162.7, 17776 357.6 / 351; Ulysses 8 x ring 2,
+    # L = 8256 79.7 / 77.1, 12288 110.7 / 106.9; head size 128 and the backward: no difference).
+    "-falign-loops=64",
     "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
     "-DUSP_BUILDING=1",
