@@ -161,8 +161,8 @@ typedef u32x2 u32x2_any __attribute__((aligned(2)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 
 // A wave's 32 finished rows (accumulators acc[db]: this lane has dims 32 db + 8 j + 4 hl .. + 3 of row lane % 32), times f,
-// to memory in whole 128-byte lines.  put(i, row, col, values) stores 16 bytes of the wave's row `row` = 8 i + lane / 8 from
-// element `col` on; eight neighbouring lanes share a line, an instruction has eight rows.
+// to memory in whole 128-byte lines.  put(c, col, v) stores the rows' lines c: v[i] are 16 bytes of the wave's row 8 i + lane / 8
+// from element `col` on; eight neighbouring lanes share a line, an instruction has eight rows.
 // Stored from where the products leave them, every instruction touches 32 rows in pieces of 8 or 16 bytes, and the address
 // path of a CU takes a cycle and more for each: 128 such instructions end every item (256 rows at head size 128), 3 to 4 us
 // that its CU does nothing else in.  The exchange through LDS is private to the wave (its instructions keep their order there, so
@@ -190,9 +190,10 @@ __device__ inline void put_rows(char* wave_lds, int lane, const f32x16 (&acc)[DB
       }
     // (the reads below are of other lanes' writes: the order stays as it is written)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    u32x4 v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      put(i, 8 * i + (lane >> 3), (d0 * 32) + (lane & 7) * (16 / (int)sizeof(OutT)), *(const u32x4*)(theirs + 8 * i * kRowsLdsStride));
+    for (int i = 0; i < 4; ++i) v[i] = *(const u32x4*)(theirs + 8 * i * kRowsLdsStride);
+    put(d0 / DBL, d0 * 32 + (lane & 7) * (16 / (int)sizeof(OutT)), v);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }

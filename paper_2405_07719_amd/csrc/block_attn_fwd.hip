@@ -847,8 +847,10 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
           ap->lse_part[blk0][((size_t)b * a.hq + h) * part_rows + (qrow - row0)] = l_tot > 0.f ? m_run[qb] * a.scale + __logf(l_tot) : -INFINITY;
         const int base = wave_row0 + qb * 32;
         float* const dst = (float*)ap->o_part[blk0] + (((size_t)b * part_rows + (base - row0)) * a.hq + h) * HS;
-        put_rows<float>(wave_lds, end_lane, oacc[qb], inv, [&](int, int r, int col, u32x4 v) {
-          if (base + r < row_end) *(u32x4*)(dst + (size_t)r * a.hq * HS + col) = v;
+        put_rows<float>(wave_lds, end_lane, oacc[qb], inv, [&](int, int col, const u32x4 (&v)[4]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (const int r = 8 * i + (end_lane >> 3); base + r < row_end) *(u32x4*)(dst + (size_t)r * a.hq * HS + col) = v[i];
         });
       }
     } else
@@ -863,8 +865,10 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         long long row_at[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) row_at[i] = __shfl(at, 8 * i + (end_lane >> 3));
-        put_rows<OutT>(wave_lds, end_lane, oacc[qb], inv, [&](int i, int r, int col, u32x4 v) {
-          if (base + r < row_end) *(u32x4_any*)((OutT*)a.o + row_at[i] + col) = v;
+        put_rows<OutT>(wave_lds, end_lane, oacc[qb], inv, [&](int, int col, const u32x4 (&v)[4]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (base + 8 * i + (end_lane >> 3) < row_end) *(u32x4_any*)((OutT*)a.o + row_at[i] + col) = v[i];
         });
       }
       if (qrow < row_end) {
