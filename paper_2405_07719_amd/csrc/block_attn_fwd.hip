@@ -165,6 +165,10 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   // weights' instructions instead of where the compiler leaves them: 5 % slower.  At head size 128, where the products take longer
   // than the weights, it fits the registers and is 1.5 to 4 % slower (L = 32768 963 -> 981, 212992 19990 -> 20770).
   constexpr float kSumLimit = 256.f;          // of a lane's weights of a tile: P stays below 2^8 here too
+  // No maximum yet: finite, so that a key that is masked has a weight of zero.  With infinity it was NaN, and while a wave had a row
+  // that saw nothing every tile was formed twice: ring steps with a state, L = 32848, ring 8, its own block last 1755 us, first 1610; now 1602
+  // and 1603.
+  constexpr float kNoMaximum = 3.4028235e38f;
   static_assert(!TRAILING || (HS == 64 && NQB == 1), "one 32-row block per wave");
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
 
@@ -368,7 +372,7 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         }
     };
 
-    float neg_mc = INFINITY;   // TRAILING: -m in the exponent's units; no maximum yet: every weight overflows, and asks for one
+    float neg_mc = kNoMaximum;   // TRAILING: -m in the exponent's units; no maximum yet: every weight overflows, and asks for one
 
     // wave-level bounds for the mask decision
     const int wave_row1 = min(row_end, wave_row0 + NQB * 32);
@@ -658,7 +662,7 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
       }
-      if (__any(!(sum <= kSumLimit))) {   // a weight out of bounds, a row's first keys (infinity, or NaN where masked): with the maxima, once more
+      if (__any(!(sum <= kSumLimit))) {   // a weight out of bounds, a row's first keys (infinity): with the maxima, once more
         float x = -INFINITY;
 #pragma unroll
         for (int kbk = 0; kbk < KB; ++kbk)
@@ -668,7 +672,7 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         const float mcn = (m_new == -INFINITY) ? 0.f : m_new * a.scale_log2;
         const float alpha = __builtin_amdgcn_exp2f(m_run[0] * a.scale_log2 - mcn);   // m_run = -inf -> 0
         m_run[0] = m_new;
-        neg_mc = (m_new == -INFINITY) ? INFINITY : -mcn;
+        neg_mc = (m_new == -INFINITY) ? kNoMaximum : -mcn;
         l_run[0] *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -732,7 +736,7 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
           for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(oacc[0][db]));
           settle(m_run[0]);
           settle(l_run[0]);
-          neg_mc = (m_run[0] == -INFINITY) ? INFINITY : -m_run[0] * a.scale_log2;
+          neg_mc = (m_run[0] == -INFINITY) ? kNoMaximum : -m_run[0] * a.scale_log2;
         }
         __syncthreads();   // step 0 overwrites K buffer 0 with tile 2
         int it = 0;
