@@ -164,7 +164,18 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   // without a mask 371 -> 357; ring 8, 32768 610 -> 598, its eight steps with a state 667 -> 656.  The products spread evenly between the
   // weights' instructions instead of where the compiler leaves them: 5 % slower.  At head size 128, where the products take longer
   // than the weights, it fits the registers and is 1.5 to 4 % slower (L = 32768 963 -> 981, 212992 19990 -> 20770).
-  constexpr float kSumLimit = 256.f;          // of a lane's weights of a tile: P stays below 2^8 here too
+  // Row maxima on demand.  A tile whose weights sum up to more than kSumLimit for a lane (a row's first keys: infinity) is formed
+  // again with its maxima, and the accumulators are scaled, at the end of the step, where nothing hides it: 900 cycles of a step's
+  // 2600 if one of the workgroup's 256 rows asks.  Twice within kMovesApart tiles, and the wave watches: it forms the maxima
+  // ahead of the next kWatched tiles' weights, as the other loop does, and lets P V of the tile before finish before it
+  // scales.  The other loop / without watching / with it, one rank of Ulysses 8, us: L = 16384, Q times 1 169 / 165 / 165, 10
+  // 175 / 194 / 183, 30 170 / 208 / 177, scores that rise by 1000 over the length 174 / 231 / 184; no mask, 17776 393 / 362 / 358,
+  // 403 / 405 / 394, 389 / 419 / 383, 407 / 523 / 408.  Watching always costs 5 % (L = 32768 570 -> 601, 17776 349 -> 368).  Limits up to 2^40
+  // instead are as fast, but a row's largest weight is then rarely 1, which bf16 has exactly: O was 12 to 20 % further from 64 bits
+  // with Q times 4 to 16 (as it is: 5 % nearer to 2 % further than the other loop's, and the same with Q times 1).
+  constexpr float kSumLimit = 1024.f;
+  constexpr float kWatchedGrowth = 5.f;       // in log2 units: 32 weights of 2^5 are within the limit
+  constexpr int kMovesApart = 12, kWatched = 32;
   // No maximum yet: finite, so that a key that is masked has a weight of zero.  With infinity it was NaN, and while a wave had a row
   // that saw nothing every tile was formed twice: ring steps with a state, L = 32848, ring 8, its own block last 1755 us, first 1610; now 1602
   // and 1603.
@@ -372,7 +383,11 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         }
     };
 
-    float neg_mc = kNoMaximum;   // TRAILING: -m in the exponent's units; no maximum yet: every weight overflows, and asks for one
+    // TRAILING
+    float neg_mc = kNoMaximum;                     // -m in the exponent's units
+    float late_alpha = 1.f;                        // the accumulators' factor for the maximum's last move,
+    bool late = false;                             // still to come, behind the products of the tile before
+    int last_move = -kMovesApart, watched = 0;     // the tile of the last move; tiles still to be watched
 
     // wave-level bounds for the mask decision
     const int wave_row1 = min(row_end, wave_row0 + NQB * 32);
@@ -607,23 +622,60 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
           oacc[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[s], oacc[0][db], 0, 0, 0);
         }
     };
+    auto scale_late = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[0][db][i] *= late_alpha;
+      late = false;
+    };
+    auto largest = [&](const f32x16 (&s)[NQB][KB]) __attribute__((always_inline)) {
+      float x = -INFINITY;
+#pragma unroll
+      for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x = fmaxf(x, s[0][kbk][i]);
+      return both_halves_max(x);
+    };
+    auto move_maximum = [&](float x) __attribute__((always_inline)) {
+#pragma clang fp contract(off)   // (a row whose maximum stays is scaled by one, exactly)
+      const float m_new = fmaxf(m_run[0], x);
+      const float mcn = (m_new == -INFINITY) ? 0.f : m_new * a.scale_log2;
+      late_alpha = __builtin_amdgcn_exp2f(-neg_mc - mcn);   // no maximum yet: 0
+      m_run[0] = m_new;
+      neg_mc = (m_new == -INFINITY) ? kNoMaximum : -mcn;
+      l_run[0] *= late_alpha;
+    };
     auto trailing_step = [&](auto steady_tag, int it, f32x16 (&s_cur)[NQB][KB], f32x16 (&s_next)[NQB][KB], const bf16x8 (&p_prev)[PS],
                              bf16x8 (&p_cur)[PS]) __attribute__((always_inline)) {
       constexpr bool STEADY = decltype(steady_tag)::value;   // a tile before, a next one and one after that exist
       const bool has1 = STEADY || it + 1 < nt;
       const bool has2 = STEADY || it + 2 < nt;
-      if (!(it < free_a || (it >= free_b0 && it < free_b1))) {
-        const int key0 = tile_of(it) * KT;
-        const int qp = a.causal ? pos_of(a.qpos, min(wave_row0 + l32, row_end - 1)) : 0;
+      const bool need_mask = !(it < free_a || (it >= free_b0 && it < free_b1));
+      if (need_mask | (watched > 0)) {
+        if (need_mask) {
+          const int key0 = tile_of(it) * KT;
+          const int qp = a.causal ? pos_of(a.qpos, min(wave_row0 + l32, row_end - 1)) : 0;
 #pragma unroll
-        for (int kbk = 0; kbk < KB; ++kbk)
+          for (int kbk = 0; kbk < KB; ++kbk)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = key0 + kbk * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
-            const int kp = a.causal ? pos_of(kpos, key) : 0;
-            const bool vis = key < Lk_b && (!a.causal || kp <= qp);
-            s_cur[0][kbk][i] = vis ? s_cur[0][kbk][i] : -INFINITY;
+            for (int i = 0; i < 16; ++i) {
+              const int key = key0 + kbk * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
+              const int kp = a.causal ? pos_of(kpos, key) : 0;
+              const bool vis = key < Lk_b && (!a.causal || kp <= qp);
+              s_cur[0][kbk][i] = vis ? s_cur[0][kbk][i] : -INFINITY;
+            }
+        }
+        if (watched > 0) {
+          --watched;
+          if (late) scale_late();   // (P(it - 2) V(it - 2) is in; a wave that is late is watched)
+          const float x = largest(s_cur);
+          if (__any((x - m_run[0]) * a.scale_log2 > kWatchedGrowth)) {   // (a row's first keys: infinity)
+            move_maximum(x);
+            late = true;
+            watched = kWatched;
           }
+        }
       }
       if (has2) fetch(kg, tile_of(it + 2), kreg);
       fetch_v(vg, tile_of(it), vreg);
@@ -662,23 +714,13 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
       }
-      if (__any(!(sum <= kSumLimit))) {   // a weight out of bounds, a row's first keys (infinity): with the maxima, once more
-        float x = -INFINITY;
-#pragma unroll
-        for (int kbk = 0; kbk < KB; ++kbk)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) x = fmaxf(x, s_cur[0][kbk][i]);
-        const float m_new = fmaxf(m_run[0], both_halves_max(x));
-        const float mcn = (m_new == -INFINITY) ? 0.f : m_new * a.scale_log2;
-        const float alpha = __builtin_amdgcn_exp2f(m_run[0] * a.scale_log2 - mcn);   // m_run = -inf -> 0
-        m_run[0] = m_new;
-        neg_mc = (m_new == -INFINITY) ? kNoMaximum : -mcn;
-        l_run[0] *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[0][db][i] *= alpha;
-        sum = weights(-mcn);
+      if (__any(!(sum <= kSumLimit))) {
+        if (late) scale_late();   // P(it - 1) V(it - 1) is in
+        move_maximum(largest(s_cur));
+        scale_late();
+        sum = weights(neg_mc);
+        if (it - last_move < kMovesApart) watched = kWatched;
+        last_move = it;
       }
       l_run[0] += sum;
       // K(it+2) replaces K(it), V(it) replaces V(it-2)
@@ -756,6 +798,8 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
           trailing_step(steady, it + 1, s1, s0, p1, p0);
         }
         while (it < nt) one();
+        if (late) scale_late();   // P(nt - 2) V(nt - 2) is in
+        last_move -= nt;   // (the next block's tiles are counted from 0 again)
         products_v(nt - 1, p0);   // (the next block's first V tile is stored two barriers from here)
         continue;
       }

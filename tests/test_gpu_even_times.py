@@ -77,3 +77,26 @@ def test_ring_steps_that_begin_with_blocks_that_half_of_the_rows_do_not_see():
     every tile twice, 1.00 where it does not."""
     L, R = 16400, 4      # runs of 2050 rows: waves with rows of both
     assert_ratio(ring_of_steps(L, R, 32, 8, [1, 2, 3, 0]), ring_of_steps(L, R, 32, 8, [0, 1, 2, 3]), 1.04)
+
+
+def forward(q, k, v):
+    """Ulysses rank 0 of 8, head size 64, with a mask."""
+    N, L, hc = 8, q.shape[2] * 8, q.shape[3]
+    p = usp.problem(1, L, hc, k.shape[3], 64, N, 1, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
+    o, lse = torch.zeros_like(q), torch.zeros((N, 1, hc // N, L), device="cuda")
+    ws = torch.zeros(max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)), dtype=torch.uint8, device="cuda")
+    return lambda: usp.usp_attn_fwd(p, q, k, v, o, lse, 0, 1, ws)
+
+
+@pytest.mark.parametrize("scores", ["times 10", "times 30", "rising"])
+def test_scores_whose_maxima_move(scores):
+    """1.18, 1.24 and 1.40 times as long as with those of normal Q and K where every move of a maximum had the tile's weights formed
+    twice; 1.11, 1.08 and 1.12 where a wave whose maxima move often forms them first."""
+    q, k, v = normal(8, 1, 2048, 32, 64), normal(8, 1, 2048, 8, 64), normal(8, 1, 2048, 8, 64)
+    if scores == "rising":      # by 1000 over the length
+        q2, k2 = q.clone(), k.clone()
+        q2[..., 0] = 8.0
+        k2[..., 0] = (torch.arange(16384, device="cuda") * (1000.0 / 16384)).bfloat16().view(8, 1, 2048, 1)
+    else:
+        q2, k2 = (q.float() * float(scores.split()[1])).bfloat16(), k
+    assert_ratio(forward(q2, k2, v), forward(q, k, v), 1.15)

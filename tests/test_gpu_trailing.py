@@ -70,6 +70,31 @@ def test_few_tiles_of_a_long_block(seen, how):
     rings(k, v, q, usp.usp_posdesc(seen + 5 - Lq, Lq, 0, 0), True, how)
 
 
+# Maxima that move twice within a few tiles are watched for 32 tiles after the last move: moves from one tile to the next, at 12
+# tiles' distance and at 13, the last one in the last tile, calm in between and at the end; a mask, a ragged tail, a second block.
+MOVES = {"once": [0], "close, then calm": [0, 3, 4, 5], "twelve and thirteen apart": [0, 12, 25, 37, 50], "every second tile": range(0, 70, 2),
+         "calm, then close": [0, 45, 46, 47], "to the last tile": [0, 2, 34, 66, 69], "watched to the end": [0, 60, 68]}
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("moves", MOVES)
+@pytest.mark.parametrize("Lk", [70 * 64, 69 * 64 + 5])
+def test_maxima_that_move_often(Lk, moves, causal):
+    q, k, v = draw(Lk, 290, Lk)
+    f, height = [], 1.0
+    for tile in range(70):
+        if tile in MOVES[moves]:
+            height *= 1.6 if len(MOVES[moves]) > 6 else 4.0
+        f.append(height if tile in MOVES[moves] else 0.3 * height)
+    k = (k.float() * torch.tensor(f, device="cuda").repeat_interleave(64)[:Lk, None, None]).bfloat16()
+    qd, first, second = usp.usp_posdesc(Lk - 150, 290, 0, 0), usp.usp_posdesc(0, Lk, 0, 0), usp.usp_posdesc(Lk, Lk, 0, 0)
+    qpos, kpos = torch.arange(Lk - 150, Lk + 140).cuda(), torch.arange(2 * Lk).cuda()
+    o, lse = torch.full((1, 290, 4, HS), float("nan"), device="cuda").bfloat16(), torch.full((1, 4, 290), float("nan"), device="cuda")
+    usp.usp_ring_attn_fwd(q[None], [k[:1], k[1:]], [v[:1], v[1:]], [first, second], o, lse, 1, 290, Lk, 4, 2, HS, 0.0, causal, qd, usp.USP_BF16,
+                          usp.USP_BF16)
+    compare(o[0], lse[0], *reference(q, k.flatten(0, 1), v.flatten(0, 1), qpos, kpos, causal))
+
+
 @pytest.mark.parametrize("how", STEPS)
 @pytest.mark.parametrize("L", [4400, 2200])
 def test_running_state_and_whole_forward(L, how):
