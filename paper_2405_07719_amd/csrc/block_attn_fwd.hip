@@ -157,8 +157,8 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
   // and 972 us) and the registers that it takes at the end changed the tile loop's (L = 212992 0.5 % slower).
   constexpr bool LINES = MIXED;
   constexpr float kRescaleThreshold = 8.0f;   // in log2 units: P stays below 2^8
-  // TRAILING (head size 64, blocks of kTrailingKeys keys and more): half the products to as many weights, and registers to spare.  The vector ALU is the busier unit (a wave issues
-  // an instruction of it every eight cycles at most, two waves one every four), so P V runs a tile behind, under the next tile's
+  // TRAILING (head size 64, where second_product_trails()): half the products to as many weights, and registers to spare.  The vector
+  // ALU is the busier unit (a wave issues an instruction of it every eight cycles at most, two waves one every four), so P V runs a tile behind, under the next tile's
   // weights like that tile's scores, and no row maxima are formed while a tile's weights stay within their bound (their sum,
   // which is formed anyway, tells).  One rank of Ulysses 8, us: L = 32768 601 -> 586, 65536 without a mask 4720 -> 4650, 17776
   // without a mask 371 -> 357; ring 8, 32768 610 -> 598, its eight steps with a state 667 -> 656.  The products spread evenly between the
@@ -1034,15 +1034,11 @@ int launch_mfma(const AttnArgs& args, hipStream_t stream, const uint16_t* listed
   return launch_status();
 }
 
-// Head size 64: every block fills and drains the pipeline of TRAILING, which is a tile longer, with steps that copy scores and
-// weights.  A ring of short blocks loses by it what its long ones gain: one rank, us, without / with: R 4, 962 keys a block 76.2 /
-// 79.8, R 8, 1502 keys 128.5 / 132.3, R 4, 1646 keys 101.5 / 104.0, ring steps with a state, 834 keys 86.6 / 88.5; 1760 keys 47.0 / 46.4,
-// 3600 51.7 / 51.2, 4096 611 / 597.  (The sets swapped from step to step instead of copied: 79.8 -> 77.2, but L = 32768 583 -> 593.)
-constexpr int64_t kTrailingKeys = 2048;
 template <typename OutT, bool STATE = false, bool VT = false, bool MIXED = false>
 int launch_mfma_64(const AttnArgs& a, hipStream_t stream, const uint16_t* listed = nullptr, int n_listed = 0) {
-  return a.Lk >= kTrailingKeys ? launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED, true>(a, stream, listed, n_listed)
-                               : launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED>(a, stream, listed, n_listed);
+  const int64_t piece = std::accumulate(a.lk_blk, a.lk_blk + a.n_blocks, int64_t{0}) / a.n_blocks;
+  return second_product_trails(a.Lk, piece) ? launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED, true>(a, stream, listed, n_listed)
+                                            : launch_mfma<64, 1, 8, 64, 2, OutT, STATE, VT, MIXED>(a, stream, listed, n_listed);
 }
 
 }  // namespace

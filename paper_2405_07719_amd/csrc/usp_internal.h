@@ -235,6 +235,16 @@ inline bool block_goes_to_waves(int bs, int64_t Lq, int64_t Lk, int hq, int hs, 
                                   6.0 + std::max(1.75 * (double)Lk / 64 * (hs / 128.0), flop / (hs == 128 ? 1.1e9 : 0.8e9));
 }
 
+// Whether the second product runs a tile behind (block_attn_fwd.hip, TRAILING; head size 64): blocks of Lk keys, of which an item
+// walks `piece` at a time on the average (Lk, where the keys are not cut).  Every block or piece fills and drains a pipeline that is a tile longer, with
+// steps that copy scores and weights.  Without / with it, one rank, us.  Blocks: ring 4, 962 keys 75.4 / 79.5, ring 8, 1502 123.8 / 131.4,
+// ring 4, 1646 99.9 / 101.5, steps with a state, 834 86.3 / 88.5, steps with partial results, 1764 143.4 / 146.5; on the other side
+// 1292 100.8 / 99.4, 1852 187.2 / 185.7, 1928 117.5 / 113.2, 4096 611 / 593.  (An even number of tiles is drained in four such steps, an odd one in
+// three.)  Pieces of blocks that are long enough, most of them without a mask: 888 keys 111.0 / 112.1, 1156 51.1 / 51.8, 1223 129.0 / 132.5,
+// 1270 193.3 / 191.7, 1522 201.5 / 198.9, 1558 212.2 / 205.4, 1751 143.1 / 140.5, 1928 69.0 / 70.1, 2138 210.1 / 206.3; of 23 from 1270 to 2666 keys
+// three lose, 1.6 and 5 % where two pieces under a mask are all that a CU has (L = 4960 85.6 / 89.9).
+inline bool second_product_trails(int64_t Lk, int64_t piece) { return Lk >= 2048 && piece >= 1250; }
+
 // Rows per workgroup of an fp32 launch: 16 where workgroups of 32 leave half of the CUs idle, or, under a causal mask, hold them
 // with items of very different lengths: then only with walks of a twelfth as many key tiles as there are workgroups, for twice
 // as many of these do not fit the chip at once and each has its own first loads and merge.  Measured, 32 and 16 rows, us (in
