@@ -19,15 +19,16 @@ BwdCut plan_bwd_cut(int, int64_t, int64_t, int, int, int, bool, bool) { return B
 """
 RECORDERS = """
 // kind of the last launch that attends: 1 waves, 2 whole, 3 every tile cut, 4 the last tiles cut, 5 listed, 6 a block
-struct Route { int kind, parts, whole, cut, different_rows, launches; };
+struct Route { int kind, parts, whole, cut, different_rows, launches, v_transposed; };
 static Route route;
 int launch_wave_split_usp_fwd(const usp_problem&, const void*, const void*, const void*, void*, float*, int, int, float, hipStream_t) {
   route.kind = 1; ++route.launches;
   return USP_OK;
 }
 int launch_ring_attn_fwd(const void*, const void* const*, const void* const*, const usp_posdesc*, int, void*, float*, int, int64_t, int64_t,
-                         int, int, int, float, int, const usp_posdesc&, int, int, hipStream_t, const SeqLayoutIO*, const RingState*, bool) {
+                         int, int, int, float, int, const usp_posdesc&, int, int, hipStream_t, const SeqLayoutIO*, const RingState*, bool v_transposed) {
   route.kind = 2; ++route.launches;
+  route.v_transposed = v_transposed;
   return USP_OK;
 }
 int launch_attn_fwd_partials(const void*, const void* const*, const void* const*, const usp_posdesc*, const int*, int n_blocks, float* const*,
@@ -35,7 +36,7 @@ int launch_attn_fwd_partials(const void*, const void* const*, const void* const*
                              const SeqLayoutIO*, const MixedLaunch* mixed) {
   route.kind = !mixed ? 3 : mixed->n_listed ? 5 : 4; ++route.launches;
   route.parts = n_blocks;
-  if (mixed) route.cut = mixed->n_split_tiles;
+  if (mixed) route.cut = mixed->n_split_tiles, route.v_transposed = mixed->v_transposed;
   if (mixed && mixed->n_listed) {
     for (int i = 0; i < mixed->n_listed; ++i) ++(mixed->listed[i] >> kListedTileBits == kListedWhole ? route.whole : route.cut);
     for (int j = 1; j < n_blocks; ++j) route.different_rows |= mixed->part_row0[j] != mixed->part_row0[0];
@@ -55,8 +56,8 @@ int launch_layout_a2a_vt(const usp_problem&, int, const void*, void*, int, int, 
 }  // namespace usp
 extern "C" void last_route(int* out) {
   using usp::route;
-  const int r[] = {route.kind, route.parts, route.whole, route.cut, route.different_rows, route.launches};
-  for (int i = 0; i < 6; ++i) out[i] = r[i];
+  const int r[] = {route.kind, route.parts, route.whole, route.cut, route.different_rows, route.launches, route.v_transposed};
+  for (int i = 0; i < 7; ++i) out[i] = r[i];
   route = usp::Route{};
 }
 // ring ranks whose items have been worked out
@@ -102,14 +103,14 @@ class HostSide:
 
     def forward(self, p, rank_begin, rank_end):
         """What usp_attn_fwd launches last: dict of kind, parts (of the keys), whole and cut (listed items; or cut tiles),
-        different_rows (partial results that begin with different rows), launches."""
+        different_rows (partial results that begin with different rows), launches, v_transposed (V in transposed tiles)."""
         ptr = [ctypes.c_void_p(i << 40) for i in range(1, 7)]     # aligned, apart, never followed
         room = ctypes.c_size_t(self.query(p, rank_end - rank_begin))
         st = self.lib.usp_attn_fwd(ctypes.byref(p), *ptr[:5], rank_begin, rank_end, ptr[5], room, None)
-        out = (ctypes.c_int * 6)()
+        out = (ctypes.c_int * 7)()
         self.lib.last_route(out)
         assert st == 0, st
-        return dict(zip(("kind", "parts", "whole", "cut", "different_rows", "launches"), [KINDS[out[0]], *out[1:]]))
+        return dict(zip(("kind", "parts", "whole", "cut", "different_rows", "launches", "v_transposed"), [KINDS[out[0]], *out[1:]]))
 
     def ranks_listed(self, p):
         return self.lib.ranks_listed(ctypes.byref(p))

@@ -5,8 +5,12 @@ import pytest
 import torch
 
 import paper_2405_07719_amd as usp
+from tests.host_side import HostSide, problem
 
-pytestmark = pytest.mark.gpu
+# L, query and KV heads, head size, Ulysses degree of forwards that are cut, with whole items beside the pieces
+CUT = [(4470, 4, 2, 128, 1), (3330, 8, 2, 128, 1), (3100, 16, 8, 64, 1), (5010, 8, 4, 64, 1), (5000, 16, 8, 64, 2)]
+# and of short ones, in the launch that splits keys over waves
+SHORT = [(L, 4, 2, hs, U) for L, U in ((2590, 1), (4100, 1), (3100, 2), (4100, 2)) for hs in (64, 128)]
 
 
 def between_guards(t, at):
@@ -20,16 +24,23 @@ def check(buf, view, at, own):
     assert (buf[:at] == 7.0).all() and (buf[at + own.numel():] == 7.0).all()
 
 
-@pytest.mark.parametrize("hs", [64, 128])
-@pytest.mark.parametrize("L,U", [(2590, 1), (4100, 1), (3100, 2), (4100, 2)])
-def test_forward_that_is_cut(L, U, hs):
+def test_routes(tmp_path):
+    host = HostSide(tmp_path)
+    for L, hc, hk, hs, U in CUT + SHORT:
+        route = host.forward(problem(1, L, hc, hk, hs, U, 1), 0, 1)
+        assert route["kind"] == ("listed" if (L, hc, hk, hs, U) in CUT else "waves"), (L, hs, U, route)
+        assert (L, hc, hk, hs, U) in SHORT or (route["whole"] > 0 and route["cut"] > 0), (L, hs, U, route)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,hc,hk,hs,U", CUT + SHORT)
+def test_forward(L, hc, hk, hs, U):
     gen = torch.Generator(device="cuda").manual_seed(L)
-    q = torch.randn((U, 1, L // U, 4, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
-    k, v = (torch.randn((U, 1, L // U, 2, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
-    p = usp.problem(1, L, 4, 2, hs, U, 1, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
-    assert usp.usp_attn_fwd_workspace_bytes(p, 1) > 0
-    ws = torch.full((usp.usp_attn_fwd_workspace_bytes(p, U),), 255, dtype=torch.uint8, device="cuda")
-    own, lse = torch.zeros_like(q), torch.zeros((U, 1, 4 // U, L), device="cuda")
+    q = torch.randn((U, 1, L // U, hc, hs), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k, v = (torch.randn((U, 1, L // U, hk, hs), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    p = usp.problem(1, L, hc, hk, hs, U, 1, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
+    ws = torch.full((max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)),), 255, dtype=torch.uint8, device="cuda")
+    own, lse = torch.zeros_like(q), torch.zeros((U, 1, hc // U, L), device="cuda")
     for rank in range(U):
         usp.usp_attn_fwd(p, q, k, v, own, lse, rank, rank + 1, ws)
     for at in (1, 3, 8):
@@ -40,12 +51,14 @@ def test_forward_that_is_cut(L, U, hs):
     # against double precision: weights and O rounded to bf16, 2^-9 relative each
     qd, kd, vd = (x.double().transpose(0, 1).reshape(L, -1, hs) for x in (q, k, v))
     hidden = torch.ones((L, L), dtype=torch.bool, device="cuda").triu(1)
-    ref = torch.stack([(qd[:, h] @ kd[:, h // 2].T * hs ** -0.5).masked_fill(hidden, float("-inf")).softmax(-1) @ vd[:, h // 2]
-                       for h in range(4)], 1)
-    got = own.double().transpose(0, 1).reshape(L, 4, hs)
-    assert ((got - ref).norm() / ref.norm()).item() < 2 ** -7
+    got = own.double().transpose(0, 1).reshape(L, hc, hs)
+    for h in range(0, hc, 3):
+        j = h // (hc // hk)
+        ref = (qd[:, h] @ kd[:, j].T * hs ** -0.5).masked_fill(hidden, float("-inf")).softmax(-1) @ vd[:, j]
+        assert ((got[:, h] - ref).norm() / ref.norm()).item() < 2 ** -7
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("hs", [64, 128])
 @pytest.mark.parametrize("L", [40, 1030, 2590])
 def test_gradients(L, hs):

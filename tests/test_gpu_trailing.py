@@ -1,12 +1,13 @@
 """The forward at head size 64, whose second product runs a tile behind in blocks of 2048 keys and more, and which forms row
 maxima there only where the weights leave their bound: one to seven key tiles and ragged ones, scores that grow and fall by
-thousands of powers of two from tile to tile, rows that see nothing, several blocks, the running state.  Against double precision."""
+thousands of powers of two from tile to tile, rows that see nothing, several blocks, V in transposed tiles, cut forwards, the running
+state; the routes on the CPU.  Against double precision."""
 import pytest
 import torch
 
 import paper_2405_07719_amd as usp
+from tests.host_side import HostSide, problem
 
-pytestmark = pytest.mark.gpu
 HS = 64
 
 
@@ -33,6 +34,14 @@ STEPS = {"even": [1.0] * 7, "growing": [0.01, 0.3, 1, 10, 100, 300, 1000], "fall
          "up and down": [0.0, 50, 0.1, 500, 0.0, 5000, 1.0]}
 
 
+def transposed(v):
+    """A block's V [1][keys][heads][64] in transposed tiles."""
+    _, Lk, hkv, _ = v.shape
+    t = torch.full((1, hkv, (Lk + 63) // 64, HS, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    usp.usp_layout_a2a(usp.problem(1, Lk, hkv, hkv, HS, 1, 1, False, usp.USP_SPLIT_CONTIG, usp.USP_BF16), hkv, usp.USP_SEQ_TO_HEAD_VT, v, t, 0, 1)
+    return t
+
+
 def rings(k, v, q, qd, causal, how):
     """One block, and two; the second lies behind the first."""
     Lk, Lq, hq, hkv = k.shape[1], q.shape[0], q.shape[1], k.shape[2]
@@ -44,6 +53,10 @@ def rings(k, v, q, qd, causal, how):
         ks, vs = [k[j].contiguous()[None] for j in range(n)], [v[j].contiguous()[None] for j in range(n)]
         usp.usp_ring_attn_fwd(q[None], ks, vs, [first, second][:n], o, lse, 1, Lq, Lk, hq, hkv, HS, 0.0, causal, qd, usp.USP_BF16, usp.USP_BF16)
         compare(o[0], lse[0], *reference(q, k[:n].flatten(0, 1), v[:n].flatten(0, 1), qpos, kpos[:n * Lk], causal))
+        # V in transposed tiles: the same products in the same order
+        o1, lse1 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
+        usp.usp_ring_attn_fwd_vt(q[None], ks, [transposed(x) for x in vs], [first, second][:n], o1, lse1, 1, Lq, Lk, hq, hkv, HS, 0.0, causal, qd)
+        assert torch.equal(o1.view(torch.int16), o.view(torch.int16)) and torch.equal(lse1.view(torch.int32), lse.view(torch.int32))
 
 
 def draw(seed, Lq, Lk):
@@ -53,6 +66,7 @@ def draw(seed, Lq, Lk):
 
 
 # short blocks (the loop without the tile behind) and long ones, whole and ragged; the rows begin ahead of the first key
+@pytest.mark.gpu
 @pytest.mark.parametrize("how", STEPS)
 @pytest.mark.parametrize("Lk", [1, 65, 192, 320, 447, 2048, 2049, 2300])
 @pytest.mark.parametrize("causal", [False, True])
@@ -62,6 +76,7 @@ def test_one_block_and_two(Lk, how, causal):
 
 
 # long blocks of which the last row sees one to seven tiles, up to a key past a tile
+@pytest.mark.gpu
 @pytest.mark.parametrize("how", STEPS)
 @pytest.mark.parametrize("seen", [1, 63, 64, 65, 128, 130, 192, 200, 256, 300, 320, 447])
 def test_few_tiles_of_a_long_block(seen, how):
@@ -76,6 +91,7 @@ MOVES = {"once": [0], "close, then calm": [0, 3, 4, 5], "twelve and thirteen apa
          "calm, then close": [0, 45, 46, 47], "to the last tile": [0, 2, 34, 66, 69], "watched to the end": [0, 60, 68]}
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("moves", MOVES)
 @pytest.mark.parametrize("Lk", [70 * 64, 69 * 64 + 5])
@@ -95,26 +111,79 @@ def test_maxima_that_move_often(Lk, moves, causal):
     compare(o[0], lse[0], *reference(q, k.flatten(0, 1), v.flatten(0, 1), qpos, kpos, causal))
 
 
+def factors(how, n):
+    """Of the scores of n keys."""
+    return torch.tensor(STEPS[how], device="cuda").repeat_interleave(64).repeat(-(-n // 448))[:n, None, None]
+
+
+# Batch, L, query and KV heads, Ulysses and ring degree, mask; the launch, V in transposed tiles.  Long enough for the tile behind.
+WHOLE = [((1, 8850, 4, 4, 1, 1, True), "listed", 0), ((1, 9004, 8, 2, 1, 2, True), "listed", 0), ((2, 9004, 8, 8, 2, 1, False), "listed", 1),
+         ((2, 6200, 8, 2, 2, 1, False), "whole", 1), ((1, 5204, 16, 16, 1, 2, False), "whole", 0)]
+
+
+def test_routes(tmp_path):
+    host = HostSide(tmp_path)
+    for (bs, L, hc, hk, U, R, causal), kind, v_transposed in WHOLE:
+        route = host.forward(problem(bs, L, hc, hk, HS, U, R, causal), 0, 1)
+        assert (route["kind"], route["v_transposed"]) == (kind, v_transposed), (L, route)
+        assert L // R >= 2048 and (kind == "whole" or L // route["parts"] >= 1250), (L, route)
+    for h, n in STATES:
+        assert not host.lib.block_goes_to_waves(1, host.long(n), host.long(n), h, HS, 1, usp.USP_BF16)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("how", STEPS)
-@pytest.mark.parametrize("L", [4400, 2200])
-def test_running_state_and_whole_forward(L, how):
-    R, h = 2, 4
-    gen = torch.Generator(device="cuda").manual_seed(7)
-    p = usp.problem(1, L, h, h, HS, 1, R, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
-    q, k, v = (torch.randn((R, 1, L // R, h, HS), generator=gen, device="cuda") for _ in range(3))
-    f = torch.tensor(STEPS[how], device="cuda").repeat_interleave(64).repeat(-(-L // R // 448))[:L // R]
-    q, k, v = q.bfloat16(), (k * f[None, None, :, None, None]).bfloat16(), v.bfloat16()
+@pytest.mark.parametrize("shape", [x for x, _, _ in WHOLE], ids=str)
+def test_whole_forward(shape, how):
+    bs, L, hc, hk, U, R, causal = shape
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    p = usp.problem(bs, L, hc, hk, HS, U, R, causal, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
+    N, h = U * R, hc // U
+    q, k, v = (torch.randn((N, bs, L // N, n, HS), generator=gen, device="cuda").bfloat16() for n in (hc, hk, hk))
     pos = [usp.usp_local_positions(p, r, 0)[1] for r in range(R)]
     at = [torch.cat([torch.arange(d.start0, d.start0 + d.len0), torch.arange(d.start1, d.start1 + d.len1)]).cuda() for d in pos]
-    o, lse = torch.zeros_like(q), torch.zeros((R, 1, h, L // R), device="cuda")
-    usp.usp_attn_fwd(p, q, k, v, o, lse, 0, R, torch.empty(max(256, usp.usp_attn_fwd_workspace_bytes(p, R)), dtype=torch.uint8, device="cuda"))
+    # (rows of a ring rank: its shards one behind the other; factors by the key's place in them, block after block)
+    k = (k.view(R, U, bs, L // N, hk, HS).transpose(1, 2).reshape(R, bs, L // R, hk, HS) * factors(how, L // R)).bfloat16()
+    k = k.view(R, bs, U, L // N, hk, HS).transpose(1, 2).reshape(N, bs, L // N, hk, HS).contiguous()
+    o, lse = torch.full_like(q, float("nan")), torch.full((N, bs, h, L // R), float("nan"), device="cuda")
+    ws = torch.full((max(256, usp.usp_attn_fwd_workspace_bytes(p, 1)),), 255, dtype=torch.uint8, device="cuda")
+    for rank in range(N):
+        usp.usp_attn_fwd(p, q, k, v, o, lse, rank, rank + 1, ws)
+    rows = lambda t, r, b: t.view(R, U, bs, L // N, -1, HS)[r, :, b].flatten(0, 1)
+    b, group = bs - 1, hc // hk
     for r in range(R):
-        ref = reference(q[r, 0], k[:, 0].flatten(0, 1), v[:, 0].flatten(0, 1), at[r], torch.cat(at), True)
-        compare(o[r, 0], lse[r, 0], *ref)
-        state = torch.zeros(usp.usp_block_attn_fwd_state_bytes(1, L // R, h, HS), dtype=torch.uint8, device="cuda")
-        o1, lse1 = torch.zeros_like(o[r]), torch.zeros_like(lse[r])
-        for i in range(R):
-            s = (r - i) % R
-            usp.usp_block_attn_fwd_state(q[r], k[s], v[s], state, o1, lse1, 1, L // R, L // R, h, h, HS, 0.0, True, pos[r], pos[s], i == 0,
-                                         i == R - 1, usp.USP_BF16)
-        compare(o1[0], lse1[0], *ref)
+        kr, vr = (torch.cat([rows(t, s, b) for s in range(R)]) for t in (k, v))
+        for head in (0, hc - 1):
+            one = slice(head, head + 1), slice(head // group, head // group + 1)
+            compare(rows(o, r, b)[:, one[0]], lse[r * U + head // h, b, head % h][None],
+                    *reference(rows(q, r, b)[:, one[0]], kr[:, one[1]], vr[:, one[1]], at[r], torch.cat(at), causal))
+
+
+# heads, rows and keys of a ring rank: steps that are too much work for one workgroup's waves
+STATES = [(32, 2200), (32, 2050)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)], ids=["own block first", "own block last"])
+@pytest.mark.parametrize("how", STEPS)
+@pytest.mark.parametrize("h,n", STATES)
+def test_running_state(h, n, how, order):
+    R, hk = 2, 4
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    p = usp.problem(1, R * n, h, hk, HS, 1, R, True, usp.USP_SPLIT_ZIGZAG, usp.USP_BF16)
+    q = torch.randn((1, n, h, HS), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((R, 1, n, hk, HS), generator=gen, device="cuda") for _ in range(2))
+    k, v = (k * factors(how, n)).bfloat16(), v.bfloat16()
+    pos = [usp.usp_local_positions(p, r, 0)[1] for r in range(R)]
+    at = [torch.cat([torch.arange(d.start0, d.start0 + d.len0), torch.arange(d.start1, d.start1 + d.len1)]).cuda() for d in pos]
+    for r in range(R):
+        state = torch.zeros(usp.usp_block_attn_fwd_state_bytes(1, n, h, HS), dtype=torch.uint8, device="cuda")
+        o, lse = torch.full_like(q, float("nan")), torch.full((1, h, n), float("nan"), device="cuda")
+        for i, step in enumerate(order):
+            s = (r - step) % R
+            usp.usp_block_attn_fwd_state(q, k[s], v[s], state, o, lse, 1, n, n, h, hk, HS, 0.0, True, pos[r], pos[s], i == 0, i == R - 1,
+                                         usp.USP_BF16)
+        for head in (0, 9, 31):
+            group = slice(head // 8, head // 8 + 1)
+            compare(o[0, :, head:head + 1], lse[0, head:head + 1],
+                    *reference(q[0, :, head:head + 1], k[:, 0, :, group].flatten(0, 1), v[:, 0, :, group].flatten(0, 1), at[r], torch.cat(at), True))
