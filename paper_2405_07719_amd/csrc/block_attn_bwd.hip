@@ -18,7 +18,7 @@
 // A launch covers up to USP_MAX_RING_BLOCKS K/V blocks (the ring loop of one rank) and as many query blocks (ranks).
 // In both kinds, the accumulator layout of the first product is the B-operand layout of the second, and the
 // transposed A operands come from LDS transpose reads of the same tile copy: a row stride of 2*hs + 48 bytes is
-// free of bank conflicts for the 16 B row reads and for the transpose reads alike.
+// free of bank conflicts for the 16 B row reads; a transpose read has two cycles of them.
 // Outputs are fp32 accumulators (overwrite or add), so ring steps and ranks can be summed before the
 // final conversion to the problem dtype.
 #include <algorithm>
@@ -297,7 +297,7 @@ template <int HS>
 __device__ __forceinline__ void dq_item(KernArgs ap, int w, const NextItem& next, char* lds) {
   constexpr int NT = 512, BM = 256, KT = 32;
   constexpr int KSTEPS = HS / 16, DB = HS / 32;
-  constexpr int USTR = HS * 2 + 48;                 // conflict-free for 16 B row reads and for transpose reads
+  constexpr int USTR = HS * 2 + 48;                 // conflict-free for 16 B row reads (two cycles of conflicts on transpose reads)
   constexpr int CPR = HS / 8;                       // 16 B chunks per row
   constexpr int STAGE = 2 * KT * USTR;              // K, V
   static_assert(KT * CPR <= NT, "one chunk per thread and tensor");
@@ -686,7 +686,7 @@ template <int HS, bool WRITE_DS>
 __device__ __forceinline__ void dkdv_item(KernArgs ap, int w, const NextItem& next, char* smem) {
   constexpr int NT = 512, BN = 256, QT = 32;
   constexpr int KSTEPS = HS / 16, DB = HS / 32;
-  constexpr int USTR = HS * 2 + 48;        // one row stride that is conflict-free for 16 B row reads AND transpose reads
+  constexpr int USTR = HS * 2 + 48;        // one row stride for row and transpose reads (as above)
   constexpr int CPR = HS / 8;
   constexpr int STAGE = 2 * QT * USTR;     // Q, dO (each row carries its statistic in the padding, see below)
   constexpr int XOFF = HS * 2;             // byte offset, inside a row, of the extra k-step that holds the statistic

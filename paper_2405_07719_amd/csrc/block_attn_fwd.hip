@@ -703,9 +703,10 @@ void block_attn_fwd_mfma(const std::conditional_t<STATE || MIXED, ListedArgs, At
       };
       float sum = weights(neg_mc);
       if constexpr (STEADY) {
-        // Operand reads eight ahead of the products, then four by four: left alone, ten of the sixteen come in one burst of all
-        // eight waves, behind the barrier.  1 to 1.5 % (the lengths above, us: 562 -> 557, 4328 -> 4262, 344.5 -> 339.5, 573 ->
-        // 569, 636 -> 628); one by one 2 % slower than left alone, pairs six ahead in between.
+        // The eight reads of K ahead of the products, then four and four of V's: left alone, ten come in one burst of all eight
+        // waves, behind the barrier.  V in transposed tiles has eight, one for a product; V as rows has sixteen, of which the
+        // groups name eight and leave the others where the compiler puts them.  1 to 1.5 % (V as rows, the lengths above, us: 562 -> 557,
+        // 4328 -> 4262, 344.5 -> 339.5, 573 -> 569, 636 -> 628); one by one 2 % slower than left alone, pairs six ahead in between.
         __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
         for (int g = 0; g < 2; ++g) {

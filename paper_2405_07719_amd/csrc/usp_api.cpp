@@ -571,7 +571,9 @@ ItemPlan work_out_items(const usp_problem& p, int r, const HeavyChoice& choice) 
   const RowTiles rows(qd, Lq, p.causal);
   const int T = rows.n, n = (p.hc / p.ulysses) * p.bs;
   if (T > kMaxListedItems || (int64_t)T * n > 4 * kPlanCUs) return best;
-  // us of an item besides its tiles, of a tile of 64 keys, of a whole item's step to the next piece; read off time stamps
+  // us of an item besides its tiles, of a tile of 64 keys, of a whole item's step to the next piece; read off time stamps (at head
+  // size 64 before the second product ran a tile behind: its tile is 1.06 to 1.1 since; the other estimates of that head size, of
+  // the choice above and of the launches that split keys over waves, are of then too)
   const double kItem = 9.0, kTile = p.hs == 128 ? 1.78 : 1.15, kCross = 3.0;
   auto pos_of = [&](int64_t i) { return i < qd.len0 ? qd.start0 + i : qd.start1 + (i - qd.len0); };
   std::vector<int64_t> qmax(T);

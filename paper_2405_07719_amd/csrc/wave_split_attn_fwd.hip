@@ -36,8 +36,6 @@ using namespace dev;
 
 constexpr int kWaves = kWaveSplitWaves, kTile = kWaveSplitTile;
 
-// The caller's tensors lie on an element's alignment, no more is claimed (this chip's wide accesses take any address).
-
 // Where the positions of ring block r begin: those of its two runs are start0 + r step0 .. and start1 - r step1 ..
 // (Algorithm 2: chunks r and 2R-1-r of 2R, or block r of R; one given block: steps of 0; no mask: one run from 0).
 struct BlockPositions {
